@@ -5,11 +5,14 @@
 // row-parallel output projection) of a weight kept once, whole, as [out][in] bf16.  Nothing is
 // copied: the kernel addresses the full matrix with its own leading dimension.
 //
-// Shaped for decode batches (M up to a few hundred rows): the weight slice is streamed from HBM
-// once per 64 batch rows and is the only HBM traffic that matters.  What limits such a product on
-// this chip is not HBM but the path from L2 into a compute unit (measured here: about 18 bytes per
-// clock per compute unit for 16-byte loads that hit L2): every weight row needs all of x, so a
-// workgroup that walks the whole input dimension pulls x (M x K, far more than fits in registers or
+// Two families of kernels serve it.  This file holds the one for decode batches on a weight slice of up to
+// about 30 MB, which keeps x in registers; kv_linear_tiles.hip the LDS-staged tiles for everything larger
+// (make_plan below says where the line lies).
+//
+// In a decode step the weight slice is streamed from HBM and is the only HBM traffic that matters.  What
+// limits such a product on this chip is not HBM but the path from L2 into a compute unit (measured here:
+// about 18 bytes per clock per compute unit for 16-byte loads that hit L2): every weight row needs all of
+// x, so a workgroup that walks the whole input dimension pulls x (M x K, far more than fits in registers or
 // LDS) through that path again and again, two to four times the bytes of the weights it streams.
 //
 // So x stays put.  The input dimension is cut into slices of at most 8 slabs of 128 input features,
@@ -37,42 +40,21 @@
 // tile in the workspace and a second, small kernel adds the slices in a fixed order (deterministic)
 // and rounds once.  NB is chosen so that the launch has at least one workgroup per compute unit.
 //
-// Measured, fused QKV weight of 6144 x 4096 at M = 64: 14.0 us for the first kernel, 4.1 us for the
-// second; in a replayed graph 16.7 us per call (W^O 4096 x 4096: 12.7 us).  Time stamps inside the
-// first kernel: x in the registers 3.2 us after the first wavefront starts, the six row blocks done
-// at 8.9 us (about 1 us per block: the 50 MB stream runs at 6 TB/s from the first request on), the
-// accumulators added and stored at 10.5 us; the rest is the launch and the write-back at the
-// kernel's end.
+// Measured at M = 64: 3072 x 4096 (TP2 slice of the fused QKV weight) 10.8 us with the second kernel, 4096 x 1024
+// (TP4 slice of W^O, one slice) 4.8 us.
 #include <string.h>
 #include <hip/hip_ext.h>
 
-#include "decode_common.h"
+#include "kv_linear_args.h"
 
 using namespace kvdec;
+using namespace kvlin;
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kColBlocks = 4;   // 16-row blocks of x per workgroup
-constexpr int kSlab = 128;      // input features per slab
-
-struct linear_args {
-    const uint16_t* x;
-    int64_t ldx;
-    const uint16_t* w;
-    int64_t ldw;
-    uint16_t* y;
-    int64_t ldy;
-    int32_t M, Nl, Kl;
-    int64_t col_start;
-    int32_t n_seg;
-    int64_t seg_start[3];   // first stored row of each segment
-    int32_t seg_first[4];   // first logical row of each segment; seg_first[n_seg] = Nl
-    int32_t splits;         // slices of the input dimension
-    int32_t slice_slabs;    // 128-wide slabs per slice (at most 8)
-    float* part;            // [splits][workgroup tile][NB * 4 tiles][64 lanes] f32x4 when splits > 1
-};
 
 // sum[i] = y[m0 + 16 cb + r][16 (blk0 + b) + 4 quad + i] for tile (b, cb) = (tile / 4, tile % 4) of a
 // workgroup: rounded to bf16 and stored
@@ -166,11 +148,7 @@ __global__ __launch_bounds__(kThreads, 1) void linear_slice_kernel(linear_args p
     auto issue = [&](int b, int slot) {
         const int blk = blk0 + b;
         const int row = min(blk, n_blocks - 1) << 4;     // (a block never straddles two segments)
-        int seg = 0;
-        seg += (p.n_seg > 1 && row >= p.seg_first[1]);
-        seg += (p.n_seg > 2 && row >= p.seg_first[2]);
-        const int64_t phys = p.seg_start[seg] + (row - p.seg_first[seg]);
-        const char* rows = reinterpret_cast<const char*>(p.w + phys * p.ldw + p.col_start);
+        const char* rows = reinterpret_cast<const char*>(p.w + stored_row(p, row) * p.ldw + p.col_start);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int64_t keep = -(int64_t)(blk < n_blocks && have[t]);
@@ -296,8 +274,8 @@ __global__ __launch_bounds__(kThreads) void linear_add_kernel(linear_args p)
 }
 
 // Slices of the input dimension and row blocks per workgroup.  A slice is what a workgroup can keep
-// of x in registers: 8 slabs; NB is the largest of 8, 6, 4, 3, 2, 1 that still gives one workgroup
-// per compute unit (more rows per workgroup use the resident piece of x for longer).
+// of x in registers: 8 slabs; NB is the largest of 3, 2, 1 that still gives one workgroup per compute
+// unit (more rows per workgroup use the resident piece of x for longer).
 constexpr int kSliceSlabs = 2 * kWaves;
 struct linear_cfg {
     int nb, splits, slice_slabs;
@@ -313,7 +291,7 @@ linear_cfg pick_cfg(int64_t m_tiles, int64_t n_l, int total_slabs)
     }
     c.splits = (total_slabs + c.slice_slabs - 1) / c.slice_slabs;
     const int64_t blocks = n_l / 16;
-    static const int kNb[] = {8, 6, 4, 3, 2, 1};
+    static const int kNb[] = {3, 2, 1};
     c.nb = 1;
     for (int nb : kNb) {
         if (m_tiles * ((blocks + nb - 1) / nb) * c.splits >= 256) {
@@ -332,6 +310,38 @@ size_t part_bytes(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
     return (size_t)c.splits * m_tiles * n_tiles * c.nb * kColBlocks * 1024;
 }
 
+// The tiled kernels (kv_linear_tiles.hip) take over where this kernel needs a second round of workgroups:
+// every round costs it a full pass over its piece of x before the first product.  Measured, this kernel
+// against the tiled ones: 64 rows of 6144 x 4096 16.3 against 14.7 us, of 4096 x 4096 12.4 against 11.7 (both with
+// more row blocks per workgroup than it has now, which is what made one round of them), of 3072 x 4096 (NB 3,
+// 256 workgroups) 10.8 against 11.6, of 768 x 4096 (NB 1, 384 workgroups of one row block, two to a compute
+// unit) 7.3 against 10.6; 100 rows of 4096 x 1024 (NB 2, 256) 6.4 against 7.3, 160 rows (NB 3, 258) 11.8
+// against 6.3.
+bool sliced_is_faster(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
+{
+    return m_tiles * ((n_l / 16 + c.nb - 1) / c.nb) * c.splits <= (c.nb == 1 ? 384 : 256);
+}
+
+// The kernel and the cut of a call: tiles.shape < 0 means the sliced kernel as `sliced` says.
+struct linear_plan {
+    linear_cfg sliced;
+    tiles_cfg tiles;
+    size_t workspace;
+};
+linear_plan make_plan(int M, int64_t n_l, int total_slabs)
+{
+    const int64_t m_tiles = ((int64_t)M + 16 * kColBlocks - 1) / (16 * kColBlocks);
+    linear_plan pl;
+    pl.sliced = pick_cfg(m_tiles, n_l, total_slabs);
+    pl.workspace = part_bytes(pl.sliced, m_tiles, n_l);
+    pl.tiles = tiles_cfg{-1, 1, total_slabs};
+    if (kv_option_linear_splits() == 0 && !sliced_is_faster(pl.sliced, m_tiles, n_l)) {
+        pl.tiles = tiles_pick(M, n_l, total_slabs, pl.workspace);
+        if (pl.tiles.shape >= 0) pl.workspace = tiles_workspace(pl.tiles, M, n_l);
+    }
+    return pl;
+}
+
 int64_t view_rows(const kv_weight_view* view)
 {
     int64_t n = 0;
@@ -346,9 +356,7 @@ extern "C" size_t kv_linear_view_workspace_bytes(const kv_weight_view* view, int
     if (!view || M <= 0 || view->n_segments < 1 || view->n_segments > 3 || view->col_count <= 0) return 0;
     const int64_t n_l = view_rows(view);
     if (n_l <= 0) return 0;
-    const int64_t m_tiles = ((int64_t)M + 16 * kColBlocks - 1) / (16 * kColBlocks);
-    const linear_cfg cfg = pick_cfg(m_tiles, n_l, (int)(view->col_count / kSlab));
-    return part_bytes(cfg, m_tiles, n_l);
+    return make_plan(M, n_l, (int)(view->col_count / kSlab)).workspace;
 }
 
 extern "C" int kv_weight_view_make(int dim, int r, int m, int64_t n_rows, int64_t n_cols, kv_weight_view* out)
@@ -436,19 +444,27 @@ extern "C" int kv_linear_view(const void* x, int64_t ldx, const void* w_full, in
     p.seg_first[3] = first;
     for (int i = view->n_segments; i < 4; ++i) p.seg_first[i] = first;
     const int64_t m_tiles = ((int64_t)M + 16 * kColBlocks - 1) / (16 * kColBlocks);
-    const linear_cfg cfg = pick_cfg(m_tiles, n_l, p.Kl / kSlab);
+    const linear_plan plan = make_plan(M, n_l, p.Kl / kSlab);
+    const linear_cfg& cfg = plan.sliced;
     const int64_t n_tiles = (n_l / 16 + cfg.nb - 1) / cfg.nb;
     // (per-lane offsets are 32 bits wide)
     if (n_tiles > 0x7fffffff || m_tiles > 65535 || (int64_t)M * ldx >= (1ll << 31) || ldw >= (1ll << 28))
         return KV_ERR_UNSUPPORTED;
-    p.splits = cfg.splits;
-    p.slice_slabs = cfg.slice_slabs;
+    const bool tiled = plan.tiles.shape >= 0;
+    p.splits = tiled ? plan.tiles.splits : cfg.splits;
+    p.slice_slabs = tiled ? plan.tiles.slice_slabs : cfg.slice_slabs;
     p.part = (float*)workspace;
     if (p.splits > 1) {
         if (!workspace || ((uintptr_t)workspace & 15)) return KV_ERR_INVALID_ARG;
-        if (workspace_bytes < part_bytes(cfg, m_tiles, n_l)) return KV_ERR_WORKSPACE;
+        if (workspace_bytes < plan.workspace) return KV_ERR_WORKSPACE;
     }
     hipStream_t st = (hipStream_t)hip_stream;
+    if (tiled) {
+        const int slot = kv_prof_begin(KV_PROF_LINEAR, st);
+        tiles_launch(plan.tiles, p, st);
+        kv_prof_end(KV_PROF_LINEAR, slot, st);
+        return kv_record_hip_error(hipGetLastError(), "kv_linear_view launch");
+    }
     const dim3 grid((unsigned)n_tiles, (unsigned)m_tiles, (unsigned)p.splits);
     // (while kv_profile is on, a single-kernel call is launched with events that take the kernel's own
     // start and end times; with a second kernel the two share a bracket of recorded events)
@@ -460,9 +476,6 @@ extern "C" int kv_linear_view(const void* x, int64_t ldx, const void* w_full, in
         else hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, p);
     };
     switch (cfg.nb) {
-        case 8: go(linear_slice_kernel<8>); break;
-        case 6: go(linear_slice_kernel<6>); break;
-        case 4: go(linear_slice_kernel<4>); break;
         case 3: go(linear_slice_kernel<3>); break;
         case 2: go(linear_slice_kernel<2>); break;
         default: go(linear_slice_kernel<1>); break;
@@ -470,9 +483,6 @@ extern "C" int kv_linear_view(const void* x, int64_t ldx, const void* w_full, in
     if (p.splits > 1) {
         const dim3 tiles((unsigned)n_tiles, (unsigned)m_tiles);
         switch (cfg.nb) {
-            case 8: hipLaunchKernelGGL(linear_add_kernel<8>, tiles, dim3(kThreads), 0, st, p); break;
-            case 6: hipLaunchKernelGGL(linear_add_kernel<6>, tiles, dim3(kThreads), 0, st, p); break;
-            case 4: hipLaunchKernelGGL(linear_add_kernel<4>, tiles, dim3(kThreads), 0, st, p); break;
             case 3: hipLaunchKernelGGL(linear_add_kernel<3>, tiles, dim3(kThreads), 0, st, p); break;
             case 2: hipLaunchKernelGGL(linear_add_kernel<2>, tiles, dim3(kThreads), 0, st, p); break;
             default: hipLaunchKernelGGL(linear_add_kernel<1>, tiles, dim3(kThreads), 0, st, p); break;

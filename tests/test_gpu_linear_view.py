@@ -127,3 +127,40 @@ def test_every_rows_per_workgroup_shape(M, N, K, what):
     y = kv.kv_linear_view(dev(x), dev(w), gpu_view(ov))
     torch.cuda.synchronize()
     check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ov, what)
+
+
+@pytest.mark.parametrize("M,N,K,what", [
+    (65, 3136, 128, "64 x 64 tiles; one batch row in the second tile; one slab"),
+    (1, 6208, 4224, "64 x 64 tiles, one batch row, two slices, 33 slabs"),
+    (65, 1088, 2304, "64 x 64 tiles, three slices of six slabs"),
+    (257, 6208, 128, "128 x 64 tiles; the last weight tile is half full"),
+    (129, 6208, 384, "64 x 128 tiles; three slabs: six stages through three buffers"),
+    (5000, 3136, 128, "128 x 128 tiles; two workgroups per compute unit"),
+    (1000, 6208, 128, "128 x 256 tiles; both last tiles partly full"),
+    (2047, 4160, 256, "192 x 256 tiles; the last weight tile has 128 of its 192 rows"),
+    (2047, 6208, 128, "256 x 256 tiles; the last weight tile has 64 of its 256 rows"),
+    (700, 4160, 1152, "more than one slice allowed: nine slabs"),
+])
+def test_tiled_kernels(M, N, K, what):
+    """Shapes that take each tile of the LDS-staged kernels, with batch rows and weight rows that fill none
+    of them evenly.  The view has three row segments in another order than stored, the weight and x are
+    column ranges of wider tensors, and y has a row stride that only allows 8-byte stores."""
+    a, b = 64 * (N // 64 // 2), 64 * (N // 64 // 3)
+    segments = ((N - a + 128, a), (0, b), (b + 64, N - a - b))
+    x, w = bits((M, K + 64), 300 + M), bits((N + 128, K + 256), 301 + (N % 97))
+    ov = ow.WeightView(segments, 128, K)
+    out = torch.full((M + 1, N + 4), 7.0, dtype=torch.bfloat16, device=DEV)
+    kv.kv_linear_view(dev(x)[:, :K], dev(w), gpu_view(ov), out=out[:M, :N])
+    torch.cuda.synchronize()
+    assert (out[M:] == 7.0).all() and (out[:, N:] == 7.0).all(), what
+    got = out[:M, :N].contiguous().cpu().view(torch.int16).numpy().view(np.uint16)
+    check(got, np.ascontiguousarray(x[:, :K]), w, ov, what)
+
+
+def test_tiled_kernel_whole_line_stores():
+    """The same kernels where y allows 16-byte stores."""
+    M, N, K = 300, 4160, 256
+    x, w = bits((M, K), 401), bits((N, K), 402)
+    y = kv.kv_linear_view(dev(x), dev(w), kv.kv_weight_view_make(0, 0, 1, N, K))
+    torch.cuda.synchronize()
+    check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ow.weight_view(0, 0, 1, N, K), "aligned rows")
