@@ -35,6 +35,7 @@ constexpr int D = 128;
 constexpr int kThreads = 256;
 constexpr int kSub = 1;               // 32-key sub-tiles per staged tile
 constexpr int kKeys = 32 * kSub;      // keys per staged tile (one barrier each)
+constexpr int kMostCut = 1024;          // sequences up to which a workgroup reads all lengths
 constexpr float kUnset = 1e30f;       // exponent addend of a column that has no reference maximum yet
 
 struct prefill_args {
@@ -50,13 +51,33 @@ struct prefill_args {
     int32_t group;          // G <= 16 query heads per KV head
     int32_t group_shift;    // log2 of G rounded up to a power of two: rows per token in the tile
     int32_t splits;         // workgroups sharing the key range of one query tile
-    int32_t wgs_per_pair;   // query tiles of the longest chunk x splits: workgroups per (sequence, KV head)
+    int32_t tile_shift;     // log2 of the new tokens per query tile
+    int32_t batch;
+    int32_t slots;          // query tiles per KV head as numbered by slot_sequence(), gaps included
+    int32_t xcds_per_head;  // how the tiles are dealt out to the XCDs, see the kernel
     int64_t rows;           // total_q * n_q_local: rows of the partial arrays
     float* part_o;          // [splits][rows][128] un-normalised sums, when splits > 1
     float* part_ml;         // [splits][rows][2]   (reference maximum in score units, sum of weights)
 };
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Inclusive sum over the 64 lanes: shifts inside rows of 16 lanes, then the totals of the rows before.
+template <int CTRL>
+__device__ __forceinline__ float dpp_shr(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_inclusive_sum(float x, int lane)
+{
+    x += dpp_shr<0x111>(x);   // row_shr:1 (lanes shifted in from outside the row read as 0)
+    x += dpp_shr<0x112>(x);
+    x += dpp_shr<0x114>(x);
+    x += dpp_shr<0x118>(x);
+    const float t0 = __shfl(x, 15), t1 = __shfl(x, 31), t2 = __shfl(x, 47);
+    const int row = lane >> 4;
+    return x + (row >= 1 ? t0 : 0.f) + (row >= 2 ? t1 : 0.f) + (row >= 3 ? t2 : 0.f);
+}
 
 typedef short bits16x4 __attribute__((ext_vector_type(4)));
 typedef short bits16x8 __attribute__((ext_vector_type(8)));
@@ -68,6 +89,72 @@ typedef __attribute__((address_space(3))) bits16x4* lds_bits16x4_ptr;
 __device__ __forceinline__ bits16x4 lds_read_transposed(const void* p)
 {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bits16x4_ptr)p);
+}
+
+// Query tiles are numbered with few gaps and without any bound on the lengths: those of sequence s start at slot
+// floor(q_off[s] / tokens per tile) + s, which the tiles of the sequences before cannot reach past.  (A grid
+// sized by the longest chunk launches as many workgroups without work as the lengths differ.)
+__device__ __forceinline__ int first_slot(const prefill_args& a, int s) { return (a.q_off[s] >> a.tile_shift) + s; }
+
+// The sequence whose range of slots holds `slot`: 64 probes at a time.
+__device__ __forceinline__ int slot_sequence(const prefill_args& a, int slot, int lane)
+{
+    int s = 0;
+    for (int span = a.batch; span > 1;) {   // it lies in [s, s + span)
+        const int step = (span + 63) >> 6, probe = lane * step;
+        const bool ok = probe < span && first_slot(a, s + min(probe, span - 1)) <= slot;
+        const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(ok)) - 1;   // lane 0 always counts
+        s += c * step;
+        span = min(step, span - c * step);
+    }
+    return uniform(s);
+}
+
+// The head's slots cut into `parts` consecutive ranges of equal work (keys seen by each query tile plus a fixed
+// cost per tile): [from, to) is the range of `part`.  All workgroups evaluate the cuts alike, so the
+// ranges meet exactly whatever the rounding.
+constexpr float kTileKeys = 96.f;
+__device__ __forceinline__ void work_range(const prefill_args& a, int part, int parts, int lane, int& from, int& to)
+{
+    const int tokens = 1 << a.tile_shift;
+    const float T = (float)tokens;
+    float total = 0.f, incl = 0.f, mine = 0.f, tiles = 0.f, first = 0.f;
+    auto load = [&](int s0) {   // work of sequence s0 + lane, and its inclusive sum over the lanes
+        tiles = first = 0.f;
+        if (s0 + lane < a.batch) {
+            const int q_len = a.q_off[s0 + lane + 1] - a.q_off[s0 + lane];
+            tiles = (float)((q_len + tokens - 1) >> a.tile_shift);
+            first = (float)(a.ctx_lens[s0 + lane] - q_len) + kTileKeys;
+        }
+        mine = tiles * (first + 0.5f * T * (tiles + 1.f));
+        incl = wave_inclusive_sum(mine, lane);
+    };
+    for (int s0 = 0; s0 < a.batch; s0 += 64) {
+        load(s0);
+        total += __shfl(incl, 63);
+    }
+    auto cut = [&](int p) -> int {
+        if (p <= 0) return 0;
+        if (p >= parts) return a.slots;
+        float left = total * ((float)p / (float)parts);
+        for (int s0 = 0; s0 < a.batch; s0 += 64) {
+            if (a.batch > 64) load(s0);
+            const unsigned long long past = __builtin_amdgcn_ballot_w64(incl >= left);
+            if (past == 0) {
+                left -= __shfl(incl, 63);
+                continue;
+            }
+            const int at = __builtin_ctzll(past);
+            left -= __shfl(incl - mine, at);
+            // tiles taken longest first: the first i of them are i c - T i^2 / 2 of work
+            const float nt = __shfl(tiles, at), c = __shfl(first, at) + T * (nt + 0.5f);
+            const float i = ceilf((c - sqrtf(fmaxf(c * c - 2.f * T * left, 0.f))) / T);
+            return first_slot(a, s0 + at) + (int)fminf(fmaxf(i, 0.f), nt);
+        }
+        return a.slots;
+    };
+    from = uniform(cut(part));
+    to = uniform(cut(part + 1));
 }
 
 // Three workgroups per compute unit (32 KiB of LDS and at most 168 registers each): with nothing staged
@@ -83,34 +170,62 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     __shared__ kv_u32x4 s_k0[512 * kSub], s_k1[512 * kSub];
     __shared__ kv_u32x4 s_v0[512 * kSub], s_v1[512 * kSub];
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = uniform(tid >> 6);
-    const int r = lane & 15, quad = lane >> 4;
+    const int lane0 = threadIdx.x & 63;
+    const int wave = uniform((int)threadIdx.x >> 6);
     const kv_view_dev& v = a.v;
     const int G = a.group;
-    // Which (sequence, KV head, query tile, key split) this workgroup takes.  The hardware deals
-    // consecutive workgroups out to the eight XCDs in turn, each with its own L2; every query tile of
-    // a (sequence, head) pair reads that pair's keys and values again, so all tiles of a pair go to
-    // one XCD: workgroup L runs on XCD L % 8 and takes the (L / 8)-th item of that XCD's eighth of the
-    // (pair-major) work list.  A pair's K/V (2 MiB per 4096 tokens) then stays in one 4 MiB L2 while
-    // its tiles are worked on, instead of streaming through all eight.
-    int item;
+    const int tokens_per_wg = 1 << a.tile_shift;
+    // Which query tiles of which KV head this workgroup takes.  The hardware deals consecutive workgroups
+    // out to the eight XCDs in turn, each with its own L2, and all query tiles of a (sequence, head) pair
+    // read the pair's keys and values again (2 MiB per 4096 tokens): an XCD is given tiles of few pairs
+    // at a time, and the XCDs are given the same amount of work whatever the lengths are.  (With a
+    // contiguous eighth of the pairs per XCD most of them wait for the one with the longest sequences:
+    // 16 prompts of 128 to 4000 tokens, 32 query heads, 1375 us instead of 805; 64 such prompts with 4
+    // query heads 564 instead of 494.  Dealing tiles out one by one balances as well but spreads every
+    // pair over all L2s: 32 prompts of 2048 tokens, 4 query heads, 187 us instead of 178.)
+    int hl, item, item_end, item_step;   // item = slot * splits + key split; slots as in slot_sequence()
     {
-        const int L = (int)blockIdx.x, N = (int)gridDim.x;
-        const int xcd = L & 7, k = L >> 3, base = N >> 3, rem = N & 7;
-        item = xcd * base + min(xcd, rem) + k;
+        const int L = (int)blockIdx.x, N = (int)gridDim.x, Hl = v.n_kv_local;
+        const int xcd = L & 7, k = L >> 3;
+        if (a.xcds_per_head == 0) {
+            // a contiguous eighth of the (head, slot, split) list per XCD; one item per workgroup
+            const int base = N >> 3, rem = N & 7;
+            const int x = xcd * base + min(xcd, rem) + k, per_head = a.slots * a.splits;
+            hl = x / per_head;
+            item = x - hl * per_head;
+            item_end = item + 1;
+            item_step = 1;
+        } else if (a.xcds_per_head == 1) {
+            // eight local heads or a multiple: each XCD works on one (at a time) of every sequence
+            hl = L % Hl;
+            item = L / Hl;
+            item_end = item + 1;
+            item_step = 1;
+        } else {
+            // fewer: the XCDs that share a head take consecutive ranges of its slots, cut where the
+            // work before (in keys) passes the same fraction of the total
+            hl = xcd % Hl;
+            work_range(a, xcd / Hl, a.xcds_per_head, lane0, item, item_end);
+            item += k;
+            item_step = N >> 3;
+        }
     }
-    const int pair = item / a.wgs_per_pair, in_pair = item - pair * a.wgs_per_pair;
-    const int s = pair / a.v.n_kv_local, hl = pair - s * a.v.n_kv_local;
-    const int tokens_per_wg = (64 * R) >> a.group_shift;
+    for (; item < item_end; item += item_step) {   // (the body is not indented for it)
+    // what is derived from the lane number is worked out anew per item: kept across the loop it costs the
+    // registers that the inner loop needs (28 spilled instead of 18, 5 % slower)
+    int lane = lane0;
+    asm volatile("" : "+v"(lane));
+    const int r = lane & 15, quad = lane >> 4;
+    const int slot = item / a.splits, split = item - slot * a.splits;
+    const int s = slot_sequence(a, slot, lane);
 
     const int n = a.ctx_lens[s];
     const int q0 = a.q_off[s];
     const int q_len = a.q_off[s + 1] - q0;
     // longest tiles first: the last query tile of a sequence sees the most keys
-    const int split = in_pair % a.splits;
-    const int j0 = (a.wgs_per_pair / a.splits - 1 - in_pair / a.splits) * tokens_per_wg;
-    if (j0 >= q_len || n <= 0) return;
+    const int tile_in_seq = slot - ((q0 >> a.tile_shift) + s);
+    const int j0 = (((q_len + tokens_per_wg - 1) >> a.tile_shift) - 1 - tile_in_seq) << a.tile_shift;
+    if (j0 < 0 || n <= 0) continue;
     const int first_pos = n - q_len;                         // position of the sequence's query 0
     const int j_last = min(j0 + tokens_per_wg, q_len) - 1;   // last query token of this tile
     const int all_tiles = (first_pos + j_last) / kKeys + 1;   // key tiles 0 .. all_tiles - 1 of the query tile
@@ -378,6 +493,7 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
             }
         }
     }
+    }
 }
 
 // out[row] = sum_z o_z 2^((m_z - M) c) / sum_z l_z 2^((m_z - M) c), M = max_z m_z; a split that saw
@@ -483,10 +599,23 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
         a.part_ml = a.part_o + (size_t)a.splits * a.rows * D;
     }
     const int tokens_per_wg = (64 * R) >> a.group_shift;
-    const int64_t q_tiles = (max_q_len + tokens_per_wg - 1) / tokens_per_wg;
-    if (q_tiles * a.splits > 0x7fffffff) return KV_ERR_UNSUPPORTED;
-    a.wgs_per_pair = (int32_t)(q_tiles * a.splits);
-    const int64_t n_wgs = q_tiles * a.splits * view->n_kv_local * batch;
+    a.tile_shift = 0;
+    while ((1 << a.tile_shift) < tokens_per_wg) ++a.tile_shift;   // (64 R and the padded group are powers of two)
+    a.batch = batch;
+    const int64_t slots = total_q / tokens_per_wg + batch;
+    const int Hl = view->n_kv_local;
+    if (slots * a.splits > 0x7fffffff) return KV_ERR_UNSUPPORTED;
+    a.slots = (int32_t)slots;
+    int64_t n_wgs = slots * a.splits * Hl;
+    a.xcds_per_head = 0;
+    if (a.splits == 1 && Hl % 8 == 0) {
+        a.xcds_per_head = 1;
+    } else if (a.splits == 1 && 8 % Hl == 0 && batch <= kMostCut) {
+        // the ranges of the XCDs hold equal work but not equally many tiles: a workgroup takes every
+        // (workgroups per XCD)-th tile of its range
+        a.xcds_per_head = 8 / Hl;
+        n_wgs = 8 * ((slots + a.xcds_per_head - 1) / a.xcds_per_head);
+    }
     if (n_wgs > 0x7fffffff) return KV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)n_wgs);
     int slot = kv_prof_begin(KV_PROF_PREFILL, st);

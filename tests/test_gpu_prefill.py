@@ -130,3 +130,27 @@ def test_sharp_and_flat_softmax(triple, scale):
     got = bf16_bits_to_f64(out.cpu().numpy().view(np.uint16))
     want = oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off, scale)
     check_close(got, want, f"scale {scale} {triple}")
+
+
+@pytest.mark.parametrize("hq,hkv,triple,batch", [
+    (8, 8, (LAYOUT_DP, 1, 0), 13),       # eight local heads: one per XCD
+    (16, 16, (LAYOUT_DP, 1, 0), 6),      # sixteen: two per XCD
+    (8, 4, (LAYOUT_DP, 1, 0), 70),       # four: two XCDs share a head; more than 64 sequences
+    (8, 2, (LAYOUT_TP, 2, 1), 130),      # one: all XCDs share it; three rounds of 64 sequences
+    (2, 2, (LAYOUT_DP, 1, 0), 65),       # two
+    (6, 3, (LAYOUT_DP, 1, 0), 33),       # three: no division by heads
+    (4, 4, (LAYOUT_DP, 1, 0), 1100),     # more sequences than a workgroup reads the lengths of
+])
+def test_tiles_dealt_out_to_the_xcds(hq, hkv, triple, batch):
+    """Ragged batches large enough for one pass over the keys per query tile, for every way the query tiles
+    are dealt out: one very long sequence among short ones, first, last or in the middle, chunks on a
+    cached prefix, sequences without new tokens.  Every output row is compared."""
+    rng = np.random.default_rng(500 + batch)
+    ctx = rng.integers(1, 70, batch).astype(np.int32)
+    ctx[[0, batch // 2, batch - 1][batch % 3]] = 1500
+    q_len = np.array([int(rng.choice([n, n, n, 1, n // 2, 0])) for n in ctx], dtype=np.int32)
+    q_len[ctx == 1500] = 700
+    w = wl.Workload("prefill_deal", 90, hq, hkv, 128, 16, batch, "x", ())
+    c = make_prefill_case(w, triple, ctx, q_len)
+    want = oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off)
+    check_close(run_gpu(c, gpu_view(w, triple)), want, f"{hq}/{hkv} {triple} batch {batch}")
