@@ -345,6 +345,8 @@ int kv_validate_tables(const kv_view* view, int64_t n_pool_blocks, const int32_t
  *                    a slice is never longer than 1024 input features nor shorter than 128);
  *                    kv_linear_view_workspace_bytes follows the option, so size the workspace after
  *                    setting it
+ * With "merge_mode", "waves_per_cu", "xcd_skew" or "piece_cost" set, small batches too take the even-split
+ * decode kernels, with as many heads per wavefront as a large batch gets.
  * Returns KV_ERR_INVALID_ARG for an unknown key or an illegal value. */
 int kv_set_option(const char* key, int64_t value);
 int64_t kv_get_option(const char* key);

@@ -1239,12 +1239,17 @@ __global__ __launch_bounds__(256) void decode_streamk_merge_kernel(kv_streamk_ar
 
 // Adjacent KV heads one wavefront takes (1: the one-head kernel).  With HPW heads the HPW * G
 // query rows of a pair must fit the 16 columns of the matrix-core tile.
-static int wide_heads(const kv_view* view, int batch, int n_waves)
+static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_len)
 {
     if (kv_option_heads_per_wave() == 1) return 1;
     // measured: a gain of 2-5 % where a wavefront then reads whole token rows or the query rows fill
     // the 16 columns
     const int G = view->group, Hl = view->n_kv_local;
+    // ... and a loss where the batch is too small for that to matter, because the pieces a wavefront leaves are
+    // that much larger (8 sequences, 8 heads, 130 MB by the length bound: 25.1 against 22.5 us; 16, 267 MB: 37.9
+    // against 35.5; 64 under TP4, 263 MB: 35.4 against 31.8; 256 short ones under TP2, 105 MB: 30.1 against 21.5;
+    // even at 32, 532 MB; a gain at 64, 1070 MB)
+    if (!kv_even_split_hooks() && (int64_t)batch * Hl * max_ctx_len * (D * 4) < 500000000) return 1;
     if (G <= 4 && Hl % 4 == 0) return 4;
     if (G > 4 && G <= 8 && Hl % 2 == 0 && Hl >= 4) return 2;
     // two-head rows with small groups (TP4 of the 8B shape): both heads of the row, 2.5 % faster than
@@ -1283,7 +1288,7 @@ size_t kv_streamk_workspace_bytes(const kv_view* view, int batch, int n_waves)
 
 int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, hipStream_t st)
 {
-    const int hpw = wide_heads(view, a.batch, a.n_waves);
+    const int hpw = wide_heads(view, a.batch, a.n_waves, a.max_ctx_len);
     a.heads_per_wave = hpw;
     a.pairs = view->n_kv_local / hpw;
     a.cols = view->group * hpw;

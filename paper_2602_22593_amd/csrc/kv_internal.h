@@ -10,6 +10,7 @@
 
 // 16-byte register vector (four dwords), the unit of every KV load and store.
 typedef uint32_t kv_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t kv_u32x2 __attribute__((ext_vector_type(2)));
 
 // Host-side resolved view (Eq. 3 / Eq. 4 of the paper and the head partition of Sec. 4.1.1).
 struct kv_view {
@@ -87,6 +88,12 @@ int64_t kv_option_merge_mode();      // 0: automatic; 1: pieces combined inside 
 int64_t kv_option_piece_cost();  // -1: library default; else 0..64 eighths of a tile
 int64_t kv_option_xcd_skew();  // -1: library default; else 0..256 in 1/1024 of an even share
 int64_t kv_option_linear_splits();
+// A test hook of the even-split decode kernels is set: they are meant then, in the form that large batches get.
+static inline bool kv_even_split_hooks()
+{
+    return kv_option_merge_mode() != 0 || kv_option_waves_per_cu() != 0 || kv_option_xcd_skew() >= 0 ||
+           kv_option_piece_cost() >= 0;
+}
 
 // Per-kernel event brackets for kv_profile_*: begin returns a slot (or -1 when disabled).
 int kv_prof_begin(int which, hipStream_t st);
@@ -117,6 +124,7 @@ struct kv_streamk_args {
     int32_t group;     // query heads per KV head
     int32_t batch;
     int32_t n_waves;   // wavefronts launched (multiple of 4)
+    int32_t max_ctx_len;   // host bound of the lengths
     float* part_acc;   // [n_waves + batch * pairs][cols][128]
     float* part_ml;    // [n_waves + batch * pairs][cols][2]
     int32_t* pair_desc;   // [batch * pairs][2] numbers of the wavefronts holding a pair's first and last piece

@@ -9,10 +9,11 @@
 // kernel merges them:  m = max m_k, l = sum l_k 2^(m_k - m), acc = sum acc_k 2^(m_k - m).
 // Scores are kept in base-2 units (multiplied by scale * log2(e)).
 //
-// Two main kernels:
-//   decode_mfma_kernel  head_dim 128, G <= 16, block capacity a multiple of 16: QK^T and PV on
-//                       the matrix cores (16x16x32 bf16 MFMA), the query group padded to 16.
-//   decode_valu_kernel  any G in {1,2,4,8}, head_dim 64 or 128, any block capacity: vector ALU.
+// Two main kernels here:
+//   decode_chunk_kernel  head_dim 64 or 128, G <= 16, block capacity a multiple of 16: QK^T and PV on the
+//                        matrix cores (16x16x32 bf16 MFMA), the query group padded to 16.
+//   decode_valu_kernel   any G in {1,2,4,8}, head_dim 64 or 128, any block capacity: vector ALU.
+// Larger batches of head_dim 128 go to the even-split kernels (decode_streamk.hip).
 #include <math.h>
 #include <string.h>
 
@@ -27,6 +28,9 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
+// Chunks up to which the last one to arrive combines them (a sequence of 1000 tokens: 7.0 us, 7.6 with a second
+// launch; 4000 tokens, 32 chunks: 11.6 against 9.5).
+constexpr int kFusedChunks = 8;
 
 struct decode_args {
     const uint16_t* q;
@@ -42,13 +46,15 @@ struct decode_args {
     int32_t max_chunks;
     float* part_acc;  // [batch][n_q_local][max_chunks][D]
     float* part_ml;   // [batch][n_q_local][max_chunks][2]
+    int32_t max_ctx_len;
+    unsigned long long* sync;   // [batch][n_kv_local] chunks arrived, zero between calls; null: a second launch merges
 };
 
-// Workgroup epilogue shared by both main kernels: the kWaves per-wave results for G heads sit in
+// Workgroup epilogue of the vector-ALU kernel: the kWaves per-wave results for G heads sit in
 // LDS (s_acc[w][g][e], s_ml[w][g][0..1]); combine them and write either the final bf16 row (the
 // sequence has a single chunk) or this chunk's partial.
 template <int D, int GMAX>
-__device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc)[kWaves][GMAX][D],
+__device__ __forceinline__ void finish_chunk_valu(const decode_args& a, float (&s_acc)[kWaves][GMAX][D],
                                              float (&s_ml)[kWaves][GMAX][2], int G, int s, int hl,
                                              int chunk, int n_chunks)
 {
@@ -80,94 +86,239 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
     }
 }
 
+// Epilogue of the matrix-core kernel: the wavefronts' (m, l, acc) sit in s_ml and s_acc.  Writes the final rows where the sequence has a
+// single chunk, else this chunk's partial; with a.sync the last chunk of the pair to arrive then combines
+// all of them: partials are written and read with device-coherent accesses, the arrival counter is
+// touched once they are acknowledged, and the arriver that completes the count puts it back to zero.
+template <int D, int NW, int GM>
+__device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc)[NW][GM][D], float (&s_ml)[NW][GM][2], int G,
+                                             int s, int hl, int chunk, int n_chunks)
+{
+    constexpr int T = NW * 64, HD = D / 2;
+    const int tid = threadIdx.x;
+    for (int idx = tid; idx < G * HD; idx += T) {
+        const int g = idx / HD, e = 2 * (idx - g * HD);
+        float mm = kNegInf;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mm = fmaxf(mm, s_ml[w][g][0]);
+        const float ms = (mm == kNegInf) ? 0.f : mm;
+        float ll = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float cw = fast_exp2(s_ml[w][g][0] - ms);
+            const f32x2 x = *reinterpret_cast<const f32x2*>(&s_acc[w][g][e]);
+            ll += s_ml[w][g][1] * cw;
+            a0 += x[0] * cw;
+            a1 += x[1] * cw;
+        }
+        const int64_t row = (int64_t)s * a.v.n_q_local + hl * G + g;
+        if (n_chunks <= 1) {
+            const float inv = ll > 0.f ? 1.0f / ll : 0.f;
+            *reinterpret_cast<uint32_t*>(a.out + row * D + e) = pack_bf16x2(a0 * inv, a1 * inv);
+        } else {
+            const int64_t rec = row * a.max_chunks + chunk;
+            if (a.sync) {
+                st_coherent2(a.part_acc + rec * D + e, a0, a1);
+                if (e == 0) st_coherent2(a.part_ml + rec * 2, mm, ll);
+            } else {
+                *reinterpret_cast<f32x2*>(a.part_acc + rec * D + e) = f32x2{a0, a1};
+                if (e == 0) *reinterpret_cast<f32x2*>(a.part_ml + rec * 2) = f32x2{mm, ll};
+            }
+        }
+    }
+    if (n_chunks <= 1 || !a.sync) return;
+
+    __shared__ int s_last;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long* word = a.sync + ((int64_t)s * a.v.n_kv_local + hl);
+        const unsigned long long seen = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool last = seen + 1 == (unsigned long long)n_chunks;
+        if (last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = last;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // lane = (pair of elements, slice of the chunk list); the slices are added up through LDS
+    const int pairs = G * HD, slices = T / pairs > 0 ? T / pairs : 1;
+    f32x4* s_red = reinterpret_cast<f32x4*>(&s_acc[0][0][0]);   // [slice][pair]: (m, l, acc0, acc1); 16 T bytes at most
+    constexpr int kBatch = kFusedChunks;
+    for (int p0 = 0; p0 < pairs; p0 += T) {
+        const int slice = tid / pairs, idx = p0 + tid - slice * pairs;
+        if (slice < slices && idx < pairs) {
+            const int g = idx / HD, e = 2 * (idx - g * HD);
+            const int64_t rec0 = ((int64_t)s * a.v.n_q_local + hl * G + g) * a.max_chunks;
+            float m = kNegInf, l = 0.f, a0 = 0.f, a1 = 0.f;
+            for (int k0 = slice; k0 < n_chunks; k0 += kBatch * slices) {
+                f32x2 ml[kBatch], av[kBatch];
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {   // (past the end: the last one again, not used)
+                    const int64_t rec = rec0 + min(k0 + u * slices, n_chunks - 1);
+                    ml[u] = ld_coherent2(a.part_ml + rec * 2);
+                    av[u] = ld_coherent2(a.part_acc + rec * D + e);
+                }
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    if (k0 + u * slices >= n_chunks) break;
+                    const float mn = fmaxf(m, ml[u][0]);   // (finite: every chunk holds a token)
+                    const float c0 = fast_exp2(m - mn), c1 = fast_exp2(ml[u][0] - mn);
+                    l = l * c0 + ml[u][1] * c1;
+                    a0 = a0 * c0 + av[u][0] * c1;
+                    a1 = a1 * c0 + av[u][1] * c1;
+                    m = mn;
+                }
+            }
+            if (slices > 1) s_red[slice * pairs + idx] = f32x4{m, l, a0, a1};
+            else {
+                const float inv = 1.0f / l;
+                *reinterpret_cast<uint32_t*>(a.out + ((int64_t)s * a.v.n_q_local + hl * G + g) * D + e) =
+                    pack_bf16x2(a0 * inv, a1 * inv);
+            }
+        }
+    }
+    if (slices == 1) return;
+    __syncthreads();
+    if (tid < pairs) {
+        const int g = tid / HD, e = 2 * (tid - g * HD);
+        float mm = kNegInf;
+        for (int k = 0; k < slices; ++k) mm = fmaxf(mm, s_red[k * pairs + tid][0]);
+        float l = 0.f, a0 = 0.f, a1 = 0.f;
+        for (int k = 0; k < slices; ++k) {   // (a slice without chunks: m = -inf, weight 0)
+            const f32x4 x = s_red[k * pairs + tid];
+            const float c = fast_exp2(x[0] - mm);
+            l += x[1] * c;
+            a0 += x[2] * c;
+            a1 += x[3] * c;
+        }
+        const float inv = 1.0f / l;
+        *reinterpret_cast<uint32_t*>(a.out + ((int64_t)s * a.v.n_q_local + hl * G + g) * D + e) = pack_bf16x2(a0 * inv, a1 * inv);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
-// Matrix-core kernel (head_dim 128).  One wavefront walks tiles of 32 tokens of its chunk.
+// Matrix-core kernel: one workgroup of NW wavefronts per (sequence, local KV head, chunk), a wavefront takes
+// every NW-th tile of 32 tokens of the chunk.
+//
+// Bound: latency.  It serves the batches that leave most of the chip's bandwidth unused (a few sequences, short
+// contexts): what counts is the chain launch -> length and block ids -> K and V -> weighted sum ->
+// combination, so the first block ids are requested together with the length, a wavefront has few tiles
+// (one, where the chip has enough wavefronts), all K and V bytes of a tile are requested before any is used, and
+// few chunks of a sequence are combined by the last workgroup to arrive, many by a second launch that spreads
+// them over eight slices of lanes.  What it measures against the even-split kernels stands at
+// small_batch_chunk(); against the vector-ALU kernel, head_dim 64: 4 sequences of 17 to 300 tokens, 2 KV heads
+// 11.0 -> 4.6 us, 32 of 100 to 4000, 8 KV heads 72 -> 49 us, one of 8000 19.3 -> 12.0 us.
 //
 // Lane l = (r = l % 16, quad = l / 16).  Both products put the KV data in the MFMA A operand
 // (row index = r) and the query group in the B operand (column index = r = query head g):
 //   S^T[token][g] = K[token][:] . Q[g][:]     A = K rows: lane (r, quad) holds the 8 elements
-//                                              [32 kk + 8 quad, +8) of row r, kk = 0..3
+//                                              [32 kk + 8 quad, +8) of row r, kk = 0 .. D / 32 - 1
 //   O^T[e][g]     = sum_t V[t][e] P[g][t]     A = V^T, B = P^T; contraction over the 32 tokens
 // The C layout of S^T (lane (g, quad) holds tokens 4 quad + i of a 16-row half) is, element for
 // element, the B layout the PV product needs if the contraction index k = 8 quad + 4 h + i stands
 // for token 16 h + 4 i + quad; so row r of half h of the K operand is token 16 h + 4 (r % 4) + r / 4,
-// and V is loaded row-wise (lane (c = r, quad) reads the 16 bytes [8c, 8c+8) of tokens
-// 4 i' + quad, i' = 0..7) and transposed inside the lane with byte permutes.  No data crosses
-// lanes except the running maximum.
+// and V is loaded row-wise (lane (c = r, quad) reads elements [EV c, EV c + EV) of tokens 4 i' + quad,
+// i' = 0..7, EV = D / 16) and transposed inside the lane with byte permutes.  No data crosses lanes
+// except the running maximum.
+//
+// SPLIT_P (head_dim 64, which is otherwise the vector-ALU kernel's): the weights enter the second product as
+// the sum of two bf16 numbers (16 bits of mantissa) and their fp32 values are summed for the denominator, so
+// that nothing is lost against the vector-ALU kernel's fp32 weights.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(decode_args a)
-{
-    constexpr int D = 128;
-    const int chunk = blockIdx.x, hl = blockIdx.y, s = blockIdx.z;
-    const int n = a.ctx_lens[s];
-    const int cs = chunk * a.chunk_tokens;
-    if (cs >= n && chunk != 0) return;
-    const int ce = min(n, cs + a.chunk_tokens);
-    const int n_chunks = (n + a.chunk_tokens - 1) / a.chunk_tokens;
+template <int D>
+struct chunk_tile {
+    static constexpr int KK = D / 32, EW = D / 32;   // K pieces per half; 32-bit words of a lane's V elements
+    kv_u32x4 k[2][KK];
+    uint32_t v[8][EW];
+};
 
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+template <int D, int NW, int GM, bool SPLIT_P>
+__global__ __launch_bounds__(NW * 64, 3) void decode_chunk_kernel(decode_args a)
+{
+    constexpr int KK = D / 32, NJ = D / 16;
+    const int chunk = blockIdx.x, hl = blockIdx.y, s = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, quad = lane >> 4;
     const int G = a.group;
     const kv_view_dev& v = a.v;
     const int32_t* trow = a.table + (int64_t)s * a.table_stride;
+    const int cs = chunk * a.chunk_tokens;
 
+    // block ids of a tile's two halves (capacity % 16 == 0: each half lies in one block).  The first tile's are
+    // requested before the length is known, at positions the table has for any length up to the bound.
+    auto ids_of = [&](int t0, int last, int (&id)[2]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            int bj, slot;
+            kv_split_token(v, min(t0 + 16 * h, last), bj, slot);
+            id[h] = trow[bj];
+        }
+    };
+    int t0 = cs + 32 * wave;
+    int id[2] = {0, 0};
+    if (a.max_ctx_len > 0) ids_of(t0, a.max_ctx_len - 1, id);
+    const int n = a.ctx_lens[s];
     // B operand of the score product: lane (g = r, quad) holds q[g][32 kk + 8 quad, +8)
-    bf16x8 qb[4];
+    bf16x8 qb[KK];
     {
         const uint16_t* qrow = a.q + ((int64_t)s * v.n_q_local + hl * G + min(r, G - 1)) * D;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
+        for (int kk = 0; kk < KK; ++kk) {
             kv_u32x4 raw = *reinterpret_cast<const kv_u32x4*>(qrow + kk * 32 + quad * 8);
             if (r >= G) raw = kv_u32x4{0u, 0u, 0u, 0u};
             qb[kk] = as_bf16x8(raw);
         }
     }
+    if (cs >= n && chunk != 0) return;
+    const int ce = min(n, cs + a.chunk_tokens);
+    const int n_chunks = (n + a.chunk_tokens - 1) / a.chunk_tokens;
+    if (n > 0 && t0 + 31 >= ce) ids_of(t0, ce - 1, id);   // a tile at the end: ids of tokens that exist
 
     float m_run = kNegInf, l_run = 0.f;
-    f32x4 oacc[8];
+    f32x4 oacc[NJ];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) oacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) oacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const uint16_t* kplane = a.pool + v.head_off + hl * D;
     const int k_row = 4 * (r & 3) + (r >> 2);  // token (within a 16-token half) held in A row r
 
-    for (int t0 = cs + 32 * wave; t0 < ce; t0 += 32 * kWaves) {
-        // the two 16-token halves of the tile each lie inside one block (capacity % 16 == 0)
-        const uint16_t* hbase[2];
-        int hstart[2];
+    auto load = [&](int t0, chunk_tile<D>& t) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int ts = min(t0 + 16 * h, ce - 1);
             int bj, slot;
-            kv_split_token(v, ts, bj, slot);
-            hstart[h] = ts - slot;  // first token of that block
-            hbase[h] = kplane + (int64_t)trow[bj] * v.block_elems;
-        }
-        kv_u32x4 kA[2][4], vN[8];
+            kv_split_token(v, min(t0 + 16 * h, ce - 1), bj, slot);
+            const int first = min(t0 + 16 * h, ce - 1) - slot;   // first token of that block
+            const uint16_t* base = kplane + (int64_t)id[h] * v.block_elems;
+            const uint16_t* p = base + (min(t0 + 16 * h + k_row, ce - 1) - first) * v.token_stride + quad * 8;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int tok = min(t0 + 16 * h + k_row, ce - 1);
-            const uint16_t* p = hbase[h] + (tok - hstart[h]) * v.token_stride + quad * 8;
+            for (int kk = 0; kk < KK; ++kk)
+                t.k[h][kk] = __builtin_nontemporal_load(reinterpret_cast<const kv_u32x4*>(p + kk * 32));
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) kA[h][kk] = *reinterpret_cast<const kv_u32x4*>(p + kk * 32);
-        }
+            for (int i = 0; i < 4; ++i) {
+                const uint16_t* q = base + v.plane_elems + (min(t0 + 16 * h + 4 * i + quad, ce - 1) - first) * v.token_stride +
+                                    r * (D / 16);
+                if constexpr (D == 128) {
+                    const kv_u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const kv_u32x4*>(q));
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int h = i >> 2;
-            const int tok = min(t0 + 4 * i + quad, ce - 1);
-            const uint16_t* p = hbase[h] + v.plane_elems + (tok - hstart[h]) * v.token_stride + r * 8;
-            vN[i] = *reinterpret_cast<const kv_u32x4*>(p);
+                    for (int w = 0; w < 4; ++w) t.v[4 * h + i][w] = x[w];
+                } else {
+                    const kv_u32x2 x = __builtin_nontemporal_load(reinterpret_cast<const kv_u32x2*>(q));
+                    t.v[4 * h + i][0] = x[0];
+                    t.v[4 * h + i][1] = x[1];
+                }
+            }
         }
-
-        // scores
+    };
+    auto compute = [&](int t0, const chunk_tile<D>& t) __attribute__((always_inline)) {
         f32x4 sacc[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             sacc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                sacc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kA[h][kk]), qb[kk], sacc[h], 0, 0, 0);
+            for (int kk = 0; kk < KK; ++kk)
+                sacc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t.k[h][kk]), qb[kk], sacc[h], 0, 0, 0);
         }
         float sv[8];
         float mx = kNegInf;
@@ -175,67 +326,73 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(decode_args a)
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int tok = t0 + 16 * h + 4 * i + quad;
-                const float x = tok < ce ? sacc[h][i] * a.scale_log2e : kNegInf;
+                const float x = t0 + 16 * h + 4 * i + quad < ce ? sacc[h][i] * a.scale_log2e : kNegInf;
                 sv[4 * h + i] = x;
                 mx = fmaxf(mx, x);
             }
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m_run, mx);  // finite: every tile holds at least one valid token
-        const float alpha = exp2f(m_run - m_new);
+        const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
-        uint32_t pw[4];
+        kv_u32x4 hi, lo;
         float psum = 0.f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint32_t b0 = f32_to_bf16_bits(exp2f(sv[2 * u] - m_new));
-            const uint32_t b1 = f32_to_bf16_bits(exp2f(sv[2 * u + 1] - m_new));
-            psum += __uint_as_float(b0 << 16) + __uint_as_float(b1 << 16);
-            pw[u] = b0 | (b1 << 16);
+            const float p0 = fast_exp2(sv[2 * u] - m_new), p1 = fast_exp2(sv[2 * u + 1] - m_new);
+            hi[u] = pack_bf16x2(p0, p1);
+            if constexpr (SPLIT_P) {
+                lo[u] = pack_bf16x2(p0 - bf16_lo(hi[u]), p1 - bf16_hi(hi[u]));
+                psum += p0 + p1;
+            } else {
+                // the denominator sums the weights as they enter the second product
+                psum += bf16_lo(hi[u]) + bf16_hi(hi[u]);
+            }
         }
         l_run = l_run * alpha + psum;
-        const bf16x8 pb = as_bf16x8(kv_u32x4{pw[0], pw[1], pw[2], pw[3]});
 #pragma unroll
-        for (int j = 0; j < 8; ++j) oacc[j] *= alpha;
+        for (int j = 0; j < NJ; ++j) oacc[j] *= alpha;
 
         // V^T operands: element j of the 8 loaded rows, packed token-pair-wise
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            kv_u32x4 lo, hi;
+        for (int j = 0; j < NJ; ++j) {
+            const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+            kv_u32x4 va;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                lo[u] = __builtin_amdgcn_perm(vN[2 * u + 1][w], vN[2 * u][w], 0x05040100u);
-                hi[u] = __builtin_amdgcn_perm(vN[2 * u + 1][w], vN[2 * u][w], 0x07060302u);
-            }
-            oacc[2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(lo), pb, oacc[2 * w], 0, 0, 0);
-            oacc[2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(hi), pb, oacc[2 * w + 1], 0, 0, 0);
+            for (int u = 0; u < 4; ++u) va[u] = __builtin_amdgcn_perm(t.v[2 * u + 1][j >> 1], t.v[2 * u][j >> 1], sel);
+            oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), as_bf16x8(hi), oacc[j], 0, 0, 0);
+            if constexpr (SPLIT_P)
+                oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), as_bf16x8(lo), oacc[j], 0, 0, 0);
         }
+    };
+    for (; t0 < ce; t0 += 32 * NW) {
+        chunk_tile<D> t;
+        load(t0, t);
+        if (t0 + 32 * NW < ce) ids_of(t0 + 32 * NW, ce - 1, id);
+        compute(t0, t);
     }
 
     // per-lane partial sums of l over the 4 quads
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
 
-    // lane (g = r, quad) holds O[g][32 quad + 8 i + j] in oacc[j][i]
-    __shared__ float s_acc[kWaves][16][D];
-    __shared__ float s_ml[kWaves][16][2];
+    // lane (g = r, quad) holds O[g][NJ (4 quad + i) + j] in oacc[j][i]
+    __shared__ float s_acc[NW][GM][D];
+    __shared__ float s_ml[NW][GM][2];
     if (r < G) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float4 lo4 = make_float4(oacc[0][i], oacc[1][i], oacc[2][i], oacc[3][i]);
-            float4 hi4 = make_float4(oacc[4][i], oacc[5][i], oacc[6][i], oacc[7][i]);
-            float* dst = &s_acc[wave][r][32 * quad + 8 * i];
-            *reinterpret_cast<float4*>(dst) = lo4;
-            *reinterpret_cast<float4*>(dst + 4) = hi4;
-        }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; j += 4)
+                *reinterpret_cast<f32x4*>(&s_acc[wave][r][NJ * (4 * quad + i) + j]) =
+                    f32x4{oacc[j][i], oacc[j + 1][i], oacc[j + 2][i], oacc[j + 3][i]};
         if (quad == 0) {
             s_ml[wave][r][0] = m_run;
             s_ml[wave][r][1] = l_run;
         }
     }
     __syncthreads();
-    finish_chunk<D, 16>(a, s_acc, s_ml, G, s, hl, chunk, n_chunks);
+    finish_chunk<D, NW, GM>(a, s_acc, s_ml, G, s, hl, chunk, n_chunks);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -371,17 +528,19 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(decode_args a)
         }
     }
     __syncthreads();
-    finish_chunk<D, G>(a, s_acc, s_ml, G, s, hl, chunk, n_chunks);
+    finish_chunk_valu<D, G>(a, s_acc, s_ml, G, s, hl, chunk, n_chunks);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Merge the partials of one (sequence, local query head).  256 lanes = 32 column groups of
-// D/32 elements x 8 slices of the chunk list; maxima first, then one weighted pass.
+// D/32 elements x 8 slices of the chunk list; a slice requests eight chunks at a time and keeps a running
+// maximum, then the slices are brought to a common one and added through LDS.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void decode_merge_kernel(decode_args a)
 {
     constexpr int EPT = D / 32;  // elements per lane
+    typedef float vec __attribute__((ext_vector_type(EPT)));
     const int qi = blockIdx.x, s = blockIdx.y;
     const int n = a.ctx_lens[s];
     const int n_chunks = (n + a.chunk_tokens - 1) / a.chunk_tokens;
@@ -390,36 +549,45 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(decode_args a)
     const int64_t rec0 = ((int64_t)s * a.v.n_q_local + qi) * a.max_chunks;
 
     __shared__ float s_red[8][D];
-    __shared__ float s_l[8];
-    __shared__ float s_max[4];
-    float mm = kNegInf;
-    for (int k = tid; k < n_chunks; k += 256) mm = fmaxf(mm, a.part_ml[(rec0 + k) * 2]);
+    __shared__ float s_l[8], s_m[8];
+    float m = kNegInf, ll = 0.f;
+    vec acc = 0.f;
+    constexpr int kBatch = 8;
+    for (int k0 = slice; k0 < n_chunks; k0 += 8 * kBatch) {
+        float2 ml[kBatch];
+        vec x[kBatch];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mm = fmaxf(mm, __shfl_xor(mm, off));
-    if ((tid & 63) == 0) s_max[tid >> 6] = mm;
-    __syncthreads();
-    mm = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-
-    float ll = 0.f, acc[EPT];
+        for (int u = 0; u < kBatch; ++u) {   // (past the end: the last one again, not used)
+            const int64_t rec = rec0 + min(k0 + 8 * u, n_chunks - 1);
+            ml[u] = *reinterpret_cast<const float2*>(a.part_ml + rec * 2);
+            x[u] = *reinterpret_cast<const vec*>(a.part_acc + rec * D + cg * EPT);
+        }
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) acc[e] = 0.f;
-    for (int k = slice; k < n_chunks; k += 8) {
-        const float cw = exp2f(a.part_ml[(rec0 + k) * 2] - mm);
-        ll += a.part_ml[(rec0 + k) * 2 + 1] * cw;
-        const float* src = a.part_acc + (rec0 + k) * D + cg * EPT;
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) acc[e] += src[e] * cw;
+        for (int u = 0; u < kBatch; ++u) {
+            if (k0 + 8 * u >= n_chunks) break;
+            const float mn = fmaxf(m, ml[u].x);   // (finite: every chunk holds a token)
+            const float c0 = exp2f(m - mn), c1 = exp2f(ml[u].x - mn);
+            ll = ll * c0 + ml[u].y * c1;
+            acc = acc * c0 + x[u] * c1;
+            m = mn;
+        }
+    }
+    if (cg == 0) {
+        s_l[slice] = ll;
+        s_m[slice] = m;
     }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) s_red[slice][cg * EPT + e] = acc[e];
-    if (cg == 0) s_l[slice] = ll;
     __syncthreads();
     if (tid < D) {
-        float tot = 0.f, lt = 0.f;
+        float mm = kNegInf, tot = 0.f, lt = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            tot += s_red[w][tid];
-            lt += s_l[w];
+        for (int w = 0; w < 8; ++w) mm = fmaxf(mm, s_m[w]);
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {   // (a slice without chunks: m = -inf, weight 0)
+            const float c = exp2f(s_m[w] - mm);
+            tot += s_red[w][tid] * c;
+            lt += s_l[w] * c;
         }
         a.out[((int64_t)s * a.v.n_q_local + qi) * D + tid] = f32_to_bf16(tot / lt);
     }
@@ -453,18 +621,28 @@ int launch_valu_for_group(const decode_args& a, dim3 grid, hipStream_t st)
     }
 }
 
+// (head_dim 128: chunks of 128 tokens and up, four wavefronts; head_dim 64: chunks of 512, eight: the tiny
+// shape below takes 4.6 us with eight and 5.2 with four)
+template <int D, int NW, bool SPLIT_P>
+void launch_chunk(const decode_args& a, dim3 grid, hipStream_t st)
+{
+    if (a.group <= 4) hipLaunchKernelGGL((decode_chunk_kernel<D, NW, 4, SPLIT_P>), grid, dim3(NW * 64), 0, st, a);
+    else if (a.group <= 8) hipLaunchKernelGGL((decode_chunk_kernel<D, NW, 8, SPLIT_P>), grid, dim3(NW * 64), 0, st, a);
+    else if constexpr (D == 128) hipLaunchKernelGGL((decode_chunk_kernel<D, NW, 16, SPLIT_P>), grid, dim3(NW * 64), 0, st, a);
+}
+
 // Which main kernel serves a call: 1 = matrix-core kernel with the even split over resident
 // wavefronts, 2 = vector-ALU kernel (chunked), 3 = matrix-core kernel (chunked), 0 = none.
 int pick_kernel(const kv_view* view, int batch)
 {
     const int D = view->geom.head_dim, G = view->group;
-    const bool mfma_ok = D == 128 && G <= 16 && view->block_tokens % 16 == 0;
-    const bool streamk_ok = mfma_ok && batch <= KV_STREAMK_MAX_BATCH;
     const bool valu_ok = (D == 64 || D == 128) && (G == 1 || G == 2 || G == 4 || G == 8);
+    const bool mfma_ok = (D == 128 ? G <= 16 : D == 64 && valu_ok) && view->block_tokens % 16 == 0;
+    const bool streamk_ok = mfma_ok && D == 128 && batch <= KV_STREAMK_MAX_BATCH;
     const int64_t forced = kv_option_force_kernel();
     if (forced == 1) return streamk_ok ? 1 : 0;
     if (forced == 2) return valu_ok ? 2 : 0;
-    if (forced == 3) return mfma_ok ? 3 : 0;
+    if (forced == 3) return mfma_ok && D == 128 ? 3 : 0;
     if (streamk_ok) return 1;
     if (mfma_ok) return 3;
     return valu_ok ? 2 : 0;
@@ -490,9 +668,8 @@ int streamk_waves()
     return (int)(n * per_cu);
 }
 
-size_t chunked_workspace_bytes(const kv_view* view, int batch, int max_ctx_len)
+size_t chunked_workspace_bytes(const kv_view* view, int batch, int max_ctx_len, int64_t chunk)
 {
-    const int chunk = pick_chunk_tokens(view, batch, max_ctx_len);
     const int64_t max_chunks = ((int64_t)max_ctx_len + chunk - 1) / chunk;
     if (max_chunks <= 1) return KV_DECODE_SYNC_BYTES + 256;
     const int64_t recs = (int64_t)batch * view->n_q_local * max_chunks;
@@ -500,13 +677,8 @@ size_t chunked_workspace_bytes(const kv_view* view, int batch, int max_ctx_len)
            align_up((size_t)recs * 2 * 4, 256);
 }
 
-// The even-split matrix-core kernel.  views/view_ids non-null: sequence s is laid out as
-// views[view_ids[s]] says (all of them expose the same heads as `view`).
-static int launch_streamk(const void* q, void* out, const void* kv_pool, const int32_t* block_table,
-                          int64_t block_table_stride, const int32_t* ctx_lens, int batch,
-                          int max_ctx_len, const kv_view* view, float sc, void* workspace,
-                          size_t workspace_bytes, hipStream_t st, const int32_t* view_ids,
-                          const kv_view* const* views, int n_views)
+// What every call that the even-split kernels can serve has to meet, whichever kernel then takes it.
+int check_streamk(const kv_view* view, int batch, int max_ctx_len, const void* workspace, size_t workspace_bytes)
 {
     // tiles (of 8 tokens at the least) over all (sequence, head) pairs must fit 31 bits
     if (((int64_t)max_ctx_len / 8 + 1) * batch * view->n_kv_local >= ((int64_t)1 << 31))
@@ -514,11 +686,45 @@ static int launch_streamk(const void* q, void* out, const void* kv_pool, const i
     // and the weighted length of one sequence's pairs (8 units per tile plus a cost per pair) 32 bits
     if (((int64_t)max_ctx_len + 8 + 64) * 8 * view->n_kv_local >= ((int64_t)1 << 31))
         return KV_ERR_UNSUPPORTED;
-    const int n_waves = streamk_waves();
-    const size_t need_sk = kv_streamk_workspace_bytes(view, batch, n_waves);
     if (!workspace) return KV_ERR_INVALID_ARG;
-    if (workspace_bytes < need_sk) return KV_ERR_WORKSPACE;
+    if (workspace_bytes < kv_streamk_workspace_bytes(view, batch, streamk_waves())) return KV_ERR_WORKSPACE;
     if (((uintptr_t)workspace & 255u) != 0) return KV_ERR_INVALID_ARG;
+    return KV_OK;
+}
+
+// Chunk length for the calls that decode_chunk_kernel serves better than the even-split kernels, or 0.
+// The even split costs every call about 13 us whatever its size (each of its 1024 wavefronts works out the
+// cut and leaves a partial per piece, and a sequence cut into hundreds of pieces takes long to combine), so
+// below some amount of cached bytes one workgroup per chunk is faster.  Measured, even split (with the heads
+// per wavefront it then had) against this kernel, us: one sequence of 1000 / 4000 tokens, 8 KV heads, 17.6 / 19.8
+// against 7.0 / 9.5; two of 3400 18.4 against 12.0; 8 KV heads x 64 sequences of 64 tokens 13.8 against 5.7;
+// 16 sequences under TP4 (41 MB) 16.8 against 14.0; 32 under TP8, G = 8 (36 MB) 17.2 against 14.4; 32 under TP8 (40
+// MB, 66 by the bound) 16.5 against 15.1; but 8 sequences, 8 heads (81 MB, 130 by the bound) 22.4 against 25,
+// 64 under TP8 (75 MB, 134 by the bound) 20.3 against 23.5.  The host knows the bound only.
+constexpr int64_t kSmallBytes = 80000000;
+constexpr int kSmallCtx = 32768;
+int64_t small_batch_chunk(const kv_view* view, int batch, int max_ctx_len)
+{
+    if (kv_option_force_kernel() != 0 || kv_option_heads_per_wave() != 0 || kv_even_split_hooks()) return 0;
+    const int64_t pairs = (int64_t)batch * view->n_kv_local;
+    if (max_ctx_len > kSmallCtx || pairs * max_ctx_len * view->geom.head_dim * 4 > kSmallBytes) return 0;
+    // one tile per wavefront where that leaves neither a long list to merge nor several rounds of workgroups
+    const int64_t c128 = ((int64_t)max_ctx_len + 127) / 128;
+    int64_t chunk = c128 <= 64 && c128 * pairs <= 1024 ? 128 : 256;
+    if (kv_option_chunk_tokens() > 0) chunk = kv_option_chunk_tokens();
+    // (the caller's workspace is the even-split kernels')
+    if (chunked_workspace_bytes(view, batch, max_ctx_len, chunk) > kv_streamk_workspace_bytes(view, batch, streamk_waves()))
+        return 0;
+    return chunk;
+}
+// The even-split matrix-core kernel.  views/view_ids non-null: sequence s is laid out as
+// views[view_ids[s]] says (all of them expose the same heads as `view`).
+static int launch_streamk(const void* q, void* out, const void* kv_pool, const int32_t* block_table,
+                          int64_t block_table_stride, const int32_t* ctx_lens, int batch, int max_ctx_len,
+                          const kv_view* view, float sc, void* workspace, hipStream_t st, const int32_t* view_ids,
+                          const kv_view* const* views, int n_views)
+{
+    const int n_waves = streamk_waves();
     kv_streamk_args k;
     k.q = (const uint16_t*)q;
     k.out = (uint16_t*)out;
@@ -531,6 +737,7 @@ static int launch_streamk(const void* q, void* out, const void* kv_pool, const i
     k.group = view->group;
     k.batch = batch;
     k.n_waves = n_waves;
+    k.max_ctx_len = max_ctx_len;
     k.part_acc = nullptr;
     k.part_ml = nullptr;
     k.pair_desc = nullptr;
@@ -550,7 +757,7 @@ extern "C" size_t paged_decode_attn_workspace_bytes(const kv_view* view, int bat
     if (!kv_view_ok(view) || batch <= 0 || max_ctx_len <= 0) return KV_DECODE_SYNC_BYTES + 256;
     const int kernel = pick_kernel(view, batch);
     if (kernel == 1) return kv_streamk_workspace_bytes(view, batch, streamk_waves());
-    return chunked_workspace_bytes(view, batch, max_ctx_len);
+    return chunked_workspace_bytes(view, batch, max_ctx_len, pick_chunk_tokens(view, batch, max_ctx_len));
 }
 
 extern "C" int paged_decode_attn(const void* q, void* out, const void* kv_pool,
@@ -574,20 +781,6 @@ extern "C" int paged_decode_attn(const void* q, void* out, const void* kv_pool,
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
     hipStream_t st = (hipStream_t)hip_stream;
 
-    if (kernel == 1 && max_ctx_len > 0)
-        return launch_streamk(q, out, kv_pool, block_table, block_table_stride, ctx_lens, batch,
-                              max_ctx_len, view, sc, workspace, workspace_bytes, st, nullptr, nullptr, 1);
-
-    const int chunk = pick_chunk_tokens(view, batch, max_ctx_len);
-    int64_t max_chunks = ((int64_t)max_ctx_len + chunk - 1) / chunk;
-    if (max_chunks < 1) max_chunks = 1;
-    const size_t need = chunked_workspace_bytes(view, batch, max_ctx_len);
-    if (max_chunks > 1) {
-        if (!workspace) return KV_ERR_INVALID_ARG;
-        if (workspace_bytes < need) return KV_ERR_WORKSPACE;
-        if (((uintptr_t)workspace & 255u) != 0) return KV_ERR_INVALID_ARG;
-    }
-
     decode_args a;
     a.q = (const uint16_t*)q;
     a.out = (uint16_t*)out;
@@ -598,10 +791,33 @@ extern "C" int paged_decode_attn(const void* q, void* out, const void* kv_pool,
     a.v = kv_view_to_dev(view);
     a.scale_log2e = sc * 1.4426950408889634f;
     a.group = view->group;
-    a.chunk_tokens = chunk;
+    a.max_ctx_len = max_ctx_len;
+    a.sync = nullptr;
+    int64_t chunk = pick_chunk_tokens(view, batch, max_ctx_len);
+
+    if (kernel == 1 && max_ctx_len > 0) {
+        const int rc = check_streamk(view, batch, max_ctx_len, workspace, workspace_bytes);
+        if (rc) return rc;
+        chunk = small_batch_chunk(view, batch, max_ctx_len);
+        if (chunk == 0)
+            return launch_streamk(q, out, kv_pool, block_table, block_table_stride, ctx_lens, batch, max_ctx_len,
+                                  view, sc, workspace, st, nullptr, nullptr, 1);
+        if (((int64_t)max_ctx_len + chunk - 1) / chunk <= kFusedChunks &&
+            (int64_t)batch * view->n_kv_local <= (int64_t)KV_DECODE_SYNC_WORDS)
+            a.sync = (unsigned long long*)workspace;
+    }
+
+    int64_t max_chunks = ((int64_t)max_ctx_len + chunk - 1) / chunk;
+    if (max_chunks < 1) max_chunks = 1;
+    if (max_chunks > 1 && kernel != 1) {
+        if (!workspace) return KV_ERR_INVALID_ARG;
+        if (workspace_bytes < chunked_workspace_bytes(view, batch, max_ctx_len, chunk)) return KV_ERR_WORKSPACE;
+        if (((uintptr_t)workspace & 255u) != 0) return KV_ERR_INVALID_ARG;
+    }
+    a.chunk_tokens = (int32_t)chunk;
     a.max_chunks = (int32_t)max_chunks;
     const int64_t recs = (int64_t)batch * view->n_q_local * max_chunks;
-    // (the chunked kernels keep off the arrival words at the start of the workspace)
+    // (the partials keep off the arrival words at the start of the workspace)
     char* ws_base = workspace ? (char*)workspace + KV_DECODE_SYNC_BYTES : nullptr;
     a.part_acc = (float*)ws_base;
     a.part_ml = max_chunks > 1 ? (float*)(ws_base + align_up((size_t)recs * D * 4, 256)) : nullptr;
@@ -609,25 +825,24 @@ extern "C" int paged_decode_attn(const void* q, void* out, const void* kv_pool,
     const dim3 grid((unsigned)max_chunks, (unsigned)view->n_kv_local, (unsigned)batch);
     int slot = kv_prof_begin(KV_PROF_DECODE_MAIN, st);
     int rc = KV_OK;
-    if (kernel == 3 || kernel == 1)
-        hipLaunchKernelGGL(decode_mfma_kernel, grid, dim3(kThreads), 0, st, a);
-    else
+    if (kernel == 3 || kernel == 1) {
+        if (D == 128) launch_chunk<128, 4, false>(a, grid, st);
+        else launch_chunk<64, 8, true>(a, grid, st);
+    } else {
         rc = (D == 128) ? launch_valu_for_group<128>(a, grid, st) : launch_valu_for_group<64>(a, grid, st);
+    }
     if (rc) return rc;
     kv_prof_end(KV_PROF_DECODE_MAIN, slot, st);
     rc = kv_record_hip_error(hipGetLastError(), "paged_decode_attn launch");
-    if (rc) return rc;
-    if (max_chunks > 1) {
-        slot = kv_prof_begin(KV_PROF_DECODE_MERGE, st);
-        dim3 mgrid((unsigned)view->n_q_local, (unsigned)batch);
-        if (D == 128)
-            hipLaunchKernelGGL(decode_merge_kernel<128>, mgrid, dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL(decode_merge_kernel<64>, mgrid, dim3(256), 0, st, a);
-        kv_prof_end(KV_PROF_DECODE_MERGE, slot, st);
-        rc = kv_record_hip_error(hipGetLastError(), "paged_decode_attn merge launch");
-    }
-    return rc;
+    if (rc || max_chunks <= 1 || a.sync) return rc;
+    slot = kv_prof_begin(KV_PROF_DECODE_MERGE, st);
+    dim3 mgrid((unsigned)view->n_q_local, (unsigned)batch);
+    if (D == 128)
+        hipLaunchKernelGGL(decode_merge_kernel<128>, mgrid, dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL(decode_merge_kernel<64>, mgrid, dim3(256), 0, st, a);
+    kv_prof_end(KV_PROF_DECODE_MERGE, slot, st);
+    return kv_record_hip_error(hipGetLastError(), "paged_decode_attn merge launch");
 }
 
 // ---- paged_decode_attn for callers that cannot allocate ------------------------------------------
@@ -712,7 +927,8 @@ extern "C" int paged_decode_attn_mixed(const void* q, void* out, const void* kv_
         if (pick_kernel(views[i], batch) != 1) return KV_ERR_UNSUPPORTED;
     if (batch > 65535 || v0->n_kv_local > 65535) return KV_ERR_UNSUPPORTED;
     const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)v0->geom.head_dim);
-    return launch_streamk(q, out, kv_pool, block_table, block_table_stride, ctx_lens, batch, max_ctx_len,
-                          v0, sc, workspace, workspace_bytes, (hipStream_t)hip_stream, view_ids, views,
-                          n_views);
+    const int rc = check_streamk(v0, batch, max_ctx_len, workspace, workspace_bytes);
+    if (rc) return rc;
+    return launch_streamk(q, out, kv_pool, block_table, block_table_stride, ctx_lens, batch, max_ctx_len, v0, sc,
+                          workspace, (hipStream_t)hip_stream, view_ids, views, n_views);
 }

@@ -1,0 +1,113 @@
+"""GPU parity of the chunked matrix-core decode kernel, which serves small batches and head_dim 64, and of the
+even-split kernels with several heads per wavefront at the sizes where the library no longer picks them
+by itself."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import LAYOUT_DP, LAYOUT_TP
+from paper_2602_22593_amd import binding as kv
+from paper_2602_22593_amd import workloads as wl
+
+from helpers import bf16_bits_to_f64, make_case
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+MAX_ABS, MEAN_ABS = 2e-2, 2e-3   # bf16 output of O(1) values, the bar of every decode kernel
+
+
+def dev_u16(a):
+    return torch.from_numpy(a.view(np.int16)).to(DEV)
+
+
+def decode(c, view, workspace, views=None, view_ids=None):
+    out = kv.paged_decode_attn(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV),
+                               torch.from_numpy(c.ctx).to(DEV), view, max_ctx_len=int(c.ctx.max()),
+                               workspace=workspace)
+    torch.cuda.synchronize()
+    return bf16_bits_to_f64(out.cpu().numpy().view(np.uint16))
+
+
+def check(got, want, what, max_abs=MAX_ABS, mean_abs=MEAN_ABS):
+    assert np.isfinite(got).all(), f"{what}: non-finite output"
+    err = np.abs(got - want)
+    assert err.max() <= max_abs and err.mean() <= mean_abs, f"{what}: {err.max():.3e} {err.mean():.3e}"
+
+
+LENS = {
+    "one token": [1],
+    "around a tile and a chunk": [31, 32, 33, 127, 128, 129, 0],
+    "eight chunks, last one full": [1024],              # the last chunk to arrive combines them
+    "eight chunks and a token": [1025, 3, 0, 640],      # a second launch does
+    "long list": [9000, 1, 130],
+    "most one-round workgroups": [2049, 5, 900, 2048],
+}
+
+
+@pytest.mark.parametrize("lens", list(LENS.values()), ids=list(LENS))
+@pytest.mark.parametrize("hq,hkv,triple,bs", [
+    (32, 8, (LAYOUT_DP, 1, 0), 16), (64, 8, (LAYOUT_TP, 8, 5), 16), (8, 8, (LAYOUT_TP, 2, 1), 32),
+    (24, 2, (LAYOUT_DP, 2, 1), 48), (32, 2, (LAYOUT_DP, 1, 0), 16), (6, 2, (LAYOUT_TP, 2, 0), 16)])
+def test_small_batches(hq, hkv, triple, bs, lens):
+    """Group sizes 4, 8, 1, 12, 16 and 3, three block sizes, every layout; two calls on one workspace give
+    the same bytes and leave its arrival words zero."""
+    w = wl.Workload("small", 85, hq, hkv, 128, bs, len(lens), "x", ())
+    c = make_case(w, triple, np.array(lens, dtype=np.int32))
+    view = kv.kv_view_create(hq, hkv, 128, bs, *triple)
+    ws = torch.zeros(kv.paged_decode_attn_workspace_bytes(view, len(lens), max(lens)), dtype=torch.uint8, device=DEV)
+    got = decode(c, view, ws)
+    check(got, oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx), f"{hq}/{hkv} {triple} {lens}")
+    assert not bool(ws[:kv.KV_DECODE_SYNC_BYTES].any())
+    assert np.array_equal(got, decode(c, view, ws))
+
+
+@pytest.mark.parametrize("lens", [[1, 16, 17, 64], [255, 256, 257, 0, 511, 512], [513, 40, 4100]])
+@pytest.mark.parametrize("hq,hkv,triple,bs", [
+    (8, 2, (LAYOUT_DP, 1, 0), 16), (16, 2, (LAYOUT_TP, 2, 1), 32), (4, 2, (LAYOUT_DP, 2, 0), 48), (8, 8, (LAYOUT_TP, 4, 3), 16)])
+def test_head_dim_64(hq, hkv, triple, bs, lens):
+    """Against the oracle, and as close to it as the vector-ALU kernel, whose weights stay in fp32: the matrix
+    cores take them as the sum of two bf16 numbers, 16 bits of mantissa, so that outputs of O(1) move by
+    2^-16 at most before the rounding to bf16.  Where that moves a value over a rounding boundary the two
+    kernels differ by one bf16 step (2^-7 relative at most)."""
+    w = wl.Workload("d64", 86, hq, hkv, 64, bs, len(lens), "x", ())
+    c = make_case(w, triple, np.array(lens, dtype=np.int32))
+    view = kv.kv_view_create(hq, hkv, 64, bs, *triple)
+    ws = torch.zeros(max(256, kv.paged_decode_attn_workspace_bytes(view, len(lens), max(lens))), dtype=torch.uint8, device=DEV)
+    want = oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx)
+    got = decode(c, view, ws)
+    check(got, want, f"{hq}/{hkv} {triple} {lens}")
+    kv.kv_set_option("force_kernel", 2)
+    try:
+        valu = decode(c, view, ws)
+    finally:
+        kv.kv_set_option("force_kernel", 0)
+    assert (np.abs(got - valu) <= np.abs(valu) * 2.0 ** -7 + 2.0 ** -15).all()
+    # squared errors against the oracle, summed: no further off than the vector-ALU kernel (rounding to
+    # bf16 dominates both; 2 % for the boundary cases that fall differently)
+    assert ((got - want) ** 2).sum() <= 1.02 * ((valu - want) ** 2).sum() + 1e-12
+
+
+@pytest.mark.parametrize("hq,hkv,triple", [
+    (32, 8, (LAYOUT_DP, 1, 0)), (32, 8, (LAYOUT_TP, 2, 1)), (64, 8, (LAYOUT_DP, 1, 0)), (32, 8, (LAYOUT_TP, 4, 1)),
+    (24, 8, (LAYOUT_DP, 1, 0))])
+def test_several_heads_per_wavefront_on_request(hq, hkv, triple):
+    """The even-split kernels with 2 and 4 heads per wavefront (kept for large batches) at every fill of their
+    last tile, with one and with two layouts in the batch."""
+    lens = np.array(list(range(41)) + [127, 128, 129, 1023, 1025, 2050], dtype=np.int32)
+    w = wl.Workload("wide2", 87, hq, hkv, 128, 16, len(lens), "x", ())
+    c = make_case(w, triple, lens)
+    view = kv.kv_view_create(hq, hkv, 128, 16, *triple)
+    want = oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx)
+    kv.kv_set_option("waves_per_cu", 4)
+    try:
+        ws = torch.zeros(kv.paged_decode_attn_workspace_bytes(view, len(lens), 2050), dtype=torch.uint8, device=DEV)
+        check(decode(c, view, ws), want, f"{hq}/{hkv} {triple}")
+        # (the same layout under two ids: the kernels that look the layout up per sequence)
+        ids = torch.from_numpy((np.arange(len(lens)) % 2).astype(np.int32)).to(DEV)
+        out = kv.paged_decode_attn_mixed(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV),
+                                         torch.from_numpy(c.ctx).to(DEV), ids, [view, view], 2050, workspace=ws)
+        torch.cuda.synchronize()
+        check(bf16_bits_to_f64(out.cpu().numpy().view(np.uint16)), want, f"mixed {hq}/{hkv} {triple}")
+    finally:
+        kv.kv_set_option("waves_per_cu", 0)
