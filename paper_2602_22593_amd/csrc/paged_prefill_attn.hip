@@ -18,9 +18,9 @@
 //                                             in the address of four consecutive elements of one
 //                                             row and receives one element of each of four rows
 // so the accumulator layout of S^T is already the B layout of the second product and the running
-// maximum crosses lanes only when it moves.  The sum of the weights of a column comes out of the
-// matrix cores as well (one more product, with an all-ones A operand), from the same bf16 weights
-// as the numerator.  Column c of row block b of wavefront w is row
+// maximum crosses lanes only when it moves.  Each lane sums the bf16 weights of its own keys, the
+// same that the numerator takes, and the four lanes of a column are added up once at the end.
+// Column c of row block b of wavefront w is row
 // rho = (w R + b) 16 + c of the tile: token rho / Gp, head rho % Gp, Gp = G rounded up to a power
 // of two (rows with head >= G are padding).  The causal mask keeps
 // token t for a query at position pos iff t <= pos; since pos < ctx_len it also masks the slots
@@ -77,6 +77,37 @@ __device__ __forceinline__ float wave_inclusive_sum(float x, int lane)
     const float t0 = __shfl(x, 15), t1 = __shfl(x, 31), t2 = __shfl(x, 47);
     const int row = lane >> 4;
     return x + (row >= 1 ? t0 : 0.f) + (row >= 2 ? t1 : 0.f) + (row >= 3 ? t2 : 0.f);
+}
+
+// Maximum over the four lanes of a column (the same r, every quad), left in all of them.  By register swaps:
+// exchanges through LDS keep address registers alive throughout the loop, for which others are spilled.
+__device__ __forceinline__ float column_max(float x)
+{
+    const uint32_t b = __builtin_bit_cast(uint32_t, x);
+    const auto rows = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const uint32_t r0 = rows[0], r1 = rows[1];   // (a bit cast of the element itself reads element 0)
+    const uint32_t c = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)));
+    const auto halves = __builtin_amdgcn_permlane32_swap(c, c, false, false);
+    const uint32_t h0 = halves[0], h1 = halves[1];
+    return fmaxf(__builtin_bit_cast(float, h0), __builtin_bit_cast(float, h1));
+}
+
+// The sum over the same lanes.
+__device__ __forceinline__ float column_sum(float x)
+{
+    const uint32_t b = __builtin_bit_cast(uint32_t, x);
+    const auto rows = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const uint32_t r0 = rows[0], r1 = rows[1];
+    const uint32_t c = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1));
+    const auto halves = __builtin_amdgcn_permlane32_swap(c, c, false, false);
+    const uint32_t h0 = halves[0], h1 = halves[1];
+    return __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
+}
+
+// l + the two bf16 values of a packed pair, summed in fp32.
+__device__ __forceinline__ float add_pair(uint32_t packed, float l)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, packed), __builtin_bit_cast(bf16x2, 0x3f803f80u), l, false);
 }
 
 typedef short bits16x4 __attribute__((ext_vector_type(4)));
@@ -157,6 +188,11 @@ __device__ __forceinline__ void work_range(const prefill_args& a, int part, int 
     to = uniform(cut(part + 1));
 }
 
+// What bounds the loop is how far operand reads run ahead of the products, and that is a matter of registers: with
+// the row sums taken by the matrix cores (eight sums, four of the all-ones operand) and the maximum exchanged
+// through LDS the compiler had one register pair of V operands to spare and waited for every read (8 prompts of
+// 4096 tokens, 32 query heads, 1095 us instead of 1069; 4 query heads 159 instead of 150; one prompt of 1000
+// tokens 37.5 instead of 34).
 // Three workgroups per compute unit (32 KiB of LDS and at most 168 registers each): with nothing staged
 // in registers the kernel fits, and a third wavefront per SIMD hides more of the chain K read -> scores ->
 // softmax -> V read -> output of the other two than the longer 64-key tiles of two workgroups did.
@@ -299,13 +335,13 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
 
     float m[R];
     float neg_mc[R];  // -m scale log2(e), the addend of the exponent; kUnset while m = -inf
-    f32x4 l[R];     // sum of the weights of the column, the same in all four entries and lanes of it
+    float l[R];     // sum of the weights of this lane's keys of the column
     f32x4 o[R][8];  // o[b][j][i] = O[column][16 j + 4 quad + i]
 #pragma unroll
     for (int b = 0; b < R; ++b) {
         m[b] = kNegInf;
         neg_mc[b] = kUnset;
-        l[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        l[b] = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -315,7 +351,6 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // the scores have it
     const int vt_tok = 4 * (r >> 2) + quad;
     const int vt_swz = 2 * ((vt_tok >> 2) & 3);   // the same for token 16 + vt_tok
-    const bf16x8 ones = as_bf16x8(kv_u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
 
     if (t_begin < n_tiles) stage_tile(t_begin, s_k0, s_v0);
     // ---- this lane's query rows (B operands), one per row block --------------------------------
@@ -341,15 +376,9 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
         for (int kk = 0; kk < 4; ++kk)
             qb[b][kk] = as_bf16x8(*reinterpret_cast<const kv_u32x4*>(qrow + kk * 64));
     }
-    // keys below this position need no mask for any column of the wavefront
-    int min_pos = pos[0];
-#pragma unroll
-    for (int b = 1; b < R; ++b) min_pos = min(min_pos, pos[b]);
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) min_pos = min(min_pos, __shfl_xor(min_pos, off));
-    min_pos = uniform(min_pos);
-    int max_pos = pos[R - 1];
-    max_pos = uniform(__shfl(max_pos, 15));  // rows ascend with the column: the last is the largest
+    // positions ascend with the column, from the first of row block 0 to the last of row block R - 1: keys
+    // up to min_pos need no mask for any column of the wavefront, keys past max_pos are for none
+    const int min_pos = uniform(pos[0]), max_pos = __builtin_amdgcn_readlane(pos[R - 1], 15);
 
     staged();
 
@@ -414,8 +443,7 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
                 if (__builtin_amdgcn_ballot_w64(tmax > kLag) != 0) {
                     float mx = fmaxf(fmaxf(fmaxf(sacc[b][0][0], sacc[b][0][1]), fmaxf(sacc[b][0][2], sacc[b][0][3])),
                                      fmaxf(fmaxf(sacc[b][1][0], sacc[b][1][1]), fmaxf(sacc[b][1][2], sacc[b][1][3])));
-                    mx = fmaxf(mx, __shfl_xor(mx, 16));
-                    mx = fmaxf(mx, __shfl_xor(mx, 32));
+                    mx = column_max(mx);
                     const float m_new = fmaxf(m[b], mx);
                     if (m_new != kNegInf) {
                         const float alpha = fast_exp2((m[b] - m_new) * a.scale_log2e);   // 0 on the first move
@@ -434,13 +462,15 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
                 float p[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) p[u] = fast_exp2(t[u]);
-                pb[b] = as_bf16x8(kv_u32x4{pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
-                                           pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])});
+                const kv_u32x4 pw = {pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
+                                     pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])};
+                // the denominator sums the same rounded weights
+#pragma unroll
+                for (int u = 0; u < 4; ++u) l[b] = add_pair(pw[u], l[b]);
+                pb[b] = as_bf16x8(pw);
             }
             // ---- O^T += V^T P^T --------------------------------------------------------------------------
             __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-            for (int b = 0; b < R; ++b) l[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[b], l[b], 0, 0, 0);
             const char* vt = reinterpret_cast<const char*>(sv) + vt_tok * 256 + (r & 1) * 8;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -469,7 +499,7 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // ---- normalise and store ------------------------------------------------------------------------
 #pragma unroll
     for (int b = 0; b < R; ++b) {
-        const float lt = l[b][0];
+        const float lt = column_sum(l[b]);
         const int64_t orow = row_of(b, false);
         if (orow >= 0 && a.splits > 1) {
             // partial of this key range: row = index of the output row

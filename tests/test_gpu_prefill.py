@@ -132,6 +132,22 @@ def test_sharp_and_flat_softmax(triple, scale):
     check_close(got, want, f"scale {scale} {triple}")
 
 
+@pytest.mark.parametrize("n", [4, 16, 17, 32, 33, 100])
+def test_reference_maximum_covers_every_key(n):
+    """Exponents hundreds apart (scale 30): a reference maximum that missed the keys held by some of a column's
+    four lanes would give weights past 2^127.  Same bound as above: the softmax is one-hot but for near ties,
+    whose scores are exact to 2^-23 x 2000, far below 1."""
+    w = wl.Workload("prefill_lanes", 88, 8, 2, 128, 16, 1, "x", ())
+    ctx = np.array([n], dtype=np.int32)
+    c = make_prefill_case(w, (LAYOUT_DP, 1, 0), ctx, ctx)
+    out = kv.paged_prefill_attn(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV),
+                                torch.from_numpy(c.ctx).to(DEV), torch.from_numpy(c.q_off.astype(np.int32)).to(DEV),
+                                gpu_view(w, (LAYOUT_DP, 1, 0)), max_ctx_len=n, max_q_len=n, scale=30.0)
+    torch.cuda.synchronize()
+    got = bf16_bits_to_f64(out.cpu().numpy().view(np.uint16))
+    check_close(got, oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off, 30.0), f"n {n}")
+
+
 @pytest.mark.parametrize("hq,hkv,triple,batch", [
     (8, 8, (LAYOUT_DP, 1, 0), 13),       # eight local heads: one per XCD
     (16, 16, (LAYOUT_DP, 1, 0), 6),      # sixteen: two per XCD
