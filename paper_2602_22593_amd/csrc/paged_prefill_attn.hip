@@ -25,6 +25,9 @@
 // of two (rows with head >= G are padding).  The causal mask keeps
 // token t for a query at position pos iff t <= pos; since pos < ctx_len it also masks the slots
 // past the end of the sequence.
+#include <algorithm>
+#include <type_traits>
+
 #include "decode_common.h"
 
 using namespace kvdec;
@@ -50,14 +53,15 @@ struct prefill_args {
     float scale_log2e;
     int32_t group;          // G <= 16 query heads per KV head
     int32_t group_shift;    // log2 of G rounded up to a power of two: rows per token in the tile
-    int32_t splits;         // workgroups sharing the key range of one query tile
     int32_t tile_shift;     // log2 of the new tokens per query tile
     int32_t batch;
     int32_t slots;          // query tiles per KV head as numbered by slot_sequence(), gaps included
     int32_t xcds_per_head;  // how the tiles are dealt out to the XCDs, see the kernel
-    int64_t rows;           // total_q * n_q_local: rows of the partial arrays
-    float* part_o;          // [splits][rows][128] un-normalised sums, when splits > 1
-    float* part_ml;         // [splits][rows][2]   (reference maximum in score units, sum of weights)
+    // launches that cut key ranges, see plan_pieces()
+    int32_t most_records;   // tokens that the partial arrays have room for
+    int4* tiles;            // [slots] (first record, pieces, first token in q, tokens), for the merge kernel
+    float* part_o;          // [record = a piece's token][n_q_local][128] un-normalised sums
+    float* part_ml;         // [record][n_q_local][2]  (reference maximum in score units, sum of weights)
 };
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -80,7 +84,7 @@ __device__ __forceinline__ float wave_inclusive_sum(float x, int lane)
 }
 
 // Maximum over the four lanes of a column (the same r, every quad), left in all of them.  By register swaps:
-// exchanges through LDS keep address registers alive throughout the loop, for which others are spilled.
+// lane exchanges through LDS hold two address registers throughout the loop, for which others are spilled.
 __device__ __forceinline__ float column_max(float x)
 {
     const uint32_t b = __builtin_bit_cast(uint32_t, x);
@@ -90,6 +94,23 @@ __device__ __forceinline__ float column_max(float x)
     const auto halves = __builtin_amdgcn_permlane32_swap(c, c, false, false);
     const uint32_t h0 = halves[0], h1 = halves[1];
     return fmaxf(__builtin_bit_cast(float, h0), __builtin_bit_cast(float, h1));
+}
+
+__device__ __forceinline__ float wave_sum(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_inclusive_sum(x, threadIdx.x & 63)), 63));
+}
+// Maximum over the 64 lanes, left in all of them.
+__device__ __forceinline__ float wave_max(float x)
+{
+    auto other = [](float y, auto ctrl) -> float {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, y), ctrl.value, 0xf, 0xf, false));
+    };
+    x = fmaxf(x, other(x, std::integral_constant<int, 0xB1>()));    // lanes 1 0 3 2
+    x = fmaxf(x, other(x, std::integral_constant<int, 0x4E>()));    // lanes 2 3 0 1
+    x = fmaxf(x, other(x, std::integral_constant<int, 0x141>()));   // mirror of the half row
+    x = fmaxf(x, other(x, std::integral_constant<int, 0x140>()));   // mirror of the row
+    return column_max(x);
 }
 
 // The sum over the same lanes.
@@ -188,6 +209,124 @@ __device__ __forceinline__ void work_range(const prefill_args& a, int part, int 
     to = uniform(cut(part + 1));
 }
 
+// How the key ranges of the query tiles are cut into pieces, one per workgroup, where the tiles alone
+// would leave compute units idle: no piece is longer than K key tiles, whichever tile it belongs to.
+// (With one number of pieces for all tiles, set by the bound on the lengths, most of the chip waits for
+// the longest sequence: 512 tokens each on 1000 to 16000 in eight sequences, 4 query heads, 130 us instead
+// of 89; a prompt of 4096 tokens, 66 instead of 44.)  K is the candidate with the least estimated time, in
+// microseconds: per key tile 1.0 with one workgroup on each compute unit, 1.2 with two, 1.7 with three
+// (measured), and for a piece of a cut tile the writing and reading of its partial sums (66 KiB).
+// Every workgroup works it out alike: lane l of a wavefront holds slots l, l + 64, .., the
+// wavefronts share the candidates.  Returns the pieces per head; s_slot[slot] = (pieces up to
+// and including it << 10 | its sequence, first record of its partials).
+constexpr int kMostSlots = 1024;        // of a launch that cuts
+constexpr int kCandidates = 32;         // K = longest range / (1, 1.25, .. 7.75, 8, 10.5, 13, 15.5)
+constexpr float kLeastSteps = 4.f;      // key tiles of the shortest piece
+constexpr float kPieceTime = 0.02f, kCutTime = 3.f;
+__device__ __forceinline__ int plan_pieces(const prefill_args& a, int2* s_slot, float* s_cost, int32_t* s_qoff,
+                                           int32_t* s_ctx, kv_u32x4* s_tile0, kv_u32x4* s_tile1)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    for (int s = tid; s <= a.batch; s += kThreads) {
+        const int q0 = a.q_off[s], n = a.ctx_lens[min(s, a.batch - 1)];   // (both on their way at once)
+        s_qoff[s] = q0;
+        s_ctx[s] = n;
+    }
+    __syncthreads();
+    const int T = 1 << a.tile_shift, groups = (a.slots + 63) >> 6;
+    // per slot: key tiles, new tokens, the first one's row in q, sequence
+    auto tile = [&](int slot) -> kv_u32x4* { return slot < 512 ? s_tile0 + slot : s_tile1 + (slot - 512); };
+    for (int slot = tid; slot < 64 * groups; slot += kThreads) {
+        int s = 0;
+        for (int span = a.batch; span > 1;) {
+            const int half = span >> 1;
+            const bool up = (s_qoff[s + half] >> a.tile_shift) + s + half <= slot;
+            s += up ? half : 0;
+            span = up ? span - half : half;
+        }
+        const int q0 = s_qoff[s], q_len = s_qoff[s + 1] - q0, n = s_ctx[s];
+        const int j0 = (((q_len + T - 1) >> a.tile_shift) - 1 - (slot - ((q0 >> a.tile_shift) + s))) << a.tile_shift;
+        const int tokens = min(T, q_len - j0);
+        const bool none = slot >= a.slots || j0 < 0 || n <= 0;
+        *tile(slot) = none ? kv_u32x4{0u, 0u, 0u, (uint32_t)s}
+                           : kv_u32x4{(uint32_t)((n - q_len + j0 + tokens - 1) / kKeys + 1), (uint32_t)tokens,
+                                      (uint32_t)(q0 + j0), (uint32_t)s};
+    }
+    __syncthreads();
+    float longest = 0.f, work = 0.f;
+    for (int g = 0; g < groups; ++g) {
+        const float steps = (float)(*tile(64 * g + lane))[0];
+        longest = fmaxf(longest, steps);
+        work += steps;
+    }
+    longest = wave_max(longest);
+    work = wave_sum(work);
+    // (a reciprocal a little low, so that rounding never makes two pieces of a tile of exactly K)
+    auto steps_of = [&](int c) -> float {
+        const float parts = 1.f + 0.25f * c + (c > 28 ? 2.25f * (c - 28) : 0.f);
+        return fmaxf(ceilf(longest * __builtin_amdgcn_rcpf(parts)), kLeastSteps);
+    };
+    auto inverse = [&](int c) -> float { return __builtin_amdgcn_rcpf(steps_of(c)) * 0.999999f; };
+    auto pieces_of = [&](uint32_t steps, float inv) -> float { return ceilf((float)steps * inv); };
+    const float heads = (float)a.v.n_kv_local;
+    constexpr int kEach = kCandidates / 4;
+    float records[kEach], count[kEach];
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) records[k] = count[k] = 0.f;
+    for (int g = 0; g < groups; ++g) {
+        const kv_u32x4 t = *tile(64 * g + lane);
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) {
+            const float p = pieces_of(t[0], inverse(4 * k + wave));
+            count[k] += p;
+            records[k] += p > 1.f ? p * (float)t[1] : 0.f;
+        }
+    }
+    float cost = 1e30f;
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const float K = steps_of(4 * k + wave), rec = wave_sum(records[k]), pieces = wave_sum(count[k]);
+        const float per_cu = pieces * heads * (1.f / 256.f), mean = work / pieces;
+        const float step = per_cu <= 1.f ? 1.f : per_cu <= 2.f ? 1.2f : per_cu <= 3.f ? 1.7f : 1e6f;   // (no second round)
+        const float c = fmaxf(K, mean * step + 0.6f * (K - mean)) +
+                        (rec > 0.f ? kCutTime + rec * heads / (float)T * kPieceTime : 0.f);
+        cost = lane == k && rec <= (float)a.most_records ? fminf(c, 1e29f) : cost;
+    }
+    if (lane < kEach) s_cost[4 * lane + wave] = cost;
+    __syncthreads();
+    // (candidate 0 cuts nothing and always fits; the first of equal ones)
+    const float mine = lane < kCandidates ? s_cost[lane] : 1e30f, least = -wave_max(-mine);
+    const int best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(mine == least));
+    const float inv = inverse(best);
+    int end = 0, base = 0;
+    for (int g = 0; g < groups; ++g) {
+        const int slot = 64 * g + lane;
+        const kv_u32x4 t = *tile(slot);
+        const float p = pieces_of(t[0], inv), rec = p > 1.f ? p * (float)t[1] : 0.f;
+        const float p_incl = wave_inclusive_sum(p, lane), r_incl = wave_inclusive_sum(rec, lane);
+        const int my_base = base + (int)(r_incl - rec);
+        if (wave == 0 && slot < a.slots) {
+            s_slot[slot] = make_int2((end + (int)p_incl) << 10 | (int)t[3], my_base);
+            if (blockIdx.x == 0) a.tiles[slot] = make_int4(my_base, (int)p, (int)t[2], (int)t[1]);
+        }
+        end += __builtin_amdgcn_readlane((int)p_incl, 63);
+        base += __builtin_amdgcn_readlane((int)r_incl, 63);
+    }
+    __syncthreads();
+    return uniform(end);
+}
+
+// The slot whose pieces include piece `idx` of the head: 64 probes at a time.
+__device__ __forceinline__ int piece_slot(const int2* s_slot, int slots, int idx, int lane)
+{
+    const int step = (slots + 63) >> 6;
+    const int last = min(lane * step + step, slots) - 1;
+    const bool before = lane * step < slots && (s_slot[max(last, 0)].x >> 10) <= idx;
+    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(before)) * step;
+    const bool in = lane < step && c + lane < slots && (s_slot[min(c + lane, slots - 1)].x >> 10) <= idx;
+    return min(c + __builtin_popcountll(__builtin_amdgcn_ballot_w64(in)), slots - 1);
+}
+
 // What bounds the loop is how far operand reads run ahead of the products, and that is a matter of registers: with
 // the row sums taken by the matrix cores (eight sums, four of the all-ones operand) and the maximum exchanged
 // through LDS the compiler had one register pair of V operands to spare and waited for every read (8 prompts of
@@ -196,7 +335,8 @@ __device__ __forceinline__ void work_range(const prefill_args& a, int part, int 
 // Three workgroups per compute unit (32 KiB of LDS and at most 168 registers each): with nothing staged
 // in registers the kernel fits, and a third wavefront per SIMD hides more of the chain K read -> scores ->
 // softmax -> V read -> output of the other two than the longer 64-key tiles of two workgroups did.
-template <int R>
+// CUT: the items are the pieces of plan_pieces() instead of whole query tiles.
+template <int R, bool CUT>
 __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefill_args a)
 {
     // [buffer][row][piece]: K pieces swizzled (piece c of row t at c ^ (t % 16)); V pieces at
@@ -205,6 +345,8 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // the operands being read from the other
     __shared__ kv_u32x4 s_k0[512 * kSub], s_k1[512 * kSub];
     __shared__ kv_u32x4 s_v0[512 * kSub], s_v1[512 * kSub];
+    __shared__ int2 s_slot[CUT ? kMostSlots : 1];
+    __shared__ float s_cost[CUT ? kCandidates : 1];
 
     const int lane0 = threadIdx.x & 63;
     const int wave = uniform((int)threadIdx.x >> 6);
@@ -219,16 +361,25 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // 16 prompts of 128 to 4000 tokens, 32 query heads, 1375 us instead of 805; 64 such prompts with 4
     // query heads 564 instead of 494.  Dealing tiles out one by one balances as well but spreads every
     // pair over all L2s: 32 prompts of 2048 tokens, 4 query heads, 187 us instead of 178.)
-    int hl, item, item_end, item_step;   // item = slot * splits + key split; slots as in slot_sequence()
-    {
+    int hl, item, item_end, item_step;   // item: a slot, as in slot_sequence(); CUT: (head, piece)
+    int per_head = 0;
+    if constexpr (CUT) {
+        // a contiguous eighth of the (head, piece) list per XCD
+        per_head = plan_pieces(a, s_slot, s_cost, reinterpret_cast<int32_t*>(s_k0), reinterpret_cast<int32_t*>(s_v0), s_k1, s_v1);
+        const int N = per_head * v.n_kv_local, xcd = (int)blockIdx.x & 7;
+        hl = 0;
+        item = xcd * (N >> 3) + min(xcd, N & 7) + ((int)blockIdx.x >> 3);
+        item_end = (xcd + 1) * (N >> 3) + min(xcd + 1, N & 7);
+        item_step = (int)gridDim.x >> 3;
+    } else {
         const int L = (int)blockIdx.x, N = (int)gridDim.x, Hl = v.n_kv_local;
         const int xcd = L & 7, k = L >> 3;
         if (a.xcds_per_head == 0) {
-            // a contiguous eighth of the (head, slot, split) list per XCD; one item per workgroup
+            // a contiguous eighth of the (head, slot) list per XCD; one item per workgroup
             const int base = N >> 3, rem = N & 7;
-            const int x = xcd * base + min(xcd, rem) + k, per_head = a.slots * a.splits;
-            hl = x / per_head;
-            item = x - hl * per_head;
+            const int x = xcd * base + min(xcd, rem) + k;
+            hl = x / a.slots;
+            item = x - hl * a.slots;
             item_end = item + 1;
             item_step = 1;
         } else if (a.xcds_per_head == 1) {
@@ -252,8 +403,19 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     int lane = lane0;
     asm volatile("" : "+v"(lane));
     const int r = lane & 15, quad = lane >> 4;
-    const int slot = item / a.splits, split = item - slot * a.splits;
-    const int s = slot_sequence(a, slot, lane);
+    int slot = item, s, piece = 0, pieces = 1, record = 0;
+    if constexpr (CUT) {
+        hl = item / per_head;
+        const int idx = item - hl * per_head;
+        slot = uniform(piece_slot(s_slot, a.slots, idx, lane));
+        const int end_s = uniform(s_slot[slot].x), before = slot > 0 ? uniform(s_slot[slot - 1].x) >> 10 : 0;
+        record = uniform(s_slot[slot].y);
+        s = end_s & 1023;
+        pieces = (end_s >> 10) - before;
+        piece = idx - before;
+    } else {
+        s = slot_sequence(a, slot, lane);
+    }
 
     const int n = a.ctx_lens[s];
     const int q0 = a.q_off[s];
@@ -266,9 +428,16 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     const int j_last = min(j0 + tokens_per_wg, q_len) - 1;   // last query token of this tile
     const int all_tiles = (first_pos + j_last) / kKeys + 1;   // key tiles 0 .. all_tiles - 1 of the query tile
     // this workgroup's share of them: [t_begin, n_tiles)
-    const int per_split = (all_tiles + a.splits - 1) / a.splits;
-    const int t_begin = split * per_split;
-    const int n_tiles = min(all_tiles, t_begin + per_split);
+    int t_begin = 0, n_tiles = all_tiles;
+    if constexpr (CUT) {
+        const int per_piece = (all_tiles + pieces - 1) / pieces;
+        t_begin = piece * per_piece;
+        n_tiles = min(all_tiles, t_begin + per_piece);
+        record += piece * (j_last - j0 + 1) - (q0 + j0);   // record of token j: record + q0 + j
+    } else {
+        // a start that the compiler knows to be 0 makes it double the loop's body and spill in it (8 % slower)
+        asm volatile("" : "+s"(t_begin), "+s"(n_tiles));
+    }
 
     // ---- staging: K and V tiles go from global memory straight into LDS, 16 bytes per lane; one
     // instruction of a wavefront fills 64 consecutive 16-byte slots = 4 rows of 16 pieces, and
@@ -501,9 +670,8 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     for (int b = 0; b < R; ++b) {
         const float lt = column_sum(l[b]);
         const int64_t orow = row_of(b, false);
-        if (orow >= 0 && a.splits > 1) {
-            // partial of this key range: row = index of the output row
-            const int64_t rec = (int64_t)split * a.rows + orow / D;
+        if (CUT && orow >= 0 && pieces > 1) {
+            const int64_t rec = (int64_t)record * v.n_q_local + orow / D;
             float* dst = a.part_o + rec * D + 4 * quad;
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(dst + 16 * jj) = o[b][jj];
@@ -526,53 +694,106 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     }
 }
 
-// out[row] = sum_z o_z 2^((m_z - M) c) / sum_z l_z 2^((m_z - M) c), M = max_z m_z; a split that saw
-// no valid key for the row has l = 0 and is skipped.  32 lanes per row, 4 columns each.
-__global__ __launch_bounds__(256) void prefill_merge_kernel(prefill_args a)
+// out[row] = sum_z o_z 2^((m_z - M) c) / sum_z l_z 2^((m_z - M) c), M = max_z m_z, over the pieces z of
+// the row's query tile; a piece that saw no valid key for the row has l = 0 and is skipped.  Block (x, y, z):
+// a sixteenth of the rows of slot x and KV head y; 32 lanes per row, 4 columns each.  Bound by the latency of its
+// loads: eight pieces are fetched at once.
+__global__ __launch_bounds__(kThreads) void prefill_merge_kernel(prefill_args a)
 {
-    const int64_t row = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-    const int cg = threadIdx.x & 31;
-    if (row >= a.rows) return;
-    float mm = kNegInf;
-    for (int z = 0; z < a.splits; ++z) {
-        const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + ((int64_t)z * a.rows + row) * 2);
-        if (ml.y > 0.f) mm = fmaxf(mm, ml.x);
-    }
+    const int4 tile = a.tiles[blockIdx.x];
+    const int pieces = tile.y, tokens = tile.w, G = a.group;
+    if (pieces <= 1) return;   // written by the main kernel, or not a tile
+    const int cg = threadIdx.x & 31, rows = tokens * G;
+    const int i = (int)blockIdx.z * (kThreads / 32) + (threadIdx.x >> 5);
+    if (i >= rows) return;
+    const int j = i / G, h = blockIdx.y * G + (i - j * G);
+    const int64_t rec0 = (int64_t)(tile.x + j) * a.v.n_q_local + h, rec_step = (int64_t)tokens * a.v.n_q_local;
+    constexpr int kBatch = 8;
+    float mm = kNegInf, lt = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float lt = 0.f;
-    for (int z = 0; z < a.splits; ++z) {
-        const int64_t rec = (int64_t)z * a.rows + row;
-        const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + rec * 2);
-        if (!(ml.y > 0.f)) continue;
-        const float w = fast_exp2((ml.x - mm) * a.scale_log2e);
-        lt += ml.y * w;
-        acc += *reinterpret_cast<const f32x4*>(a.part_o + rec * D + cg * 4) * w;
+    for (int z0 = 0; z0 < pieces; z0 += kBatch) {
+        float2 ml[kBatch];
+        f32x4 x[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {   // (past the end: the last one again, not used)
+            const int64_t rec = rec0 + min(z0 + u, pieces - 1) * rec_step;
+            ml[u] = *reinterpret_cast<const float2*>(a.part_ml + rec * 2);
+            x[u] = *reinterpret_cast<const f32x4*>(a.part_o + rec * D + cg * 4);
+        }
+        float mn = mm;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (z0 + u >= pieces || !(ml[u].y > 0.f)) ml[u] = make_float2(kNegInf, 0.f);
+            mn = fmaxf(mn, ml[u].x);
+        }
+        if (mn == kNegInf) continue;
+        const float keep = fast_exp2((mm - mn) * a.scale_log2e);
+        lt *= keep;
+        acc *= keep;
+        mm = mn;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float w = fast_exp2((ml[u].x - mn) * a.scale_log2e);
+            lt += ml[u].y * w;
+            acc += x[u] * w;
+        }
     }
     const float inv = 1.0f / lt;   // every query sees at least key 0
     uint2 pk;
     pk.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
     pk.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-    *reinterpret_cast<uint2*>(a.out + row * D + cg * 4) = pk;
+    *reinterpret_cast<uint2*>(a.out + ((int64_t)(tile.z + j) * a.v.n_q_local + h) * D + cg * 4) = pk;
 }
 
 constexpr int kRowBlocks = 2;  // 16-row blocks per wavefront (4 measured 2x slower: one wavefront per SIMD)
 
-// Workgroups sharing the key range of a query tile: only when the launch would otherwise leave
-// compute units idle (few sequences, few query tokens, long contexts): enough to fill the 768
-// workgroup slots of the chip (three per compute unit) once, measured better than one and a half
-// times; at least 512 keys each.
-int prefill_splits(const kv_view* view, int batch, int max_ctx_len, int max_q_len)
+// Key ranges are cut (plan_pieces) only where the launch would otherwise leave compute units idle: few
+// sequences, few new tokens, long contexts.  The partial sums get room for so many pieces per query
+// tile on average as fill the 768 workgroup slots of the chip (three per compute unit) once, one more
+// where the lengths may differ, kMostPieces at most, and none below `least` keys.
+constexpr int kMostPieces = 16;
+int query_tile_tokens(const kv_view* view)
 {
     int shift = 0;
     while ((1 << shift) < view->group) ++shift;
-    const int tokens_per_wg = (64 * kRowBlocks) >> shift;
-    const int64_t wgs = (int64_t)((max_q_len + tokens_per_wg - 1) / tokens_per_wg) * view->n_kv_local * batch;
+    return (64 * kRowBlocks) >> shift;
+}
+int prefill_pieces(int64_t wgs, int max_ctx_len, int least)
+{
     if (wgs >= 512) return 1;
     int s = (int)((768 + wgs - 1) / wgs);
-    const int most = max_ctx_len / 512;
-    if (s > most) s = most;
-    if (s > 16) s = 16;
+    if (s > max_ctx_len / least) s = max_ctx_len / least;
+    if (s > kMostPieces) s = kMostPieces;
     return s < 1 ? 1 : s;
+}
+// Room asked for, and the least that is accepted where there is more than the tiles alone need.
+struct prefill_room {
+    int64_t slots;
+    size_t ask, least;   // bytes; least = 0: an unusable workspace only means that nothing is cut
+    bool cut;
+};
+prefill_room prefill_workspace(const kv_view* view, int batch, int64_t total_q, int max_ctx_len, int max_q_len)
+{
+    const int tokens = query_tile_tokens(view);
+    const int64_t bound = (int64_t)((max_q_len + tokens - 1) / tokens) * view->n_kv_local * batch;
+    prefill_room r;
+    r.slots = total_q / tokens + batch;
+    const int64_t wgs = std::min(bound, r.slots * view->n_kv_local);
+    const int at_least = prefill_pieces(bound, max_ctx_len, 512);
+    // Planning and combining cost 4 us: a launch with a workgroup for each compute unit cuts long contexts only (one
+    // prompt of 2000 tokens, 8 KV heads, 66 us uncut, 69 cut), and pieces below 512 keys are for half a chip's tiles
+    // at most (33 tokens of eight sequences of 800, 1 KV head, 28.8 -> 21.3 us, but four prompts of 700, 2 KV
+    // heads, 26 -> 32).
+    int most = 1;
+    if (r.slots <= kMostSlots && (wgs <= 256 ? at_least > 1 || (wgs <= 128 && max_ctx_len >= 768)
+                                             : at_least > 1 && max_ctx_len >= 4096))
+        most = std::max(at_least, std::min(prefill_pieces(wgs, max_ctx_len, 256) + 1, kMostPieces));
+    const size_t record = (size_t)total_q * view->n_q_local * (D + 2) * 4;
+    r.least = at_least > 1 ? record * at_least : 0;
+    // (the list of the tiles comes on top, without which as many pieces as there is room for would just not fit)
+    r.ask = most > 1 ? record * most + (most < kMostPieces ? r.slots * sizeof(int4) : 0) : r.least;
+    r.cut = most > 1;
+    return r;
 }
 
 }  // namespace
@@ -581,8 +802,7 @@ extern "C" size_t paged_prefill_attn_workspace_bytes(const kv_view* view, int ba
                                                      int max_ctx_len, int max_q_len)
 {
     if (!kv_view_ok(view) || batch <= 0 || total_q <= 0 || max_ctx_len <= 0 || max_q_len <= 0) return 0;
-    const int s = prefill_splits(view, batch, max_ctx_len, max_q_len);
-    return s > 1 ? (size_t)s * total_q * view->n_q_local * (D + 2) * 4 : 0;
+    return prefill_workspace(view, batch, total_q, max_ctx_len, max_q_len).ask;
 }
 
 extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool, int64_t n_pool_blocks,
@@ -617,30 +837,45 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     while ((1 << a.group_shift) < G) ++a.group_shift;
     hipStream_t st = (hipStream_t)hip_stream;
     constexpr int R = kRowBlocks;
-    a.splits = prefill_splits(view, batch, max_ctx_len, max_q_len);
-    a.rows = total_q * view->n_q_local;
+    a.most_records = 0;
+    a.tiles = nullptr;
     a.part_o = nullptr;
     a.part_ml = nullptr;
-    if (a.splits > 1) {
-        const size_t need = (size_t)a.splits * a.rows * (D + 2) * 4;
-        if (!workspace || ((uintptr_t)workspace & 255u)) return KV_ERR_INVALID_ARG;
-        if (workspace_bytes < need) return KV_ERR_WORKSPACE;
-        a.part_o = (float*)workspace;
-        a.part_ml = a.part_o + (size_t)a.splits * a.rows * D;
+    const prefill_room room = prefill_workspace(view, batch, total_q, max_ctx_len, max_q_len);
+    const bool aligned = workspace && !((uintptr_t)workspace & 255u);
+    if (room.least > 0) {
+        if (!aligned) return KV_ERR_INVALID_ARG;
+        if (workspace_bytes < room.least) return KV_ERR_WORKSPACE;
     }
-    const int tokens_per_wg = (64 * R) >> a.group_shift;
+    bool cut = false;
+    if (room.cut && aligned) {
+        // the tile list, then as many records as fit
+        const size_t head = (size_t)room.slots * sizeof(int4), bytes = std::min(workspace_bytes, room.ask);
+        const size_t record = (size_t)view->n_q_local * (D + 2) * 4;
+        const int64_t records = bytes > head ? (int64_t)((bytes - head) / record) : 0;
+        if (records >= 2) {
+            cut = true;
+            a.most_records = (int32_t)std::min<int64_t>(records, 1 << 24);
+            a.tiles = (int4*)workspace;
+            a.part_o = (float*)((char*)workspace + head);
+            a.part_ml = a.part_o + (size_t)records * view->n_q_local * D;
+        }
+    }
+    const int tokens_per_wg = query_tile_tokens(view);
     a.tile_shift = 0;
     while ((1 << a.tile_shift) < tokens_per_wg) ++a.tile_shift;   // (64 R and the padded group are powers of two)
     a.batch = batch;
-    const int64_t slots = total_q / tokens_per_wg + batch;
+    const int64_t slots = room.slots;
     const int Hl = view->n_kv_local;
-    if (slots * a.splits > 0x7fffffff) return KV_ERR_UNSUPPORTED;
+    if (slots > 0x7fffffff) return KV_ERR_UNSUPPORTED;
     a.slots = (int32_t)slots;
-    int64_t n_wgs = slots * a.splits * Hl;
+    int64_t n_wgs = slots * Hl;
     a.xcds_per_head = 0;
-    if (a.splits == 1 && Hl % 8 == 0) {
+    if (cut) {
+        n_wgs = std::max<int64_t>(768, 8 * ((n_wgs + 7) / 8));   // a workgroup takes further pieces if there are more
+    } else if (Hl % 8 == 0) {
         a.xcds_per_head = 1;
-    } else if (a.splits == 1 && 8 % Hl == 0 && batch <= kMostCut) {
+    } else if (8 % Hl == 0 && batch <= kMostCut) {
         // the ranges of the XCDs hold equal work but not equally many tiles: a workgroup takes every
         // (workgroups per XCD)-th tile of its range
         a.xcds_per_head = 8 / Hl;
@@ -649,9 +884,12 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     if (n_wgs > 0x7fffffff) return KV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)n_wgs);
     int slot = kv_prof_begin(KV_PROF_PREFILL, st);
-    hipLaunchKernelGGL(prefill_kernel<R>, grid, dim3(kThreads), 0, st, a);
-    if (a.splits > 1)
-        hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)((a.rows + 7) / 8)), dim3(256), 0, st, a);
+    if (cut) {
+        hipLaunchKernelGGL((prefill_kernel<R, true>), grid, dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)slots, (unsigned)Hl, 64 * kRowBlocks / (kThreads / 32)), dim3(kThreads), 0, st, a);
+    } else {
+        hipLaunchKernelGGL((prefill_kernel<R, false>), grid, dim3(kThreads), 0, st, a);
+    }
     kv_prof_end(KV_PROF_PREFILL, slot, st);
     return kv_record_hip_error(hipGetLastError(), "paged_prefill_attn launch");
 }

@@ -170,3 +170,36 @@ def test_tiles_dealt_out_to_the_xcds(hq, hkv, triple, batch):
     c = make_prefill_case(w, triple, ctx, q_len)
     want = oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off)
     check_close(run_gpu(c, gpu_view(w, triple)), want, f"{hq}/{hkv} {triple} batch {batch}")
+
+
+@pytest.mark.parametrize("hq,hkv,triple,ctx,qlen", [
+    (32, 8, (LAYOUT_DP, 1, 0), [9000, 700, 40], [33, 64, 40]),              # one long range among short ones
+    (32, 8, (LAYOUT_TP, 8, 3), [3000], [3000]),                             # a prompt: ranges of 1 to 94 key tiles
+    (12, 2, (LAYOUT_DP, 1, 0), [6000, 1, 2500], [65, 1, 0]),                # padded groups, no new tokens
+    (2, 2, (LAYOUT_DP, 1, 0), [5000, 4100, 129], [300, 1, 129]),            # one query head per KV head
+    (8, 1, (LAYOUT_DP, 1, 0), [900] * 70 + [4500], [1, 17] * 35 + [16]),    # more than 64 sequences and slots
+    (4, 1, (LAYOUT_DP, 1, 0), [600] * 300, [2] * 300),                      # several rounds of slots per lane
+])
+@pytest.mark.parametrize("room", ["asked", "least"])
+def test_key_ranges_cut_by_length(hq, hkv, triple, ctx, qlen, room):
+    """Launches of few query tiles, whose key ranges are cut into pieces of one greatest length: ragged lengths,
+    tiles of every length, partial tiles, with the scratch asked for (garbage at the start) and with the 512 keys
+    per piece that are always enough.  Every output row is compared."""
+    w = wl.Workload("prefill_cut", 85, hq, hkv, 128, 16, len(ctx), "x", ())
+    ctx, qlen = np.array(ctx, dtype=np.int32), np.array(qlen, dtype=np.int32)
+    c = make_prefill_case(w, triple, ctx, qlen)
+    view = gpu_view(w, triple)
+    asked = kv.lib().paged_prefill_attn_workspace_bytes(view.handle, len(ctx), int(qlen.sum()), int(ctx.max()), int(qlen.max()))
+    tokens = 128 // (1 << int(np.ceil(np.log2(view.n_q_local // view.n_kv_local))))
+    wgs = -(-int(qlen.max()) // tokens) * view.n_kv_local * len(ctx)
+    pieces = min(-(-768 // wgs), int(ctx.max()) // 512, 16) if wgs < 512 else 1
+    least = pieces * int(qlen.sum()) * view.n_q_local * 130 * 4 if pieces > 1 else 0
+    assert asked >= least
+    ws = torch.full((asked if room == "asked" else least,), 0x7F, dtype=torch.uint8, device=DEV)
+    out = torch.full((int(qlen.sum()), view.n_q_local, 128), float("nan"), dtype=torch.bfloat16, device=DEV)
+    kv.paged_prefill_attn(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV), torch.from_numpy(c.ctx).to(DEV),
+                          torch.from_numpy(c.q_off.astype(np.int32)).to(DEV), view, int(ctx.max()), int(qlen.max()),
+                          out=out, workspace=ws)
+    torch.cuda.synchronize()
+    got = bf16_bits_to_f64(out.cpu().view(torch.int16).numpy().view(np.uint16))
+    check_close(got, oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off), f"cut {triple} {room}")
