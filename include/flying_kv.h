@@ -259,8 +259,7 @@ int kv_weight_view_fused_qkv(const kv_geometry* g, int64_t hidden, int r, int m,
  *   workspace device scratch of at least kv_linear_view_workspace_bytes(view, M) bytes (may be
  *           0: then null is accepted), 16-byte aligned; contents need not be initialised
  * fp32 accumulation, one rounding to bf16 at the end.  For the row-parallel layer y is the
- * rank's partial sum (the all-reduce over ranks is the caller's).  Tuned for decode batches (M up
- * to a few hundred); any M is accepted.
+ * rank's partial sum (the all-reduce over ranks is the caller's).  Any M is accepted.
  * Errors: KV_ERR_INVALID_ARG (null pointers, view outside the weight, strides too small),
  * KV_ERR_WORKSPACE,
  * KV_ERR_UNSUPPORTED (col_count not a multiple of 128, a row segment not a multiple of 64,
