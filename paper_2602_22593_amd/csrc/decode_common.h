@@ -8,6 +8,9 @@
 namespace kvdec {
 
 constexpr float kNegInf = -INFINITY;
+// Where a running maximum starts that is subtracted from scores: finite, so that scores of -inf (keys holding
+// infinities, products past the range) get weight 0 rather than exp2(-inf + inf), and below every finite score.
+constexpr float kLowest = -3.402823466e38f;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

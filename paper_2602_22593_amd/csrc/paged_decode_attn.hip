@@ -150,7 +150,7 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
         if (slice < slices && idx < pairs) {
             const int g = idx / HD, e = 2 * (idx - g * HD);
             const int64_t rec0 = ((int64_t)s * a.v.n_q_local + hl * G + g) * a.max_chunks;
-            float m = kNegInf, l = 0.f, a0 = 0.f, a1 = 0.f;
+            float m = kLowest, l = 0.f, a0 = 0.f, a1 = 0.f;
             for (int k0 = slice; k0 < n_chunks; k0 += kBatch * slices) {
                 f32x2 ml[kBatch], av[kBatch];
 #pragma unroll
@@ -162,7 +162,7 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
                     if (k0 + u * slices >= n_chunks) break;
-                    const float mn = fmaxf(m, ml[u][0]);   // (finite: every chunk holds a token)
+                    const float mn = fmaxf(m, ml[u][0]);
                     const float c0 = fast_exp2(m - mn), c1 = fast_exp2(ml[u][0] - mn);
                     l = l * c0 + ml[u][1] * c1;
                     a0 = a0 * c0 + av[u][0] * c1;
@@ -185,7 +185,7 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
         float mm = kNegInf;
         for (int k = 0; k < slices; ++k) mm = fmaxf(mm, s_red[k * pairs + tid][0]);
         float l = 0.f, a0 = 0.f, a1 = 0.f;
-        for (int k = 0; k < slices; ++k) {   // (a slice without chunks: m = -inf, weight 0)
+        for (int k = 0; k < slices; ++k) {   // (a slice without chunks holds zeros)
             const f32x4 x = s_red[k * pairs + tid];
             const float c = fast_exp2(x[0] - mm);
             l += x[1] * c;
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(NW * 64, 3) void decode_chunk_kernel(decode_args a)
     const int n_chunks = (n + a.chunk_tokens - 1) / a.chunk_tokens;
     if (n > 0 && t0 + 31 >= ce) ids_of(t0, ce - 1, id);   // a tile at the end: ids of tokens that exist
 
-    float m_run = kNegInf, l_run = 0.f;
+    float m_run = kLowest, l_run = 0.f;
     f32x4 oacc[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) oacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(NW * 64, 3) void decode_chunk_kernel(decode_args a)
             }
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx);  // finite: every tile holds at least one valid token
+        const float m_new = fmaxf(m_run, mx);
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
         kv_u32x4 hi, lo;
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(decode_args a)
 
     __shared__ float s_red[8][D];
     __shared__ float s_l[8], s_m[8];
-    float m = kNegInf, ll = 0.f;
+    float m = kLowest, ll = 0.f;
     vec acc = 0.f;
     constexpr int kBatch = 8;
     for (int k0 = slice; k0 < n_chunks; k0 += 8 * kBatch) {
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(decode_args a)
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             if (k0 + 8 * u >= n_chunks) break;
-            const float mn = fmaxf(m, ml[u].x);   // (finite: every chunk holds a token)
+            const float mn = fmaxf(m, ml[u].x);   // (-inf where every score of a vector-ALU chunk is)
             const float c0 = exp2f(m - mn), c1 = exp2f(ml[u].x - mn);
             ll = ll * c0 + ml[u].y * c1;
             acc = acc * c0 + x[u] * c1;
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(decode_args a)
 #pragma unroll
         for (int w = 0; w < 8; ++w) mm = fmaxf(mm, s_m[w]);
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {   // (a slice without chunks: m = -inf, weight 0)
+        for (int w = 0; w < 8; ++w) {   // (a slice without chunks holds zeros)
             const float c = exp2f(s_m[w] - mm);
             tot += s_red[w][tid] * c;
             lt += s_l[w] * c;

@@ -111,3 +111,33 @@ def test_several_heads_per_wavefront_on_request(hq, hkv, triple):
         check(bf16_bits_to_f64(out.cpu().numpy().view(np.uint16)), want, f"mixed {hq}/{hkv} {triple}")
     finally:
         kv.kv_set_option("waves_per_cu", 0)
+
+
+@pytest.mark.parametrize("kernel,chunk", [(0, 0), (2, 64)])
+@pytest.mark.parametrize("d,hq,hkv", [(64, 8, 2), (128, 8, 2), (128, 8, 1)])
+def test_scores_of_minus_infinity(d, hq, hkv, kernel, chunk):
+    """Tokens whose score is -inf (a key element of -inf against a positive query element) have weight 0, also where
+    they are all that a tile, a wavefront's share of a chunk, a chunk or a slice of the chunk list holds.
+    kernel 2: the vector-ALU kernel's partials, combined by the same second launch."""
+    dead = [(33, [32]), (129, [128]), (300, range(0, 32)), (300, range(1, 300)), (700, list(range(128, 256)) + [600]),
+            (1030, range(0, 1029)), (1200, range(0, 1152)), (1700, range(64, 1664)), (40, [])]
+    lens = np.array([n for n, _ in dead], dtype=np.int32)
+    w = wl.Workload("neginf", 88, hq, hkv, d, 16, len(lens), "x", ())
+    K, V = wl.logical_kv(w, lens)
+    q = wl.queries(w)
+    q[:, :, 0] = 0x3F80                                  # 1.0
+    off = wl.seq_offsets(lens)
+    for s, (_, tokens) in enumerate(dead):
+        K[off[s] + np.array(tokens, dtype=np.int64), :, 0] = 0xFF80     # -inf
+    c = make_case(w, (LAYOUT_DP, 1, 0), lens, K=K, V=V, q_full=q)
+    view = kv.kv_view_create(hq, hkv, d, 16, LAYOUT_DP, 1, 0)
+    want = oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx)
+    assert np.isfinite(want).all()
+    kv.kv_set_option("force_kernel", kernel)
+    kv.kv_set_option("chunk_tokens", chunk)
+    try:
+        ws = torch.zeros(kv.paged_decode_attn_workspace_bytes(view, len(lens), int(lens.max())), dtype=torch.uint8, device=DEV)
+        check(decode(c, view, ws), want, f"d {d} {hq}/{hkv} kernel {kernel}")
+    finally:
+        kv.kv_set_option("force_kernel", 0)
+        kv.kv_set_option("chunk_tokens", 0)
