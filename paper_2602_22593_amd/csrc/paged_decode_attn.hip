@@ -222,9 +222,9 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
 // i' = 0..7, EV = D / 16) and transposed inside the lane with byte permutes.  No data crosses lanes
 // except the running maximum.
 //
-// SPLIT_P (head_dim 64, which is otherwise the vector-ALU kernel's): the weights enter the second product as
-// the sum of two bf16 numbers (16 bits of mantissa) and their fp32 values are summed for the denominator, so
-// that nothing is lost against the vector-ALU kernel's fp32 weights.
+// SPLIT_P (head_dim 64, which is otherwise the vector-ALU kernel's): the weights enter the second product as the
+// sum of three bf16 numbers, which hold all 24 bits of an fp32 mantissa, and their fp32 values are summed for
+// the denominator: the same weights above and below, as in the vector-ALU kernel.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 struct chunk_tile {
@@ -335,14 +335,16 @@ __global__ __launch_bounds__(NW * 64, 3) void decode_chunk_kernel(decode_args a)
         const float m_new = fmaxf(m_run, mx);
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
-        kv_u32x4 hi, lo;
+        kv_u32x4 hi, mid, lo;
         float psum = 0.f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const float p0 = fast_exp2(sv[2 * u] - m_new), p1 = fast_exp2(sv[2 * u + 1] - m_new);
             hi[u] = pack_bf16x2(p0, p1);
             if constexpr (SPLIT_P) {
-                lo[u] = pack_bf16x2(p0 - bf16_lo(hi[u]), p1 - bf16_hi(hi[u]));
+                const float r0 = p0 - bf16_lo(hi[u]), r1 = p1 - bf16_hi(hi[u]);   // (exact, as are the next)
+                mid[u] = pack_bf16x2(r0, r1);
+                lo[u] = pack_bf16x2(r0 - bf16_lo(mid[u]), r1 - bf16_hi(mid[u]));
                 psum += p0 + p1;
             } else {
                 // the denominator sums the weights as they enter the second product
@@ -361,8 +363,10 @@ __global__ __launch_bounds__(NW * 64, 3) void decode_chunk_kernel(decode_args a)
 #pragma unroll
             for (int u = 0; u < 4; ++u) va[u] = __builtin_amdgcn_perm(t.v[2 * u + 1][j >> 1], t.v[2 * u][j >> 1], sel);
             oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), as_bf16x8(hi), oacc[j], 0, 0, 0);
-            if constexpr (SPLIT_P)
+            if constexpr (SPLIT_P) {
+                oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), as_bf16x8(mid), oacc[j], 0, 0, 0);
                 oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), as_bf16x8(lo), oacc[j], 0, 0, 0);
+            }
         }
     };
     for (; t0 < ce; t0 += 32 * NW) {

@@ -66,10 +66,9 @@ def test_small_batches(hq, hkv, triple, bs, lens):
 @pytest.mark.parametrize("hq,hkv,triple,bs", [
     (8, 2, (LAYOUT_DP, 1, 0), 16), (16, 2, (LAYOUT_TP, 2, 1), 32), (4, 2, (LAYOUT_DP, 2, 0), 48), (8, 8, (LAYOUT_TP, 4, 3), 16)])
 def test_head_dim_64(hq, hkv, triple, bs, lens):
-    """Against the oracle, and as close to it as the vector-ALU kernel, whose weights stay in fp32: the matrix
-    cores take them as the sum of two bf16 numbers, 16 bits of mantissa, so that outputs of O(1) move by
-    2^-16 at most before the rounding to bf16.  Where that moves a value over a rounding boundary the two
-    kernels differ by one bf16 step (2^-7 relative at most)."""
+    """Against the oracle, and as close to it as the vector-ALU kernel: the weights are the same to fp32 in both, so
+    that outputs of O(1) differ in the order of their sums only.  Where that moves a value over a rounding
+    boundary the two kernels differ by one bf16 step (2^-7 relative at most)."""
     w = wl.Workload("d64", 86, hq, hkv, 64, bs, len(lens), "x", ())
     c = make_case(w, triple, np.array(lens, dtype=np.int32))
     view = kv.kv_view_create(hq, hkv, 64, bs, *triple)
@@ -141,3 +140,49 @@ def test_scores_of_minus_infinity(d, hq, hkv, kernel, chunk):
     finally:
         kv.kv_set_option("force_kernel", 0)
         kv.kv_set_option("chunk_tokens", 0)
+
+
+@pytest.mark.parametrize("kernel", [0, 2])
+def test_head_dim_64_weights_keep_fp32(kernel):
+    """Values chosen so that the weighted sum cancels to about 2^-13 of S = sum_t p_t |v_t|: the values of the two
+    heaviest tokens are set, one after the other, to what brings the sum of all others there, as far as a
+    bf16 number can.  Bound: half a bf16 step of the output (2^-9 relative) and 2^-21 S, for eight roundings to fp32 on the
+    way (the exponential, the weight's share of its sum, and where partial results are brought to a common maximum,
+    up to three times in the vector-ALU kernel).  Weights with 24 bits are off by 2^-25 S here; weights with
+    16 bits by up to 2^-19 S, which takes one output in ten of the shortest sequences past the bound (both
+    computed on the CPU)."""
+    lens, hkv, d = np.array([17, 20, 33, 64, 20, 25, 18, 17], dtype=np.int32), 8, 64
+    w = wl.Workload("cancel", 89, hkv, hkv, d, 16, len(lens), "x", ())
+    K, V = wl.logical_kv(w, lens)
+    q = wl.randn_bf16((len(lens), hkv, d), wl.generator(89, 700))
+    q = np.where((q & 0x7F80) > (4 << 7), q - (4 << 7), q).astype(np.uint16)      # sixteenths: nearly equal weights
+    off = wl.seq_offsets(lens)
+    want, S = np.zeros((len(lens), hkv, d)), np.zeros((len(lens), hkv, d))
+
+    def bf16(x):
+        u = np.asarray(x, dtype=np.float32).view(np.uint32)
+        return ((u + 0x7FFF + ((u >> 16) & 1)) >> 16).astype(np.uint16)
+
+    for s, n in enumerate(lens):
+        for h in range(hkv):
+            at = slice(int(off[s]), int(off[s + 1]))
+            score = bf16_bits_to_f64(K[at, h]) @ bf16_bits_to_f64(q[s, h]) / np.sqrt(d)
+            p = np.exp(score - score.max())
+            p /= p.sum()
+            v = bf16_bits_to_f64(V[at, h])
+            a, b = np.argsort(-p)[:2]
+            v[[a, b]] = 0.0
+            for t, share in ((a, 0.0), (b, 2.0 ** -13)):
+                V[off[s] + t, h] = bf16((share * (p @ np.abs(v)) - p @ v) / p[t])
+                v[t] = bf16_bits_to_f64(V[off[s] + t, h])
+            want[s, h], S[s, h] = p @ v, p @ np.abs(v)
+    assert np.median(np.abs(want) / S) < 2.0 ** -12
+    c = make_case(w, (LAYOUT_DP, 1, 0), lens, K=K, V=V, q_full=q)
+    view = kv.kv_view_create(hkv, hkv, d, 16, LAYOUT_DP, 1, 0)
+    ws = torch.zeros(max(256, kv.paged_decode_attn_workspace_bytes(view, len(lens), int(lens.max()))), dtype=torch.uint8, device=DEV)
+    kv.kv_set_option("force_kernel", kernel)
+    try:
+        got = decode(c, view, ws)
+    finally:
+        kv.kv_set_option("force_kernel", 0)
+    assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -9 * (1 + 2.0 ** -6) + S * 2.0 ** -21).all()
