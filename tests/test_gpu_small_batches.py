@@ -186,3 +186,27 @@ def test_head_dim_64_weights_keep_fp32(kernel):
     finally:
         kv.kv_set_option("force_kernel", 0)
     assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -9 * (1 + 2.0 ** -6) + S * 2.0 ** -21).all()
+
+
+@pytest.mark.parametrize("d,hq,hkv,batch,longest,kernel,chunk", [
+    (64, 8, 2, 70, 33000, 0, 0), (64, 16, 2, 70, 33000, 0, 0), (128, 8, 2, 30, 9001, 3, 64), (128, 24, 2, 30, 9001, 3, 64)])
+def test_launches_of_many_workgroups(d, hq, hkv, batch, longest, kernel, chunk):
+    """More than 8192 workgroups, most of them past the end of their sequence: one long sequence among short and
+    empty ones."""
+    lens = np.random.default_rng(90).integers(0, 200, batch).astype(np.int32)
+    lens[[0, 7]] = 0
+    lens[11] = longest
+    w = wl.Workload("many", 90, hq, hkv, d, 16, batch, "x", ())
+    c = make_case(w, (LAYOUT_DP, 1, 0), lens)
+    view = kv.kv_view_create(hq, hkv, d, 16, LAYOUT_DP, 1, 0)
+    kv.kv_set_option("force_kernel", kernel)
+    kv.kv_set_option("chunk_tokens", chunk)
+    try:
+        assert -(-longest // (chunk or 512)) * batch * hkv > 8192
+        ws = torch.zeros(kv.paged_decode_attn_workspace_bytes(view, batch, longest), dtype=torch.uint8, device=DEV)
+        got = decode(c, view, ws)
+    finally:
+        kv.kv_set_option("force_kernel", 0)
+        kv.kv_set_option("chunk_tokens", 0)
+    check(got, oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx), f"d {d} {hq}/{hkv}")
+    assert (got[lens == 0] == 0).all()
