@@ -1245,18 +1245,30 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     // measured: a gain of 2-5 % where a wavefront then reads whole token rows or the query rows fill
     // the 16 columns
     const int G = view->group, Hl = view->n_kv_local;
-    // ... and a loss where the batch is too small for that to matter, because the pieces a wavefront leaves are
-    // that much larger (8 sequences, 8 heads, 130 MB by the length bound: 25.1 against 22.5 us; 16, 267 MB: 37.9
-    // against 35.5; 64 under TP4, 263 MB: 35.4 against 31.8; 256 short ones under TP2, 105 MB: 30.1 against 21.5;
-    // even at 32, 532 MB; a gain at 64, 1070 MB)
-    if (!kv_even_split_hooks() && (int64_t)batch * Hl * max_ctx_len * (D * 4) < 500000000) return 1;
-    if (G <= 4 && Hl % 4 == 0) return 4;
-    if (G > 4 && G <= 8 && Hl % 2 == 0 && Hl >= 4) return 2;
+    int heads = 1;
+    if (G <= 4 && Hl % 4 == 0) heads = 4;
+    else if (G > 4 && G <= 8 && Hl % 2 == 0 && Hl >= 4) heads = 2;
     // two-head rows with small groups (TP4 of the 8B shape): both heads of the row, 2.5 % faster than
     // one on a batch of many sequences (95.5 -> 93.1 us at batch 128); not where a few very long
     // sequences are cut into long piece lists, whose records it doubles (60.3 against 59.9 us)
-    if (G <= 4 && Hl % 2 == 0 && (int64_t)batch * Hl * kMergeLong > n_waves) return 2;
-    return 1;
+    else if (G <= 4 && Hl % 2 == 0 && (int64_t)batch * Hl * kMergeLong > n_waves) heads = 2;
+    // Below some amount of cached bytes several heads per wavefront lose, because the pieces that a wavefront leaves
+    // are that much larger.  Measured, several heads against one, us (MB by the length bound):
+    // - four query heads and more per KV head: below 500 MB (G = 4, 8 sequences, 8 heads, 130 MB: 25.1 against 22.5;
+    //   16, 267 MB: 37.9 against 35.5; 64 under TP4, 263 MB: 35.4 against 31.8; 256 short ones under TP2, 105 MB:
+    //   30.1 against 21.5; even at 32, 532 MB; a gain at 64, 1070 MB);
+    // - one or two: only where the pairs are few, whose lists of pieces then are long (G = 1, 4 heads: one sequence of
+    //   60000, 123 MB, 40.3 against 32.4; with three short ones, 492 MB, 41.0 against 33.9; G = 2, 8 of 200 to 2000, 4
+    //   heads, 134 MB: 15.1 against 12.0, but 8 of 8000 to 16000, 252 MB: 43.3 against 44.9).  With more pairs a single head's 256-byte rows with a column or two of work each
+    //   are the slower stream (G = 1, 8 of 500 to 4000, 8 heads, 130 MB: 20.8 against 28.5; 64 of 1000, 262 MB: 48.6
+    //   against 55.8; G = 2, 16 of 500 to 4000, 4 heads, 125 MB: 23.4 against 27.6);
+    // - three: the same, and four heads lose below 100 MB (16 of 1000, 66 MB: 23.0 against 22.2; but 8 of 500 to
+    //   4000, 117 MB: 23.5 against 27.7).
+    int64_t least = 500000000;
+    if (G <= 3 && (int64_t)batch * Hl * 64 > n_waves)
+        least = (int64_t)batch * Hl * 32 <= n_waves ? 200000000 : G == 3 && heads == 4 ? 100000000 : 0;
+    if (!kv_even_split_hooks() && (int64_t)batch * Hl * max_ctx_len * (D * 4) < least) return 1;
+    return heads;
 }
 
 // Partial results: one slot per (wavefront, pair) piece, n_waves + batch * pairs at most, each
