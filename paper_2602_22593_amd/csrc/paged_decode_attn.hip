@@ -728,9 +728,14 @@ int64_t small_batch_chunk(const kv_view* view, int batch, int max_ctx_len)
     if (kv_option_force_kernel() != 0 || kv_option_heads_per_wave() != 0 || kv_even_split_hooks()) return 0;
     const int64_t pairs = (int64_t)batch * view->n_kv_local;
     if (max_ctx_len > kSmallCtx || pairs * max_ctx_len * view->geom.head_dim * 4 > kSmallBytes) return 0;
-    // one tile per wavefront where that leaves neither a long list to merge nor several rounds of workgroups
+    // One tile per wavefront (128 tokens) where that leaves neither a long list to merge nor more workgroups than
+    // start at once; there are fewer of those if every sequence may be full, as up to 8 chunks are (128 pairs of
+    // 1000 tokens, G = 2: 20.5 us with 128, 17.4 with 256, G = 16: 29.0 and 22.6; but 16 pairs of 200 to 2000 under a
+    // bound of 8192: 12.2 and 14.2).  Nothing to merge at all for many short sequences (512 pairs of 100 to 300 tokens,
+    // G = 1: 19.6 with 128, 24.4 with 256, 15.9 with 512; 256 pairs 11.1, 15.1, 10.4).
     const int64_t c128 = ((int64_t)max_ctx_len + 127) / 128;
-    int64_t chunk = c128 <= 64 && c128 * pairs <= 1024 ? 128 : 256;
+    int64_t chunk = c128 <= 64 && c128 * pairs <= (c128 <= kFusedChunks ? 768 : 1024) ? 128 : 256;
+    if (max_ctx_len <= 512 && pairs >= 256) chunk = 512;
     if (kv_option_chunk_tokens() > 0) chunk = kv_option_chunk_tokens();
     // (the caller's workspace is the even-split kernels')
     if (chunked_workspace_bytes(view, batch, max_ctx_len, chunk) > kv_streamk_workspace_bytes(view, batch, streamk_waves()))
