@@ -1263,10 +1263,13 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     //   are the slower stream (G = 1, 8 of 500 to 4000, 8 heads, 130 MB: 20.8 against 28.5; 64 of 1000, 262 MB: 48.6
     //   against 55.8; G = 2, 16 of 500 to 4000, 4 heads, 125 MB: 23.4 against 27.6);
     // - three: the same, and four heads lose below 100 MB (16 of 1000, 66 MB: 23.0 against 22.2; but 8 of 500 to
-    //   4000, 117 MB: 23.5 against 27.7).
+    //   4000, 117 MB: 23.5 against 27.7);
+    // - five and six: as often the one as the other (34 shapes from 40 to 1000 MB: 0.76 to 1.21 times, 1.01 on
+    //   average; G = 5, 6 of 1200 to 3800, 8 heads, 94 MB: 22.9 against 30.3).
     int64_t least = 500000000;
     if (G <= 3 && (int64_t)batch * Hl * 64 > n_waves)
         least = (int64_t)batch * Hl * 32 <= n_waves ? 200000000 : G == 3 && heads == 4 ? 100000000 : 0;
+    else if (G == 5 || G == 6) least = 0;
     if (!kv_even_split_hooks() && (int64_t)batch * Hl * max_ctx_len * (D * 4) < least) return 1;
     return heads;
 }
