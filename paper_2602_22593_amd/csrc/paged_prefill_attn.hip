@@ -39,6 +39,8 @@ constexpr int kThreads = 256;
 constexpr int kSub = 1;               // 32-key sub-tiles per staged tile
 constexpr int kKeys = 32 * kSub;      // keys per staged tile (one barrier each)
 constexpr int kMostCut = 1024;          // sequences up to which a workgroup reads all lengths
+// How the workgroups of a launch that cuts no key ranges find their query tiles, see the host code below
+constexpr int kSlots = 0, kDense = 1, kLongestFirst = 2;
 constexpr float kUnset = 1e30f;       // exponent addend of a column that has no reference maximum yet
 
 struct prefill_args {
@@ -56,6 +58,7 @@ struct prefill_args {
     int32_t tile_shift;     // log2 of the new tokens per query tile
     int32_t batch;
     int32_t slots;          // query tiles per KV head as numbered by slot_sequence(), gaps included
+    int32_t order;          // kSlots, kDense or kLongestFirst
     int32_t xcds_per_head;  // how the tiles are dealt out to the XCDs, see the kernel
     // launches that cut key ranges, see plan_pieces()
     int32_t most_records;   // tokens that the partial arrays have room for
@@ -160,6 +163,75 @@ __device__ __forceinline__ int slot_sequence(const prefill_args& a, int slot, in
         span = min(step, span - c * step);
     }
     return uniform(s);
+}
+
+// Tile `idx` of a head whose tiles are numbered without gaps: its sequence and its place there; false past the end.
+__device__ __forceinline__ bool dense_tile(const prefill_args& a, int idx, int lane, int& s, int& tile_in_seq)
+{
+    const int tokens = 1 << a.tile_shift;
+    for (int s0 = 0; s0 < a.batch; s0 += 64) {
+        int tiles = 0;
+        if (s0 + lane < a.batch) tiles = (a.q_off[s0 + lane + 1] - a.q_off[s0 + lane] + tokens - 1) >> a.tile_shift;
+        const int incl = (int)wave_inclusive_sum((float)tiles, lane);   // (exact: no more than the grid)
+        const int all = __builtin_amdgcn_readlane(incl, 63);
+        if (idx < all) {
+            const int at = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= idx));
+            s = s0 + at;
+            tile_in_seq = idx - __builtin_amdgcn_readlane(incl - tiles, at);
+            return true;
+        }
+        idx -= all;
+    }
+    return false;
+}
+
+// Sum and maximum over the 64 lanes of numbers that are not negative.
+template <int CTRL>
+__device__ __forceinline__ int dpp_shr_int(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true); }
+__device__ __forceinline__ int wave_count(int x)
+{
+    x += dpp_shr_int<0x111>(x);
+    x += dpp_shr_int<0x112>(x);
+    x += dpp_shr_int<0x114>(x);
+    x += dpp_shr_int<0x118>(x);
+    return __builtin_amdgcn_readlane(x, 15) + __builtin_amdgcn_readlane(x, 31) + __builtin_amdgcn_readlane(x, 47) +
+           __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ int wave_most(int x)
+{
+    x = max(x, dpp_shr_int<0x111>(x));
+    x = max(x, dpp_shr_int<0x112>(x));
+    x = max(x, dpp_shr_int<0x114>(x));
+    x = max(x, dpp_shr_int<0x118>(x));
+    return max(max(__builtin_amdgcn_readlane(x, 15), __builtin_amdgcn_readlane(x, 31)),
+               max(__builtin_amdgcn_readlane(x, 47), __builtin_amdgcn_readlane(x, 63)));
+}
+
+// Tile `idx` of a head's tiles in descending order of the keys they see, counted in whole tiles: tile j of sequence
+// s has level (ctx - q_len) / T + j.  The level is found by bisection on how many tiles lie at or above one, lane s
+// counting those of sequence s (64 sequences at most).  False past the last tile.
+__device__ __forceinline__ bool level_tile(const prefill_args& a, int idx, int lane, int& s, int& tile_in_seq)
+{
+    int tiles = 0, base = 0;
+    if (lane < a.batch) {
+        const int q_len = a.q_off[lane + 1] - a.q_off[lane], n = a.ctx_lens[lane];
+        tiles = n > 0 ? (q_len + (1 << a.tile_shift) - 1) >> a.tile_shift : 0;
+        base = max(n - q_len, 0) >> a.tile_shift;
+    }
+    const int end = base + tiles;
+    if (idx >= wave_count(tiles)) return false;
+    int lo = 0, hi = wave_most(end);   // more than idx tiles at lo and above, at hi none
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (wave_count(min(max(end - mid, 0), tiles)) > idx) lo = mid;
+        else hi = mid;
+    }
+    idx -= wave_count(min(max(end - lo - 1, 0), tiles));
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(base <= lo && lo < end);
+    const int before = __builtin_popcountll(at & ((1ull << lane) - 1));
+    s = __builtin_ctzll(__builtin_amdgcn_ballot_w64(base <= lo && lo < end && before == idx));
+    tile_in_seq = __builtin_amdgcn_readlane(end - 1 - lo, s);
+    return true;
 }
 
 // The head's slots cut into `parts` consecutive ranges of equal work (keys seen by each query tile plus a fixed
@@ -362,7 +434,7 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // query heads 564 instead of 494.  Dealing tiles out one by one balances as well but spreads every
     // pair over all L2s: 32 prompts of 2048 tokens, 4 query heads, 187 us instead of 178.)
     int hl, item, item_end, item_step;   // item: a slot, as in slot_sequence(); CUT: (head, piece)
-    int per_head = 0;
+    int per_head = 0, own_s = 0, own_place = 0;
     if constexpr (CUT) {
         // a contiguous eighth of the (head, piece) list per XCD
         per_head = plan_pieces(a, s_slot, s_cost, reinterpret_cast<int32_t*>(s_k0), reinterpret_cast<int32_t*>(s_v0), s_k1, s_v1);
@@ -374,7 +446,17 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     } else {
         const int L = (int)blockIdx.x, N = (int)gridDim.x, Hl = v.n_kv_local;
         const int xcd = L & 7, k = L >> 3;
-        if (a.xcds_per_head == 0) {
+        if (a.order != kSlots) {
+            // few tiles, none of them idle, one per workgroup: the heads go round the XCDs, and so do a head's tiles
+            // where XCDs share one
+            hl = L % Hl;
+            item = L / Hl;
+            if (!(a.order == kLongestFirst ? level_tile(a, item, lane0, own_s, own_place)
+                                           : dense_tile(a, item, lane0, own_s, own_place)))
+                return;
+            item_end = item + 1;
+            item_step = 1;
+        } else if (a.xcds_per_head == 0) {
             // a contiguous eighth of the (head, slot) list per XCD; one item per workgroup
             const int base = N >> 3, rem = N & 7;
             const int x = xcd * base + min(xcd, rem) + k;
@@ -414,14 +496,14 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
         pieces = (end_s >> 10) - before;
         piece = idx - before;
     } else {
-        s = slot_sequence(a, slot, lane);
+        s = a.order != kSlots ? own_s : slot_sequence(a, slot, lane);
     }
 
     const int n = a.ctx_lens[s];
     const int q0 = a.q_off[s];
     const int q_len = a.q_off[s + 1] - q0;
     // longest tiles first: the last query tile of a sequence sees the most keys
-    const int tile_in_seq = slot - ((q0 >> a.tile_shift) + s);
+    const int tile_in_seq = !CUT && a.order != kSlots ? own_place : slot - ((q0 >> a.tile_shift) + s);
     const int j0 = (((q_len + tokens_per_wg - 1) >> a.tile_shift) - 1 - tile_in_seq) << a.tile_shift;
     if (j0 < 0 || n <= 0) continue;
     const int first_pos = n - q_len;                         // position of the sequence's query 0
@@ -766,6 +848,20 @@ int prefill_pieces(int64_t wgs, int max_ctx_len, int least)
     if (s > kMostPieces) s = kMostPieces;
     return s < 1 ? 1 : s;
 }
+// How the tiles of a launch that cuts nothing are dealt out, by their number:
+// - up to one per compute unit: in the order of their numbers; where a gap lies does not matter;
+// - up to 512, two per compute unit: numbered without gaps, so that no compute unit gets a third while another has one
+//   (4 chunks of 512 tokens on 12000, 8 KV heads, 4 query heads each: 488 us with the gaps, 396 without).  Ranges of
+//   equal work take up to twice the time in both cases, because the range with the shortest tiles has more of
+//   them than workgroups (8 of 33 tokens on 300 to 800, 4 KV heads: 47.8, 25.2), and 4 us in every workgroup for the
+//   cuts (8 prompts of 30 to 100, 2 KV heads: 13.5, 8.0);
+// - up to 2304 (three rounds of 768 workgroups): longest first as well, so that the last to start are the shortest (the
+//   greedy rule).  Against ranges of equal work 5 to 45 % less time on 1 to 4 heads (8 prompts of 4000, 1 KV head, 1000
+//   tiles: 147, 134; 40 chunks of 128 on 1000 to 3000, 4 KV heads, 640 tiles: 158, 125), on 8 heads, one per XCD
+//   either way, 0 to 10 %.  Finding the tile takes 1 us, too much for fewer;
+// - more: ranges that keep a pair's tiles together in one L2.
+constexpr int64_t kMostDense = 512, kMostOrdered = 2304;
+
 // Room asked for, and the least that is accepted where there is more than the tiles alone need.
 struct prefill_room {
     int64_t slots;
@@ -871,15 +967,23 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     a.slots = (int32_t)slots;
     int64_t n_wgs = slots * Hl;
     a.xcds_per_head = 0;
+    a.order = kSlots;
+    const int64_t tiles = (slots - batch) * Hl + (int64_t)batch * Hl / 2;   // (half a tile more per sequence, on average)
     if (cut) {
         n_wgs = std::max<int64_t>(768, 8 * ((n_wgs + 7) / 8));   // a workgroup takes further pieces if there are more
+    } else if (n_wgs <= 256) {
+        a.xcds_per_head = Hl % 8 == 0 ? 1 : 0;
+    } else if (tiles <= kMostDense && batch <= kMostCut) {
+        a.order = kDense;
+    } else if (tiles <= kMostOrdered && batch <= 64) {
+        a.order = kLongestFirst;
     } else if (Hl % 8 == 0) {
         a.xcds_per_head = 1;
     } else if (8 % Hl == 0 && batch <= kMostCut) {
         // the ranges of the XCDs hold equal work but not equally many tiles: a workgroup takes every
         // (workgroups per XCD)-th tile of its range
         a.xcds_per_head = 8 / Hl;
-        n_wgs = 8 * ((slots + a.xcds_per_head - 1) / a.xcds_per_head);
+        n_wgs = 8 * std::max((slots + a.xcds_per_head - 1) / a.xcds_per_head, std::min<int64_t>(slots, 96));
     }
     if (n_wgs > 0x7fffffff) return KV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)n_wgs);

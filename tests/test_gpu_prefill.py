@@ -172,6 +172,42 @@ def test_tiles_dealt_out_to_the_xcds(hq, hkv, triple, batch):
     check_close(run_gpu(c, gpu_view(w, triple)), want, f"{hq}/{hkv} {triple} batch {batch}")
 
 
+@pytest.mark.parametrize("hq,hkv,triple,batch,longest,most", [
+    (8, 8, (LAYOUT_DP, 1, 0), 30, 700, 512),      # a head per XCD, tiles numbered without gaps
+    (8, 2, (LAYOUT_DP, 1, 0), 50, 300, 512),      # two heads, the same
+    (16, 1, (LAYOUT_DP, 1, 0), 70, 90, 512),      # more than 64 sequences, tiles of 8 tokens
+    (16, 2, (LAYOUT_TP, 2, 1), 64, 700, 2304),    # longest first, a lane for each of 64 sequences
+    (48, 4, (LAYOUT_TP, 2, 0), 9, 700, 2304),     # padded groups, two heads
+    (32, 8, (LAYOUT_DP, 1, 0), 15, 700, 2304),    # eight heads
+    (12, 3, (LAYOUT_DP, 1, 0), 40, 700, 2304),    # three heads
+])
+def test_few_tiles(hq, hkv, triple, batch, longest, most):
+    """Launches of more than one query tile per compute unit and at most `most`: prompts, chunks on a cached prefix,
+    single tokens, sequences with no new tokens and with nothing cached, whole tiles and one token more.  Contexts
+    below 768 tokens, so that no key range is cut.  Every output row is compared."""
+    rng = np.random.default_rng(700 + batch)
+    T = 128 // (1 << int(np.ceil(np.log2(hq // hkv))))
+    ctx = rng.integers(1, longest, batch).astype(np.int32)
+    q_len = np.array([int(rng.choice([n, n, n, n, 1, n // 2, 0, min(n, T), min(n, T + 1)])) for n in ctx], dtype=np.int32)
+    ctx[3], q_len[3] = 0, 0
+    q_len[[0, -1]] = [ctx[0], 0]
+    ctx[5], q_len[5] = longest, longest
+    heads = hkv // triple[1]
+    tiles = int((-(-q_len // T)).sum()) * heads
+    slots = (int(q_len.sum()) // T + batch) * heads
+    counted = (2 * (int(q_len.sum()) // T) + batch) * heads // 2
+    assert slots > 256 and (most == 512) == (counted <= 512) and counted <= 2304 and tiles <= slots
+    w = wl.Workload("prefill_few", 91, hq, hkv, 128, 16, batch, "x", ())
+    c = make_prefill_case(w, triple, ctx, q_len)
+    want = oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off)
+    out = torch.full((int(q_len.sum()), c.info["n_q_local"], 128), float("nan"), dtype=torch.bfloat16, device=DEV)
+    kv.paged_prefill_attn(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV), torch.from_numpy(c.ctx).to(DEV),
+                          torch.from_numpy(c.q_off.astype(np.int32)).to(DEV), gpu_view(w, triple), int(ctx.max()),
+                          int(q_len.max()), out=out)
+    torch.cuda.synchronize()
+    check_close(bf16_bits_to_f64(out.cpu().view(torch.int16).numpy().view(np.uint16)), want, f"{hq}/{hkv} {triple} {batch}")
+
+
 @pytest.mark.parametrize("hq,hkv,triple,ctx,qlen", [
     (32, 8, (LAYOUT_DP, 1, 0), [9000, 700, 40], [33, 64, 40]),              # one long range among short ones
     (32, 8, (LAYOUT_TP, 8, 3), [3000], [3000]),                             # a prompt: ranges of 1 to 94 key tiles
