@@ -876,19 +876,19 @@ prefill_room prefill_workspace(const kv_view* view, int batch, int64_t total_q, 
     r.slots = total_q / tokens + batch;
     const int64_t wgs = std::min(bound, r.slots * view->n_kv_local);
     const int at_least = prefill_pieces(bound, max_ctx_len, 512);
-    // Planning and combining cost 4 us: a launch with a workgroup for each compute unit cuts long contexts only (one
-    // prompt of 2000 tokens, 8 KV heads, 66 us uncut, 69 cut), and pieces below 512 keys are for half a chip's tiles
-    // at most (33 tokens of eight sequences of 800, 1 KV head, 28.8 -> 21.3 us, but four prompts of 700, 2 KV
-    // heads, 26 -> 32).
-    int most = 1;
-    if (r.slots <= kMostSlots && (wgs <= 256 ? at_least > 1 || (wgs <= 128 && max_ctx_len >= 768)
-                                             : at_least > 1 && max_ctx_len >= 4096))
-        most = std::max(at_least, std::min(prefill_pieces(wgs, max_ctx_len, 256) + 1, kMostPieces));
+    // Planning and combining cost 4 us and more.  With tiles for one workgroup and a half per compute unit that is made
+    // up for from about 1000 keys on, where at_least passes 1, with more on long contexts only (16 prompts of 100 to
+    // 4000 tokens, 1 KV head, 110 us uncut, 57 cut; 2 of 1500 to 2500, 8 KV heads, 79, 60; one of 2000, 8 KV heads, 4
+    // query heads each, 66, 69; but 40 chunks of 150 on 2000, 400 tiles, 73, 83); pieces below 512 keys are for half
+    // a chip's tiles at most (33 tokens of eight sequences of 800, 1 KV head, 28.8 -> 21.3 us, but four prompts of 700,
+    // 2 KV heads, 26 -> 32).
+    r.cut = r.slots <= kMostSlots && (wgs <= 384 ? at_least > 1 || (wgs <= 128 && max_ctx_len >= 768)
+                                                  : at_least > 1 && max_ctx_len >= 4096);
+    const int most = r.cut ? std::max(at_least, std::min(prefill_pieces(wgs, max_ctx_len, 256) + 1, kMostPieces)) : 1;
     const size_t record = (size_t)total_q * view->n_q_local * (D + 2) * 4;
-    r.least = at_least > 1 ? record * at_least : 0;
+    r.least = r.cut && at_least > 1 ? record * at_least : 0;   // (nothing is asked for that nothing uses)
     // (the list of the tiles comes on top, without which as many pieces as there is room for would just not fit)
-    r.ask = most > 1 ? record * most + (most < kMostPieces ? r.slots * sizeof(int4) : 0) : r.least;
-    r.cut = most > 1;
+    r.ask = r.cut ? record * most + (most < kMostPieces ? r.slots * sizeof(int4) : 0) : 0;
     return r;
 }
 

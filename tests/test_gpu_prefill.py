@@ -214,7 +214,8 @@ def test_few_tiles(hq, hkv, triple, batch, longest, most):
     (12, 2, (LAYOUT_DP, 1, 0), [6000, 1, 2500], [65, 1, 0]),                # padded groups, no new tokens
     (2, 2, (LAYOUT_DP, 1, 0), [5000, 4100, 129], [300, 1, 129]),            # one query head per KV head
     (8, 1, (LAYOUT_DP, 1, 0), [900] * 70 + [4500], [1, 17] * 35 + [16]),    # more than 64 sequences and slots
-    (4, 1, (LAYOUT_DP, 1, 0), [600] * 300, [2] * 300),                      # several rounds of slots per lane
+    (4, 1, (LAYOUT_DP, 1, 0), [1100] * 299 + [2100], [32] * 300),           # 600 slots: both halves of the tile table
+    (32, 8, (LAYOUT_DP, 1, 0), [2000] * 8, [150] * 8),                      # more tiles than compute units
 ])
 @pytest.mark.parametrize("room", ["asked", "least"])
 def test_key_ranges_cut_by_length(hq, hkv, triple, ctx, qlen, room):
@@ -231,6 +232,7 @@ def test_key_ranges_cut_by_length(hq, hkv, triple, ctx, qlen, room):
     pieces = min(-(-768 // wgs), int(ctx.max()) // 512, 16) if wgs < 512 else 1
     least = pieces * int(qlen.sum()) * view.n_q_local * 130 * 4 if pieces > 1 else 0
     assert asked >= least
+    assert least > 0
     ws = torch.full((asked if room == "asked" else least,), 0x7F, dtype=torch.uint8, device=DEV)
     out = torch.full((int(qlen.sum()), view.n_q_local, 128), float("nan"), dtype=torch.bfloat16, device=DEV)
     kv.paged_prefill_attn(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV), torch.from_numpy(c.ctx).to(DEV),
@@ -239,3 +241,6 @@ def test_key_ranges_cut_by_length(hq, hkv, triple, ctx, qlen, room):
     torch.cuda.synchronize()
     got = bf16_bits_to_f64(out.cpu().view(torch.int16).numpy().view(np.uint16))
     check_close(got, oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off), f"cut {triple} {room}")
+    # the list of the tiles at its start: the launch did plan its pieces, and cut some
+    tiles = ws[:16 * (int(qlen.sum()) // tokens + len(ctx))].cpu().view(torch.int32).numpy().reshape(-1, 4)
+    assert (tiles != 0x7F7F7F7F).any(axis=1).all() and tiles[:, 1].max() > 1
