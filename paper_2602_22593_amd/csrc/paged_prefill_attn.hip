@@ -858,9 +858,10 @@ int prefill_pieces(int64_t wgs, int max_ctx_len, int least)
 // - up to 2304 (three rounds of 768 workgroups): longest first as well, so that the last to start are the shortest (the
 //   greedy rule).  Against ranges of equal work 5 to 45 % less time on 1 to 4 heads (8 prompts of 4000, 1 KV head, 1000
 //   tiles: 147, 134; 40 chunks of 128 on 1000 to 3000, 4 KV heads, 640 tiles: 158, 125), on 8 heads, one per XCD
-//   either way, 0 to 10 %.  Finding the tile takes 1 us, too much for fewer;
+//   either way, 0 to 10 %, and for two rounds at most (40 chunks of 150 on 2000, 1800 tiles: 236, 267).  Finding the tile
+//   takes 1 us, too much for fewer;
 // - more: ranges that keep a pair's tiles together in one L2.
-constexpr int64_t kMostDense = 512, kMostOrdered = 2304;
+constexpr int64_t kMostDense = 512, kMostOrdered = 2304, kMostOrdered8 = 1536;
 
 // Room asked for, and the least that is accepted where there is more than the tiles alone need.
 struct prefill_room {
@@ -975,7 +976,7 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
         a.xcds_per_head = Hl % 8 == 0 ? 1 : 0;
     } else if (tiles <= kMostDense && batch <= kMostCut) {
         a.order = kDense;
-    } else if (tiles <= kMostOrdered && batch <= 64) {
+    } else if (tiles <= (Hl % 8 == 0 ? kMostOrdered8 : kMostOrdered) && batch <= 64) {
         a.order = kLongestFirst;
     } else if (Hl % 8 == 0) {
         a.xcds_per_head = 1;
