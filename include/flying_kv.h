@@ -257,7 +257,10 @@ int kv_weight_view_fused_qkv(const kv_geometry* g, int64_t hidden, int r, int m,
  *   w_full  device, bf16 [w_rows][ldw]: the whole stored weight, ldw its row length (read)
  *   y       device, bf16 [M][sum of row_count], row stride ldy elements          (written)
  *   workspace device scratch of at least kv_linear_view_workspace_bytes(view, M) bytes (may be
- *           0: then null is accepted), 16-byte aligned; contents need not be initialised
+ *           0: then null is accepted), 16-byte aligned; contents need not be initialised.  The
+ *           figure never shrinks as M grows (64 MiB at most without "linear_splits"), so that one
+ *           workspace sized for the largest batch serves every smaller one; a call that needs less
+ *           than that for its own M accepts less
  * fp32 accumulation, one rounding to bf16 at the end.  For the row-parallel layer y is the
  * rank's partial sum (the all-reduce over ranks is the caller's).  Any M is accepted.
  * Errors: KV_ERR_INVALID_ARG (null pointers, view outside the weight, strides too small),

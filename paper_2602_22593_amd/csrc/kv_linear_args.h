@@ -34,10 +34,10 @@ __device__ __forceinline__ int64_t stored_row(const linear_args& p, int row)
     return p.seg_start[seg] + (row - p.seg_first[seg]);
 }
 
-// The tiled kernels (kv_linear_tiles.hip): which tile serves a call, and its workspace.  `shape` < 0: the
-// sliced kernel (kv_linear_view.hip) is the faster one.
+// The tiled kernels (kv_linear_tiles.hip): the tile and the slices for a call (`shape` < 0: none), and its workspace.
 struct tiles_cfg {
     int shape, splits, slice_slabs;
+    double us;   // estimated
 };
 tiles_cfg tiles_pick(int M, int64_t n_l, int total_slabs, size_t most_workspace);
 size_t tiles_workspace(const tiles_cfg& c, int M, int64_t n_l);

@@ -314,23 +314,26 @@ constexpr tile_shape kShapes[] = {
 };
 constexpr int kShapeCount = sizeof(kShapes) / sizeof(kShapes[0]);
 
-size_t part_bytes(const tile_shape& t, int64_t M, int64_t n_l, int splits)
+int64_t tile_count(const tile_shape& t, int64_t M, int64_t n_l)
 {
-    if (splits <= 1) return 0;
-    return (size_t)splits * ((n_l + t.bn - 1) / t.bn) * ((M + t.bm - 1) / t.bm) * t.bn * t.bm * 4;
+    return ((n_l + t.bn - 1) / t.bn) * ((M + t.bm - 1) / t.bm);
+}
+
+size_t part_bytes(const tile_shape& t, int64_t tiles, int splits)
+{
+    return splits <= 1 ? 0 : (size_t)splits * tiles * t.bn * t.bm * 4;
 }
 
 // Estimated time of a launch (us).
-double estimate(const tile_shape& t, int64_t M, int64_t n_l, int slabs, int splits, int slice_slabs)
+double estimate(const tile_shape& t, int64_t tiles, int splits, int slice_slabs)
 {
-    const double tiles = (double)((n_l + t.bn - 1) / t.bn) * (double)((M + t.bm - 1) / t.bm);
-    const double wgs = tiles * splits, full = floor(wgs / 256.0), rest = wgs / 256.0 - full;
+    const int64_t wgs = tiles * splits, whole = wgs >> 8;
+    const double full = (double)whole, rest = (double)(wgs & 255) * (1.0 / 256.0);
     // a round that does not fill the chip is only slightly shorter than one that does
     const double partly = rest > 0.0 ? 0.83 + 0.17 * rest : 0.0;
-    const double stage = full < 1.0 ? t.first * partly : t.first + t.next * (full - 1.0 + partly);
-    const double rounds = ceil(wgs / 256.0);
-    double us = 3.1 + 2.0 * slice_slabs * stage + 2.7 * (t.bn * t.bm / 65536.0) * rounds;
-    if (splits > 1) us += 2.3 + (double)part_bytes(t, M, n_l, splits) / 3.0e6;   // second launch, partial sums
+    const double stage = whole < 1 ? t.first * partly : t.first + t.next * (full - 1.0 + partly);
+    double us = 3.1 + 2.0 * slice_slabs * stage + 2.7 * (t.bn * t.bm / 65536.0) * (full + (rest > 0.0 ? 1.0 : 0.0));
+    if (splits > 1) us += 2.3 + (double)part_bytes(t, tiles, splits) / 3.0e6;   // second launch, partial sums
     return us;
 }
 
@@ -352,30 +355,29 @@ void launch_shape(const linear_args& p, hipStream_t st)
 // Which tile and how many slices of the input dimension: the cheapest by estimate().  Its constants were
 // fitted to a sweep of 15 weight shapes (320 x 640 to 10240 x 8192) x 22 batch sizes (20 to 8192) x all tiles x 1
 // to 8 slices: the choice is 0.8 % slower than the best one of the sweep on average and 14 % at most.
-// Never more workspace than `most_workspace`, what the sliced kernel would take.
+// Never more workspace than `most_workspace`.
 tiles_cfg tiles_pick(int M, int64_t n_l, int total_slabs, size_t most_workspace)
 {
-    tiles_cfg best = {-1, 1, total_slabs};
-    double best_us = 0.0;
+    tiles_cfg best = {-1, 1, total_slabs, 0.0};
     if (n_l > (1 << 30)) return best;
     for (int i = 0; i < kShapeCount; ++i) {
         const tile_shape& t = kShapes[i];
-        const int64_t tiles = ((n_l + t.bn - 1) / t.bn) * (((int64_t)M + t.bm - 1) / t.bm);
+        const int64_t tiles = tile_count(t, M, n_l);
         for (int want = 1; want <= 8 && want <= total_slabs; ++want) {
             const int per = (total_slabs + want - 1) / want, splits = (total_slabs + per - 1) / per;
             if (splits != want || tiles * splits > 0x7fffffff) continue;
-            if (splits > 1 && part_bytes(t, M, n_l, splits) > most_workspace) continue;
-            const double us = estimate(t, M, n_l, total_slabs, splits, per);
-            if (best.shape < 0 || us < best_us) {
-                best = tiles_cfg{i, splits, per};
-                best_us = us;
-            }
+            if (splits > 1 && part_bytes(t, tiles, splits) > most_workspace) continue;
+            const double us = estimate(t, tiles, splits, per);
+            if (best.shape < 0 || us < best.us) best = tiles_cfg{i, splits, per, us};
         }
     }
     return best;
 }
 
-size_t tiles_workspace(const tiles_cfg& c, int M, int64_t n_l) { return part_bytes(kShapes[c.shape], M, n_l, c.splits); }
+size_t tiles_workspace(const tiles_cfg& c, int M, int64_t n_l) 
+{
+    return part_bytes(kShapes[c.shape], tile_count(kShapes[c.shape], M, n_l), c.splits);
+}
 
 void tiles_launch(const tiles_cfg& c, linear_args p, hipStream_t st)
 {

@@ -5,9 +5,9 @@
 // row-parallel output projection) of a weight kept once, whole, as [out][in] bf16.  Nothing is
 // copied: the kernel addresses the full matrix with its own leading dimension.
 //
-// Two families of kernels serve it.  This file holds the one for decode batches on a weight slice of up to
-// about 30 MB, which keeps x in registers; kv_linear_tiles.hip the LDS-staged tiles for everything larger
-// (make_plan below says where the line lies).
+// Two families of kernels serve it.  This file holds the one that keeps x in registers, for decode batches on weight
+// slices of up to about 30 MB; kv_linear_tiles.hip the LDS-staged tiles for what is larger (make_plan below chooses by
+// estimated time).
 //
 // In a decode step the weight slice is streamed from HBM and is the only HBM traffic that matters.  What
 // limits such a product on this chip is not HBM but the path from L2 into a compute unit (measured here:
@@ -38,12 +38,14 @@
 // barrier until the end, where the four wavefronts add their accumulators through LDS.  With one
 // slice the sums are rounded to bf16 and stored; with several, each workgroup leaves an fp32 partial
 // tile in the workspace and a second, small kernel adds the slices in a fixed order (deterministic)
-// and rounds once.  NB is chosen so that the launch has at least one workgroup per compute unit.
+// and rounds once.  NB, 1 to 6, is chosen by estimated time, in practice so that one round of workgroups does it.
 //
-// Measured at M = 64: 3072 x 4096 (TP2 slice of the fused QKV weight) 10.8 us with the second kernel, 4096 x 1024
-// (TP4 slice of W^O, one slice) 4.8 us.
+// Measured at M = 64, weights from HBM: 3072 x 4096 (TP2 slice of the fused QKV weight) 10.8 us with the second kernel,
+// 4096 x 1024 (TP4 slice of W^O, one slice) 5.3 us.
 #include <string.h>
 #include <hip/hip_ext.h>
+
+#include <type_traits>
 
 #include "kv_linear_args.h"
 
@@ -56,55 +58,27 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kColBlocks = 4;   // 16-row blocks of x per workgroup
 
-// sum[i] = y[m0 + 16 cb + r][16 (blk0 + b) + 4 quad + i] for tile (b, cb) = (tile / 4, tile % 4) of a
-// workgroup: rounded to bf16 and stored
-template <int NB>
-__device__ __forceinline__ void store_tile(const linear_args& p, f32x4 sum, int tile, int m0, int blk0, int n_blocks,
-                                           int r, int quad)
+// sum[i] = y[m0 + 16 cb + r][16 blk + 4 quad + i] of row block blk and column block cb: rounded to bf16 and stored
+__device__ __forceinline__ void store_tile(const linear_args& p, f32x4 sum, int blk, int cb, int m0, int r, int quad)
 {
-    const int b = tile / kColBlocks, cb = tile % kColBlocks;
     const int m = m0 + 16 * cb + r;
-    if (m >= p.M || blk0 + b >= n_blocks) return;
+    if (m >= p.M) return;
     uint2 pk;
     pk.x = pack_bf16x2(sum[0], sum[1]);
     pk.y = pack_bf16x2(sum[2], sum[3]);
-    *reinterpret_cast<uint2*>(p.y + (int64_t)m * p.ldy + (16 * (blk0 + b) + 4 * quad)) = pk;
+    *reinterpret_cast<uint2*>(p.y + (int64_t)m * p.ldy + (16 * blk + 4 * quad)) = pk;
 }
 
-// The partial tiles of all slices of one workgroup tile, added in slice order and stored.  Wavefront
-// w takes tiles w NB .. w NB + NB - 1.
-template <int NB>
-__device__ __forceinline__ void add_slices(const linear_args& p, int64_t wg_tiles, int64_t wg_tile, int m0, int blk0,
-                                           int n_blocks, int wave, int lane)
+// Partial tiles of slice z and row blocks from blk on: [row block][column block][64 lanes x 4 floats, as they lie in the
+// registers].  The arrangement knows row blocks, not workgroups: it has no padding and one size for every NB.
+__device__ __forceinline__ float* part_tiles(const linear_args& p, int z, int blk)
 {
-    const int r = lane & 15, quad = lane >> 4;
-    const int64_t slice_step = wg_tiles * (NB * kColBlocks) * 256;   // floats between two slices
-    const float* src = p.part + ((wg_tile * (NB * kColBlocks) + wave * NB) * 64 + lane) * 4;
-    f32x4 sum[NB];
-#pragma unroll
-    for (int t = 0; t < NB; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // four slices of all this wavefront's tiles are requested before any is added: one memory round
-    // trip per four slices
-    for (int z0 = 0; z0 < p.splits; z0 += 4) {
-        f32x4 v[NB][4];
-#pragma unroll
-        for (int t = 0; t < NB; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                v[t][j] = *reinterpret_cast<const f32x4*>(src + t * 256 + (int64_t)min(z0 + j, p.splits - 1) * slice_step);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (z0 + j >= p.splits) break;
-#pragma unroll
-            for (int t = 0; t < NB; ++t) sum[t] += v[t][j];
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < NB; ++t) store_tile<NB>(p, sum[t], wave * NB + t, m0, blk0, n_blocks, r, quad);
+    return p.part + (((int64_t)z * gridDim.y + blockIdx.y) * (p.Nl >> 4) + blk) * (kColBlocks * 256);
 }
 
+// (two workgroups of NB 1 or 2 share a compute unit: make_plan counts on it)
 template <int NB>
-__global__ __launch_bounds__(kThreads, 1) void linear_slice_kernel(linear_args p)
+__global__ __launch_bounds__(kThreads, NB <= 2 ? 2 : 1) void linear_slice_kernel(linear_args p)
 {
     constexpr int NR = 2;             // row blocks requested ahead
     constexpr int kStagePieces = 2 * 256;                       // per wavefront: 2 slabs x 16 rows x 16 pieces
@@ -242,26 +216,27 @@ __global__ __launch_bounds__(kThreads, 1) void linear_slice_kernel(linear_args p
 #pragma unroll
         for (int cb = 0; cb < kColBlocks; ++cb) red[((wave * NB + b) * kColBlocks + cb) * 64 + lane] = acc[b][cb];
     __syncthreads();
-    const int64_t wg_tiles = (int64_t)gridDim.x * gridDim.y;
-    const int64_t wg_tile = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    auto finish = [&](auto whole) {   // (tests per row block in between keep the sums from being read and stored together)
 #pragma unroll
-    for (int t = 0; t < NB; ++t) {
-        const int tile = wave * NB + t;           // of the 4 NB (b, cb) tiles
-        const int b = tile / kColBlocks, cb = tile % kColBlocks;
-        f32x4 sum = red[((0 * NB + b) * kColBlocks + cb) * 64 + lane];
+        for (int t = 0; t < NB; ++t) {
+            const int tile = wave * NB + t;           // of the 4 NB (b, cb) tiles
+            const int b = tile / kColBlocks, cb = tile % kColBlocks;
+            f32x4 sum = red[((0 * NB + b) * kColBlocks + cb) * 64 + lane];
 #pragma unroll
-        for (int k = 1; k < kWaves; ++k) sum += red[((k * NB + b) * kColBlocks + cb) * 64 + lane];
-        if (p.splits > 1) {
-            // partial tile, kept lane for lane as it lies in the registers: 1 KiB contiguous per store
-            *reinterpret_cast<f32x4*>(
-                p.part + ((((int64_t)blockIdx.z * wg_tiles + wg_tile) * (NB * kColBlocks) + tile) * 64 + lane) * 4) = sum;
-        } else {
-            store_tile<NB>(p, sum, tile, m0, blk0, n_blocks, r, quad);
+            for (int k = 1; k < kWaves; ++k) sum += red[((k * NB + b) * kColBlocks + cb) * 64 + lane];
+            if (!whole.value && blk0 + b >= n_blocks) continue;
+            if (p.splits > 1)   // 1 KiB contiguous per store
+                *reinterpret_cast<f32x4*>(part_tiles(p, blockIdx.z, blk0) + tile * 256 + lane * 4) = sum;
+            else store_tile(p, sum, blk0 + b, cb, m0, r, quad);
         }
-    }
+    };
+    if (4 % NB == 0 || blk0 + NB <= n_blocks) finish(std::true_type());   // (row blocks come in fours)
+    else finish(std::false_type());
 }
 
-// The second kernel of a launch with several slices: one workgroup per workgroup tile adds them.
+// The second kernel of a launch with several slices: the workgroup with the number of a workgroup tile adds its slices
+// in slice order, so that it mostly runs on the XCD whose L2 holds them (workgroups of one row block each, spread
+// over the chip otherwise, take 1 to 1.5 us longer).
 // (Letting the last slice to arrive do this inside the first kernel was measured and gains nothing:
 // partials that cross XCDs inside a kernel need write-through stores, their acknowledgement, an
 // arrival counter and cache-bypassing loads, a chain as long as the second launch.)
@@ -269,20 +244,52 @@ template <int NB>
 __global__ __launch_bounds__(kThreads) void linear_add_kernel(linear_args p)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    add_slices<NB>(p, (int64_t)gridDim.x * gridDim.y, (int64_t)blockIdx.y * gridDim.x + blockIdx.x,
-                   blockIdx.y * (16 * kColBlocks), blockIdx.x * NB, p.Nl >> 4, wave, lane);
+    const int blk0 = blockIdx.x * NB, n_blocks = p.Nl >> 4, last = (n_blocks - blk0) * kColBlocks - 1;
+    const float* src = part_tiles(p, 0, blk0) + lane * 4;
+    const int64_t slice_step = (int64_t)gridDim.y * n_blocks * (kColBlocks * 256);
+    auto add = [&](auto whole) {
+        f32x4 sum[NB];
+#pragma unroll
+        for (int t = 0; t < NB; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // four slices of all this wavefront's tiles are requested before any is added: one memory round
+        // trip per four slices (past the last row block: that one again, not stored)
+        for (int z0 = 0; z0 < p.splits; z0 += 4) {
+            f32x4 v[NB][4];
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int tile = whole.value ? wave * NB + t : min(wave * NB + t, last);
+                    v[t][j] = *reinterpret_cast<const f32x4*>(src + tile * 256 + min(z0 + j, p.splits - 1) * slice_step);
+                }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (z0 + j >= p.splits) break;
+#pragma unroll
+                for (int t = 0; t < NB; ++t) sum[t] += v[t][j];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            const int tile = wave * NB + t;
+            if (whole.value || tile <= last)
+                store_tile(p, sum[t], blk0 + tile / kColBlocks, tile % kColBlocks, 16 * kColBlocks * blockIdx.y, lane & 15,
+                           lane >> 4);
+        }
+    };
+    if (4 % NB == 0 || blk0 + NB <= n_blocks) add(std::true_type());
+    else add(std::false_type());
 }
 
-// Slices of the input dimension and row blocks per workgroup.  A slice is what a workgroup can keep
-// of x in registers: 8 slabs; NB is the largest of 3, 2, 1 that still gives one workgroup per compute
-// unit (more rows per workgroup use the resident piece of x for longer).
+// Slices of the input dimension: a slice is what a workgroup can keep of x in registers, 8 slabs.
 constexpr int kSliceSlabs = 2 * kWaves;
 struct linear_cfg {
     int nb, splits, slice_slabs;
 };
-linear_cfg pick_cfg(int64_t m_tiles, int64_t n_l, int total_slabs)
+linear_cfg sliced_cfg(int total_slabs)
 {
     linear_cfg c;
+    c.nb = 1;
     c.slice_slabs = total_slabs < kSliceSlabs ? total_slabs : kSliceSlabs;
     const int64_t forced = kv_option_linear_splits();   // test hook: at least this many slices
     if (forced > 0) {
@@ -290,55 +297,95 @@ linear_cfg pick_cfg(int64_t m_tiles, int64_t n_l, int total_slabs)
         c.slice_slabs = per < 1 ? 1 : per > kSliceSlabs ? kSliceSlabs : per;
     }
     c.splits = (total_slabs + c.slice_slabs - 1) / c.slice_slabs;
-    const int64_t blocks = n_l / 16;
-    static const int kNb[] = {3, 2, 1};
-    c.nb = 1;
-    for (int nb : kNb) {
-        if (m_tiles * ((blocks + nb - 1) / nb) * c.splits >= 256) {
-            c.nb = nb;
-            break;
-        }
-    }
     return c;
 }
 
-// Workspace of a launch with several slices: one padded fp32 tile per slice and workgroup tile.
-size_t part_bytes(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
+int64_t workgroups(const linear_cfg& c, int nb, int64_t m_tiles, int64_t n_l)
 {
-    if (c.splits <= 1) return 0;
-    const int64_t n_tiles = (n_l / 16 + c.nb - 1) / c.nb;
-    return (size_t)c.splits * m_tiles * n_tiles * c.nb * kColBlocks * 1024;
+    return m_tiles * ((n_l / 16 + nb - 1) / nb) * c.splits;
 }
 
-// The tiled kernels (kv_linear_tiles.hip) take over where this kernel needs a second round of workgroups:
-// every round costs it a full pass over its piece of x before the first product.  Measured, this kernel
-// against the tiled ones: 64 rows of 6144 x 4096 16.3 against 14.7 us, of 4096 x 4096 12.4 against 11.7 (both with
-// more row blocks per workgroup than it has now, which is what made one round of them), of 3072 x 4096 (NB 3,
-// 256 workgroups) 10.8 against 11.6, of 768 x 4096 (NB 1, 384 workgroups of one row block, two to a compute
-// unit) 7.3 against 10.6; 100 rows of 4096 x 1024 (NB 2, 256) 6.4 against 7.3, 160 rows (NB 3, 258) 11.8
-// against 6.3.
-bool sliced_is_faster(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
+// Workspace of a sliced launch: an fp32 tile per slice, row block and column block.
+size_t part_bytes(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
 {
-    return m_tiles * ((n_l / 16 + c.nb - 1) / c.nb) * c.splits <= (c.nb == 1 ? 384 : 256);
+    return c.splits <= 1 ? 0 : (size_t)c.splits * m_tiles * (n_l / 16) * kColBlocks * 1024;
+}
+
+// What kv_linear_view_workspace_bytes asks for, and the most that any plan may take: the sliced kernel's need up to
+// a limit.  It grows with M, so that a workspace for the largest batch serves every smaller one, which the needs
+// themselves do not (64 rows of a weight may need slices that 65 or 4096 do not).  No shape of the 8B and 70B layers
+// is slower for the limit by more than an estimated 3 %.
+constexpr size_t kMostScratch = (size_t)64 << 20;
+size_t scratch_bytes(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
+{
+    const size_t all = part_bytes(c, m_tiles, n_l);
+    if (n_l > (1 << 30) || m_tiles * (n_l / 64) > 0x7fffffff) return all;   // (the sliced kernel may be the only one)
+    return kv_option_linear_splits() > 0 || all < kMostScratch ? all : kMostScratch;
+}
+
+constexpr int kNb[] = {1, 2, 3, 4, 6};
+
+// Estimated time (us) of the sliced kernel with NB row blocks per workgroup: the first round of workgroups (two per
+// compute unit fit for NB 1 and 2), the next, the second kernel and its partial sums, the weights; workgroups of the
+// second kernel find their slices in their own XCD's L2 if tiles come in eights.  Fitted to 46 weight shapes x 15
+// batches (1 to 1000 rows) x NB, weights from HBM and from the caches in equal parts: 7 % off.  Beyond these rounds the
+// tiled kernels are the better ones: every round costs this one a full pass over its piece of x before the first
+// product.  Their estimate is brought to the same footing: with weights from HBM they are slower than it says.
+// So chosen, on 620 of those points: 0.94 times the time of a fixed line at 256 workgroups, and 0.2 % off the better of
+// the two on average.  Examples, sliced with the best NB against tiled, us with weights from HBM / from the caches: 64
+// rows of 3072 x 4096 (NB 3) 10.8 / 9.6 against 13.4 / 11.0; 128 of 1536 x 4096 (3) 9.5 / 9.1, 12.8 / 10.6; 256 of
+// 1024 x 4096 (4) 10.9 / 10.6, 13.2 / 11.1; 256 of 1536 x 4096 (6) 13.7 / 13.5, 15.9 / 13.0; 64 of 6144 x 4096 (6) 16.6 /
+// 15.4, 18.7 / 13.7; 100 of 4096 x 2048 (4) 10.8 / 10.2, 11.6 / 9.2; 300 of 4096 x 1024 (1) 12, 8.
+double sliced_estimate(const linear_cfg& c, int nb, int64_t m_tiles, int64_t n_l, int total_slabs)
+{
+    static const double kFirst[] = {0.0, 4.5, 5.8, 6.2, 7.3, 0.0, 8.8};
+    const int64_t wgs = workgroups(c, nb, m_tiles, n_l);
+    const double weight_bytes = (double)n_l * total_slabs * kSlab * 2;
+    double us = kFirst[nb] + (wgs > 256 ? 2.1 : 0.0) + weight_bytes / (nb == 6 ? 20.0e6 : 40.0e6);
+    if (c.splits > 1) {
+        us += 1.5 + (double)part_bytes(c, m_tiles, n_l) / 1.95e6;
+        if (wgs / c.splits % 8 != 0) us += 0.43 * c.splits;
+    }
+    return us;
+}
+double tiled_estimate(const tiles_cfg& t, int64_t n_l, int total_slabs)
+{
+    return 1.2 * t.us - 0.9 + (double)n_l * total_slabs * kSlab * 2 / 32.0e6;
 }
 
 // The kernel and the cut of a call: tiles.shape < 0 means the sliced kernel as `sliced` says.
 struct linear_plan {
     linear_cfg sliced;
     tiles_cfg tiles;
-    size_t workspace;
+    size_t workspace;   // needed
 };
 linear_plan make_plan(int M, int64_t n_l, int total_slabs)
 {
     const int64_t m_tiles = ((int64_t)M + 16 * kColBlocks - 1) / (16 * kColBlocks);
     linear_plan pl;
-    pl.sliced = pick_cfg(m_tiles, n_l, total_slabs);
+    pl.sliced = sliced_cfg(total_slabs);
     pl.workspace = part_bytes(pl.sliced, m_tiles, n_l);
-    pl.tiles = tiles_cfg{-1, 1, total_slabs};
-    if (kv_option_linear_splits() == 0 && !sliced_is_faster(pl.sliced, m_tiles, n_l)) {
-        pl.tiles = tiles_pick(M, n_l, total_slabs, pl.workspace);
-        if (pl.tiles.shape >= 0) pl.workspace = tiles_workspace(pl.tiles, M, n_l);
+    pl.tiles = tiles_cfg{-1, 1, total_slabs, 0.0};
+    if (kv_option_linear_splits() > 0) {   // the largest NB that gives a workgroup to every compute unit
+        for (int nb : kNb)
+            if (workgroups(pl.sliced, nb, m_tiles, n_l) >= 256) pl.sliced.nb = nb;
+        return pl;
     }
+    pl.tiles = tiles_pick(M, n_l, total_slabs, scratch_bytes(pl.sliced, m_tiles, n_l));
+    double best = pl.tiles.shape < 0 ? 0.0 : tiled_estimate(pl.tiles, n_l, total_slabs);
+    bool sliced = pl.tiles.shape < 0;
+    for (int nb : kNb) {
+        if (workgroups(pl.sliced, nb, m_tiles, n_l) > (nb <= 2 ? 512 : 256)) continue;
+        if (nb == 6 && m_tiles > 4) continue;   // (512 rows of 768 x 4096: 17.6 us, tiled 15.4 / 13.0)
+        // (a tie goes to this kernel, but for NB 6)
+        const double us = (nb < 6 ? 0.96 : 1.0) * sliced_estimate(pl.sliced, nb, m_tiles, n_l, total_slabs);
+        if (best > 0.0 && us >= best) continue;
+        best = us;
+        pl.sliced.nb = nb;
+        sliced = true;
+    }
+    if (sliced) pl.tiles.shape = -1;
+    else pl.workspace = tiles_workspace(pl.tiles, M, n_l);
     return pl;
 }
 
@@ -356,7 +403,8 @@ extern "C" size_t kv_linear_view_workspace_bytes(const kv_weight_view* view, int
     if (!view || M <= 0 || view->n_segments < 1 || view->n_segments > 3 || view->col_count <= 0) return 0;
     const int64_t n_l = view_rows(view);
     if (n_l <= 0) return 0;
-    return make_plan(M, n_l, (int)(view->col_count / kSlab)).workspace;
+    const int64_t m_tiles = ((int64_t)M + 16 * kColBlocks - 1) / (16 * kColBlocks);
+    return scratch_bytes(sliced_cfg((int)(view->col_count / kSlab)), m_tiles, n_l);
 }
 
 extern "C" int kv_weight_view_make(int dim, int r, int m, int64_t n_rows, int64_t n_cols, kv_weight_view* out)
@@ -471,22 +519,18 @@ extern "C" int kv_linear_view(const void* x, int64_t ldx, const void* w_full, in
     hipEvent_t e0, e1;
     const bool own_events = p.splits == 1 && kv_prof_kernel_events(KV_PROF_LINEAR, &e0, &e1);
     const int slot = own_events ? -1 : kv_prof_begin(KV_PROF_LINEAR, st);
-    auto go = [&](auto kernel) {
-        if (own_events) hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, e0, e1, 0, p);
-        else hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, p);
+    auto go = [&](auto nb) {
+        constexpr int NB = decltype(nb)::value;
+        if (own_events) hipExtLaunchKernelGGL(linear_slice_kernel<NB>, grid, dim3(kThreads), 0, st, e0, e1, 0, p);
+        else hipLaunchKernelGGL(linear_slice_kernel<NB>, grid, dim3(kThreads), 0, st, p);
+        if (p.splits > 1) hipLaunchKernelGGL(linear_add_kernel<NB>, dim3(grid.x, grid.y), dim3(kThreads), 0, st, p);
     };
     switch (cfg.nb) {
-        case 3: go(linear_slice_kernel<3>); break;
-        case 2: go(linear_slice_kernel<2>); break;
-        default: go(linear_slice_kernel<1>); break;
-    }
-    if (p.splits > 1) {
-        const dim3 tiles((unsigned)n_tiles, (unsigned)m_tiles);
-        switch (cfg.nb) {
-            case 3: hipLaunchKernelGGL(linear_add_kernel<3>, tiles, dim3(kThreads), 0, st, p); break;
-            case 2: hipLaunchKernelGGL(linear_add_kernel<2>, tiles, dim3(kThreads), 0, st, p); break;
-            default: hipLaunchKernelGGL(linear_add_kernel<1>, tiles, dim3(kThreads), 0, st, p); break;
-        }
+        case 6: go(std::integral_constant<int, 6>()); break;
+        case 4: go(std::integral_constant<int, 4>()); break;
+        case 3: go(std::integral_constant<int, 3>()); break;
+        case 2: go(std::integral_constant<int, 2>()); break;
+        default: go(std::integral_constant<int, 1>()); break;
     }
     if (!own_events) kv_prof_end(KV_PROF_LINEAR, slot, st);
     return kv_record_hip_error(hipGetLastError(), "kv_linear_view launch");

@@ -233,3 +233,15 @@ def linear_tolerance(x_bits: np.ndarray, w_bits: np.ndarray, view, want: np.ndar
     S = ow.linear_view(x_bits & mask, w_bits & mask, view)
     acc = 4.0 * np.sqrt(K) * 2.0 ** -24 * S
     return (np.abs(want) + acc) * 2.0 ** -8 + acc + 1e-30
+
+
+def kernels_of(call) -> str:
+    """Names of the GPU kernels that call() launches, one per line, as the profiler sees them: which form of
+    a kernel the library took."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return "\n".join(e.name for e in p.events() if "<" in e.name or "kernel" in e.name)

@@ -196,6 +196,17 @@ def test_weight_view_and_linear_view_checks_without_a_gpu():
     assert L.kv_linear_view(fake, 512, fake, 256, 512, C.byref(thin), fake, 32, 4, fake, 1 << 30, None) == kv.KV_ERR_UNSUPPORTED
 
 
+def test_linear_workspace_grows_with_the_batch():
+    """One allocation for the largest batch serves every smaller one: the size asked for never shrinks as M grows."""
+    L = kv.lib()
+    for rows, cols in [(6144, 4096), (4096, 4096), (3072, 4096), (1536, 4096), (768, 4096), (4096, 1024), (10240, 8192),
+                       (1280, 8192), (64, 128), (320, 640), (28672, 8192)]:
+        v = kv.kv_weight_view_make(0, 0, 1, rows, cols)
+        ask = [L.kv_linear_view_workspace_bytes(C.byref(v), M) for M in list(range(1, 700, 7)) + [1000, 2048, 4096, 100000]]
+        assert ask == sorted(ask), (rows, cols)
+        assert max(ask) <= 64 << 20
+
+
 def test_prefill_entry_point_checks_without_a_gpu():
     L = kv.lib()
     fake = C.c_void_p(256)

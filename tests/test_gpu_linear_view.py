@@ -9,7 +9,7 @@ from oracle import weights as ow
 from paper_2602_22593_amd import binding as kv
 from paper_2602_22593_amd import workloads as wl
 
-from helpers import bf16_bits_to_f64, linear_tolerance
+from helpers import bf16_bits_to_f64, kernels_of, linear_tolerance
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -108,40 +108,88 @@ def test_every_cut_of_the_input_dimension(slabs, splits):
     check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ov, f"slabs {slabs} splits {splits}")
 
 
-@pytest.mark.parametrize("M,N,K,what", [
-    (64, 8256, 4096, "8 row blocks per workgroup, four slices; the last workgroup of a column has 4 of its 8 blocks"),
-    (64, 6208, 4096, "6 row blocks, four slices; the last workgroup has 4 of its 6"),
-    (64, 4160, 4096, "4 row blocks, four slices"),
-    (128, 1600, 4096, "3 row blocks, two batch tiles; the last workgroup has 1 of its 3"),
-    (256, 1344, 2048, "2 row blocks, four batch tiles, two slices"),
-    (40, 832, 640, "1 row block, one slice of 5 slabs: wavefront 0 has two slabs, the others one"),
-    (200, 320, 1152, "1 row block, four batch tiles, slices of 8 slabs and of 1"),
+@pytest.mark.parametrize("M,N,K,nb,what", [
+    (64, 8256, 4096, 6, "four slices"),
+    (64, 6208, 4096, 6, "four slices; the last workgroup has 4 of its 6 row blocks"),
+    (64, 4160, 4096, 4, "four slices"),
+    (128, 1600, 4096, 3, "two batch tiles, four slices; the last workgroup has 1 of its 3 row blocks"),
+    (300, 704, 3200, 3, "five batch tiles, the last partly full, four slices, the last of one slab; 2 of 3 row blocks"),
+    (256, 1344, 2048, 2, "four batch tiles, two slices"),
+    (40, 832, 640, 1, "one slice of 5 slabs: wavefront 0 has two slabs, the others one"),
+    (200, 320, 1152, 1, "four batch tiles, slices of 8 slabs and of 1"),
 ])
-def test_every_rows_per_workgroup_shape(M, N, K, what):
-    """Shapes that make the library pick each of its row-blocks-per-workgroup instantiations (8, 6, 4,
-    3, 2, 1), with block counts that do not divide evenly (trailing blocks are requested from idle
-    addresses and multiplied by zero) and slices whose slab count is not a multiple of the four
-    wavefronts.  Rows and columns are a sub-range of a larger stored weight."""
+def test_every_rows_per_workgroup_shape(M, N, K, nb, what):
+    """Each of the row-blocks-per-workgroup instantiations of the sliced kernel (linear_splits = 1 asks for that
+    kernel, cut as the input dimension needs), with block counts that do not divide evenly by three and six (trailing
+    blocks are requested from idle addresses and multiplied by zero) and slices whose slab count is not a
+    multiple of the four wavefronts.  Rows and columns are a sub-range of a larger stored weight."""
     x, w = bits((M, K), 60 + M), bits((N + 128, K + 256), 61 + (N % 97))
     ov = ow.WeightView(((64, N),), 128, K)
-    y = kv.kv_linear_view(dev(x), dev(w), gpu_view(ov))
-    torch.cuda.synchronize()
+    gv, dx, dw = gpu_view(ov), dev(x), dev(w)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    kv.kv_set_option("linear_splits", 1)
+    try:
+        ran = kernels_of(lambda: kv.kv_linear_view(dx, dw, gv, out=y))
+    finally:
+        kv.kv_set_option("linear_splits", 0)
+    assert f"linear_slice_kernel<{nb}>" in ran and ("linear_add_kernel" in ran) == (K > 1024), ran
     check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ov, what)
 
 
-@pytest.mark.parametrize("M,N,K,what", [
-    (65, 3136, 128, "64 x 64 tiles; one batch row in the second tile; one slab"),
-    (1, 6208, 4224, "64 x 64 tiles, one batch row, two slices, 33 slabs"),
-    (65, 1088, 2304, "64 x 64 tiles, three slices of six slabs"),
-    (257, 6208, 128, "128 x 64 tiles; the last weight tile is half full"),
-    (129, 6208, 384, "64 x 128 tiles; three slabs: six stages through three buffers"),
-    (5000, 3136, 128, "128 x 128 tiles; two workgroups per compute unit"),
-    (1000, 6208, 128, "128 x 256 tiles; both last tiles partly full"),
-    (2047, 4160, 256, "192 x 256 tiles; the last weight tile has 128 of its 192 rows"),
-    (2047, 6208, 128, "256 x 256 tiles; the last weight tile has 64 of its 256 rows"),
-    (700, 4160, 1152, "more than one slice allowed: nine slabs"),
+@pytest.mark.parametrize("M,N,K,nb,what", [
+    (1, 1024, 1024, 1, "64 workgroups, one slice"),
+    (64, 2048, 4096, 2, "256 workgroups, four slices"),
+    (33, 1408, 4096, 1, "352 workgroups, two to some compute units"),
+    (64, 3072, 4096, 3, "256 workgroups; the last has 1 of its 3 row blocks"),
+    (64, 4096, 4096, 4, "256 workgroups"),
+    (256, 1536, 4096, 6, "256 workgroups, four batch tiles"),
 ])
-def test_tiled_kernels(M, N, K, what):
+def test_sliced_kernel_by_choice(M, N, K, nb, what):
+    """Sizes at which the library takes the sliced kernel by itself, with each number of row blocks."""
+    x, w = bits((M, K), 70 + M), bits((N, K), 71 + (N % 97))
+    ov = ow.weight_view(0, 0, 1, N, K)
+    dx, dw, gv = dev(x), dev(w), gpu_view(ov)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    ran = kernels_of(lambda: kv.kv_linear_view(dx, dw, gv, out=y))
+    assert f"linear_slice_kernel<{nb}>" in ran, ran
+    check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ov, what)
+
+
+def test_one_workspace_for_every_batch_size():
+    """A workspace of the size asked for the largest batch serves every smaller one, whichever kernels they take; what
+    a call writes stays inside the size asked for its own."""
+    N, K = 6144, 4096
+    x, w = bits((600, K), 80), bits((N, K), 81)
+    ov = ow.weight_view(0, 0, 1, N, K)
+    gv, dx, dw = gpu_view(ov), dev(x), dev(w)
+    ask = [kv.lib().kv_linear_view_workspace_bytes(C.byref(gv), M) for M in (1, 64, 65, 200, 257, 384, 512, 600)]
+    assert ask == sorted(ask)
+    rows = np.array([0, 31, 63, 64, 199, 255, 256, 383, 511, 599])
+    want = ow.linear_view(x[rows], w, ov)
+    tol = linear_tolerance(x[rows], w, ov, want)
+    for M, own in zip((1, 64, 65, 200, 257, 384, 512, 600), ask):
+        ws = torch.full((ask[-1],), 0x5A, dtype=torch.uint8, device=DEV)
+        y = kv.kv_linear_view(dx[:M], dw, gv, workspace=ws)
+        torch.cuda.synchronize()
+        assert (ws[own:] == 0x5A).all(), M
+        keep = rows < M
+        got = bf16_bits_to_f64(y.cpu().view(torch.int16).numpy().view(np.uint16)[rows[keep]])
+        assert (np.abs(got - want[keep]) <= tol[keep]).all(), M
+
+
+@pytest.mark.parametrize("M,N,K,tile,what", [
+    (65, 3136, 128, (64, 64), "one batch row in the second tile; one slab"),
+    (1, 6208, 4224, (64, 64), "one batch row, two slices, 33 slabs"),
+    (65, 1472, 2304, (64, 64), "three slices of six slabs"),
+    (257, 6208, 128, (128, 64), "the last weight tile is half full"),
+    (129, 6208, 384, (64, 128), "three slabs: six stages through three buffers"),
+    (5000, 3136, 128, (128, 128), "two workgroups per compute unit"),
+    (1000, 6208, 128, (128, 256), "both last tiles partly full"),
+    (2047, 4160, 256, (192, 256), "the last weight tile has 128 of its 192 rows"),
+    (2047, 6208, 128, (256, 256), "the last weight tile has 64 of its 256 rows"),
+    (700, 4160, 1152, None, "more than one slice allowed: nine slabs"),
+])
+def test_tiled_kernels(M, N, K, tile, what):
     """Shapes that take each tile of the LDS-staged kernels, with batch rows and weight rows that fill none
     of them evenly.  The view has three row segments in another order than stored, the weight and x are
     column ranges of wider tensors, and y has a row stride that only allows 8-byte stores."""
@@ -150,8 +198,9 @@ def test_tiled_kernels(M, N, K, what):
     x, w = bits((M, K + 64), 300 + M), bits((N + 128, K + 256), 301 + (N % 97))
     ov = ow.WeightView(segments, 128, K)
     out = torch.full((M + 1, N + 4), 7.0, dtype=torch.bfloat16, device=DEV)
-    kv.kv_linear_view(dev(x)[:, :K], dev(w), gpu_view(ov), out=out[:M, :N])
-    torch.cuda.synchronize()
+    dx, dw, gv = dev(x), dev(w), gpu_view(ov)
+    ran = kernels_of(lambda: kv.kv_linear_view(dx[:, :K], dw, gv, out=out[:M, :N]))
+    assert (f"linear_tile_kernel<{tile[0]}, {tile[1]}," if tile else "linear_tile_kernel<") in ran, ran
     assert (out[M:] == 7.0).all() and (out[:, N:] == 7.0).all(), what
     got = out[:M, :N].contiguous().cpu().view(torch.int16).numpy().view(np.uint16)
     check(got, np.ascontiguousarray(x[:, :K]), w, ov, what)
