@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256) void linear_tile_add_kernel(linear_args p, int
 {
     constexpr int TN = BN / WN, TM = BM / WM, NB = TN / 32, MB = TM / 32, kPerTile = WN * WM * NB * MB;
     constexpr int kPitch = 40;
-    __shared__ uint16_t s[4 * 32 * kPitch];
+    __shared__ __align__(16) uint16_t s[4 * 32 * kPitch];   // (written in pieces of 8 bytes, read in pieces of 16)
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tiles = (int64_t)n_tiles * m_tiles;
     const int64_t unit = (int64_t)blockIdx.x * 4 + wv;
