@@ -86,48 +86,12 @@ __device__ __forceinline__ void finish_chunk_valu(const decode_args& a, float (&
     }
 }
 
-// Epilogue of the matrix-core kernel: the wavefronts' (m, l, acc) sit in s_ml and s_acc.  Writes the final rows where the sequence has a
-// single chunk, else this chunk's partial; with a.sync the last chunk of the pair to arrive then combines
-// all of them: partials are written and read with device-coherent accesses, the arrival counter is
-// touched once they are acknowledged, and the arriver that completes the count puts it back to zero.
+// The last chunk of a (sequence, KV head) pair to arrive combines the partials of all of them.
 template <int D, int NW, int GM>
-__device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc)[NW][GM][D], float (&s_ml)[NW][GM][2], int G,
-                                             int s, int hl, int chunk, int n_chunks)
+__device__ __forceinline__ void combine_chunks(const decode_args& a, float (&s_acc)[NW][GM][D], int G, int s, int hl, int n_chunks)
 {
     constexpr int T = NW * 64, HD = D / 2;
     const int tid = threadIdx.x;
-    for (int idx = tid; idx < G * HD; idx += T) {
-        const int g = idx / HD, e = 2 * (idx - g * HD);
-        float mm = kNegInf;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) mm = fmaxf(mm, s_ml[w][g][0]);
-        const float ms = (mm == kNegInf) ? 0.f : mm;
-        float ll = 0.f, a0 = 0.f, a1 = 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float cw = fast_exp2(s_ml[w][g][0] - ms);
-            const f32x2 x = *reinterpret_cast<const f32x2*>(&s_acc[w][g][e]);
-            ll += s_ml[w][g][1] * cw;
-            a0 += x[0] * cw;
-            a1 += x[1] * cw;
-        }
-        const int64_t row = (int64_t)s * a.v.n_q_local + hl * G + g;
-        if (n_chunks <= 1) {
-            const float inv = ll > 0.f ? 1.0f / ll : 0.f;
-            *reinterpret_cast<uint32_t*>(a.out + row * D + e) = pack_bf16x2(a0 * inv, a1 * inv);
-        } else {
-            const int64_t rec = row * a.max_chunks + chunk;
-            if (a.sync) {
-                st_coherent2(a.part_acc + rec * D + e, a0, a1);
-                if (e == 0) st_coherent2(a.part_ml + rec * 2, mm, ll);
-            } else {
-                *reinterpret_cast<f32x2*>(a.part_acc + rec * D + e) = f32x2{a0, a1};
-                if (e == 0) *reinterpret_cast<f32x2*>(a.part_ml + rec * 2) = f32x2{mm, ll};
-            }
-        }
-    }
-    if (n_chunks <= 1 || !a.sync) return;
-
     __shared__ int s_last;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -194,6 +158,52 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
         }
         const float inv = 1.0f / l;
         *reinterpret_cast<uint32_t*>(a.out + ((int64_t)s * a.v.n_q_local + hl * G + g) * D + e) = pack_bf16x2(a0 * inv, a1 * inv);
+    }
+}
+
+// Epilogue of the matrix-core kernel: the wavefronts' (m, l, acc) sit in s_ml and s_acc.  Writes the final rows where
+// the sequence has a single chunk, else this chunk's partial; with a.sync (head_dim 128 only) the last chunk of the
+// pair to arrive then combines all of them: partials are written and read with device-coherent accesses, the arrival
+// counter is touched once they are acknowledged, and the arriver that completes the count puts it back to zero.
+template <int D, int NW, int GM>
+__device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc)[NW][GM][D], float (&s_ml)[NW][GM][2], int G,
+                                             int s, int hl, int chunk, int n_chunks)
+{
+    constexpr int T = NW * 64, HD = D / 2;
+    constexpr bool kCombines = D == 128;
+    const int tid = threadIdx.x;
+    for (int idx = tid; idx < G * HD; idx += T) {
+        const int g = idx / HD, e = 2 * (idx - g * HD);
+        float mm = kNegInf;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mm = fmaxf(mm, s_ml[w][g][0]);
+        const float ms = (mm == kNegInf) ? 0.f : mm;
+        float ll = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float cw = fast_exp2(s_ml[w][g][0] - ms);
+            const f32x2 x = *reinterpret_cast<const f32x2*>(&s_acc[w][g][e]);
+            ll += s_ml[w][g][1] * cw;
+            a0 += x[0] * cw;
+            a1 += x[1] * cw;
+        }
+        const int64_t row = (int64_t)s * a.v.n_q_local + hl * G + g;
+        if (n_chunks <= 1) {
+            const float inv = ll > 0.f ? 1.0f / ll : 0.f;
+            *reinterpret_cast<uint32_t*>(a.out + row * D + e) = pack_bf16x2(a0 * inv, a1 * inv);
+        } else {
+            const int64_t rec = row * a.max_chunks + chunk;
+            if (kCombines && a.sync) {
+                st_coherent2(a.part_acc + rec * D + e, a0, a1);
+                if (e == 0) st_coherent2(a.part_ml + rec * 2, mm, ll);
+            } else {
+                *reinterpret_cast<f32x2*>(a.part_acc + rec * D + e) = f32x2{a0, a1};
+                if (e == 0) *reinterpret_cast<f32x2*>(a.part_ml + rec * 2) = f32x2{mm, ll};
+            }
+        }
+    }
+    if constexpr (kCombines) {
+        if (n_chunks > 1 && a.sync) combine_chunks<D, NW, GM>(a, s_acc, G, s, hl, n_chunks);
     }
 }
 
