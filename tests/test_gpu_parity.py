@@ -10,7 +10,7 @@ from oracle import LAYOUT_DP, LAYOUT_TP
 from paper_2602_22593_amd import binding as kv
 from paper_2602_22593_amd import workloads as wl
 
-from helpers import make_mixed_case, bf16_bits_to_f64, geometry, make_case, q_slice
+from helpers import make_mixed_case, bf16_bits_to_f64, geometry, kernels_of, make_case, q_slice
 
 pytestmark = pytest.mark.gpu
 
@@ -67,7 +67,7 @@ def test_tiny_config_all_views(triple, chunk):
 RAGGED = np.array([1, 15, 16, 17, 0, 511, 513, 1300, 2049, 64], dtype=np.int32)
 
 
-@pytest.mark.parametrize("kernel", [0, 2, 3])   # 0 = automatic (even-split matrix-core kernel at d = 128), 2 = vector-ALU, 3 = chunked matrix-core
+@pytest.mark.parametrize("kernel", [0, 1, 2, 3])   # 0 = automatic (by size: the even split or chunks), 1 = even split, 2 = vector-ALU, 3 = chunked matrix-core
 @pytest.mark.parametrize("chunk", [0, 256])
 @pytest.mark.parametrize("hq,hkv,triple", [
     (32, 8, (LAYOUT_DP, 1, 0)), (32, 8, (LAYOUT_TP, 2, 1)), (32, 8, (LAYOUT_TP, 4, 3)),
@@ -147,15 +147,20 @@ def test_several_heads_per_wavefront_every_tail_length(hq, hkv, triple):
     """The kernel that gives a wavefront 2 or 4 adjacent KV heads: every context length from 0 to
     40 (every fill of the last 8- or 16-token tile, with and without full tiles before it), plus
     lengths around block and window boundaries; the pool is NaN-poisoned outside the valid tokens.
-    Same shapes with one head per wavefront as the cross-check of the option."""
+    Same shapes with one head per wavefront as the cross-check of the option.  waves_per_cu at its default value
+    asks for the even split in the form that large batches get."""
     lens = np.array(list(range(41)) + [127, 128, 129, 1023, 1025, 2050], dtype=np.int32)
     w = wl.Workload("wide", 80 + hq // 8, hq, hkv, 128, 16, len(lens), "x", ())
     c = make_case(w, triple, lens)
     want = oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx)
     try:
+        kv.kv_set_option("waves_per_cu", 4)
         for one_head in (0, 1):
             kv.kv_set_option("heads_per_wave", one_head)
-            got = run_gpu_decode(c, gpu_view(w, triple))
+            result = []
+            ran = kernels_of(lambda: result.append(run_gpu_decode(c, gpu_view(w, triple))))
+            assert ("decode_streamk_kernel<" if one_head else f"decode_wide_kernel<{2 if hq // hkv > 4 else 4},") in ran, ran
+            got = result[0]
             check_close(got, want, f"{hq}/{hkv} {triple} one_head {one_head}")
             assert (got[0] == 0).all()
             G = hq // hkv
@@ -164,6 +169,7 @@ def test_several_heads_per_wavefront_every_tail_length(hq, hkv, triple):
                 assert np.array_equal(got[1, i], bf16_bits_to_f64(c.V[c.seq_off[1], g]))
     finally:
         kv.kv_set_option("heads_per_wave", 0)
+        kv.kv_set_option("waves_per_cu", 0)
 
 
 @pytest.mark.parametrize("merge_mode", [0, 1, 2])
@@ -177,11 +183,15 @@ def test_long_sequences_cut_over_every_wavefront_head_groups(merge_mode):
     c = make_case(w, (LAYOUT_DP, 1, 0), ctx)
     want = oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx)
     kv.kv_set_option("merge_mode", merge_mode)
+    kv.kv_set_option("waves_per_cu", 4)      # (its default value: the even split in the form of a large batch)
     try:
-        got = run_gpu_decode(c, gpu_view(w, (LAYOUT_DP, 1, 0)))
+        result = []
+        ran = kernels_of(lambda: result.append(run_gpu_decode(c, gpu_view(w, (LAYOUT_DP, 1, 0)))))
     finally:
         kv.kv_set_option("merge_mode", 0)
-    check_close(got, want, f"long sequence, head groups, merge mode {merge_mode}")
+        kv.kv_set_option("waves_per_cu", 0)
+    assert "decode_wide_kernel<4," in ran and ("decode_streamk_merge_kernel" in ran) == (merge_mode != 1), ran
+    check_close(result[0], want, f"long sequence, head groups, merge mode {merge_mode}")
 
 
 @pytest.mark.parametrize("cost", [0, 8, 64])
