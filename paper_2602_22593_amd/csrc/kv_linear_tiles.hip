@@ -362,6 +362,7 @@ tiles_cfg tiles_pick(int M, int64_t n_l, int total_slabs, size_t most_workspace)
     if (n_l > (1 << 30)) return best;
     for (int i = 0; i < kShapeCount; ++i) {
         const tile_shape& t = kShapes[i];
+        if (t.bm > 64 && t.bm >= 2 * (int64_t)M) continue;   // (a smaller one does as well: not worth its share of the call)
         const int64_t tiles = tile_count(t, M, n_l);
         for (int want = 1; want <= 8 && want <= total_slabs; ++want) {
             const int per = (total_slabs + want - 1) / want, splits = (total_slabs + per - 1) / per;
