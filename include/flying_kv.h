@@ -335,7 +335,8 @@ int kv_validate_tables(const kv_view* view, int64_t n_pool_blocks, const int32_t
  *   "waves_per_cu"   wavefronts per compute unit launched by the even-split kernel, a multiple of 4.
  *                    paged_decode_attn_workspace_bytes follows "force_kernel", "waves_per_cu" and
  *                    "chunk_tokens": size the workspace after setting them
- *   "heads_per_wave" 1: one KV head per wavefront even where several adjacent heads are possible
+ *   "heads_per_wave" 1: one KV head per wavefront even where several adjacent heads are possible (and,
+ *                    like the four options named at the end, the even split for small batches too)
  *   "merge_mode"     how the pieces of a sequence cut over several wavefronts are combined:
  *                    1 inside the main kernel by the last piece to arrive, 2 by a second launch
  *   "xcd_skew"       even-split decode kernels: share moved from each odd-numbered to each even-numbered

@@ -1,5 +1,5 @@
-// kv_linear_view in LDS-staged tiles, y = x W_active^T: prompts, chunks and large batches, and decode batches on
-// a weight slice that the x-resident kernel of kv_linear_view.hip cannot cover with one round of workgroups.
+// kv_linear_view in LDS-staged tiles, y = x W_active^T: prompts, chunks and large batches, and the decode batches on
+// weight slices that the x-resident kernel of kv_linear_view.hip is estimated to take longer for (make_plan there).
 //
 // Bound: the matrix cores for many batch rows (4096 rows of the 6144 x 4096 QKV weight are 206 GFLOP: 140 us at
 // the 1.47 PFLOP/s that a large library product reaches on this card), the weight stream for few.
@@ -18,9 +18,10 @@
 // y leave through LDS, 128 bytes or more of a row per store (8-byte stores straight from the registers
 // cost 10 us of 117 at 4096 x 4096 x 4096).
 //
-// Measured (4096 batch rows, the 6144 x 4096 weight): 159-175 us = 1.18-1.30 PFLOP/s with 192 x 256 tiles,
-// two full rounds of the 256 compute units; the sliced kernel took 670 us.  With no loads at all the loop runs
-// at 1.7 PFLOP/s (matrix pipe and LDS reads); the rest is the wait for L2.
+// Measured (4096 batch rows, the 6144 x 4096 weight): 181 us = 1.14 PFLOP/s with 192 x 256 tiles, two full rounds
+// of the 256 compute units (163 on a chip that has been idle, before its clock comes down); the sliced kernel took
+// 670 us.  Matrix pipe busy 65 % of the cycles, LDS reads 56 %, wavefronts waiting 30 % of theirs.  With no loads
+// at all the loop runs at 1.7 PFLOP/s (matrix pipe and LDS reads); the rest is the wait for L2.
 #include "kv_linear_args.h"
 
 using namespace kvdec;
@@ -324,7 +325,7 @@ size_t part_bytes(const tile_shape& t, int64_t tiles, int splits)
     return splits <= 1 ? 0 : (size_t)splits * tiles * t.bn * t.bm * 4;
 }
 
-// Estimated time of a launch (us).
+// Estimated time of a launch (us) on the 256 compute units of an MI355X, which the constants were fitted on.
 double estimate(const tile_shape& t, int64_t tiles, int splits, int slice_slabs)
 {
     const int64_t wgs = tiles * splits, whole = wgs >> 8;
@@ -355,7 +356,8 @@ void launch_shape(const linear_args& p, hipStream_t st)
 // Which tile and how many slices of the input dimension: the cheapest by estimate().  Its constants were
 // fitted to a sweep of 15 weight shapes (320 x 640 to 10240 x 8192) x 22 batch sizes (20 to 8192) x all tiles x 1
 // to 8 slices: the choice is 0.8 % slower than the best one of the sweep on average and 14 % at most.
-// Never more workspace than `most_workspace`.
+// Never more workspace than `most_workspace`.  The estimate with the choice is what make_plan weighs against the
+// x-resident kernel.
 tiles_cfg tiles_pick(int M, int64_t n_l, int total_slabs, size_t most_workspace)
 {
     tiles_cfg best = {-1, 1, total_slabs, 0.0};
@@ -375,7 +377,7 @@ tiles_cfg tiles_pick(int M, int64_t n_l, int total_slabs, size_t most_workspace)
     return best;
 }
 
-size_t tiles_workspace(const tiles_cfg& c, int M, int64_t n_l) 
+size_t tiles_workspace(const tiles_cfg& c, int M, int64_t n_l)
 {
     return part_bytes(kShapes[c.shape], tile_count(kShapes[c.shape], M, n_l), c.splits);
 }

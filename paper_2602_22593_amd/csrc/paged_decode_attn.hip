@@ -217,8 +217,8 @@ __device__ __forceinline__ void finish_chunk(const decode_args& a, float (&s_acc
 // (one, where the chip has enough wavefronts), all K and V bytes of a tile are requested before any is used, and
 // few chunks of a sequence are combined by the last workgroup to arrive, many by a second launch that spreads
 // them over eight slices of lanes.  What it measures against the even-split kernels stands at
-// small_batch_chunk(); against the vector-ALU kernel, head_dim 64: 4 sequences of 17 to 300 tokens, 2 KV heads
-// 11.0 -> 4.6 us, 32 of 100 to 4000, 8 KV heads 72 -> 49 us, one of 8000 19.3 -> 12.0 us.
+// small_batch_chunk(); against the vector-ALU kernel, head_dim 64, G = 4, us per call in a replayed graph: 4 sequences of
+// 17 to 300 tokens, 2 KV heads 9.4 -> 4.6; 32 of 100 to 4000, 8 KV heads 60 -> 49; one of 8000, 8 KV heads 16.8 -> 8.9.
 //
 // Lane l = (r = l % 16, quad = l / 16).  Both products put the KV data in the MFMA A operand
 // (row index = r) and the query group in the B operand (column index = r = query head g):
@@ -731,6 +731,10 @@ int check_streamk(const kv_view* view, int batch, int max_ctx_len, const void* w
 // 16 sequences under TP4 (41 MB) 16.8 against 14.0; 32 under TP8, G = 8 (36 MB) 17.2 against 14.4; 32 under TP8 (40
 // MB, 66 by the bound) 16.5 against 15.1; but 8 sequences, 8 heads (81 MB, 130 by the bound) 22.4 against 25,
 // 64 under TP8 (75 MB, 134 by the bound) 20.3 against 23.5.  The host knows the bound only.
+// The limit on the lengths, geometric means over one to three sequences of few heads, this kernel against the even
+// split: 9000 to 16000 tokens 13.5 against 18.2 (35 shapes); 16000 to 32000, 15.8 against 22.0 (26); 33000 to 65000,
+// 21.5 against 24.3 (21); longer ones 31.0 against 29.6 (14): the second launch reads ever more chunks there, while the
+// even split costs what it cost.  32768 is on the safe side of that crossing.
 constexpr int64_t kSmallBytes = 80000000;
 constexpr int kSmallCtx = 32768;
 int64_t small_batch_chunk(const kv_view* view, int batch, int max_ctx_len)
