@@ -1259,9 +1259,10 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     //   30.1 against 21.5; even at 32, 532 MB; a gain at 64, 1070 MB);
     // - one or two: only where the pairs are few, whose lists of pieces then are long (G = 1, 4 heads: one sequence of
     //   60000, 123 MB, 40.3 against 32.4; with three short ones, 492 MB, 41.0 against 33.9; G = 2, 8 of 200 to 2000, 4
-    //   heads, 134 MB: 15.1 against 12.0, but 8 of 8000 to 16000, 252 MB: 43.3 against 44.9).  With more pairs a single head's 256-byte rows with a column or two of work each
-    //   are the slower stream (G = 1, 8 of 500 to 4000, 8 heads, 130 MB: 20.8 against 28.5; 64 of 1000, 262 MB: 48.6
-    //   against 55.8; G = 2, 16 of 500 to 4000, 4 heads, 125 MB: 23.4 against 27.6);
+    //   heads, 134 MB: 15.1 against 12.0, but 8 of 8000 to 16000, 252 MB: 43.3 against 44.9).  With more pairs a
+    //   single head's 256-byte rows with a column or two of work each are the slower stream (G = 1, 8 of 500 to
+    //   4000, 8 heads, 130 MB: 20.8 against 28.5; 64 of 1000, 262 MB: 48.6 against 55.8; G = 2, 16 of 500 to 4000,
+    //   4 heads, 125 MB: 23.4 against 27.6);
     // - three: the same, and four heads lose below 100 MB (16 of 1000, 66 MB: 23.0 against 22.2; but 8 of 500 to
     //   4000, 117 MB: 23.5 against 27.7);
     // - five and six: as often the one as the other (34 shapes from 40 to 1000 MB: 0.76 to 1.21 times, 1.01 on
