@@ -326,31 +326,27 @@ size_t scratch_bytes(const linear_cfg& c, int64_t m_tiles, int64_t n_l)
 constexpr int kNb[] = {1, 2, 3, 4, 6};
 
 // Estimated time (us) of the sliced kernel with NB row blocks per workgroup: the first round of workgroups (two per
-// compute unit fit for NB 1 and 2), the next, the second kernel and its partial sums, the weights; workgroups of the
-// second kernel find their slices in their own XCD's L2 if tiles come in eights.  Fitted to 46 weight shapes x 15
-// batches (1 to 1000 rows) x NB, weights from HBM and from the caches in equal parts: 7 % off.  Beyond these rounds the
-// tiled kernels are the better ones: every round costs this one a full pass over its piece of x before the first
-// product.  Their estimate is brought to the same footing: with weights from HBM they are slower than it says.
-// So chosen, on 620 of those points: 0.94 times the time of a fixed line at 256 workgroups, and 0.2 % off the better of
-// the two on average.  Examples, sliced with the best NB against tiled, us with weights from HBM / from the caches: 64
-// rows of 3072 x 4096 (NB 3) 10.8 / 9.6 against 13.4 / 11.0; 128 of 1536 x 4096 (3) 9.5 / 9.1, 12.8 / 10.6; 256 of
-// 1024 x 4096 (4) 10.9 / 10.6, 13.2 / 11.1; 256 of 1536 x 4096 (6) 13.7 / 13.5, 15.9 / 13.0; 64 of 6144 x 4096 (6) 16.6 /
-// 15.4, 18.7 / 13.7; 100 of 4096 x 2048 (4) 10.8 / 10.2, 11.6 / 9.2; 300 of 4096 x 1024 (1) 12, 8.
+// compute unit fit for NB 1 and 2), the next, the weights, the second kernel and its partial sums; workgroups of the
+// second kernel find their slices in their own XCD's L2 if tiles come in eights.  Beyond these rounds the tiled
+// kernels are the better ones: every round costs this one a full pass over its piece of x before the first product.
+//
+// All estimates were fitted together to the time of every kernel, tile, cut and NB on 37 weights (640 x 640 to 12288 x
+// 4096 and 10240 x 8192) x 24 batches (1 to 4096 rows), weights from HBM and from the caches in equal parts, replayed
+// from a graph: 7 % off.  Examples, sliced with the best NB against the best tile (us): 64 rows of 3072 x 4096
+// 10.9 / 12.7, of 1536 x 4096 8.7 / 10.5, of 6144 x 4096 16.5 / 15.7; 72 of 3072 x 4096 14.1 / 13.8; 100 of 4096 x 1024
+// 6.3 / 5.9.
 double sliced_estimate(const linear_cfg& c, int nb, int64_t m_tiles, int64_t n_l, int total_slabs)
 {
-    static const double kFirst[] = {0.0, 4.5, 5.8, 6.2, 7.3, 0.0, 8.8};
+    static const double kFirst[] = {0.0, 4.78, 5.8, 6.54, 7.61, 0.0, 8.21};
+    static const double kBytesPerUs[] = {0.0, 62.8e6, 26.1e6, 24.9e6, 31.4e6, 0.0, 21.4e6};
     const int64_t wgs = workgroups(c, nb, m_tiles, n_l);
     const double weight_bytes = (double)n_l * total_slabs * kSlab * 2;
-    double us = kFirst[nb] + (wgs > 256 ? 2.1 : 0.0) + weight_bytes / (nb == 6 ? 20.0e6 : 40.0e6);
+    double us = kFirst[nb] + (wgs > 256 ? 1.92 : 0.0) + weight_bytes / kBytesPerUs[nb];
     if (c.splits > 1) {
-        us += 1.5 + (double)part_bytes(c, m_tiles, n_l) / 1.95e6;
-        if (wgs / c.splits % 8 != 0) us += 0.43 * c.splits;
+        us += 1.34 + (double)part_bytes(c, m_tiles, n_l) / 1.67e6;
+        if (wgs / c.splits % 8 != 0) us += 0.295 * c.splits;
     }
     return us;
-}
-double tiled_estimate(const tiles_cfg& t, int64_t n_l, int total_slabs)
-{
-    return 1.2 * t.us - 0.9 + (double)n_l * total_slabs * kSlab * 2 / 32.0e6;
 }
 
 // The kernel and the cut of a call: tiles.shape < 0 means the sliced kernel as `sliced` says.
@@ -372,13 +368,13 @@ linear_plan make_plan(int M, int64_t n_l, int total_slabs)
         return pl;
     }
     pl.tiles = tiles_pick(M, n_l, total_slabs, scratch_bytes(pl.sliced, m_tiles, n_l));
-    double best = pl.tiles.shape < 0 ? 0.0 : tiled_estimate(pl.tiles, n_l, total_slabs);
+    double best = pl.tiles.shape < 0 ? 0.0 : pl.tiles.us;
     bool sliced = pl.tiles.shape < 0;
     for (int nb : kNb) {
         if (workgroups(pl.sliced, nb, m_tiles, n_l) > (nb <= 2 ? 512 : 256)) continue;
-        if (nb == 6 && m_tiles > 4) continue;   // (512 rows of 768 x 4096: 17.6 us, tiled 15.4 / 13.0)
-        // (a tie goes to this kernel, but for NB 6)
-        const double us = (nb < 6 ? 0.96 : 1.0) * sliced_estimate(pl.sliced, nb, m_tiles, n_l, total_slabs);
+        // (NB 6 for two to four batch tiles: 64 rows of 6144 x 4096 16.5 us, streamed 15.1; 512 of 768 x 4096 17.6, tiled 13)
+        if (nb == 6 && (m_tiles < 2 || m_tiles > 4)) continue;
+        const double us = sliced_estimate(pl.sliced, nb, m_tiles, n_l, total_slabs);
         if (best > 0.0 && us >= best) continue;
         best = us;
         pl.sliced.nb = nb;

@@ -213,3 +213,22 @@ def test_tiled_kernel_whole_line_stores():
     y = kv.kv_linear_view(dev(x), dev(w), kv.kv_weight_view_make(0, 0, 1, N, K))
     torch.cuda.synchronize()
     check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ow.weight_view(0, 0, 1, N, K), "aligned rows")
+
+
+@pytest.mark.parametrize("M,N,K,kernel,what", [
+    (2500, 3328, 384, "192, 256, 2, 4, 2, 1, 3", "six stages: two buffers of weights, three of x, once round"),
+    (2500, 3328, 640, "192, 256, 2, 4, 2, 1, 3", "ten stages: once round and four"),
+    (2500, 4928, 512, "256, 256, 2, 4, 2, 1, 3", "eight stages: once round and two"),
+    (300, 6592, 384, "192, 64, 2, 2, 4, 1, 4", "six stages through four buffers; requests past the end"),
+    (2500, 1216, 640, "128, 128, 2, 2, 4, 1, 4", "ten stages through four buffers"),
+    (100, 1472, 2304, "64, 64, 2, 2, 4, 2, 4", "weight tiles that start at another stage each"),
+])
+def test_stages_through_the_buffers(M, N, K, kernel, what):
+    """Every remainder of the stage loop, with tiles that neither dimension fills."""
+    x, w = bits((M, K), 500 + K), bits((N, K + 64), 501 + (N % 97))
+    ov = ow.WeightView(((0, N),), 64, K)
+    dx, dw, gv = dev(x), dev(w), gpu_view(ov)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    ran = kernels_of(lambda: kv.kv_linear_view(dx, dw, gv, out=y))
+    assert f"linear_tile_kernel<{kernel}>" in ran, ran
+    check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ov, what)
