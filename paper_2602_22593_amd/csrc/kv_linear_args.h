@@ -43,4 +43,12 @@ tiles_cfg tiles_pick(int M, int64_t n_l, int total_slabs, size_t most_workspace)
 size_t tiles_workspace(const tiles_cfg& c, int M, int64_t n_l);
 void tiles_launch(const tiles_cfg& c, linear_args p, hipStream_t st);
 
+// The streaming kernel (kv_linear_stream.hip): 16 nb weight rows x 16 mb batch rows per workgroup (`nb` 0: none).
+struct stream_cfg {
+    int nb, mb;
+    double us;   // estimated
+};
+stream_cfg stream_pick(int M, int64_t n_l, int total_slabs);
+void stream_launch(const stream_cfg& c, linear_args p, hipStream_t st);
+
 }  // namespace kvlin

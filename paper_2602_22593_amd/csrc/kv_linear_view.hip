@@ -5,9 +5,9 @@
 // row-parallel output projection) of a weight kept once, whole, as [out][in] bf16.  Nothing is
 // copied: the kernel addresses the full matrix with its own leading dimension.
 //
-// Two families of kernels serve it.  This file holds the one that keeps x in registers, for decode batches on weight
-// slices of up to about 30 MB; kv_linear_tiles.hip the LDS-staged tiles for what is larger (make_plan below chooses by
-// estimated time).
+// Three families of kernels serve it, chosen by estimated time (make_plan below).  kv_linear_stream.hip streams the weight
+// rows of a workgroup whole, in one launch: most decode batches.  This file holds the one that keeps x in registers, for
+// decode batches of 33 rows and more on small weight slices; kv_linear_tiles.hip the LDS-staged tiles for what is larger.
 //
 // In a decode step the weight slice is streamed from HBM and is the only HBM traffic that matters.  What
 // limits such a product on this chip is not HBM but the path from L2 into a compute unit (measured here:
@@ -349,10 +349,12 @@ double sliced_estimate(const linear_cfg& c, int nb, int64_t m_tiles, int64_t n_l
     return us;
 }
 
-// The kernel and the cut of a call: tiles.shape < 0 means the sliced kernel as `sliced` says.
+// The kernel and the cut of a call: the streaming kernel if stream.nb > 0, the tiled ones if tiles.shape >= 0, otherwise the
+// sliced kernel as `sliced` says.
 struct linear_plan {
     linear_cfg sliced;
     tiles_cfg tiles;
+    stream_cfg stream;
     size_t workspace;   // needed
 };
 linear_plan make_plan(int M, int64_t n_l, int total_slabs)
@@ -362,6 +364,7 @@ linear_plan make_plan(int M, int64_t n_l, int total_slabs)
     pl.sliced = sliced_cfg(total_slabs);
     pl.workspace = part_bytes(pl.sliced, m_tiles, n_l);
     pl.tiles = tiles_cfg{-1, 1, total_slabs, 0.0};
+    pl.stream = stream_cfg{0, 0, 0.0};
     if (kv_option_linear_splits() > 0) {   // the largest NB that gives a workgroup to every compute unit
         for (int nb : kNb)
             if (workgroups(pl.sliced, nb, m_tiles, n_l) >= 256) pl.sliced.nb = nb;
@@ -382,6 +385,11 @@ linear_plan make_plan(int M, int64_t n_l, int total_slabs)
     }
     if (sliced) pl.tiles.shape = -1;
     else pl.workspace = tiles_workspace(pl.tiles, M, n_l);
+    const stream_cfg stream = stream_pick(M, n_l, total_slabs);
+    if (stream.nb > 0 && (best == 0.0 || stream.us < best)) {
+        pl.stream = stream;
+        pl.workspace = 0;
+    }
     return pl;
 }
 
@@ -494,8 +502,8 @@ extern "C" int kv_linear_view(const void* x, int64_t ldx, const void* w_full, in
     // (per-lane offsets are 32 bits wide)
     if (n_tiles > 0x7fffffff || m_tiles > 65535 || (int64_t)M * ldx >= (1ll << 31) || ldw >= (1ll << 28))
         return KV_ERR_UNSUPPORTED;
-    const bool tiled = plan.tiles.shape >= 0;
-    p.splits = tiled ? plan.tiles.splits : cfg.splits;
+    const bool streamed = plan.stream.nb > 0, tiled = plan.tiles.shape >= 0;
+    p.splits = streamed ? 1 : tiled ? plan.tiles.splits : cfg.splits;
     p.slice_slabs = tiled ? plan.tiles.slice_slabs : cfg.slice_slabs;
     p.part = (float*)workspace;
     if (p.splits > 1) {
@@ -503,9 +511,10 @@ extern "C" int kv_linear_view(const void* x, int64_t ldx, const void* w_full, in
         if (workspace_bytes < plan.workspace) return KV_ERR_WORKSPACE;
     }
     hipStream_t st = (hipStream_t)hip_stream;
-    if (tiled) {
+    if (streamed || tiled) {
         const int slot = kv_prof_begin(KV_PROF_LINEAR, st);
-        tiles_launch(plan.tiles, p, st);
+        if (streamed) stream_launch(plan.stream, p, st);
+        else tiles_launch(plan.tiles, p, st);
         kv_prof_end(KV_PROF_LINEAR, slot, st);
         return kv_record_hip_error(hipGetLastError(), "kv_linear_view launch");
     }

@@ -232,3 +232,31 @@ def test_stages_through_the_buffers(M, N, K, kernel, what):
     ran = kernels_of(lambda: kv.kv_linear_view(dx, dw, gv, out=y))
     assert f"linear_tile_kernel<{kernel}>" in ran, ran
     check(y.cpu().view(torch.int16).numpy().view(np.uint16), x, w, ov, what)
+
+
+@pytest.mark.parametrize("M,N,K,variant,what", [
+    (1, 640, 1664, "1, 1, 6", "26 stages: two wavefronts have seven, one more than the buffers, two have six"),
+    (16, 2176, 512, "1, 1, 6", "two stages per wavefront, fewer than the buffers"),
+    (17, 2176, 512, "1, 2, 4", "one row in the second block; two stages per wavefront"),
+    (64, 2176, 640, "1, 4, 2", "ten stages: three, three, two and two"),
+    (1, 4224, 384, "2, 1, 4", "six stages: two, two, one and one"),
+    (32, 4224, 640, "2, 2, 4", "132 row tiles: the last deal over the XCDs has four"),
+    (33, 4224, 384, "2, 4, 2", "one row in the third block"),
+    (16, 8320, 640, "3, 1, 4", "the last row tile has 16 of its 48 rows"),
+    (20, 8320, 1152, "3, 2, 3", "the same; four rows in the second block"),
+    (65, 4352, 4096, "3, 4, 2", "one row in the second batch tile; the last row tile has 32 of its 48 rows"),
+])
+def test_streaming_kernel(M, N, K, variant, what):
+    """Each variant of the one-launch kernel for decode batches.  The view has three row segments in another order than
+    stored, weight and x are column ranges of wider tensors, y has a row stride that only allows 8-byte stores."""
+    a, b = 64 * (N // 64 // 2), 64 * (N // 64 // 3)
+    segments = ((N - a + 128, a), (0, b), (b + 64, N - a - b))
+    x, w = bits((M, K + 64), 600 + M), bits((N + 128, K + 256), 601 + (N % 97))
+    ov = ow.WeightView(segments, 128, K)
+    out = torch.full((M + 1, N + 4), 7.0, dtype=torch.bfloat16, device=DEV)
+    dx, dw, gv = dev(x), dev(w), gpu_view(ov)
+    ran = kernels_of(lambda: kv.kv_linear_view(dx[:, :K], dw, gv, out=out[:M, :N]))
+    assert f"linear_stream_kernel<{variant}>" in ran, ran
+    assert (out[M:] == 7.0).all() and (out[:, N:] == 7.0).all(), what
+    got = out[:M, :N].contiguous().cpu().view(torch.int16).numpy().view(np.uint16)
+    check(got, np.ascontiguousarray(x[:, :K]), w, ov, what)
