@@ -162,6 +162,27 @@ def _dev_rows(t: torch.Tensor, dtypes, name: str) -> int:
 
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
 _workspaces = {}
+_calls_module = None
+
+
+def _calls():
+    """The module that marshals whole calls in C (csrc/binding_calls.c).  Its functions return the call's status, or None
+    for what the checks here have to answer: an argument that they refuse, or one out of the ordinary."""
+    global _calls_module
+    if _calls_module is None:
+        L = lib()
+        try:
+            from . import _calls as m
+        except ImportError as e:
+            raise RuntimeError(f"{os.path.join(_PKG, '_calls.so')} not usable: build it with "
+                               "`python -m paper_2602_22593_amd.build`") from e
+        functions = (L.paged_decode_attn, L.paged_prefill_attn, L.paged_prefill_attn_workspace_bytes, L.kv_linear_view,
+                     L.kv_linear_view_workspace_bytes, L.kv_append, L.kv_repack)
+        m.setup(tuple(C.cast(f, C.c_void_p).value for f in functions),
+                (torch.Tensor, torch.nn.Parameter, kv_weight_view), (_BF16, torch.int32, torch.uint8),
+                (torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream), _workspaces)
+        _calls_module = m
+    return _calls_module
 
 
 def paged_decode_attn_workspace_bytes(view: KVView, batch: int, max_ctx_len: int) -> int:
@@ -194,6 +215,12 @@ def paged_decode_attn(q: torch.Tensor, kv_pool: torch.Tensor, block_table: torch
 
     ``max_ctx_len`` is the caller's host-side bound of ``ctx_lens`` (no device sync here).
     """
+    if out is not None and workspace is not None:
+        rc = (_calls_module or _calls()).decode(q, kv_pool, block_table, ctx_lens, view, max_ctx_len, out, scale,
+                                                workspace, stream)
+        if rc is not None:
+            _check(rc, "paged_decode_attn")
+            return out
     batch = int(ctx_lens.shape[0])
     if tuple(q.shape) != (batch, view.n_q_local, view.head_dim):
         raise ValueError(f"q has shape {tuple(q.shape)}, expected {(batch, view.n_q_local, view.head_dim)}")
@@ -275,6 +302,12 @@ def paged_prefill_attn(q: torch.Tensor, kv_pool: torch.Tensor, block_table: torc
     q: bf16 [total_q][n_q_local][head_dim]; q_offsets: int32 [batch + 1] (device); the K/V of the
     new tokens are already in the pool.  ``max_ctx_len`` / ``max_q_len`` are host-side bounds.
     """
+    if out is not None:
+        rc = (_calls_module or _calls()).prefill(q, kv_pool, block_table, ctx_lens, q_offsets, view, max_ctx_len, max_q_len,
+                                                 out, scale, workspace, stream)
+        if rc is not None:
+            _check(rc, "paged_prefill_attn")
+            return out
     batch = int(ctx_lens.shape[0])
     if q.dim() != 3 or tuple(q.shape[1:]) != (view.n_q_local, view.head_dim):
         raise ValueError(f"q has shape {tuple(q.shape)}, expected [total_q, {view.n_q_local}, {view.head_dim}]")
@@ -328,6 +361,11 @@ def kv_linear_view(x: torch.Tensor, w_full: torch.Tensor, view: kv_weight_view,
                    out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                    stream=None) -> torch.Tensor:
     """y[M][view rows] (bf16) = x @ W_active^T, W_active = ``view`` of the stored ``w_full`` [out][in]."""
+    if out is not None:
+        rc = (_calls_module or _calls()).linear(x, w_full, view, out, workspace, stream)
+        if rc is not None:
+            _check(rc, "kv_linear_view")
+            return out
     if x.dim() != 2 or w_full.dim() != 2 or x.shape[1] != view.col_count:
         raise ValueError("x must be [M][view.col_count], w_full [out][in]")
     M = int(x.shape[0])
@@ -348,6 +386,10 @@ def kv_repack(kv_pool: torch.Tensor, src_view: KVView, dst_view: KVView,
               src_block_table: torch.Tensor, dst_block_table: torch.Tensor,
               n_tokens: torch.Tensor, max_tokens: int, stream=None) -> None:
     """Copy the heads common to both views from src-view blocks to dst-view blocks, in the pool."""
+    rc = (_calls_module or _calls()).repack(kv_pool, src_view, dst_view, src_block_table, dst_block_table, n_tokens,
+                                            max_tokens, stream)
+    if rc is not None:
+        return _check(rc, "kv_repack")
     n_seqs = int(n_tokens.shape[0])
     n_pool_blocks = kv_pool.numel() * kv_pool.element_size() // src_view.block_bytes
     rc = lib().kv_repack(
@@ -361,6 +403,9 @@ def kv_repack(kv_pool: torch.Tensor, src_view: KVView, dst_view: KVView,
 def kv_append(kv_pool: torch.Tensor, view: KVView, k_new: torch.Tensor, v_new: torch.Tensor,
               block_table: torch.Tensor, positions: torch.Tensor, stream=None) -> None:
     """Write each sequence's new K and V rows at token index positions[s] through ``view``."""
+    rc = (_calls_module or _calls()).append(kv_pool, view, k_new, v_new, block_table, positions, stream)
+    if rc is not None:
+        return _check(rc, "kv_append")
     n_seqs = int(positions.shape[0])
     want = (n_seqs, view.n_kv_local, view.head_dim)
     if tuple(k_new.shape) != want or tuple(v_new.shape) != want:

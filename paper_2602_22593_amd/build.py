@@ -1,4 +1,4 @@
-"""Build libflyingkv.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libflyingkv.so (HIP, gfx950 only) in-tree with hipcc, and the binding's _calls.so with the C compiler.
 
 ``python -m paper_2602_22593_amd.build`` compiles every ``csrc/*.hip`` into an object under
 ``_build/`` and links them into ``paper_2602_22593_amd/libflyingkv.so``.  hipcc cross-compiles
@@ -11,12 +11,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libflyingkv.so")
+CALLS = os.path.join(PKG, "_calls.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -47,6 +49,19 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_calls(force: bool) -> None:
+    src, header = os.path.join(CSRC, "binding_calls.c"), os.path.join(ROOT, "include", "flying_kv.h")
+    if not force and os.path.exists(CALLS) and all(os.path.getmtime(CALLS) >= os.path.getmtime(d) for d in (src, header)):
+        return
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), src, "-o", CALLS]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"the C compiler failed for {src}:\n{r.stderr}")
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sources()
@@ -56,6 +71,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
+    _build_calls(force)
     if verbose:
         print(f"built {LIB} from {len(objs)} objects")
     return LIB
