@@ -36,8 +36,7 @@ namespace {
 
 constexpr int D = 128;
 constexpr int kThreads = 256;
-constexpr int kSub = 1;               // 32-key sub-tiles per staged tile
-constexpr int kKeys = 32 * kSub;      // keys per staged tile (one barrier each)
+constexpr int kKeys = 32;             // keys per staged tile (one barrier each)
 constexpr int kMostCut = 1024;          // sequences up to which a workgroup reads all lengths
 // How the workgroups of a launch that cuts no key ranges find their query tiles, see the host code below
 constexpr int kSlots = 0, kDense = 1, kLongestFirst = 2;
@@ -56,6 +55,7 @@ struct prefill_args {
     int32_t group;          // G <= 16 query heads per KV head
     int32_t group_shift;    // log2 of G rounded up to a power of two: rows per token in the tile
     int32_t tile_shift;     // log2 of the new tokens per query tile
+    uint32_t group_inverse, group_inverse_shift;   // x / (block_tokens / 16) = hi32(2 x * inverse) >> shift, x < 2^31
     int32_t batch;
     int32_t slots;          // query tiles per KV head as numbered by slot_sequence(), gaps included
     int32_t order;          // kSlots, kDense or kLongestFirst
@@ -405,7 +405,7 @@ __device__ __forceinline__ int piece_slot(const int2* s_slot, int slots, int idx
     return min(c + __builtin_popcountll(__builtin_amdgcn_ballot_w64(in)), slots - 1);
 }
 
-// What bounds the loop is how far operand reads run ahead of the products, and that is a matter of registers: with
+// How far operand reads run ahead of the products is a matter of registers: with
 // the row sums taken by the matrix cores (eight sums, four of the all-ones operand) and the maximum exchanged
 // through LDS the compiler had one register pair of V operands to spare and waited for every read (8 prompts of
 // 4096 tokens, 32 query heads, 1095 us instead of 1069; 4 query heads 159 instead of 150; one prompt of 1000
@@ -421,8 +421,8 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // c ^ (2 * ((t / 4) % 4)), which puts the four rows a transposing read touches in different banks
     // one array per buffer: the compiler then knows that the loads landing in one buffer do not touch
     // the operands being read from the other
-    __shared__ kv_u32x4 s_k0[512 * kSub], s_k1[512 * kSub];
-    __shared__ kv_u32x4 s_v0[512 * kSub], s_v1[512 * kSub];
+    __shared__ kv_u32x4 s_k0[512], s_k1[512];
+    __shared__ kv_u32x4 s_v0[512], s_v1[512];
     __shared__ int2 s_slot[CUT ? kMostSlots : 1];
     __shared__ float s_cost[CUT ? kCandidates : 1];
 
@@ -530,57 +530,60 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // ---- staging: K and V tiles go from global memory straight into LDS, 16 bytes per lane; one
     // instruction of a wavefront fills 64 consecutive 16-byte slots = 4 rows of 16 pieces, and
     // which piece of its row a lane fetches is the LDS swizzle applied on the global side.
-    // Instruction i of wavefront w fills rows 16 i + 4 w .. + 3 of the tile (group i of 16 rows lies
-    // in one block).
+    // A wavefront fills eight rows of a tile, all of one group of 16 (wave / 2), which lies in one block: per tile it works
+    // out one address, from a block id asked for a tile before.  What bounds the loop is how many instructions a
+    // wavefront issues (one in 4 to 5 cycles, and the matrix products of another hold back its vector ones), so
+    // what does not compute is kept short: with four rows of either group, two ids and two addresses per tile, and
+    // operand addresses added up for every read (below) there were 83 scalar and 78 vector instructions beside 32
+    // products, now 57 and 64.  16 prompts of 128 to 4000 tokens, 32 query heads on 8, 798 -> 772 us, 4 of 8192
+    // 2016 -> 1938 (1.13 PFLOP/s), one of 4096 150 -> 138.
     const int dma_r = lane >> 4, dma_c = lane & 15;
-    const int row16 = 4 * wave + dma_r;                       // row within its group of 16
+    const int row8 = 8 * (wave & 1) + dma_r;                  // and + 4: rows within the group
     const int token_stride_bytes = v.token_stride * 2;
     const int64_t plane_bytes = v.plane_elems * 2;
-    const int halves_per_block = v.block_tokens >> 4;
-    const int half_shift = v.block_shift >= 4 ? v.block_shift - 4 : -1;
-    const int last_half = (n - 1) >> 4;
+    const int groups_per_block = v.block_tokens >> 4;
+    const int last_group = (n - 1) >> 4;
     typedef const __attribute__((address_space(4))) int32_t* const_ids;
     const const_ids ids = (const_ids)(a.table + (int64_t)s * a.table_stride);
     const char* pool_head = reinterpret_cast<const char*>(a.pool + v.head_off + hl * D);
     const int64_t block_bytes = (int64_t)v.block_elems * 2;
-    const uint32_t k_piece = (uint32_t)((dma_c ^ row16) << 4);
-    const uint32_t v_piece = (uint32_t)((dma_c ^ (2 * wave)) << 4);   // 2 ((row / 4) % 4), row / 4 = 4 i + w
-    const uint32_t lane_off_k = (uint32_t)(row16 * token_stride_bytes) + k_piece;
-    const uint32_t lane_off_v = (uint32_t)(row16 * token_stride_bytes) + v_piece;
+    const uint32_t group_bytes = 16u * (uint32_t)token_stride_bytes;
+    uint32_t k_lane[2], v_lane[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = row8 + 4 * i;
+        k_lane[i] = (uint32_t)(row * token_stride_bytes) + (uint32_t)((dma_c ^ row) << 4);
+        v_lane[i] = (uint32_t)(row * token_stride_bytes) + (uint32_t)((dma_c ^ (2 * (row >> 2))) << 4);
+    }
     typedef const __attribute__((address_space(1))) void* global_ptr;
     typedef __attribute__((address_space(3))) void* lds_ptr;
-    const int last_tile = n_tiles - 1;
+    // the group to be fetched next: its number, place in its block, and the block's id.  Past the end it is the last one
+    // (what is fetched then is masked, or of a tile past the last)
+    int g_at = 2 * t_begin + (wave >> 1) - 2, g_in = 0, g_id = 0;
+    auto hop = [&]() {
+        g_at = min(g_at + 2, last_group);
+        const uint32_t blk = __umulhi(2u * (uint32_t)g_at, a.group_inverse) >> a.group_inverse_shift;
+        g_in = g_at - (int)blk * groups_per_block;
+        g_id = ids[blk];
+    };
+    hop();
     // rows past the end of the sequence are replaced by its last token (finite data, masked later)
-    auto stage_tile = [&](int tile, kv_u32x4* dk, kv_u32x4* dv) {
-        int hh[2 * kSub], hb[2 * kSub], blk[2 * kSub];
-#pragma unroll
-        for (int h = 0; h < 2 * kSub; ++h) hh[h] = min(2 * kSub * tile + h, last_half);
-        if (half_shift >= 0) {
-#pragma unroll
-            for (int h = 0; h < 2 * kSub; ++h) hb[h] = hh[h] >> half_shift;
-        } else {
-#pragma unroll
-            for (int h = 0; h < 2 * kSub; ++h) hb[h] = hh[h] / halves_per_block;
-        }
-#pragma unroll
-        for (int h = 0; h < 2 * kSub; ++h) blk[h] = ids[hb[h]];
+    auto stage_tile = [&](kv_u32x4* dk, kv_u32x4* dv) {
+        const char* rows = pool_head + (uint64_t)(uint32_t)g_id * (uint64_t)block_bytes + (uint64_t)(uint32_t)g_in * group_bytes;
         // ordinary (cached) loads: every query tile of the sequence reads these keys again
-        if (2 * kSub * tile + 2 * kSub - 1 < last_half) {
+        if (g_at < last_group) {
 #pragma unroll
-            for (int h = 0; h < 2 * kSub; ++h) {
-                const char* base = pool_head + blk[h] * block_bytes +
-                                   (int64_t)(16 * hh[h] - hb[h] * v.block_tokens) * token_stride_bytes;
-                __builtin_amdgcn_global_load_lds((global_ptr)(base + lane_off_k), (lds_ptr)(dk + (4 * h + wave) * 64), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((global_ptr)(base + plane_bytes + lane_off_v), (lds_ptr)(dv + (4 * h + wave) * 64), 16, 0, 0);
+            for (int i = 0; i < 2; ++i) {
+                __builtin_amdgcn_global_load_lds((global_ptr)(rows + k_lane[i]), (lds_ptr)(dk + (2 * wave + i) * 64), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((global_ptr)(rows + plane_bytes + v_lane[i]), (lds_ptr)(dv + (2 * wave + i) * 64), 16, 0, 0);
             }
         } else {
 #pragma unroll
-            for (int h = 0; h < 2 * kSub; ++h) {
-                const int tok = min(16 * hh[h] + row16, n - 1);
-                const int slot = tok - hb[h] * v.block_tokens;
-                const char* p = pool_head + blk[h] * block_bytes + (int64_t)slot * token_stride_bytes;
-                __builtin_amdgcn_global_load_lds((global_ptr)(p + k_piece), (lds_ptr)(dk + (4 * h + wave) * 64), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((global_ptr)(p + plane_bytes + v_piece), (lds_ptr)(dv + (4 * h + wave) * 64), 16, 0, 0);
+            for (int i = 0; i < 2; ++i) {
+                const int row = row8 + 4 * i;
+                const uint32_t past = (uint32_t)(max(row - (n - 1 - 16 * g_at), 0) * token_stride_bytes);
+                __builtin_amdgcn_global_load_lds((global_ptr)(rows + (k_lane[i] - past)), (lds_ptr)(dk + (2 * wave + i) * 64), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((global_ptr)(rows + plane_bytes + (v_lane[i] - past)), (lds_ptr)(dv + (2 * wave + i) * 64), 16, 0, 0);
             }
         }
     };
@@ -609,7 +612,10 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     const int vt_tok = 4 * (r >> 2) + quad;
     const int vt_swz = 2 * ((vt_tok >> 2) & 3);   // the same for token 16 + vt_tok
 
-    if (t_begin < n_tiles) stage_tile(t_begin, s_k0, s_v0);
+    if (t_begin < n_tiles) {
+        stage_tile(s_k0, s_v0);
+        hop();
+    }
     // ---- this lane's query rows (B operands), one per row block --------------------------------
     bf16x8 qb[R][4];
     int pos[R];       // position of the column's query token
@@ -640,14 +646,22 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     staged();
 
     const int k_row = 4 * (r & 3) + (r >> 2);
+    // Byte offsets of this lane's operands in a K and a V tile; buffers, halves and later columns are constants that the
+    // reads carry.  Opaque: otherwise the compiler holds nine registers more, for both buffers, and adds one to
+    // another before every second read of V.
+    uint32_t k_off[4], v_off[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        k_off[u] = (uint32_t)(k_row * 256 + ((4 * u + quad) ^ k_row) * 16);
+        v_off[u] = (uint32_t)(vt_tok * 256 + ((2 * u + ((r & 3) >> 1)) ^ vt_swz) * 16 + (r & 1) * 8);
+        asm volatile("" : "+v"(k_off[u]), "+v"(v_off[u]));
+    }
     constexpr float kLag = 8.0f;
     auto compute = [&](int buf, int tile) {
-#pragma unroll
-      for (int sub = 0; sub < kSub; ++sub) {
-        const int base = kKeys * tile + 32 * sub;
-        const kv_u32x4* const sk = (buf ? s_k1 : s_k0) + 512 * sub;
-        const kv_u32x4* const sv = (buf ? s_v1 : s_v0) + 512 * sub;
-        if (base <= max_pos) {  // else every key of the sub-tile lies after all of this wavefront's queries
+        const int base = kKeys * tile;
+        const char* const sk = reinterpret_cast<const char*>(buf ? s_k1 : s_k0);
+        const char* const sv = reinterpret_cast<const char*>(buf ? s_v1 : s_v0);
+        if (base <= max_pos) {  // else every key of the tile lies after all of this wavefront's queries
             // ---- S^T = K q^T ------------------------------------------------------------------------
             f32x4 sacc[R][2];
 #pragma unroll
@@ -657,7 +671,7 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
-                    const kv_u32x4 ka = sk[(16 * h + k_row) * 16 + ((4 * kk + quad) ^ k_row)];
+                    const kv_u32x4 ka = *reinterpret_cast<const kv_u32x4*>(sk + k_off[kk] + 16 * 256 * h);
 #pragma unroll
                     for (int b = 0; b < R; ++b)
                         sacc[b][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka), qb[b][kk],
@@ -728,13 +742,12 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
             }
             // ---- O^T += V^T P^T --------------------------------------------------------------------------
             __builtin_amdgcn_s_setprio(2);
-            const char* vt = reinterpret_cast<const char*>(sv) + vt_tok * 256 + (r & 1) * 8;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 // elements [16 j + 4 (r % 4), + 4) of the row: piece 2 j + (r % 4) / 2 (swizzled), half r % 2
-                const int piece_off = ((2 * j + ((r & 3) >> 1)) ^ vt_swz) * 16;
-                const bits16x4 lo = lds_read_transposed(vt + piece_off);
-                const bits16x4 hi = lds_read_transposed(vt + piece_off + 16 * 256);
+                const char* const vt = sv + v_off[j & 3] + 128 * (j >> 2);
+                const bits16x4 lo = lds_read_transposed(vt);
+                const bits16x4 hi = lds_read_transposed(vt + 16 * 256);
                 const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
                 for (int b = 0; b < R; ++b)
@@ -742,13 +755,14 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
             }
             __builtin_amdgcn_s_setprio(0);
         }
-      }
     };
     for (int tile = t_begin; tile < n_tiles; tile += 2) {
-        stage_tile(min(tile + 1, last_tile), s_k1, s_v1);
+        stage_tile(s_k1, s_v1);
+        hop();
         compute(0, tile);
         staged();
-        stage_tile(min(tile + 2, last_tile), s_k0, s_v0);
+        stage_tile(s_k0, s_v0);
+        hop();
         if (tile + 1 < n_tiles) compute(1, tile + 1);
         staged();
     }
@@ -938,6 +952,11 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     a.group = G;
     a.group_shift = 0;
     while ((1 << a.group_shift) < G) ++a.group_shift;
+    // Granlund and Montgomery's division by an invariant d: inverse = ceil(2^(31 + shift) / d), 2^shift >= d
+    const uint64_t d = (uint64_t)(view->block_tokens / 16);
+    a.group_inverse_shift = 0;
+    while ((1ull << a.group_inverse_shift) < d) ++a.group_inverse_shift;
+    a.group_inverse = (uint32_t)(((1ull << (31 + a.group_inverse_shift)) + d - 1) / d);
     hipStream_t st = (hipStream_t)hip_stream;
     constexpr int R = kRowBlocks;
     a.most_records = 0;

@@ -244,3 +244,22 @@ def test_key_ranges_cut_by_length(hq, hkv, triple, ctx, qlen, room):
     # the list of the tiles at its start: the launch did plan its pieces, and cut some
     tiles = ws[:16 * (int(qlen.sum()) // tokens + len(ctx))].cpu().view(torch.int32).numpy().reshape(-1, 4)
     assert (tiles != 0x7F7F7F7F).any(axis=1).all() and tiles[:, 1].max() > 1
+
+
+@pytest.mark.parametrize("block,triple", [
+    (16, (LAYOUT_DP, 1, 0)), (32, (LAYOUT_DP, 2, 1)), (48, (LAYOUT_DP, 1, 0)), (80, (LAYOUT_TP, 2, 1)), (112, (LAYOUT_TP, 1, 0)),
+    (16, (LAYOUT_TP, 2, 0))])
+@pytest.mark.parametrize("cut", [False, True])
+def test_blocks_of_any_number_of_row_groups(block, triple, cut):
+    """Keys are fetched by groups of 16 rows, two of a tile: blocks of 1, 2, 3, 4, 7 and 10 groups, contexts that end in
+    the first and the last row of either group and of a block, alone and in pieces of the key range."""
+    if cut:
+        ctx = np.array([block * 31 + 1, 1009, 1024, 16 * 77 + 15], dtype=np.int32)
+        ql = np.array([33, 1, 16, 50], dtype=np.int32)
+    else:
+        ctx = np.array([1, 15, 16, 17, 31, 32, 33, block, block + 1, 2 * block - 1, 7 * block + 16, 500], dtype=np.int32)
+        ql = np.minimum(ctx, np.array([1, 15, 9, 17, 2, 32, 33, 40, 1, 31, 60, 128], dtype=np.int32))
+    w = wl.Workload("prefill_blocks", 88, 8, 2, 128, block, len(ctx), "x", ())
+    c = make_prefill_case(w, triple, ctx, ql)
+    check_close(run_gpu(c, gpu_view(w, triple)), oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off),
+                f"{block} {triple} {cut}")
