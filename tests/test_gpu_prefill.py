@@ -263,3 +263,14 @@ def test_blocks_of_any_number_of_row_groups(block, triple, cut):
     c = make_prefill_case(w, triple, ctx, ql)
     check_close(run_gpu(c, gpu_view(w, triple)), oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off),
                 f"{block} {triple} {cut}")
+
+
+@pytest.mark.parametrize("step,longest", [(190, 16), (64, 40)])
+def test_tiles_of_every_number_of_pieces(step, longest):
+    """One launch whose tiles see from one to `longest` times `step` keys: no piece is longer than a common length, so they
+    have one piece, two, three and so on, around the two, four and eight that the combining kernel fetches at once."""
+    ctx = np.array([step * (k + 1) for k in range(longest)], dtype=np.int32)
+    w = wl.Workload("prefill_pieces", 89, 4, 1, 128, 16, longest, "x", ())
+    c = make_prefill_case(w, (LAYOUT_DP, 1, 0), ctx, np.full(longest, 3, dtype=np.int32))
+    check_close(run_gpu(c, gpu_view(w, (LAYOUT_DP, 1, 0))),
+                oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off), f"{longest} x {step}")
