@@ -19,13 +19,6 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E peak
 
 
-def ensure_built():
-    from paper_2602_22593_amd import binding
-    if not os.path.exists(binding.LIB_PATH):
-        from paper_2602_22593_amd.build import build
-        build()
-
-
 def cpu_model() -> str:
     try:
         for line in open("/proc/cpuinfo"):
@@ -171,6 +164,7 @@ def main():
               "use --gpus 1", file=sys.stderr)
         sys.exit(2)
 
+    from paper_2602_22593_amd.build import ensure_built
     ensure_built()
     import numpy as np
     import torch

@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -165,17 +166,29 @@ _workspaces = {}
 _calls_module = None
 
 
+class _InPython:
+    """Stands in for the module where it is not to be had: the Python code marshals every call."""
+
+    def _none(*_):
+        return None
+
+    decode = prefill = linear = append = repack = _none
+
+
 def _calls():
     """The module that marshals whole calls in C (csrc/binding_calls.c).  Its functions return the call's status, or None
-    for what the checks here have to answer: an argument that they refuse, or one out of the ordinary."""
+    for what the checks here have to answer: an argument that they refuse, or one out of the ordinary.  Without it (no C
+    compiler or Python headers at the build, another interpreter) the same kernels run, a call takes 1 to 2 us longer."""
     global _calls_module
     if _calls_module is None:
         L = lib()
         try:
             from . import _calls as m
         except ImportError as e:
-            raise RuntimeError(f"{os.path.join(_PKG, '_calls.so')} not usable: build it with "
-                               "`python -m paper_2602_22593_amd.build`") from e
+            _calls_module = _InPython()
+            warnings.warn(f"{e}: calls are marshalled in Python; build the module with "
+                          "`python -m paper_2602_22593_amd.build`", RuntimeWarning, stacklevel=3)
+            return _calls_module
         functions = (L.paged_decode_attn, L.paged_prefill_attn, L.paged_prefill_attn_workspace_bytes, L.kv_linear_view,
                      L.kv_linear_view_workspace_bytes, L.kv_append, L.kv_repack)
         m.setup(tuple(C.cast(f, C.c_void_p).value for f in functions),

@@ -1,8 +1,9 @@
-"""Build libflyingkv.so (HIP, gfx950 only) in-tree with hipcc, and the binding's _calls.so with the C compiler.
+"""Build libflyingkv.so (HIP, gfx950 only) in-tree with hipcc, and the binding's _calls module with the C compiler.
 
 ``python -m paper_2602_22593_amd.build`` compiles every ``csrc/*.hip`` into an object under
 ``_build/`` and links them into ``paper_2602_22593_amd/libflyingkv.so``.  hipcc cross-compiles
-without a GPU, so this runs on a CPU-only machine too.
+without a GPU, so this runs on a CPU-only machine too.  The _calls module belongs to the interpreter that runs the build (its
+headers and file suffix); where it cannot be compiled the library still is, and the binding does without it.
 """
 from __future__ import annotations
 
@@ -18,7 +19,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libflyingkv.so")
-CALLS = os.path.join(PKG, "_calls.so")
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -50,16 +51,33 @@ def _compile(src: str, force: bool) -> str:
 
 
 def _build_calls(force: bool) -> None:
+    untagged = os.path.join(PKG, "_calls.so")   # of an earlier build: any interpreter would load it
+    if os.path.exists(untagged):
+        os.remove(untagged)
     src, header = os.path.join(CSRC, "binding_calls.c"), os.path.join(ROOT, "include", "flying_kv.h")
     if not force and os.path.exists(CALLS) and all(os.path.getmtime(CALLS) >= os.path.getmtime(d) for d in (src, header)):
         return
     cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
            "-I", os.path.join(ROOT, "include"), src, "-o", CALLS]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"the C compiler failed for {src}:\n{r.stderr}")
-    if r.stderr.strip():
-        sys.stderr.write(r.stderr)
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        failed, said = r.returncode != 0, r.stderr.strip()
+    except OSError as e:
+        failed, said = True, str(e)
+    if failed:
+        if os.path.exists(CALLS):
+            os.remove(CALLS)   # of older sources
+        said = f"{src} not compiled, calls are marshalled in Python:\n{said}"
+    if said:
+        sys.stderr.write(said + "\n")
+
+
+def ensure_built() -> None:
+    """Build what is missing: everything without the library, the _calls module alone without that."""
+    if not os.path.exists(LIB):
+        build()
+    elif not os.path.exists(CALLS):
+        _build_calls(force=True)
 
 
 def build(force: bool = True, verbose: bool = False) -> str:

@@ -4,8 +4,12 @@ header says.  No kernel is launched here."""
 import ctypes as C
 import os
 import re
+import sys
+import sysconfig
+import warnings
 
 import pytest
+import torch
 
 import oracle
 from paper_2602_22593_amd import binding as kv
@@ -15,9 +19,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module", autouse=True)
 def built_library():
-    if not os.path.exists(kv.LIB_PATH):
-        from paper_2602_22593_amd.build import build
-        build()
+    from paper_2602_22593_amd.build import ensure_built
+    ensure_built()
     return kv.lib()
 
 
@@ -266,6 +269,41 @@ def test_strerror_and_options():
     with pytest.raises(kv.KVError):
         kv.kv_set_option("linear_splits", 17)
     kv.kv_set_option("linear_splits", 0)
+
+
+def test_calls_without_the_module_in_c(monkeypatch):
+    """A tree without _calls (another interpreter, no Python headers at the build) answers in Python, and says so once."""
+    import paper_2602_22593_amd as package
+    monkeypatch.setitem(sys.modules, "paper_2602_22593_amd._calls", None)
+    monkeypatch.delattr(package, "_calls", raising=False)
+    monkeypatch.setattr(kv, "_calls_module", None)
+    view = kv.kv_view_create(8, 2, 64, 16, kv.KV_LAYOUT_DP)
+    pool, rows = torch.zeros(4, 2 * 16 * 2 * 64, dtype=torch.bfloat16), torch.zeros(1, 2, 64, dtype=torch.bfloat16)
+    table, at = torch.zeros(1, 4, dtype=torch.int32), torch.zeros(1, dtype=torch.int32)
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"), pytest.raises(ValueError, match="device memory"):
+        kv.kv_append(pool, view, rows, rows, table, at)
+    with warnings.catch_warnings(), pytest.raises(ValueError, match="device memory"):
+        warnings.simplefilter("error")
+        kv.kv_repack(pool, view, view, table, table, at, 16)
+
+
+def test_missing_module_in_c_is_built_alone(monkeypatch, tmp_path, capsys):
+    """With the library there, only the _calls module is built, for this interpreter; one without a tag, which any would
+    load, goes; and where there is no compiler nothing is raised."""
+    from paper_2602_22593_amd import build as b
+    calls = tmp_path / os.path.basename(b.CALLS)
+    assert calls.name == "_calls" + sysconfig.get_config_var("EXT_SUFFIX")
+    for name, value in (("PKG", str(tmp_path)), ("LIB", str(tmp_path / "libflyingkv.so")), ("CALLS", str(calls)),
+                        ("build", lambda *a, **k: pytest.fail("the library is there"))):
+        monkeypatch.setattr(b, name, value)
+    (tmp_path / "libflyingkv.so").touch()
+    (tmp_path / "_calls.so").touch()
+    monkeypatch.setenv("CC", str(tmp_path / "no_such_compiler"))
+    b.ensure_built()
+    assert not calls.exists() and "marshalled in Python" in capsys.readouterr().err
+    monkeypatch.delenv("CC")
+    b.ensure_built()
+    assert calls.exists() and not (tmp_path / "_calls.so").exists()
 
 
 def test_product_package_does_not_import_the_oracle():
