@@ -1,4 +1,6 @@
 """The calls that csrc/binding_calls.c marshals answer as the Python code they stand in for."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -86,22 +88,66 @@ def test_calls_in_c(name, stream, own):
     assert count.made == (0 if own and name == "decode" else 1)
 
 
-@pytest.mark.parametrize("bad", [
-    {"q": torch.zeros(2, 8, 128)}, {"q": "half"}, {"q": "strided"}, {"out": "strided"}, {"pool": "ragged"},
-    {"table": "long"}, {"table": "flat"}, {"lens": "short"}, {"q_off": "short"}, {"k": "rows"}, {"v": "half"}, {"ws": "small"},
-    {"ws": "half"}, {"x": "wide"}, {"x": "columns"}, {"w": "half"}, {"y": "strided"}, {"dst": "long"},
-    {"scale": 1},
-], ids=str)
-@pytest.mark.parametrize("name", ["decode", "prefill", "linear", "append", "repack"])
-def test_refusals_are_the_same(name, bad):
+def test_parameter_as_weight():
+    """An nn.Parameter, the one class besides Tensor that the C code takes."""
+    bad = {"w": torch.nn.Parameter(_bf(128, 256), requires_grad=False)}
+    count = _Counting(kv._calls())
+    got, want = _outcome("linear", bad, count), _outcome("linear", bad, _Nothing())
+    assert count.made == 1 and all(torch.equal(g, w) for g, w in zip(got, want))
+
+
+def test_workspace_that_has_to_grow():
+    """The binding's own workspace of a stream, too small for the next call: Python makes the larger one, then C uses it."""
+    stream, x, w = torch.cuda.Stream(), _bf(64, 4096), _bf(3072, 4096)
+    big = kv.kv_weight_view_make(0, 0, 1, 3072, 4096)
+    need = kv.lib().kv_linear_view_workspace_bytes(C.byref(big), 64)
+    key = (0, stream.cuda_stream, "scratch")
+    torch.cuda.synchronize()
+    kv._workspaces.pop(key, None)
+    kv.kv_linear_view(x[:3, :256].contiguous(), w[:128, :256].contiguous(), kv.kv_weight_view_make(0, 0, 1, 128, 256),
+                      stream=stream)
+    assert kv._workspaces[key].numel() < need
+    outs, made, was = [], [], kv._calls_module
+    for _ in range(2):
+        kv._calls_module = count = _Counting(kv._calls())
+        try:
+            y = torch.empty(64, 3072, dtype=torch.bfloat16, device=DEV)
+            torch.cuda.synchronize()
+            kv.kv_linear_view(x, w, big, out=y, stream=stream)
+        finally:
+            kv._calls_module = was
+        torch.cuda.synchronize()
+        outs.append(y)
+        made.append(count.made)
+    assert made == [0, 1] and kv._workspaces[key].numel() >= need and torch.equal(*outs)
+
+
+# What each call takes of the arguments below, and which of the swapped ones are no reason to refuse it
+TAKES = {"decode": ("q", "out", "pool", "table", "lens", "ws", "scale"),
+         "prefill": ("q", "out", "pool", "table", "lens", "q_off", "ws", "scale"),
+         "linear": ("x", "w", "y", "ws"), "append": ("pool", "k", "v", "table", "lens"),
+         "repack": ("pool", "table", "dst", "lens")}
+TAKEN = {("decode", "scale", 1), ("prefill", "scale", 1), ("prefill", "pool", "ragged"), ("append", "pool", "ragged"),
+         ("repack", "pool", "ragged"), ("append", "table", "flat"), ("repack", "lens", "short"),
+         ("prefill", "ws", "small"), ("linear", "ws", "small")}
+
+
+@pytest.mark.parametrize("name,arg,what", [(n, arg, what) for arg, what in [
+    ("q", "host"), ("q", "half"), ("q", "strided"), ("out", "strided"), ("pool", "ragged"), ("table", "long"),
+    ("table", "flat"), ("lens", "short"), ("q_off", "short"), ("k", "rows"), ("v", "half"), ("ws", "small"), ("ws", "half"),
+    ("x", "wide"), ("x", "columns"), ("w", "half"), ("y", "strided"), ("dst", "long"), ("scale", 1),
+] for n, takes in TAKES.items() if arg in takes])
+def test_refusals_are_the_same(name, arg, what):
     """Arguments that the binding or the library refuses, or that only Python takes: the same error, or the same bytes."""
-    make = {"half": lambda t: t.half() if t.dtype != torch.uint8 else t.view(torch.float16), "long": lambda t: t.long(),
+    make = {"host": lambda t: t.cpu(), "half": lambda t: t.half() if t.dtype != torch.uint8 else t.view(torch.float16),
+            "long": lambda t: t.long(),
             "strided": lambda t: torch.zeros(t.shape + (2,), dtype=t.dtype, device=DEV)[..., 0], "rows": lambda t: t[:1],
             "ragged": lambda t: t.flatten()[:-5000].contiguous(), "flat": lambda t: t.flatten(), "short": lambda t: t[:1],
             "small": lambda t: t[:256], "wide": lambda t: torch.cat([t, t], dim=1), "columns": lambda t: t.t().contiguous().t()}
     base, _ = _calls({})
-    bad = {k: make[v](base[k]) if isinstance(v, str) else v for k, v in bad.items()}
+    bad = {arg: make[what](base[arg]) if isinstance(what, str) else what}
     got, want = _outcome(name, bad, kv._calls()), _outcome(name, bad, _Nothing())
+    assert isinstance(want, tuple) == ((name, arg, what) not in TAKEN), want
     assert type(got) is type(want)
     if isinstance(want, tuple):
         assert got == want
