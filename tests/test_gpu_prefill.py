@@ -248,7 +248,7 @@ def test_key_ranges_cut_by_length(hq, hkv, triple, ctx, qlen, room):
 
 @pytest.mark.parametrize("block,triple", [
     (16, (LAYOUT_DP, 1, 0)), (32, (LAYOUT_DP, 2, 1)), (48, (LAYOUT_DP, 1, 0)), (80, (LAYOUT_TP, 2, 1)), (112, (LAYOUT_TP, 1, 0)),
-    (16, (LAYOUT_TP, 2, 0))])
+    (16, (LAYOUT_TP, 2, 0)), (32, (LAYOUT_TP, 2, 0))])
 @pytest.mark.parametrize("cut", [False, True])
 def test_blocks_of_any_number_of_row_groups(block, triple, cut):
     """Keys are fetched by groups of 16 rows, two of a tile: blocks of 1, 2, 3, 4, 7 and 10 groups, contexts that end in
@@ -269,8 +269,18 @@ def test_blocks_of_any_number_of_row_groups(block, triple, cut):
 def test_tiles_of_every_number_of_pieces(step, longest):
     """One launch whose tiles see from one to `longest` times `step` keys: no piece is longer than a common length, so they
     have one piece, two, three and so on, around the two, four and eight that the combining kernel fetches at once."""
-    ctx = np.array([step * (k + 1) for k in range(longest)], dtype=np.int32)
+    ctx, ql = np.array([step * (k + 1) for k in range(longest)], dtype=np.int32), np.full(longest, 3, dtype=np.int32)
     w = wl.Workload("prefill_pieces", 89, 4, 1, 128, 16, longest, "x", ())
-    c = make_prefill_case(w, (LAYOUT_DP, 1, 0), ctx, np.full(longest, 3, dtype=np.int32))
-    check_close(run_gpu(c, gpu_view(w, (LAYOUT_DP, 1, 0))),
+    c = make_prefill_case(w, (LAYOUT_DP, 1, 0), ctx, ql)
+    view = gpu_view(w, (LAYOUT_DP, 1, 0))
+    asked = kv.lib().paged_prefill_attn_workspace_bytes(view.handle, longest, int(ql.sum()), int(ctx.max()), 3)
+    ws = torch.full((asked,), 0x7F, dtype=torch.uint8, device=DEV)
+    out = kv.paged_prefill_attn(dev_u16(c.q), dev_u16(c.pool), torch.from_numpy(c.table).to(DEV), torch.from_numpy(c.ctx).to(DEV),
+                                torch.from_numpy(c.q_off.astype(np.int32)).to(DEV), view, int(ctx.max()), 3, workspace=ws)
+    torch.cuda.synchronize()
+    check_close(bf16_bits_to_f64(out.cpu().view(torch.int16).numpy().view(np.uint16)),
                 oracle.paged_prefill(c.view, c.q, c.pool, c.table, c.ctx, c.q_off), f"{longest} x {step}")
+    # the pieces of every tile, as the launch planned them, are in the list at the workspace's start (32 tokens per tile)
+    pieces = set(ws[:16 * (int(ql.sum()) // 32 + longest)].cpu().view(torch.int32).numpy().reshape(-1, 4)[:, 1].tolist())
+    for least, most in ((1, 1), (2, 2), (3, 4), (5, 8), (9, 1 << 20)):
+        assert any(least <= p <= most for p in pieces), (least, most, sorted(pieces))
