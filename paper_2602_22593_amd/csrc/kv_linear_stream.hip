@@ -159,19 +159,19 @@ void launch_stream(const linear_args& p, hipStream_t st)
                        0, st, p, n_tiles, m_tiles);
 }
 
-// The variants, and the parts of their estimate (us): what a call costs at least, and a megabyte that a compute unit
-// fetches.  The number of buffers is what measured best: more of them only lengthen the first requests.
+// The variants, and the parts of their estimate (us): what one round of workgroups costs at least, and a megabyte that a
+// compute unit fetches.  The number of buffers is what measured best: more of them only lengthen the first requests.
 struct stream_variant {
     int nb, mb;
     float start, per_mb;
     void (*launch)(const linear_args&, hipStream_t);
 };
 const stream_variant kVariants[] = {
-    {1, 1, 3.19f, 11.21f, launch_stream<1, 1, 6>}, {2, 1, 3.20f, 10.98f, launch_stream<2, 1, 4>},
-    {3, 1, 3.67f, 9.41f, launch_stream<3, 1, 4>},  {1, 2, 2.62f, 14.76f, launch_stream<1, 2, 4>},
-    {2, 2, 3.46f, 11.77f, launch_stream<2, 2, 4>}, {3, 2, 3.85f, 8.99f, launch_stream<3, 2, 3>},
-    {1, 4, 3.29f, 12.21f, launch_stream<1, 4, 2>}, {2, 4, 3.60f, 9.56f, launch_stream<2, 4, 2>},
-    {3, 4, 4.48f, 8.78f, launch_stream<3, 4, 2>},
+    {1, 1, 3.76f, 8.03f, launch_stream<1, 1, 6>}, {2, 1, 3.76f, 10.81f, launch_stream<2, 1, 4>},
+    {3, 1, 4.23f, 7.97f, launch_stream<3, 1, 4>}, {1, 2, 3.78f, 9.08f, launch_stream<1, 2, 4>},
+    {2, 2, 3.80f, 9.62f, launch_stream<2, 2, 4>}, {3, 2, 4.76f, 8.06f, launch_stream<3, 2, 3>},
+    {1, 4, 3.37f, 9.75f, launch_stream<1, 4, 2>}, {2, 4, 3.95f, 8.68f, launch_stream<2, 4, 2>},
+    {3, 4, 4.46f, 9.39f, launch_stream<3, 4, 2>},
 };
 
 }  // namespace
@@ -189,10 +189,15 @@ stream_cfg stream_pick(int M, int64_t n_l, int total_slabs)
     const double k_bytes = (double)total_slabs * kSlab * 2;
     for (const stream_variant& v : kVariants) {
         if (v.mb != mb) continue;
-        const int64_t wgs = (n_l + 16 * v.nb - 1) / (16 * v.nb) * ((M + 16 * mb - 1) / (16 * mb));
-        const double rounds = (double)((wgs + 255) >> 8);
-        const int rows = 16 * v.nb + (M < 16 * mb ? M : 16 * mb);
-        const double us = v.start + rounds * rows * k_bytes * 1e-6 * v.per_mb + n_l * k_bytes / 10.9e6;
+        // Rounds of the fullest XCD: 32 compute units with a workgroup each, and every eighth row tile with all its batch
+        // tiles.  (Counted over the whole chip, 152 rows of 2688 x 4096 with {2, 4} are 252 workgroups, one round, but 33 on
+        // some XCDs: 19.5 us, 14.7 with {3, 4}.)  A round more pays its first requests and sums again: without that, 17
+        // rows of 8192 x 1024 took {1, 2} in two rounds, 8.9 us, where the sliced kernel takes 6.9.
+        const int64_t n_tiles = (n_l + 16 * v.nb - 1) / (16 * v.nb), m_tiles = (M + 16 * mb - 1) / (16 * mb);
+        const double rounds = (double)(((n_tiles + 7) / 8 * m_tiles + 31) / 32);
+        // (rows past the batch are the last one again: they cost half)
+        const double rows = 16 * (v.nb + mb) - (M < 16 * mb ? 0.483 * (16 * mb - M) : 0.0);
+        const double us = v.start + 1.25 * (rounds - 1.0) + rounds * rows * k_bytes * 1e-6 * v.per_mb + n_l * k_bytes / 12.1e6;
         if (best.nb == 0 || us < best.us) best = stream_cfg{v.nb, v.mb, us};
     }
     return best;

@@ -309,10 +309,10 @@ struct tile_shape {
     float first, next;
 };
 constexpr tile_shape kShapes[] = {
-    {192, 256, 0.940f, 0.914f}, {256, 256, 1.190f, 1.260f}, {128, 256, 0.661f, 0.968f},
-    {128, 128, 0.422f, 0.376f},   // two workgroups per compute unit, two buffers
-    {128, 128, 0.421f, 0.478f},   // one, four buffers: few workgroups and long slices
-    {64, 128, 0.295f, 0.235f},  {64, 64, 0.180f, 0.172f},   {128, 64, 0.324f, 0.238f},  {192, 64, 0.422f, 0.417f},
+    {192, 256, 0.839f, 1.039f}, {256, 256, 0.993f, 1.271f}, {128, 256, 0.609f, 1.053f},
+    {128, 128, 0.414f, 0.402f},   // two workgroups per compute unit, two buffers
+    {128, 128, 0.401f, 0.532f},   // one, four buffers: few workgroups and long slices
+    {64, 128, 0.268f, 0.237f},  {64, 64, 0.178f, 0.212f},   {128, 64, 0.305f, 0.337f},  {192, 64, 0.440f, 0.421f},
 };
 constexpr int kShapeCount = sizeof(kShapes) / sizeof(kShapes[0]);
 
@@ -329,14 +329,10 @@ size_t part_bytes(const tile_shape& t, int64_t tiles, int splits)
 // Estimated time of a launch (us) on the 256 compute units of an MI355X, which the constants were fitted on.
 double estimate(const tile_shape& t, int64_t tiles, int splits, int slice_slabs, double weight_bytes)
 {
-    const int64_t wgs = tiles * splits, whole = wgs >> 8;
-    const double full = (double)whole, rest = (double)(wgs & 255) * (1.0 / 256.0);
-    // a round that does not fill the chip is only slightly shorter than one that does
-    const double partly = rest > 0.0 ? 0.837 + 0.163 * rest : 0.0;
-    const double stage = whole < 1 ? t.first * partly : t.first + t.next * (full - 1.0 + partly);
-    double us = 2.92 + 2.0 * slice_slabs * stage + 6.65 * (t.bn * t.bm / 65536.0) * (full + (rest > 0.0 ? 1.0 : 0.0)) +
-                weight_bytes / 17.8e6;
-    if (splits > 1) us += 3.93 + (double)part_bytes(t, tiles, splits) / 5.40e6;   // second launch, partial sums
+    // (rounds of 256 workgroups; the last takes as long as a full one)
+    const double rounds = (double)((tiles * splits + 255) >> 8), stage = t.first + t.next * (rounds - 1.0);
+    double us = 3.07 + 2.0 * slice_slabs * stage + 7.19 * (t.bn * t.bm / 65536.0) * rounds + weight_bytes / 17.5e6;
+    if (splits > 1) us += 2.63 + 0.16 * splits + (double)part_bytes(t, tiles, splits) / 4.84e6;   // second launch, partial sums
     return us;
 }
 

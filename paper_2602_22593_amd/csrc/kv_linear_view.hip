@@ -330,21 +330,24 @@ constexpr int kNb[] = {1, 2, 3, 4, 6};
 // second kernel find their slices in their own XCD's L2 if tiles come in eights.  Beyond these rounds the tiled
 // kernels are the better ones: every round costs this one a full pass over its piece of x before the first product.
 //
-// All estimates were fitted together to the time of every kernel, tile, cut and NB on 37 weights (640 x 640 to 12288 x
-// 4096 and 10240 x 8192) x 24 batches (1 to 4096 rows), weights from HBM and from the caches in equal parts, replayed
-// from a graph: 7 % off.  Examples, sliced with the best NB against the best tile (us): 64 rows of 3072 x 4096
-// 10.9 / 12.7, of 1536 x 4096 8.7 / 10.5, of 6144 x 4096 16.5 / 15.7; 72 of 3072 x 4096 14.1 / 13.8; 100 of 4096 x 1024
-// 6.3 / 5.9.
+// All estimates (sliced, streamed, tiled) were fitted together on 91 weights (320 x 640 to 14336 x 1024 and 10240 x 8192) x 24 to
+// 27 batches (1 to 4096 rows), 2304 points at which every kernel, tile, cut and NB was timed, weights from HBM and from the
+// caches in equal parts, replayed from a graph: first each to its own kernel's times, then all to the time of what they
+// choose.  Against the kernels and the choice before 16 x 16 x 32 tiles and the streaming kernel the chosen ones
+// take 0.935 of the time, and more than 1.03 of it at 29 points, 1.075 at most (300 rows of 768 x 4096, 12.6 us against
+// 11.7).  With a fit to the times alone these were 0.943, 159 points and 1.57 (2 rows of 12288 x 512, 8.8 us against 5.6).  Examples, best sliced / best streamed / best tile (us): 64 rows of 3072 x 4096
+// 11.4 / 12.2 / 12.6, of 1536 x 4096 9.5 / 11.2 / 11.6, of 6144 x 4096 16.9 / 15.4 / 15.9; 17 of 8192 x 1024 6.9 / 6.4 / 6.9; 100 of
+// 4096 x 1024 6.6 / 6.9 / 6.9.
 double sliced_estimate(const linear_cfg& c, int nb, int64_t m_tiles, int64_t n_l, int total_slabs)
 {
-    static const double kFirst[] = {0.0, 4.78, 5.8, 6.54, 7.61, 0.0, 8.21};
-    static const double kBytesPerUs[] = {0.0, 62.8e6, 26.1e6, 24.9e6, 31.4e6, 0.0, 21.4e6};
+    static const double kFirst[] = {0.0, 4.59, 5.82, 6.98, 7.72, 0.0, 8.42};
+    static const double kBytesPerUs[] = {0.0, 100.3e6, 23.4e6, 29.6e6, 26.0e6, 0.0, 20.2e6};
     const int64_t wgs = workgroups(c, nb, m_tiles, n_l);
     const double weight_bytes = (double)n_l * total_slabs * kSlab * 2;
-    double us = kFirst[nb] + (wgs > 256 ? 1.92 : 0.0) + weight_bytes / kBytesPerUs[nb];
+    double us = kFirst[nb] + (wgs > 256 ? 2.57 : 0.0) + weight_bytes / kBytesPerUs[nb];
     if (c.splits > 1) {
-        us += 1.34 + (double)part_bytes(c, m_tiles, n_l) / 1.67e6;
-        if (wgs / c.splits % 8 != 0) us += 0.295 * c.splits;
+        us += 1.20 + (double)part_bytes(c, m_tiles, n_l) / 1.99e6;
+        if (wgs / c.splits % 8 != 0) us += 0.248 * c.splits;
     }
     return us;
 }

@@ -260,3 +260,22 @@ def test_streaming_kernel(M, N, K, variant, what):
     assert (out[M:] == 7.0).all() and (out[:, N:] == 7.0).all(), what
     got = out[:M, :N].contiguous().cpu().view(torch.int16).numpy().view(np.uint16)
     check(got, np.ascontiguousarray(x[:, :K]), w, ov, what)
+
+
+@pytest.mark.parametrize("M,N,K,kernel,what", [
+    (2, 12288, 512, "linear_tile_kernel<64, 64,", "16 rows per workgroup would be three rounds of workgroups"),
+    (17, 8192, 1024, "linear_stream_kernel<2, 2, 4>", "32 rows per workgroup in one round, 16 in two"),
+    (152, 2688, 4096, "linear_tile_kernel<64, 64,", "252 streamed workgroups, but 33 on some XCDs"),
+    (128, 5120, 5120, "linear_tile_kernel<64, 128,", "a long input dimension against few row tiles"),
+    (1500, 8192, 2048, "linear_tile_kernel<256, 256,", "one round of the largest tile against three of 128 x 128"),
+])
+def test_choice_by_rounds(M, N, K, kernel, what):
+    """Sizes at which the rounds of workgroups decide between the kernels; sampled rows against the oracle."""
+    x, w = bits((M, K), 700 + M), bits((N, K), 701 + (N % 97))
+    ov = ow.weight_view(0, 0, 1, N, K)
+    dx, dw, gv = dev(x), dev(w), gpu_view(ov)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    ran = kernels_of(lambda: kv.kv_linear_view(dx, dw, gv, out=y))
+    assert kernel in ran, ran
+    rows = np.unique([0, 1, M // 2, M - 1])
+    check(np.ascontiguousarray(y.cpu().view(torch.int16).numpy().view(np.uint16)[rows]), np.ascontiguousarray(x[rows]), w, ov, what)
