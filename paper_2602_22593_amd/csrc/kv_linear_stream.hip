@@ -177,14 +177,16 @@ const stream_variant kVariants[] = {
 }  // namespace
 
 // The variant with the least estimated time, which make_plan weighs against the other kernels' (the constants come from
-// the same fit).  Batches of up to 200 rows: the sweep's, and by then the tiles are faster nearly everywhere (6144 x
-// 4096: 100 rows 15.7 against 17.3 us, 128 rows 17 against 18.7, 200 rows more than 24).  Weights of 2 MB and less stay
-// with the sliced kernel, to which a call of that size is a single launch too (1024 x 1024, 4.6 against 4.1 us), and so do
-// row counts that are not whole multiples of 128, which no projection of heads or hidden features has and the sweep had not.
+// the same fit).  Any row count that kv_linear_view takes: a row tile that the rows do not fill requests the last ones again
+// and stores what there is (1 row of 2112 x 4096 6.8 us, by the sliced kernel 10.7; of 6080 x 4096 11.6, tiled 14.8; 16 of 4032 x
+// 4096 8.5, tiled 12.3).  Batches of up to 200 rows: the sweep's, and by then the tiles are faster nearly everywhere (6144 x
+// 4096: 100 rows 16.3 against 17.7 us, 128 rows 17.4 against 18.8, 200 rows 27.4 against 25.2).  Weights of 2 MB and less
+// stay with the sliced kernel, to which such a call is a single launch up to 1024 input features and as fast (1024 x 1024, 1
+// row 4.8 us against 4.7, 64 rows 5.1 against 5.9).
 stream_cfg stream_pick(int M, int64_t n_l, int total_slabs)
 {
     stream_cfg best = {0, 0, 0.0};
-    if (M > 200 || n_l % 128 != 0 || n_l > (1 << 26) || n_l * total_slabs * kSlab <= (1 << 20)) return best;
+    if (M > 200 || n_l > (1 << 26) || n_l * total_slabs * kSlab <= (1 << 20)) return best;
     const int mb = M <= 16 ? 1 : M <= 32 ? 2 : 4;
     const double k_bytes = (double)total_slabs * kSlab * 2;
     for (const stream_variant& v : kVariants) {

@@ -334,8 +334,10 @@ constexpr int kNb[] = {1, 2, 3, 4, 6};
 // 27 batches (1 to 4096 rows), 2304 points at which every kernel, tile, cut and NB was timed, weights from HBM and from the
 // caches in equal parts, replayed from a graph: first each to its own kernel's times, then all to the time of what they
 // choose.  Against the kernels and the choice before 16 x 16 x 32 tiles and the streaming kernel the chosen ones
-// take 0.935 of the time, and more than 1.03 of it at 29 points, 1.075 at most (300 rows of 768 x 4096, 12.6 us against
-// 11.7).  With a fit to the times alone these were 0.943, 159 points and 1.57 (2 rows of 12288 x 512, 8.8 us against 5.6).  Examples, best sliced / best streamed / best tile (us): 64 rows of 3072 x 4096
+// take 0.915 of the time, and more than 1.03 of it at 24 points, 1.10 at most (48 rows of 2112 x 4096, 12.3 us against
+// 11.1); at 532 other points (19 weights x 28 batches, up to 12000 rows) 0.876, and none more than 1.01.  With a fit to the
+// times alone, and odd multiples of 64 rows never streamed, these were 0.943, 159 points and 1.57 (2
+// rows of 12288 x 512, 8.8 us against 5.6).  Examples, best sliced / best streamed / best tile (us): 64 rows of 3072 x 4096
 // 11.4 / 12.2 / 12.6, of 1536 x 4096 9.5 / 11.2 / 11.6, of 6144 x 4096 16.9 / 15.4 / 15.9; 17 of 8192 x 1024 6.9 / 6.4 / 6.9; 100 of
 // 4096 x 1024 6.6 / 6.9 / 6.9.
 double sliced_estimate(const linear_cfg& c, int nb, int64_t m_tiles, int64_t n_l, int total_slabs)

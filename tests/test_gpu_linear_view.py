@@ -179,8 +179,8 @@ def test_one_workspace_for_every_batch_size():
 
 @pytest.mark.parametrize("M,N,K,tile,what", [
     (65, 3136, 128, (64, 64), "one batch row in the second tile; one slab"),
-    (1, 6208, 4224, (64, 64), "one batch row, two slices, 33 slabs"),
-    (65, 1472, 2304, (64, 64), "three slices of six slabs"),
+    (129, 1472, 4224, (64, 64), "one batch row in the third tile, three slices of 11 slabs"),
+    (65, 1472, 4224, (64, 64), "five slices, four of seven slabs and one of five"),
     (257, 6208, 128, (128, 64), "the last weight tile is half full"),
     (129, 6208, 384, (64, 128), "three slabs: six stages through three buffers"),
     (5000, 3136, 128, (128, 128), "two workgroups per compute unit"),
@@ -221,7 +221,7 @@ def test_tiled_kernel_whole_line_stores():
     (2500, 4928, 512, "256, 256, 2, 4, 2, 1, 3", "eight stages: once round and two"),
     (300, 6592, 384, "192, 64, 2, 2, 4, 1, 4", "six stages through four buffers; requests past the end"),
     (2500, 1216, 640, "128, 128, 2, 2, 4, 1, 4", "ten stages through four buffers"),
-    (100, 1472, 2304, "64, 64, 2, 2, 4, 2, 4", "weight tiles that start at another stage each"),
+    (100, 6208, 2304, "64, 64, 2, 2, 4, 2, 4", "weight tiles that start at another stage each"),
 ])
 def test_stages_through_the_buffers(M, N, K, kernel, what):
     """Every remainder of the stage loop, with tiles that neither dimension fills."""
@@ -245,6 +245,11 @@ def test_stages_through_the_buffers(M, N, K, kernel, what):
     (16, 8320, 640, "3, 1, 4", "the last row tile has 16 of its 48 rows"),
     (20, 8320, 1152, "3, 2, 3", "the same; four rows in the second block"),
     (65, 4352, 4096, "3, 4, 2", "one row in the second batch tile; the last row tile has 32 of its 48 rows"),
+    (1, 6208, 4224, "2, 1, 4", "rows an odd multiple of 64; 66 stages"),
+    (65, 1472, 2304, "1, 4, 2", "the same"),
+    (16, 8384, 640, "3, 1, 4", "the same, 32 rows in the last tile of 48"),
+    (20, 8384, 1152, "3, 2, 3", "the same"),
+    (65, 4288, 4096, "3, 4, 2", "the same, 16 rows in the last tile of 48"),
 ])
 def test_streaming_kernel(M, N, K, variant, what):
     """Each variant of the one-launch kernel for decode batches.  The view has three row segments in another order than
