@@ -1,5 +1,5 @@
-// kv_linear_view in LDS-staged tiles, y = x W_active^T: prompts, chunks and large batches, and the decode batches on
-// weight slices that the x-resident kernel of kv_linear_view.hip is estimated to take longer for (make_plan there).
+// kv_linear_view in LDS-staged tiles, y = x W_active^T: prompts, chunks and large batches, and the decode batches
+// that the sliced and the streaming kernel are estimated to take longer for (make_plan in kv_linear_view.hip).
 //
 // Bound: the matrix cores for many batch rows (4096 rows of the 6144 x 4096 QKV weight are 206 GFLOP: 140 us at
 // the 1.47 PFLOP/s that a large library product reaches on this card), the weight stream for few.
@@ -10,20 +10,26 @@
 // swizzled on the global side so that eight consecutive rows' pieces lie in eight different bank groups, into
 // one of ST buffers for the weights and SX for x; a buffer is an array of its own, so that the compiler knows that
 // reads of one do not wait for loads into another.  (The two largest tiles have room for a third buffer of one operand
-// only.  With two of each, a request has one stage's products, 0.8 us, to come back in, less than HBM takes.)  A wavefront holds TN x TM sums (16 x 16 x 32 products, weights as A operand, batch
-// rows as B: a lane's sums then are runs of four output features) and requests the operands of a 32-wide step
+// only.  With two of each, a request has one stage's products, 0.8 us, to come back in, less than HBM takes.)  A wavefront
+// holds TN x TM sums (16 x 16 x 32 products, weights as A operand, batch rows as B: a lane's sums then are runs of four
+// output features) and requests the operands of a 32-wide step
 // while the products of the step before it run; the first step of the next stage is requested behind the only
 // barrier of a stage, with half of the stage's products still to issue, and the requests of the stage after
 // that are spread over them.  Workgroups are dealt out so that an XCD works on neighbouring tiles (8 row tiles
 // side by side), which share their lines in its L2.  The rows of y leave through LDS, 64 to 192 bytes of a row per
 // store (8-byte stores straight from the registers cost 10 us of 117 at 4096 x 4096 x 4096).
 //
-// Large products run at the card's power limit, not at its clock: the loop below keeps the matrix pipe busy 90 % of the
-// cycles at 1.65 GHz, while 32 x 32 x 16 products (which move a quarter more register bytes per multiplication) reached
-// 81 % at the same clock.  Measured in turn, 4096 batch rows of the 6144 x 4096 weight, operands in the caches / from
-// HBM, us: 32 x 32 x 16 products 163 / 181, 16 x 16 x 32 156 / 180, with the requests spread over the products
-// 149 / 175, with the third buffer for x 148 / 157 (1.31 PFLOP/s; a third one for the weights instead 147 / 166; a library
-// product of that shape 157 / 163).  The loop without any loads takes 109.
+// The remaining stages of a slice (kCycle - 1 at most, 4 of 64 in the two largest tiles) run behind branches.  There the
+// compiler does not know how many requests are outstanding and waits for all of them, on entry and in some of the steps,
+// those past the end included; the 192 x 256 tile also keeps four registers in memory across the loop, 256 x 256 two.
+//
+// What bounds a large product is the matrix pipe, at the clock that the card holds under it: counters of 4096 rows of the
+// 6144 x 4096 weight give 329 thousand cycles in 168 us (1.95 GHz), the pipe busy in 60 % of them, and the first launch after
+// a pause is 11 % faster than the tenth.  16 x 16 x 32 products move fewer register bytes per multiplication than 32 x 32 x 16.
+// Measured in turn, that case with operands in the caches / from HBM, us: 32 x 32 x 16 products 163 / 181, 16 x 16 x 32
+// 156 / 180, with the requests spread over the products 149 / 175, with the third buffer for x 148 / 157 (1.31 PFLOP/s; a
+// third one for the weights instead 147 / 166; a library product of that shape 157 / 163).  The loop without any loads takes
+// 109.
 #include <type_traits>
 
 #include "kv_linear_args.h"

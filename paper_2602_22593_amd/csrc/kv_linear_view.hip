@@ -5,9 +5,11 @@
 // row-parallel output projection) of a weight kept once, whole, as [out][in] bf16.  Nothing is
 // copied: the kernel addresses the full matrix with its own leading dimension.
 //
-// Three families of kernels serve it, chosen by estimated time (make_plan below).  kv_linear_stream.hip streams the weight
-// rows of a workgroup whole, in one launch: most decode batches.  This file holds the one that keeps x in registers, for
-// decode batches of 33 rows and more on small weight slices; kv_linear_tiles.hip the LDS-staged tiles for what is larger.
+// Three families of kernels serve it; a call takes the one with the least estimated time (make_plan below).
+// kv_linear_stream.hip streams the weight rows of a workgroup whole, in one launch: most decode batches, of up to 200 rows on
+// weights of more than 2 MB.  This file holds the one that keeps x in registers: most weights of 2 MB and less, and of those up
+// to about 32 MB input dimensions of up to 1024 (one launch), few rows of long ones, and batches of 33 to 256 rows.
+// kv_linear_tiles.hip has the LDS-staged tiles for what is larger.
 //
 // In a decode step the weight slice is streamed from HBM and is the only HBM traffic that matters.  What
 // limits such a product on this chip is not HBM but the path from L2 into a compute unit (measured here:
@@ -335,7 +337,7 @@ constexpr int kNb[] = {1, 2, 3, 4, 6};
 // caches in equal parts, replayed from a graph: first each to its own kernel's times, then all to the time of what they
 // choose.  Against the kernels and the choice before 16 x 16 x 32 tiles and the streaming kernel the chosen ones
 // take 0.915 of the time, and more than 1.03 of it at 24 points, 1.10 at most (48 rows of 2112 x 4096, 12.3 us against
-// 11.1); at 532 other points (19 weights x 28 batches, up to 12000 rows) 0.876, and none more than 1.01.  With a fit to the
+// 11.1); at 532 other points (19 weights x 28 batches, up to 12000 rows) 0.875, and none more than 1.01.  With a fit to the
 // times alone, and odd multiples of 64 rows never streamed, these were 0.943, 159 points and 1.57 (2
 // rows of 12288 x 512, 8.8 us against 5.6).  Examples, best sliced / best streamed / best tile (us): 64 rows of 3072 x 4096
 // 11.4 / 12.2 / 12.6, of 1536 x 4096 9.5 / 11.2 / 11.6, of 6144 x 4096 16.9 / 15.4 / 15.9; 17 of 8192 x 1024 6.9 / 6.4 / 6.9; 100 of
