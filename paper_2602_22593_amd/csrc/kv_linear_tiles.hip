@@ -24,9 +24,9 @@
 // those past the end included; the 192 x 256 tile also keeps four registers in memory across the loop, 256 x 256 two.
 //
 // What bounds a large product is the matrix pipe, at the clock that the card holds under it: counters of 4096 rows of the
-// 6144 x 4096 weight give 329 thousand cycles in 168 us (1.95 GHz), the pipe busy in 60 % of them, and the first launch after
-// a pause is 11 % faster than the tenth.  16 x 16 x 32 products move fewer register bytes per multiplication than 32 x 32 x 16.
-// Measured in turn, that case with operands in the caches / from HBM, us: 32 x 32 x 16 products 163 / 181, 16 x 16 x 32
+// 6144 x 4096 weight give 329 thousand cycles in 168 us (1.95 GHz), the pipe busy in 60 % of them; after a pause launches take
+// 161 to 166 us, from the thirtieth in a row on 185 to 191.  16 x 16 x 32 products move fewer register bytes per
+// multiplication than 32 x 32 x 16.  Measured in turn, that case with operands in the caches / from HBM, us: 32 x 32 x 16 products 163 / 181, 16 x 16 x 32
 // 156 / 180, with the requests spread over the products 149 / 175, with the third buffer for x 148 / 157 (1.31 PFLOP/s; a
 // third one for the weights instead 147 / 166; a library product of that shape 157 / 163).  The loop without any loads takes
 // 109.
