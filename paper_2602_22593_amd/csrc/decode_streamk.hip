@@ -21,9 +21,10 @@
 // the last.  The sum tells every arriver how many pieces there are and how many have arrived; the
 // one that completes the count reads all partials back (device-coherent loads), writes the output
 // rows and puts the word back to zero.  Batches in which a pair is cut over very many wavefronts
-// (few, very long sequences) use a second launch instead, decode_streamk_merge_kernel, which
-// spreads each long list over a workgroup; there the wavefronts holding a pair's first and last
-// piece leave their numbers in the pair's descriptor.
+// (few, very long sequences), and pairs of more than 8 rows, use a second launch instead,
+// decode_streamk_merge_kernel: the four wavefronts of a workgroup add their pieces up in LDS, the
+// workgroup leaves the sums in slot workgroup + pair_index, and the workgroups holding a pair's first and
+// last piece leave their numbers in the pair's descriptor.
 //
 // Per tile, lane l = (r = l % 16, quad = l / 16).  Both products put the KV data in the MFMA
 // A operand (row index r) and the query group, padded to 16, in the B operand (column r = g):
@@ -502,6 +503,20 @@ __device__ __forceinline__ float group_sum(float x)
     return x;
 }
 
+// The same over all 64 lanes.
+__device__ __forceinline__ float wave_max(float x)
+{
+    x = group_max<16>(x);
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ float wave_sum(float x)
+{
+    x = group_sum<16>(x);
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
 // Combine the pieces of a pair (sequence s, pair `sub` of it) held in the slots of wavefronts
 // w_first..w_last and write the pair's output rows.  One wavefront does it, at the very end of the
 // kernel, so the work per piece is kept to a load and two multiply-adds per row and lane.
@@ -588,7 +603,7 @@ __device__ __forceinline__ void merge_pieces(const kv_streamk_args& a, int s, in
 __device__ __forceinline__ void settle_pieces(const kv_streamk_args& a, const cut_pieces& cp, int lane, int w,
                                               kv_u32x4* stage)
 {
-    if (!a.fused || cp.n == 0) return;
+    if (cp.n == 0) return;
     // every partial this wavefront stored has reached the point of coherence
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -644,21 +659,142 @@ __device__ __forceinline__ void empty_wavefront(const kv_streamk_args& a, const 
     const int rel = x - 1 - uniform(s_prefix[lo]) * pairs;
     const int pr = rel / ts;
     const bool inside = (rel - pr * ts) + 1 < ts;
-    const int64_t pair = (int64_t)lo * pairs + pr;
-    if (a.fused && !inside) return;
-    store_empty_partial(a, (int64_t)w + pair, lane);
-    if (a.fused) {
-        cut_pieces cp;
-        cp.n = 0;
-        note_piece(cp, lo, pr, w, false, false);
-        settle_pieces(a, cp, lane, w, stage);
+    if (!inside) return;
+    store_empty_partial(a, (int64_t)w + (int64_t)lo * pairs + pr, lane);
+    cut_pieces cp;
+    cp.n = 0;
+    note_piece(cp, lo, pr, w, false, false);
+    settle_pieces(a, cp, lane, w, stage);
+}
+
+// ---- the pieces of a workgroup's four wavefronts added up before they leave it -------------------
+// Where a second launch combines the pieces, a wavefront leaves those of cut pairs in LDS: that of the pair its
+// range starts inside in record 2 wave, that of the pair its range ends inside in record 2 wave + 1 (a range that
+// lies inside one pair leaves one, in the first), so that in the order of the records the pieces of a pair are
+// neighbours.  The workgroup adds them up and leaves two partials at most, a quarter of the pieces that the second
+// launch has to read (two sequences of 131072 tokens: 113 a pair and not 450; us per call 57.0 -> 53.8 with
+// both kernels, 64 sequences of 512 to 4096 with 16 rows a pair 109.6 -> 106.8).  Not where the pieces are combined inside the main kernel: there a
+// wavefront that is done sends its partial off while others still stream, and waiting for the workgroup
+// makes the chain from the last tile to the last row 1 us longer (256 sequences under TP8 29.4 -> 31.3).
+constexpr int kRowUnits = D / 4;   // 16-byte units of a row
+struct group_pieces {
+    kv_u32x4 rows[2 * kSkWaves][16 * kRowUnits];   // row r of a record: unit p at r * 32 + (p ^ r)
+    f32x2 ml[2 * kSkWaves][16];
+    int2 note[2 * kSkWaves];                       // pair (-1: no piece), kPieceFirst | kPieceLast
+    int tiles[kSkWaves];                           // tiles of a wavefront's range
+};
+constexpr int kPieceFirst = 1, kPieceLast = 2;
+
+// Lane (r, quad), r < cols, holds o[j][i] = O[row r][32 quad + 8 i + j] of the piece; m and l are the row's maximum
+// and denominator (the same in the four lanes of a row).  The exclusive-or spreads the 16 rows over the banks.
+__device__ __forceinline__ void leave_piece(group_pieces& gp, int rec, int cols, int r, int quad, const f32x4 (&o)[8],
+                                            float m, float l, int pair, bool first, bool last, int lane)
+{
+    __builtin_amdgcn_wave_barrier();
+    if (r < cols) {
+        f32x4* row = reinterpret_cast<f32x4*>(gp.rows[rec]) + r * kRowUnits;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            row[(8 * quad + 2 * i) ^ r] = f32x4{o[0][i], o[1][i], o[2][i], o[3][i]};
+            row[(8 * quad + 2 * i + 1) ^ r] = f32x4{o[4][i], o[5][i], o[6][i], o[7][i]};
+        }
+        if (quad == 0) gp.ml[rec][r] = f32x2{m, l};
     }
+    if (lane == 0) gp.note[rec] = int2{pair, (first ? kPieceFirst : 0) | (last ? kPieceLast : 0)};
+}
+
+// The records of `mask` (neighbours, all of one pair) added up by the whole workgroup: written as final rows
+// where they are the whole pair, else as the workgroup's partial.
+__device__ __forceinline__ void add_records(const kv_streamk_args& a, const group_pieces& gp, uint32_t mask, int pair,
+                                            int flags, int group)
+{
+    const int tid = threadIdx.x, cols = a.cols;
+    const int64_t slot = (int64_t)group + pair;
+    const bool whole = flags == (kPieceFirst | kPieceLast);
+    for (int idx = tid; idx < cols * kRowUnits; idx += kSkThreads) {
+        const int row = idx / kRowUnits, p = idx % kRowUnits;   // elements [4 p, 4 p + 4)
+        float m = kNegInf;
+        for (uint32_t k = mask; k != 0; k &= k - 1) m = fmaxf(m, gp.ml[__builtin_ctz(k)][row][0]);
+        const float ref = (m == kNegInf) ? 0.f : m;
+        float l = 0.f;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        for (uint32_t k = mask; k != 0; k &= k - 1) {
+            const int rec = __builtin_ctz(k);
+            const f32x2 ml = gp.ml[rec][row];
+            const float w = fast_exp2(ml[0] - ref);
+            l += w * ml[1];
+            x += w * reinterpret_cast<const f32x4*>(gp.rows[rec])[row * kRowUnits + (p ^ row)];
+        }
+        if (whole) {   // (the rows of a pair and of the pairs of a sequence follow each other)
+            const float inv = 1.0f / l;
+            *reinterpret_cast<kv_u32x2*>(a.out + ((int64_t)pair * cols + row) * D + 4 * p) =
+                kv_u32x2{pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv)};
+        } else {
+            *reinterpret_cast<f32x4*>(a.part_acc + (slot * cols + row) * D + 4 * p) = x;
+            if (p == 0) *reinterpret_cast<f32x2*>(a.part_ml + (slot * cols + row) * 2) = f32x2{m, l};
+        }
+    }
+    if (tid == 0) {   // (a pair that is whole here is not the merge kernel's: first == last)
+        if (flags & kPieceFirst) a.pair_desc[(int64_t)pair * 2] = group;
+        if (flags & kPieceLast) a.pair_desc[(int64_t)pair * 2 + 1] = group;
+    }
+}
+
+// A workgroup without tiles (fewer tiles than workgroups).  Its range is the empty one at tile x: if tiles x - 1
+// and x belong to the same pair, that pair is cut between the neighbouring workgroups and this one counts among
+// its pieces, with an empty partial (m = -inf, l = 0, zeros).
+__device__ __forceinline__ void empty_group(const kv_streamk_args& a, const int32_t* s_prefix, int x, int group)
+{
+    if (x <= 0) return;
+    const int tid = threadIdx.x, pairs = a.pairs;
+    int lo = 0, hi = a.batch;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (uniform(s_prefix[mid]) * pairs <= x - 1) lo = mid; else hi = mid;
+    }
+    const int ts = uniform(s_prefix[lo + 1]) - uniform(s_prefix[lo]);
+    const int rel = x - 1 - uniform(s_prefix[lo]) * pairs;
+    const int pr = rel / ts;
+    if ((rel - pr * ts) + 1 >= ts) return;
+    const int64_t slot = (int64_t)group + (int64_t)lo * pairs + pr;
+    for (int e = tid; e < a.cols * D; e += kSkThreads) a.part_acc[slot * a.cols * D + e] = 0.f;
+    if (tid < a.cols) *reinterpret_cast<f32x2*>(a.part_ml + (slot * a.cols + tid) * 2) = f32x2{kNegInf, 0.f};
+}
+
+// End of a workgroup's ranges (whole workgroup; `x`: the first tile of this wavefront's range, `tiles` how many it had).
+__device__ __forceinline__ void add_up_group(const kv_streamk_args& a, group_pieces& gp, const int32_t* s_prefix, int x,
+                                             int tiles, int wave, int lane)
+{
+    if (lane == 0) gp.tiles[wave] = tiles;
+    __syncthreads();
+    int any = 0;
+#pragma unroll
+    for (int i = 0; i < kSkWaves; ++i) any |= uniform(gp.tiles[i]);
+    if (any == 0) {   // (all four at the same x)
+        empty_group(a, s_prefix, x, blockIdx.x);
+        return;
+    }
+    int pair = -1, flags = 0;
+    uint32_t mask = 0;
+    for (int i = 0; i < 2 * kSkWaves; ++i) {
+        const int p = uniform(gp.note[i].x);
+        if (p < 0) continue;
+        if (p != pair && mask != 0) {
+            add_records(a, gp, mask, pair, flags, blockIdx.x);
+            mask = 0;
+            flags = 0;
+        }
+        pair = p;
+        mask |= 1u << i;
+        flags |= uniform(gp.note[i].y);
+    }
+    if (mask != 0) add_records(a, gp, mask, pair, flags, blockIdx.x);
 }
 
 template <bool MIXED>
 __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_streamk_args a)
 {
-    __shared__ kv_u32x4 s_kstage[kSkWaves * 512];
+    __shared__ group_pieces s_pieces;
     __shared__ int32_t s_prefix[kMaxBatch + 1];             // tiles of the sequences before s
     __shared__ int32_t s_ctx[kMaxBatch];
     __shared__ unsigned long long s_wpos[kMaxBatch + 1];    // weighted position of the first tile of s
@@ -668,16 +804,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
     const int wave = uniform(tid >> 6);
     const kv_view_dev& v = a.v;
     const int Hl = v.n_kv_local, G = a.group;
-    kv_u32x4* kstage = s_kstage + wave * 512;
+    kv_u32x4* kstage = s_pieces.rows[2 * wave + 1];   // K tiles on their way, then the wavefront's last piece
+    if (lane < 2) s_pieces.note[2 * wave + lane] = int2{-1, 0};
 
     split_pos sp;
     const splitter sx = split_prologue<5>(a, Hl, s_prefix, s_wpos, s_ctx, s_wsum, sp);
     int x0 = sp.x0, s = sp.s, tiles_s = sp.tiles_s, hl = sp.pair, tile = sp.tile;
     const int w = sp.w;
-    if (x0 >= sx.total) {   // the range starts where the batch ends: no tiles
-        empty_wavefront(a, s_prefix, Hl, x0, w, lane, kstage);
-        return;
-    }
     cut_pieces cp;
     cp.n = 0;
 
@@ -747,19 +880,19 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
     // The first pair is opened and its first tile requested before the end of the range is worked
     // out: that arithmetic then runs while the loads are under way.
     tile_regs ta, tb;
-    open_pair();
-    bool primed = tile < n_full;
-    if (primed) {
-        const char* kb[2] = {half_base(2 * tile), half_base(2 * tile + 1)};
-        load_full(ta, kb, plane_bytes, lc);
+    bool primed = false;
+    if (x0 < sx.total) {   // (else the range starts where the batch ends: no tiles)
+        open_pair();
+        primed = tile < n_full;
+        if (primed) {
+            const char* kb[2] = {half_base(2 * tile), half_base(2 * tile + 1)};
+            load_full(ta, kb, plane_bytes, lc);
+        }
     }
     const int x1 = sx.range_end(w);
-    if (x0 >= x1) {
-        empty_wavefront(a, s_prefix, Hl, x1, w, lane, kstage);
-        return;
-    }
+    const int x_start = x0;
 
-    for (;;) {
+    while (x0 < x1) {
         const int seg_end = min(tiles_s, tile + (x1 - x0));
         const int full_end = min(seg_end, n_full);
 
@@ -810,16 +943,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
         if (is_first && is_last) {
             store_final(a.out + ((int64_t)s * v.n_q_local + hl * G) * D, G, lc.r, lc.quad, st.o, st.l);
             if (!a.fused && lane == 0)   // one piece: the merge kernel must find first == last here
-                *reinterpret_cast<int2*>(a.pair_desc + pair * 2) = int2{w, w};
-        } else {
+                *reinterpret_cast<int2*>(a.pair_desc + pair * 2) = int2{(int)blockIdx.x, (int)blockIdx.x};
+        } else if (a.fused) {
             store_partial(a, (int64_t)w + pair, G, lc.r, lc.quad, st.o, st.m, st.l, kstage, lane);
-            if (a.fused) {
-                note_piece(cp, s, hl, w, is_first, is_last);
-            } else if (lane == 0) {
-                // first and last piece of the pair tell the merge kernel where its pieces lie
-                if (is_first) a.pair_desc[pair * 2] = w;
-                if (is_last) a.pair_desc[pair * 2 + 1] = w;
-            }
+            note_piece(cp, s, hl, w, is_first, is_last);
+        } else {
+            leave_piece(s_pieces, 2 * wave + (is_first ? 1 : 0), G, lc.r, lc.quad, st.o, st.m, st.l, (int)pair, is_first,
+                        is_last, lane);
         }
 
         // ---- next pair --------------------------------------------------------------------------
@@ -835,7 +965,9 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
         }
         open_pair();
     }
-    settle_pieces(a, cp, lane, w, kstage);
+    if (!a.fused) add_up_group(a, s_pieces, s_prefix, x_start, x1 - x_start, wave, lane);
+    else if (x_start >= x1) empty_wavefront(a, s_prefix, Hl, x1, w, lane, kstage);
+    else settle_pieces(a, cp, lane, w, kstage);
 }
 
 // ---- several adjacent KV heads per wavefront ----------------------------------------------------
@@ -979,7 +1111,7 @@ template <int HPW, bool MIXED>
 __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_args a)
 {
     constexpr int TG = 16 / HPW, TSHIFT = HPW == 4 ? 3 : 4, TILE = 1 << TSHIFT;
-    __shared__ kv_u32x4 s_kstage[kSkWaves * 512];
+    __shared__ group_pieces s_pieces;
     __shared__ int32_t s_prefix[kMaxBatch + 1];             // tiles of the sequences before s
     __shared__ int32_t s_ctx[kMaxBatch];
     __shared__ unsigned long long s_wpos[kMaxBatch + 1];    // weighted position of the first tile of s
@@ -989,16 +1121,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
     const int wave = uniform(tid >> 6);
     const kv_view_dev& v = a.v;
     const int P = a.pairs, C = a.cols, G = a.group;
-    kv_u32x4* kstage = s_kstage + wave * 512;
+    kv_u32x4* kstage = s_pieces.rows[2 * wave + 1];   // K tiles on their way, then the wavefront's last piece
+    if (lane < 2) s_pieces.note[2 * wave + lane] = int2{-1, 0};
 
     split_pos sp;
     const splitter sx = split_prologue<TSHIFT>(a, P, s_prefix, s_wpos, s_ctx, s_wsum, sp);
     int x0 = sp.x0, s = sp.s, tiles_s = sp.tiles_s, hg = sp.pair, tile = sp.tile;
     const int w = sp.w;
-    if (x0 >= sx.total) {   // the range starts where the batch ends: no tiles
-        empty_wavefront(a, s_prefix, P, x0, w, lane, kstage);
-        return;
-    }
     cut_pieces cp;
     cp.n = 0;
 
@@ -1078,16 +1207,16 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
     // The first pair is opened and its first tile requested before the end of the range is worked
     // out: that arithmetic then runs while the loads are under way.
     wide_tile ta, tb;
-    open_pair();
-    bool primed = tile < n_full;
-    if (primed) load_wide<HPW>(ta, tile_base(tile), plane_bytes, wl, stride_bytes);
-    const int x1 = sx.range_end(w);
-    if (x0 >= x1) {
-        empty_wavefront(a, s_prefix, P, x1, w, lane, kstage);
-        return;
+    bool primed = false;
+    if (x0 < sx.total) {   // (else the range starts where the batch ends: no tiles)
+        open_pair();
+        primed = tile < n_full;
+        if (primed) load_wide<HPW>(ta, tile_base(tile), plane_bytes, wl, stride_bytes);
     }
+    const int x1 = sx.range_end(w);
+    const int x_start = x0;
 
-    for (;;) {
+    while (x0 < x1) {
         const int seg_end = min(tiles_s, tile + (x1 - x0));
         const int full_end = min(seg_end, n_full);
 
@@ -1121,15 +1250,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
         if (is_first && is_last) {
             store_final(a.out + ((int64_t)s * v.n_q_local + hg * C) * D, C, wl.r, wl.quad, st.o, st.l);
             if (!a.fused && lane == 0)   // one piece: the merge kernel must find first == last here
-                *reinterpret_cast<int2*>(a.pair_desc + pair * 2) = int2{w, w};
-        } else {
+                *reinterpret_cast<int2*>(a.pair_desc + pair * 2) = int2{(int)blockIdx.x, (int)blockIdx.x};
+        } else if (a.fused) {
             store_partial(a, (int64_t)w + pair, C, wl.r, wl.quad, st.o, m_col, st.l, kstage, lane);
-            if (a.fused) {
-                note_piece(cp, s, hg, w, is_first, is_last);
-            } else if (lane == 0) {
-                if (is_first) a.pair_desc[pair * 2] = w;
-                if (is_last) a.pair_desc[pair * 2 + 1] = w;
-            }
+            note_piece(cp, s, hg, w, is_first, is_last);
+        } else {
+            leave_piece(s_pieces, 2 * wave + (is_first ? 1 : 0), C, wl.r, wl.quad, st.o, m_col, st.l, (int)pair, is_first,
+                        is_last, lane);
         }
 
         // ---- next pair ------------------------------------------------------------------------------
@@ -1145,92 +1272,154 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
         }
         open_pair();
     }
-    settle_pieces(a, cp, lane, w, kstage);
+    if (!a.fused) add_up_group(a, s_pieces, s_prefix, x_start, x1 - x_start, wave, lane);
+    else if (x_start >= x1) empty_wavefront(a, s_prefix, P, x1, w, lane, kstage);
+    else settle_pieces(a, cp, lane, w, kstage);
 }
 
-// Merge the pieces of one (sequence, local query head), or write zeros for an empty context.
-// The 256 lanes of a workgroup are column groups of 4 elements x slices of the piece list.  A
-// short list (the common case: a pair cut over a few wavefronts) is merged by one workgroup as
-// 32 column groups x 8 slices; a long one (one sequence cut over hundreds of wavefronts) by
-// kMergeSplit workgroups, each owning 128 / kMergeSplit columns as 8 column groups x 32 slices.
-// The host launches kMergeSplit workgroups per row only when the batch has few pairs for the
-// wavefronts launched (long lists are then the rule); in such a grid all but the first leave at
-// once for a short list.  Which slots hold the pieces of a pair is read from the pair's descriptor:
-// the numbers of the wavefronts that held its first and its last piece, left by the main kernel,
-// so this kernel does not depend on how the tiles were cut.
+// Merge the partials that the workgroups left of one (sequence, local query head), or write zeros for an empty
+// context.  Which slots hold those of a pair is read from the pair's descriptor: the numbers of the workgroups
+// that held its first and its last piece, left by the main kernel, so this kernel does not depend on how
+// the tiles were cut.
+//
+// Short lists (LONG false: the batch has enough pairs that few are cut over many workgroups): one wavefront a row,
+// lane e elements 2 e and 2 e + 1.  What bounds it is latency, so all (m, l) of a list, one a lane, and the first eight
+// partials' rows are requested together, the weights reach the lanes through scalar registers, and no barrier is
+// needed.  Against a workgroup a row (eight slices of the list, mostly empty, added through LDS), 256 sequences x 32
+// heads of 100 to 600 tokens: 72.3 -> 66.9 us per call.
+//
+// Long lists: kMergeSplit workgroups a row, each owning 128 / kMergeSplit columns as 8 column groups of 4 elements x 32
+// slices of the list.  In such a grid all but the first leave at once for a short list, which that one merges as
+// 32 column groups x 8 slices.
 constexpr int kMergeSplit = 4;
-constexpr int kMergeLong = 24;  // pieces from which a list counts as long
+constexpr int kMergeLong = 6;  // partials from which a list counts as long
+
+__device__ __forceinline__ float readlane_f(float x, int lane)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+
+template <bool LONG>
 __global__ __launch_bounds__(256) void decode_streamk_merge_kernel(kv_streamk_args a)
 {
-    const int qi = blockIdx.x, s = blockIdx.y, z = blockIdx.z, tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int qi = LONG ? blockIdx.x : blockIdx.x * 4 + uniform(tid >> 6), s = blockIdx.y, z = LONG ? blockIdx.z : 0;
     const kv_view_dev& v = a.v;
+    if (!LONG && qi >= v.n_q_local) return;
     const int Hl = a.pairs, G = a.cols;  // pairs per sequence, output rows per pair
-    __shared__ float s_max[32];
-    __shared__ float s_acc[8 * D];
-    __shared__ float s_l[32];
     uint16_t* dst = a.out + ((int64_t)s * v.n_q_local + qi) * D;
     const int hl = qi / G, g = qi - hl * G;
-    // the context length, and the numbers of the wavefronts that held the pair's first and last piece,
-    // left by the main kernel (both requested before either is looked at: one round trip, not two)
+    // the context length and the pair's descriptor (both requested before either is looked at: one round trip)
     const int2 ends = *reinterpret_cast<const int2*>(a.pair_desc + ((int64_t)s * Hl + hl) * 2);
     const int n = a.ctx_lens[s];
     if (n == 0) {
-        if (z == 0 && tid < D) dst[tid] = 0;
+        if (z == 0) {
+            if (!LONG) reinterpret_cast<uint32_t*>(dst)[lane] = 0u;
+            else if (tid < D) dst[tid] = 0;
+        }
         return;
     }
     // (clamped: whatever the words hold, the slots read below lie inside the workspace)
-    const int w_first = min(max(ends.x, 0), a.n_waves - 1), w_last = min(ends.y, a.n_waves - 1);
-    if (w_first >= w_last) return;                      // one piece: written in place by the main kernel
-    const bool wide = (gridDim.z > 1 && w_last - w_first + 1 >= kMergeLong);
-    if (!wide && z != 0) return;
+    const int n_groups = a.n_waves / kSkWaves;
+    const int w_first = min(max(ends.x, 0), n_groups - 1), w_last = min(ends.y, n_groups - 1);
+    if (w_first >= w_last) return;                      // one partial: written in place by the main kernel
     const int64_t pair = (int64_t)s * Hl + hl;
-    const int ncg = wide ? D / 4 / kMergeSplit : D / 4;  // column groups of this workgroup
-    const int cols = ncg * 4, nsl = 256 / ncg;
-    const int col0 = wide ? z * cols : 0;
-    const int cg = tid % ncg, slice = tid / ncg;
 
-    // one pass over the pieces of this slice, rescaling on the fly; the slices are then brought
-    // to the common maximum and summed through LDS
-    float mr = kNegInf, ll = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int kBatch = 8;
-    // (eight pieces requested at a time: one memory round trip per eight pieces, not one per piece)
-    for (int w0 = w_first + slice; w0 <= w_last; w0 += kBatch * nsl) {
-        float2 ml[kBatch];
-        f32x4 part[kBatch];
+    if constexpr (!LONG) {
+        constexpr int kBatch = 8;
+        const int n_parts = w_last - w_first + 1;
+        const int64_t rec0 = (w_first + pair) * G + g;
+        float m_run = kNegInf, l_run = 0.f;
+        f32x2 sum = {0.f, 0.f};
+        for (int base = 0; base < n_parts; base += 64) {
+            const int cnt = min(64, n_parts - base);
+            const f32x2 ml = *reinterpret_cast<const f32x2*>(a.part_ml + (rec0 + (int64_t)(base + min(lane, cnt - 1)) * G) * 2);
+            f32x2 x[kBatch];
+            auto request = [&](int k0) __attribute__((always_inline)) {   // (past the end: the last one again, weighted 0)
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int64_t rec = (min(w0 + j * nsl, w_last) + pair) * G + g;
-            ml[j] = *reinterpret_cast<const float2*>(a.part_ml + rec * 2);
-            part[j] = *reinterpret_cast<const f32x4*>(a.part_acc + rec * D + col0 + cg * 4);
-        }
+                for (int k = 0; k < kBatch; ++k)
+                    x[k] = *reinterpret_cast<const f32x2*>(a.part_acc + (rec0 + (int64_t)(base + min(k0 + k, cnt - 1)) * G) * D +
+                                                           2 * lane);
+            };
+            request(0);
+            // (a workgroup that had no tiles left m = -inf, l = 0 and zeros: its weight comes out as 0)
+            const float m = lane < cnt ? ml[0] : kNegInf;
+            const float m_new = fmaxf(m_run, wave_max(m));
+            const float ref = (m_new == kNegInf) ? 0.f : m_new;
+            const float keep = fast_exp2(m_run - ref), wgt = fast_exp2(m - ref);
+            l_run = l_run * keep + wave_sum(lane < cnt ? ml[1] * wgt : 0.f);
+            m_run = m_new;
+            sum *= keep;
+            for (int k0 = 0;;) {
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            if (w0 + j * nsl > w_last) break;
-            // (a wavefront that had no tiles left m = -inf, l = 0 and zeros: its weight comes out as 0)
-            const float mn = fmaxf(mr, ml[j].x);
-            const float ref = (mn == kNegInf) ? 0.f : mn;
-            const float c_old = fast_exp2(mr - ref), c_new = fast_exp2(ml[j].x - ref);
-            ll = ll * c_old + ml[j].y * c_new;
-            acc = acc * c_old + part[j] * c_new;
-            mr = mn;
+                for (int k = 0; k < kBatch; ++k)
+                    if (k0 + k < cnt) {
+                        const float w = readlane_f(wgt, k0 + k);
+                        sum[0] = fmaf(w, x[k][0], sum[0]);
+                        sum[1] = fmaf(w, x[k][1], sum[1]);
+                    }
+                k0 += kBatch;
+                if (k0 >= cnt) break;
+                request(k0);
+            }
         }
-    }
-    if (cg == 0) s_max[slice] = mr;
-    __syncthreads();
-    float mm = kNegInf;
-    for (int k = 0; k < nsl; ++k) mm = fmaxf(mm, s_max[k]);
-    const float cs = fast_exp2(mr - mm);           // 0 for a slice without pieces
-    *reinterpret_cast<f32x4*>(&s_acc[slice * cols + cg * 4]) = acc * cs;
-    if (cg == 0) s_l[slice] = ll * cs;
-    __syncthreads();
-    if (tid < cols) {
-        float tot = 0.f, lt = 0.f;
-        for (int k = 0; k < nsl; ++k) {
-            tot += s_acc[k * cols + tid];
-            lt += s_l[k];
+        const float inv = 1.0f / l_run;
+        reinterpret_cast<uint32_t*>(dst)[lane] = pack_bf16x2(sum[0] * inv, sum[1] * inv);
+        return;
+    } else {
+        __shared__ float s_max[32];
+        __shared__ float s_acc[8 * D];
+        __shared__ float s_l[32];
+        const bool wide = w_last - w_first + 1 >= kMergeLong;
+        if (!wide && z != 0) return;
+        const int ncg = wide ? D / 4 / kMergeSplit : D / 4;  // column groups of this workgroup
+        const int cols = ncg * 4, nsl = 256 / ncg;
+        const int col0 = wide ? z * cols : 0;
+        const int cg = tid % ncg, slice = tid / ncg;
+
+        // one pass over the partials of this slice, rescaling on the fly; the slices are then brought
+        // to the common maximum and summed through LDS
+        float mr = kNegInf, ll = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        constexpr int kBatch = 8;
+        // (eight requested at a time: one memory round trip per eight, not one each)
+        for (int w0 = w_first + slice; w0 <= w_last; w0 += kBatch * nsl) {
+            float2 ml[kBatch];
+            f32x4 part[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int64_t rec = (min(w0 + j * nsl, w_last) + pair) * G + g;
+                ml[j] = *reinterpret_cast<const float2*>(a.part_ml + rec * 2);
+                part[j] = *reinterpret_cast<const f32x4*>(a.part_acc + rec * D + col0 + cg * 4);
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (w0 + j * nsl > w_last) break;
+                // (a workgroup that had no tiles left m = -inf, l = 0 and zeros: its weight comes out as 0)
+                const float mn = fmaxf(mr, ml[j].x);
+                const float ref = (mn == kNegInf) ? 0.f : mn;
+                const float c_old = fast_exp2(mr - ref), c_new = fast_exp2(ml[j].x - ref);
+                ll = ll * c_old + ml[j].y * c_new;
+                acc = acc * c_old + part[j] * c_new;
+                mr = mn;
+            }
         }
-        dst[col0 + tid] = f32_to_bf16(tot / lt);
+        if (cg == 0) s_max[slice] = mr;
+        __syncthreads();
+        float mm = kNegInf;
+        for (int k = 0; k < nsl; ++k) mm = fmaxf(mm, s_max[k]);
+        const float cs = fast_exp2(mr - mm);           // 0 for a slice without partials
+        *reinterpret_cast<f32x4*>(&s_acc[slice * cols + cg * 4]) = acc * cs;
+        if (cg == 0) s_l[slice] = ll * cs;
+        __syncthreads();
+        if (tid < cols) {
+            float tot = 0.f, lt = 0.f;
+            for (int k = 0; k < nsl; ++k) {
+                tot += s_acc[k * cols + tid];
+                lt += s_l[k];
+            }
+            dst[col0 + tid] = f32_to_bf16(tot / lt);
+        }
     }
 }
 
@@ -1251,12 +1440,14 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     // two-head rows with small groups (TP4 of the 8B shape): both heads of the row, 2.5 % faster than
     // one on a batch of many sequences (95.5 -> 93.1 us at batch 128); not where a few very long
     // sequences are cut into long piece lists, whose records it doubles (60.3 against 59.9 us)
-    else if (G <= 4 && Hl % 2 == 0 && (int64_t)batch * Hl * kMergeLong > n_waves) heads = 2;
+    else if (G <= 4 && Hl % 2 == 0 && (int64_t)batch * Hl * kMergeLong > n_waves / kSkWaves) heads = 2;
     // Below some amount of cached bytes several heads per wavefront lose, because the pieces that a wavefront leaves
     // are that much larger.  Measured, several heads against one, us (MB by the length bound):
-    // - four query heads and more per KV head: below 500 MB (G = 4, 8 sequences, 8 heads, 130 MB: 25.1 against 22.5;
-    //   16, 267 MB: 37.9 against 35.5; 64 under TP4, 263 MB: 35.4 against 31.8; 256 short ones under TP2, 105 MB:
-    //   30.1 against 21.5; even at 32, 532 MB; a gain at 64, 1070 MB);
+    // - four query heads and more per KV head, 16 rows a pair: below 300 MB (G = 4, 16 sequences of 400 to 4000, 8 heads,
+    //   260 MB: 32.2 against 31.5; 16 of 1000 to 2000, 130 MB: 26.9 against 25.2; at 340 MB 16 of 500 to 5200 35.3 against
+    //   34.9, but 64 of 130 to 1300 42.2 against 42.7, 4 of 10000 to 20000 51.4 against 54.2; at 450 MB every one of nine
+    //   shapes 2 to 6 % faster; G = 8, 64 of 500 to 1000, 8 heads, 260 MB: 41.5 against 42.5);
+    // - the same with 8 rows a pair (two-head rows): below 500 MB (64 of 2600 to 5200 under TP4, 340 MB: 48.1 against 47.1);
     // - one or two: only where the pairs are few, whose lists of pieces then are long (G = 1, 4 heads: one sequence of
     //   60000, 123 MB, 40.3 against 32.4; with three short ones, 492 MB, 41.0 against 33.9; G = 2, 8 of 200 to 2000, 4
     //   heads, 134 MB: 15.1 against 12.0, but 8 of 8000 to 16000, 252 MB: 43.3 against 44.9).  With more pairs a
@@ -1267,7 +1458,7 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     //   4000, 117 MB: 23.5 against 27.7);
     // - five and six: as often the one as the other (34 shapes from 40 to 1000 MB: 0.76 to 1.21 times, 1.01 on
     //   average; G = 5, 6 of 1200 to 3800, 8 heads, 94 MB: 22.9 against 30.3).
-    int64_t least = 500000000;
+    int64_t least = G >= 4 && G * heads > 8 ? 300000000 : 500000000;
     if (G <= 3 && (int64_t)batch * Hl * 64 > n_waves)
         least = (int64_t)batch * Hl * 32 <= n_waves ? 200000000 : G == 3 && heads == 4 ? 100000000 : 0;
     else if (G == 5 || G == 6) least = 0;
@@ -1321,7 +1512,7 @@ int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, h
     // into kMergeLong pieces or more on average: one wavefront walking such a list would take
     // longer than the second launch, whose merge kernel spreads a long list over a workgroup.
     const int64_t n_pairs = (int64_t)a.batch * a.pairs;
-    const bool long_lists = n_pairs * kMergeLong <= a.n_waves;
+    const bool long_lists = n_pairs * kMergeLong <= a.n_waves / kSkWaves;
     const int64_t mode = kv_option_merge_mode();
     // (measured: with up to 8 output rows per pair the one launch is 0.5-1.5 us faster; with the 16 rows
     // of several heads per wavefront the last wavefront's walk over the larger records costs 4 us more
@@ -1368,8 +1559,11 @@ int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, h
     }
     int rc = kv_record_hip_error(hipGetLastError(), "paged_decode_attn launch");
     if (rc || a.fused) return rc;
-    launch(decode_streamk_merge_kernel,
-           dim3((unsigned)view->n_q_local, (unsigned)a.batch, long_lists ? (unsigned)kMergeSplit : 1u), dim3(256),
-           KV_PROF_DECODE_MERGE);
+    if (long_lists)
+        launch(decode_streamk_merge_kernel<true>, dim3((unsigned)view->n_q_local, (unsigned)a.batch, (unsigned)kMergeSplit), dim3(256),
+               KV_PROF_DECODE_MERGE);
+    else
+        launch(decode_streamk_merge_kernel<false>, dim3(((unsigned)view->n_q_local + 3) / 4, (unsigned)a.batch), dim3(256),
+               KV_PROF_DECODE_MERGE);
     return kv_record_hip_error(hipGetLastError(), "paged_decode_attn merge launch");
 }

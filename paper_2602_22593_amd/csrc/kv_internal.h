@@ -127,7 +127,7 @@ struct kv_streamk_args {
     int32_t max_ctx_len;   // host bound of the lengths
     float* part_acc;   // [n_waves + batch * pairs][cols][128]
     float* part_ml;    // [n_waves + batch * pairs][cols][2]
-    int32_t* pair_desc;   // [batch * pairs][2] numbers of the wavefronts holding a pair's first and last piece
+    int32_t* pair_desc;   // [batch * pairs][2] numbers of the workgroups holding a pair's first and last piece
                           // (read by the merge kernel; unused when the main kernel combines the pieces)
     unsigned long long* pair_sync;  // [batch * pairs] arrival words of the pairs, zero between calls
     int32_t fused;        // 1: the last piece of a pair to arrive combines them all (no merge kernel)
