@@ -503,20 +503,6 @@ __device__ __forceinline__ float group_sum(float x)
     return x;
 }
 
-// The same over all 64 lanes.
-__device__ __forceinline__ float wave_max(float x)
-{
-    x = group_max<16>(x);
-    x = fmaxf(x, __shfl_xor(x, 16));
-    return fmaxf(x, __shfl_xor(x, 32));
-}
-__device__ __forceinline__ float wave_sum(float x)
-{
-    x = group_sum<16>(x);
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
-}
-
 // Combine the pieces of a pair (sequence s, pair `sub` of it) held in the slots of wavefronts
 // w_first..w_last and write the pair's output rows.  One wavefront does it, at the very end of the
 // kernel, so the work per piece is kept to a load and two multiply-adds per row and lane.
@@ -673,7 +659,7 @@ __device__ __forceinline__ void empty_wavefront(const kv_streamk_args& a, const 
 // lies inside one pair leaves one, in the first), so that in the order of the records the pieces of a pair are
 // neighbours.  The workgroup adds them up and leaves two partials at most, a quarter of the pieces that the second
 // launch has to read (two sequences of 131072 tokens: 113 a pair and not 450; us per call 57.0 -> 53.8 with
-// both kernels, 64 sequences of 512 to 4096 with 16 rows a pair 109.6 -> 106.8).  Not where the pieces are combined inside the main kernel: there a
+// both kernels, 64 sequences of 512 to 4096 with 16 rows a pair 109.6 -> 105.6).  Not where the pieces are combined inside the main kernel: there a
 // wavefront that is done sends its partial off while others still stream, and waiting for the workgroup
 // makes the chain from the last tile to the last row 1 us longer (256 sequences under TP8 29.4 -> 31.3).
 constexpr int kRowUnits = D / 4;   // 16-byte units of a row
@@ -1283,21 +1269,15 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
 // the tiles were cut.
 //
 // Short lists (LONG false: the batch has enough pairs that few are cut over many workgroups): one wavefront a row,
-// lane e elements 2 e and 2 e + 1.  What bounds it is latency, so all (m, l) of a list, one a lane, and the first eight
-// partials' rows are requested together, the weights reach the lanes through scalar registers, and no barrier is
-// needed.  Against a workgroup a row (eight slices of the list, mostly empty, added through LDS), 256 sequences x 32
-// heads of 100 to 600 tokens: 72.3 -> 66.9 us per call.
+// lane e elements 2 e and 2 e + 1.  What bounds it is latency, so everything four partials hold for a row is requested
+// together (most lists are no longer), every lane works out the weights by itself, and no barrier is needed.  Against a workgroup a row (eight slices of the list, mostly empty, added through LDS), 256 sequences x 32
+// heads of 100 to 600 tokens: 72.3 -> 66.1 us per call.
 //
 // Long lists: kMergeSplit workgroups a row, each owning 128 / kMergeSplit columns as 8 column groups of 4 elements x 32
 // slices of the list.  In such a grid all but the first leave at once for a short list, which that one merges as
 // 32 column groups x 8 slices.
 constexpr int kMergeSplit = 4;
 constexpr int kMergeLong = 6;  // partials from which a list counts as long
-
-__device__ __forceinline__ float readlane_f(float x, int lane)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
-}
 
 template <bool LONG>
 __global__ __launch_bounds__(256) void decode_streamk_merge_kernel(kv_streamk_args a)
@@ -1326,41 +1306,35 @@ __global__ __launch_bounds__(256) void decode_streamk_merge_kernel(kv_streamk_ar
     const int64_t pair = (int64_t)s * Hl + hl;
 
     if constexpr (!LONG) {
-        constexpr int kBatch = 8;
-        const int n_parts = w_last - w_first + 1;
-        const int64_t rec0 = (w_first + pair) * G + g;
+        constexpr int kBatch = 4;
+        const int64_t rec0 = pair * G + g;
         float m_run = kNegInf, l_run = 0.f;
         f32x2 sum = {0.f, 0.f};
-        for (int base = 0; base < n_parts; base += 64) {
-            const int cnt = min(64, n_parts - base);
-            const f32x2 ml = *reinterpret_cast<const f32x2*>(a.part_ml + (rec0 + (int64_t)(base + min(lane, cnt - 1)) * G) * 2);
-            f32x2 x[kBatch];
-            auto request = [&](int k0) __attribute__((always_inline)) {   // (past the end: the last one again, weighted 0)
+        for (int w0 = w_first; w0 <= w_last; w0 += kBatch) {
+            f32x2 ml[kBatch], x[kBatch];
 #pragma unroll
-                for (int k = 0; k < kBatch; ++k)
-                    x[k] = *reinterpret_cast<const f32x2*>(a.part_acc + (rec0 + (int64_t)(base + min(k0 + k, cnt - 1)) * G) * D +
-                                                           2 * lane);
-            };
-            request(0);
+            for (int k = 0; k < kBatch; ++k) {   // (past the end: the last one again, with weight and rows of zero)
+                const int64_t rec = rec0 + (int64_t)min(w0 + k, w_last) * G;
+                ml[k] = *reinterpret_cast<const f32x2*>(a.part_ml + rec * 2);
+                x[k] = *reinterpret_cast<const f32x2*>(a.part_acc + rec * D + 2 * lane);
+            }
+            float m_new = m_run;
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) m_new = fmaxf(m_new, ml[k][0]);
             // (a workgroup that had no tiles left m = -inf, l = 0 and zeros: its weight comes out as 0)
-            const float m = lane < cnt ? ml[0] : kNegInf;
-            const float m_new = fmaxf(m_run, wave_max(m));
             const float ref = (m_new == kNegInf) ? 0.f : m_new;
-            const float keep = fast_exp2(m_run - ref), wgt = fast_exp2(m - ref);
-            l_run = l_run * keep + wave_sum(lane < cnt ? ml[1] * wgt : 0.f);
-            m_run = m_new;
+            const float keep = fast_exp2(m_run - ref);
+            l_run *= keep;
             sum *= keep;
-            for (int k0 = 0;;) {
+            m_run = m_new;
 #pragma unroll
-                for (int k = 0; k < kBatch; ++k)
-                    if (k0 + k < cnt) {
-                        const float w = readlane_f(wgt, k0 + k);
-                        sum[0] = fmaf(w, x[k][0], sum[0]);
-                        sum[1] = fmaf(w, x[k][1], sum[1]);
-                    }
-                k0 += kBatch;
-                if (k0 >= cnt) break;
-                request(k0);
+            for (int k = 0; k < kBatch; ++k) {
+                // (selects, no branch: the compiler would move each load behind its own and wait for one at a time)
+                const bool valid = w0 + k <= w_last;
+                const float w = valid ? fast_exp2(ml[k][0] - ref) : 0.f;
+                l_run = fmaf(w, ml[k][1], l_run);
+                sum[0] = fmaf(w, valid ? x[k][0] : 0.f, sum[0]);
+                sum[1] = fmaf(w, valid ? x[k][1] : 0.f, sum[1]);
             }
         }
         const float inv = 1.0f / l_run;
