@@ -1432,7 +1432,7 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     //   4000, 117 MB: 23.5 against 27.7);
     // - five and six: as often the one as the other (34 shapes from 40 to 1000 MB: 0.76 to 1.21 times, 1.01 on
     //   average; G = 5, 6 of 1200 to 3800, 8 heads, 94 MB: 22.9 against 30.3).
-    int64_t least = G >= 4 && G * heads > 8 ? 300000000 : 500000000;
+    int64_t least = G >= 4 && G * heads > 8 ? 300000000 : G == 4 ? 400000000 : 500000000;
     if (G <= 3 && (int64_t)batch * Hl * 64 > n_waves)
         least = (int64_t)batch * Hl * 32 <= n_waves ? 200000000 : G == 3 && heads == 4 ? 100000000 : 0;
     else if (G == 5 || G == 6) least = 0;
@@ -1481,18 +1481,27 @@ int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, h
     a.part_acc = (float*)(ws + KV_DECODE_SYNC_BYTES);
     a.part_ml = (float*)(ws + KV_DECODE_SYNC_BYTES + acc);
     a.pair_desc = (int32_t*)(ws + KV_DECODE_SYNC_BYTES + acc + ml);
-    // How the pieces of a cut pair are combined.  Inside the main kernel, by the last piece to
-    // arrive, unless the batch has so few pairs for the wavefronts launched that a pair is cut
-    // into kMergeLong pieces or more on average: one wavefront walking such a list would take
-    // longer than the second launch, whose merge kernel spreads a long list over a workgroup.
+    // How the pieces of a cut pair are combined.  Not inside the main kernel where the batch has so few pairs that one is
+    // cut over kMergeLong workgroups or more on average: one wavefront walking such a list takes longer than the second
+    // launch, whose merge kernel spreads a long list over four workgroups; nor with 16 rows a pair, whose records one
+    // wavefront walks for 3 us more than the merge kernel takes.  For the others, us with one launch against two (MB by the
+    // length bound):
+    // - up to 4 rows: two launches cost 1 us more (32 query heads under TP8, 130 sequences of 700 to 7200, 480 MB: 46.3
+    //   against 47.7; 256 of 140 to 1400 24.0 against 25.0), unless there are many pairs and much to stream, since the
+    //   stores and loads past the caches then meet a busy memory (under TP4, 130 of 1800 to 3600, 480 MB: 64.8 against 63.8;
+    //   all 8 heads, 130 of 270 to 540, 290 MB: 46.1 against 43.9; 256 of 85 to 171, 180 MB: 33.6 against 33.2; but 130
+    //   of 18 to 187, 100 MB: 20.4 against 20.7; TP4, 256 of 70 to 690, 180 MB: 24.5 against 24.9): the line is drawn
+    //   through pairs times MB = 110000;
+    // - 5 to 8: two launches are faster (64 query heads under TP8, 256 of 1 to 16384: 72.6 against 70.9; 64 of 305 to 3050:
+    //   19.5 against 18.7; TP4, 24 of 400 to 4000: 21.0 against 19.1; 8 heads, 64 of 550 to 1100: 45.0 against 42.9), but
+    //   for many short sequences (130 under TP4 of 375 to 750, 100 MB: 21.6 against 21.9).
     const int64_t n_pairs = (int64_t)a.batch * a.pairs;
+    const int64_t bytes = (int64_t)a.batch * view->n_kv_local * a.max_ctx_len * (D * 4);
     const bool long_lists = n_pairs * kMergeLong <= a.n_waves / kSkWaves;
     const int64_t mode = kv_option_merge_mode();
-    // (measured: with up to 8 output rows per pair the one launch is 0.5-1.5 us faster; with the 16 rows
-    // of several heads per wavefront the last wavefront's walk over the larger records costs 4 us more
-    // than the merge kernel)
-    a.fused = (mode == 1 || (mode == 0 && !long_lists && a.cols <= 8)) && n_pairs <= KV_DECODE_SYNC_WORDS &&
-              a.n_waves < (1 << 16);
+    const bool one_launch = !long_lists && (a.cols <= 4 ? (double)n_pairs * (double)bytes < 1.1e11
+                                                        : a.cols <= 8 && n_pairs >= 256 && bytes < 150000000);
+    a.fused = (mode == 1 || (mode == 0 && one_launch)) && n_pairs <= KV_DECODE_SYNC_WORDS && a.n_waves < (1 << 16);
     // Weights of the XCDs.  Workgroup L runs on XCD L mod 8 (read back from the hardware's XCC_ID by
     // kv_probe_read_placed), and the XCDs do not stream equally fast: with equal shares the
     // wavefronts of the odd-numbered ones end later on average (a plain read of equal contiguous
