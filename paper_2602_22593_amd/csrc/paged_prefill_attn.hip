@@ -2,26 +2,24 @@
 // prefill, or the recompute step of Soft Preempt (Sec. 5.2.2 of the paper), both of which
 // attend from several new tokens of a sequence to everything cached up to each of them.
 //
-// A workgroup of four wavefronts owns, for one (sequence, local KV head), a tile of query rows:
-// 64 R rows = (64 R / G) consecutive new tokens x the G query heads that share the KV head; each
-// wavefront holds R blocks of 16 rows.  The workgroup walks the cached tokens in staged tiles of
-// 32, each K and V tile going once from global memory straight into LDS
-// (16 bytes per lane with the load-to-LDS instruction, no registers in between; double buffered:
-// the next tile lands while the current one is consumed); each wavefront then takes its MFMA
-// operands from LDS and re-uses every K / V operand for its R row blocks.
+// A workgroup of four wavefronts owns, for one (sequence, local KV head), a tile of 128 query rows = 128 / G
+// consecutive new tokens x the G query heads that share the KV head; each wavefront holds 32 rows.  The workgroup
+// walks the cached tokens in staged tiles of 32, each K and V tile going once from global memory straight into
+// LDS (16 bytes per lane with the load-to-LDS instruction, no registers in between; double buffered: the next tiles land
+// while the current ones are consumed); each wavefront takes its MFMA operands from LDS.
 //
-// Per tile and row block, lane l = (c = l % 16, quad = l / 16), exactly as in the decode kernel:
-//   S^T[token][c] = K[token][:] . q[c][:]     A operand = K rows from LDS (token 16 h + 4 (r % 4)
-//                                             + r / 4 in A row r of half h), B operand = q
+// Per tile, lane l = (c = l % 32, half = l / 32), products of 32 x 32 x 16:
+//   S^T[token][c] = K[token][:] . q[c][:]     A operand = K rows from LDS, B operand = q
 //   O^T[e][c]     = sum_t V[t][e] P[c][t]     A operand = V^T, read from the row-major V tile in
 //                                             LDS with the transposing 64-bit read: a lane hands
 //                                             in the address of four consecutive elements of one
 //                                             row and receives one element of each of four rows
-// so the accumulator layout of S^T is already the B layout of the second product and the running
-// maximum crosses lanes only when it moves.  Each lane sums the bf16 weights of its own keys, the
-// same that the numerator takes, and the four lanes of a column are added up once at the end.
-// Column c of row block b of wavefront w is row
-// rho = (w R + b) 16 + c of the tile: token rho / Gp, head rho % Gp, Gp = G rounded up to a power
+// The accumulator layout of S^T (register 4 a + i: token 8 a + 4 half + i) is the B layout of the second product if
+// contraction index 8 half + 4 a' + i of its step c stands for token 16 c + 8 a' + 4 half + i, so the weights
+// never leave their lane and the running maximum crosses lanes only when it moves.  Each lane sums the bf16
+// weights of its own keys, the same that the numerator takes, and the two lanes of a column are added up
+// once at the end.
+// Column c of wavefront w is row rho = 32 w + c of the tile: token rho / Gp, head rho % Gp, Gp = G rounded up to a power
 // of two (rows with head >= G are padding).  The causal mask keeps
 // token t for a query at position pos iff t <= pos; since pos < ctx_len it also masks the slots
 // past the end of the sequence.
@@ -86,17 +84,31 @@ __device__ __forceinline__ float wave_inclusive_sum(float x, int lane)
     return x + (row >= 1 ? t0 : 0.f) + (row >= 2 ? t1 : 0.f) + (row >= 3 ? t2 : 0.f);
 }
 
-// Maximum over the four lanes of a column (the same r, every quad), left in all of them.  By register swaps:
-// lane exchanges through LDS hold two address registers throughout the loop, for which others are spilled.
-__device__ __forceinline__ float column_max(float x)
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Maximum / sum over the two lanes of a column, 32 apart, left in both.  By register swaps: lane exchanges
+// through LDS hold two address registers throughout the loop.
+__device__ __forceinline__ float half_max(float x)
 {
-    const uint32_t b = __builtin_bit_cast(uint32_t, x);
-    const auto rows = __builtin_amdgcn_permlane16_swap(b, b, false, false);
-    const uint32_t r0 = rows[0], r1 = rows[1];   // (a bit cast of the element itself reads element 0)
-    const uint32_t c = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)));
+    const uint32_t c = __builtin_bit_cast(uint32_t, x);
     const auto halves = __builtin_amdgcn_permlane32_swap(c, c, false, false);
     const uint32_t h0 = halves[0], h1 = halves[1];
     return fmaxf(__builtin_bit_cast(float, h0), __builtin_bit_cast(float, h1));
+}
+__device__ __forceinline__ float half_sum(float x)
+{
+    const uint32_t c = __builtin_bit_cast(uint32_t, x);
+    const auto halves = __builtin_amdgcn_permlane32_swap(c, c, false, false);
+    const uint32_t h0 = halves[0], h1 = halves[1];
+    return __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
+}
+// Maximum over the scores of a column: sixteen in each of its two lanes.
+__device__ __forceinline__ float column_max(const f32x16& x)
+{
+    float mx = x[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+    return half_max(mx);
 }
 
 __device__ __forceinline__ float wave_sum(float x)
@@ -113,19 +125,8 @@ __device__ __forceinline__ float wave_max(float x)
     x = fmaxf(x, other(x, std::integral_constant<int, 0x4E>()));    // lanes 2 3 0 1
     x = fmaxf(x, other(x, std::integral_constant<int, 0x141>()));   // mirror of the half row
     x = fmaxf(x, other(x, std::integral_constant<int, 0x140>()));   // mirror of the row
-    return column_max(x);
-}
-
-// The sum over the same lanes.
-__device__ __forceinline__ float column_sum(float x)
-{
-    const uint32_t b = __builtin_bit_cast(uint32_t, x);
-    const auto rows = __builtin_amdgcn_permlane16_swap(b, b, false, false);
-    const uint32_t r0 = rows[0], r1 = rows[1];
-    const uint32_t c = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1));
-    const auto halves = __builtin_amdgcn_permlane32_swap(c, c, false, false);
-    const uint32_t h0 = halves[0], h1 = halves[1];
-    return __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return half_max(x);
 }
 
 // l + the two bf16 values of a packed pair, summed in fp32.
@@ -405,20 +406,29 @@ __device__ __forceinline__ int piece_slot(const int2* s_slot, int slots, int idx
     return min(c + __builtin_popcountll(__builtin_amdgcn_ballot_w64(in)), slots - 1);
 }
 
-// How far operand reads run ahead of the products is a matter of registers: with
-// the row sums taken by the matrix cores (eight sums, four of the all-ones operand) and the maximum exchanged
-// through LDS the compiler had one register pair of V operands to spare and waited for every read (8 prompts of
-// 4096 tokens, 32 query heads, 1095 us instead of 1069; 4 query heads 159 instead of 150; one prompt of 1000
-// tokens 37.5 instead of 34).
-// Three workgroups per compute unit (32 KiB of LDS and at most 168 registers each): with nothing staged
-// in registers the kernel fits, and a third wavefront per SIMD hides more of the chain K read -> scores ->
-// softmax -> V read -> output of the other two than the longer 64-key tiles of two workgroups did.
+// What bounds it.  Short launches: how much of a wavefront's own chain (K read -> scores -> softmax -> V read ->
+// output) is exposed.  So the chain is cut across tiles: the weights of tile t are made beside the score products of tile
+// t + 1, its output products run beside the exponents of tile t + 1, and the order is pinned, one product, the
+// four vector instructions that fit under it and the operand read of the second product after it at a time.
+// Products of 32 x 32 x 16 hide four vector instructions of 4 to 5 cycles, of the wavefront itself or of another; of
+// 16 x 16 x 32 they hide two at a cost (32 products and the softmax of a tile in one wavefront 703 cycles where the
+// products take 520; beside another wavefront's 32 x 32 x 16 products the softmax is free).  Long launches: the power
+// that the chip may draw.  The matrix pipe is busy 52 % of the cycles at 2.09 GHz with the tile by tile order
+// this replaces, and 61 % at 1.6 to 1.75 GHz with two of these wavefronts per SIMD; 16 x 16 x 32 products in the same order
+// 51 % at 2.09 GHz.  There the three orders are within 3 % of each other, and taking out the loads that stage K and V (in a
+// timing-only build) is worth 11 %, the exponentials 3 to 6 %.
+// us per call, tile by tile -> now: 16 prompts of 128 to 4000 tokens, 32 query heads on 8, 748 -> 728; 6 of 500 to 3900
+// 286 -> 266; one of 1000 30.9 -> 23.3; 64 of 30 to 600 125 -> 118; 4 of 8192 1927 -> 1930; 512 on 4096 to 16384 in
+// four sequences, 4 heads, 203 -> 194.
+// Three workgroups per compute unit (32 KiB of LDS and at most 168 registers each; nothing is spilled in the loop): with two
+// of up to 190 registers launches of many tiles are slower (tp2 chunks above 221, 64 of 30 to 600 135).  Eight
+// wavefronts that share the staged tiles (half the loads) wait for each other: 16 prompts 810, 4 of 8192 1969.
 // CUT: the items are the pieces of plan_pieces() instead of whole query tiles.
-template <int R, bool CUT>
-__global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefill_args a)
+template <bool CUT>
+__global__ __launch_bounds__(kThreads, 3) void prefill_kernel(prefill_args a)
 {
-    // [buffer][row][piece]: K pieces swizzled (piece c of row t at c ^ (t % 16)); V pieces at
-    // c ^ (2 * ((t / 4) % 4)), which puts the four rows a transposing read touches in different banks
+    // [row][piece]: K pieces swizzled (piece c of row t at c ^ (t % 16)); V pieces at c ^ (4 * (t % 4)), which puts
+    // the four rows that half a wavefront reads at once in different banks (no conflicts are counted)
     // one array per buffer: the compiler then knows that the loads landing in one buffer do not touch
     // the operands being read from the other
     __shared__ kv_u32x4 s_k0[512], s_k1[512];
@@ -490,7 +500,7 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // registers that the inner loop needs (28 spilled instead of 18, 5 % slower)
     int lane = lane0;
     asm volatile("" : "+v"(lane));
-    const int r = lane & 15, quad = lane >> 4;
+    const int col = lane & 31, half = lane >> 5;
     int slot = item, s, piece = 0, pieces = 1, record = 0;
     if constexpr (CUT) {
         hl = item / per_head;
@@ -531,20 +541,17 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     // instruction of a wavefront fills 64 consecutive 16-byte slots = 4 rows of 16 pieces, and
     // which piece of its row a lane fetches is the LDS swizzle applied on the global side.
     // A wavefront fills eight rows of a tile, all of one group of 16 (wave / 2), which lies in one block: per tile it works
-    // out one address, from a block id asked for a tile before.  What bounds the loop is how many instructions a
-    // wavefront issues (one in 4 to 5 cycles, and the matrix products of another hold back its vector ones), so
-    // what does not compute is kept short: with four rows of either group, two ids and two addresses per tile, and
-    // operand addresses added up for every read (below) there were 83 scalar and 78 vector instructions beside 32
-    // products, now 57 and 64.  16 prompts of 128 to 4000 tokens, 32 query heads on 8, 798 -> 772 us, 4 of 8192
-    // 2016 -> 1938 (1.13 PFLOP/s), one of 4096 150 -> 138.
+    // out one address, from a block id asked for a tile before.
     const int dma_r = lane >> 4, dma_c = lane & 15;
     const int row8 = 8 * (wave & 1) + dma_r;                  // and + 4: rows within the group
     const int token_stride_bytes = v.token_stride * 2;
     const int64_t plane_bytes = v.plane_elems * 2;
     const int groups_per_block = v.block_tokens >> 4;
     const int last_group = (n - 1) >> 4;
-    typedef const __attribute__((address_space(4))) int32_t* const_ids;
-    const const_ids ids = (const_ids)(a.table + (int64_t)s * a.table_stride);
+    // Within the loop block ids come by vector loads: a scalar load under way shares the counter of the LDS reads and
+    // returns out of order, so that every product would wait for all reads issued instead of its own.
+    const int32_t* const ids = a.table + (int64_t)s * a.table_stride;
+    const __amdgpu_buffer_rsrc_t id_row = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(ids), 0, 0x7ffffff0, 0x00020000);
     const char* pool_head = reinterpret_cast<const char*>(a.pool + v.head_off + hl * D);
     const int64_t block_bytes = (int64_t)v.block_elems * 2;
     const uint32_t group_bytes = 16u * (uint32_t)token_stride_bytes;
@@ -553,37 +560,48 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
     for (int i = 0; i < 2; ++i) {
         const int row = row8 + 4 * i;
         k_lane[i] = (uint32_t)(row * token_stride_bytes) + (uint32_t)((dma_c ^ row) << 4);
-        v_lane[i] = (uint32_t)(row * token_stride_bytes) + (uint32_t)((dma_c ^ (2 * (row >> 2))) << 4);
+        v_lane[i] = (uint32_t)(row * token_stride_bytes) + (uint32_t)((dma_c ^ (4 * (row & 3))) << 4);
     }
-    typedef const __attribute__((address_space(1))) void* global_ptr;
     typedef __attribute__((address_space(3))) void* lds_ptr;
+    // where a tile's rows of this wavefront lie, and the number of their group
+    struct tile_rows {
+        const char* rows;
+        int group;
+    };
     // the group to be fetched next: its number, place in its block, and the block's id.  Past the end it is the last one
     // (what is fetched then is masked, or of a tile past the last)
     int g_at = 2 * t_begin + (wave >> 1) - 2, g_in = 0, g_id = 0;
-    auto hop = [&]() {
+    auto next_block = [&]() {
         g_at = min(g_at + 2, last_group);
         const uint32_t blk = __umulhi(2u * (uint32_t)g_at, a.group_inverse) >> a.group_inverse_shift;
         g_in = g_at - (int)blk * groups_per_block;
-        g_id = ids[blk];
+        return blk;
     };
-    hop();
-    // rows past the end of the sequence are replaced by its last token (finite data, masked later)
-    auto stage_tile = [&](kv_u32x4* dk, kv_u32x4* dv) {
-        const char* rows = pool_head + (uint64_t)(uint32_t)g_id * (uint64_t)block_bytes + (uint64_t)(uint32_t)g_in * group_bytes;
+    auto rows_of = [&](int id) -> tile_rows {
+        return {pool_head + (uint64_t)(uint32_t)id * (uint64_t)block_bytes + (uint64_t)(uint32_t)g_in * group_bytes, g_at};
+    };
+    auto request_id = [&](uint32_t blk) { return (int)__builtin_amdgcn_raw_buffer_load_b32(id_row, 0, 4 * blk, 0); };
+    auto next_rows = [&]() {
+        const tile_rows x = rows_of(uniform(g_id));
+        g_id = request_id(next_block());
+        return x;
+    };
+    // Rows past the end of the sequence are replaced by its last token (finite data, masked later).  Buffer loads: the
+    // global form counts for the compiler as one that may read LDS, and while it is under way every LDS read would wait for
+    // all that were issued.
+    auto stage_rows = [&](const tile_rows& x, const uint32_t* at, int64_t plane, kv_u32x4* dst) {
+        const __amdgpu_buffer_rsrc_t rows =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(x.rows + plane), 0, 0x7ffffff0, 0x00020000);
         // ordinary (cached) loads: every query tile of the sequence reads these keys again
-        if (g_at < last_group) {
+        if (x.group < last_group) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                __builtin_amdgcn_global_load_lds((global_ptr)(rows + k_lane[i]), (lds_ptr)(dk + (2 * wave + i) * 64), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((global_ptr)(rows + plane_bytes + v_lane[i]), (lds_ptr)(dv + (2 * wave + i) * 64), 16, 0, 0);
-            }
+            for (int i = 0; i < 2; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_ptr)(dst + (2 * wave + i) * 64), 16, at[i], 0, 0, 0);
         } else {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const int row = row8 + 4 * i;
-                const uint32_t past = (uint32_t)(max(row - (n - 1 - 16 * g_at), 0) * token_stride_bytes);
-                __builtin_amdgcn_global_load_lds((global_ptr)(rows + (k_lane[i] - past)), (lds_ptr)(dk + (2 * wave + i) * 64), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((global_ptr)(rows + plane_bytes + (v_lane[i] - past)), (lds_ptr)(dv + (2 * wave + i) * 64), 16, 0, 0);
+                const uint32_t past = (uint32_t)(max(row8 + 4 * i - (n - 1 - 16 * x.group), 0) * token_stride_bytes);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_ptr)(dst + (2 * wave + i) * 64), 16, at[i] - past, 0, 0, 0);
             }
         }
     };
@@ -593,204 +611,250 @@ __global__ __launch_bounds__(kThreads, R <= 2 ? 3 : 1) void prefill_kernel(prefi
         __syncthreads();
     };
 
-    float m[R];
-    float neg_mc[R];  // -m scale log2(e), the addend of the exponent; kUnset while m = -inf
-    float l[R];     // sum of the weights of this lane's keys of the column
-    f32x4 o[R][8];  // o[b][j][i] = O[column][16 j + 4 quad + i]
+    float neg_mc = kUnset;   // the addend of the exponent: -r of the column, see below; kUnset while it has none
+    float l = 0.f;           // sum of the weights of this lane's keys of the column
+    f32x16 o[4];             // o[j][4 a + i] = O[column][32 j + 8 a + 4 half + i]
 #pragma unroll
-    for (int b = 0; b < R; ++b) {
-        m[b] = kNegInf;
-        neg_mc[b] = kUnset;
-        l[b] = 0.f;
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) o[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    // this lane's part of the V^T operand of output block j: elements [16 j + 4 (r % 4), + 4) of
-    // tokens 4 (r / 4) + quad (first read) and 16 + 4 (r / 4) + quad (second) of the tile; A row r
-    // then is element 16 j + r, contraction index 8 quad + 4 h + i is token 16 h + 4 i + quad, as
-    // the scores have it
-    const int vt_tok = 4 * (r >> 2) + quad;
-    const int vt_swz = 2 * ((vt_tok >> 2) & 3);   // the same for token 16 + vt_tok
+        for (int i = 0; i < 16; ++i) o[j][i] = 0.f;
 
+    // of tiles t + 1 and t + 2, see stage_ahead(); the ids of the first two come by scalar loads, in one round trip
+    typedef const __attribute__((address_space(4))) int32_t* const_ids;
+    const const_ids first_ids = (const_ids)ids;
+    const int id0 = first_ids[next_block()];
+    const int in0 = g_in, at0 = g_at;
+    const int id1 = first_ids[next_block()];
+    tile_rows rows2 = rows_of(id1);
+    tile_rows rows1 = {pool_head + (uint64_t)(uint32_t)id0 * (uint64_t)block_bytes + (uint64_t)(uint32_t)in0 * group_bytes, at0};
+    g_id = request_id(next_block());
     if (t_begin < n_tiles) {
-        stage_tile(s_k0, s_v0);
-        hop();
+        stage_rows(rows1, k_lane, 0, s_k0);
+        stage_rows(rows1, v_lane, plane_bytes, s_v0);
     }
-    // ---- this lane's query rows (B operands), one per row block --------------------------------
-    bf16x8 qb[R][4];
-    int pos[R];       // position of the column's query token
-    // element offset of the row of column r of row block b in q and out, or -1 if the column is
+    if (t_begin + 1 < n_tiles) stage_rows(rows2, k_lane, 0, s_k1);
+    // ---- this lane's query row (B operand) ------------------------------------------------------
+    // element offset of the row of the column in q and out, or -1 if the column is
     // padding (recomputed at the end rather than kept in registers through the loop)
-    auto row_of = [&](int b, bool or_padding) -> int64_t {
-        const int rho = (wave * R + b) * 16 + r;
+    auto row_of = [&](bool or_padding) -> int64_t {
+        const int rho = wave * 32 + col;   // row of the tile
         // a token takes 2^group_shift rows of the tile, the first G of which are its query heads
         const int jt = j0 + (rho >> a.group_shift), g = rho & ((1 << a.group_shift) - 1);
         const int jc = min(jt, q_len - 1);
         const int64_t row = ((int64_t)(q0 + jc) * v.n_q_local + hl * G + min(g, G - 1)) * D;
         return (or_padding || (jt < q_len && g < G)) ? row : -1;
     };
+    bf16x8 qb[8];
+    // position of the column's query token
+    const int pos = first_pos + min(j0 + ((wave * 32 + col) >> a.group_shift), q_len - 1);
+    {
+        const char* qrow = reinterpret_cast<const char*>(a.q + row_of(true)) + half * 16;
 #pragma unroll
-    for (int b = 0; b < R; ++b) {
-        const int rho = (wave * R + b) * 16 + r;
-        pos[b] = first_pos + min(j0 + (rho >> a.group_shift), q_len - 1);
-        const int64_t row = row_of(b, true);
-        const char* qrow = reinterpret_cast<const char*>(a.q + row) + quad * 16;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-            qb[b][kk] = as_bf16x8(*reinterpret_cast<const kv_u32x4*>(qrow + kk * 64));
+        for (int kk = 0; kk < 8; ++kk) qb[kk] = as_bf16x8(*reinterpret_cast<const kv_u32x4*>(qrow + kk * 32));
     }
-    // positions ascend with the column, from the first of row block 0 to the last of row block R - 1: keys
-    // up to min_pos need no mask for any column of the wavefront, keys past max_pos are for none
-    const int min_pos = uniform(pos[0]), max_pos = __builtin_amdgcn_readlane(pos[R - 1], 15);
+    // positions ascend with the column: keys up to min_pos need no mask for any column of the wavefront, tiles
+    // past that of max_pos are for none
+    const int min_pos = uniform(pos), max_pos = __builtin_amdgcn_readlane(pos, 31);
+    const int my_tiles = min(n_tiles, max_pos / kKeys + 1);
+    const int my_pos = pos - 4 * half;   // this lane's keys of a tile start 4 half on
 
     staged();
 
-    const int k_row = 4 * (r & 3) + (r >> 2);
     // Byte offsets of this lane's operands in a K and a V tile; buffers, halves and later columns are constants that the
-    // reads carry.  Opaque: otherwise the compiler holds nine registers more, for both buffers, and adds one to
-    // another before every second read of V.
-    uint32_t k_off[4], v_off[4];
+    // reads carry.
+    uint32_t k_off, v_off[4];
+    {
+        const int p = lane & 15, sub = (lane >> 4) & 1;
+        k_off = (uint32_t)(col * 256 + (half ^ p) * 16);
+        asm volatile("" : "+v"(k_off));
+        // V^T operand of output block j, keys 16 c + 8 a + 4 half + (p / 4): elements 32 j + 16 sub + 4 (p % 4)
+        const int vrow = 4 * half + (p >> 2);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        k_off[u] = (uint32_t)(k_row * 256 + ((4 * u + quad) ^ k_row) * 16);
-        v_off[u] = (uint32_t)(vt_tok * 256 + ((2 * u + ((r & 3) >> 1)) ^ vt_swz) * 16 + (r & 1) * 8);
-        asm volatile("" : "+v"(k_off[u]), "+v"(v_off[u]));
+        for (int j = 0; j < 4; ++j) {
+            v_off[j] = (uint32_t)(vrow * 256 + ((4 * j + 2 * sub + ((p & 3) >> 1)) ^ (4 * (vrow & 3))) * 16 + (p & 1) * 8);
+            asm volatile("" : "+v"(v_off[j]));
+        }
     }
     constexpr float kLag = 8.0f;
-    auto compute = [&](int buf, int tile) {
+    f32x16 sc, ex;   // scores of the next tile; exponents of the tile whose weights come next
+    uint32_t pw[8];  // its weights
+    constexpr int kAhead = 2;   // operand reads under way
+    auto zero = [&]() {
+        f32x16 x;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = 0.f;
+        return x;
+    };
+    auto k_operand = [&](const kv_u32x4* sk, int kk) {
+        uint32_t off = k_off;   // (opaque: the compiler would keep all eight offsets in registers that the loop needs)
+        if (kk > 0) asm volatile("v_xor_b32 %0, %1, %2" : "=v"(off) : "i"(32 * kk), "v"(k_off));
+        return as_bf16x8(*reinterpret_cast<const kv_u32x4*>(reinterpret_cast<const char*>(sk) + off));
+    };
+    auto v_operand = [&](const kv_u32x4* sv, int u) {   // u = 4 c + j
+        const char* const vt = reinterpret_cast<const char*>(sv) + v_off[u & 3] + (u >> 2) * 16 * 256;
+        const bits16x4 lo = lds_read_transposed(vt);
+        const bits16x4 hi = lds_read_transposed(vt + 8 * 256);
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // The causal mask, only on the tiles that reach past some query of this wavefront: one uniform branch around all of
+    // it, since most tiles lie wholly before every query.  A column that has seen no key yet (with the key range
+    // cut it may see none; or only scores of -inf) has no reference maximum: its addend is kUnset, its exponents are
+    // -inf, and the first tile that has a key for it sets the reference.
+    bool unset = false;
+    auto mask = [&](int tile) {
         const int base = kKeys * tile;
-        const char* const sk = reinterpret_cast<const char*>(buf ? s_k1 : s_k0);
-        const char* const sv = reinterpret_cast<const char*>(buf ? s_v1 : s_v0);
-        if (base <= max_pos) {  // else every key of the tile lies after all of this wavefront's queries
-            // ---- S^T = K q^T ------------------------------------------------------------------------
-            f32x4 sacc[R][2];
+        if (base + 31 > min_pos || unset) {
 #pragma unroll
-            for (int b = 0; b < R; ++b) sacc[b][0] = sacc[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-            __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    const kv_u32x4 ka = *reinterpret_cast<const kv_u32x4*>(sk + k_off[kk] + 16 * 256 * h);
-#pragma unroll
-                    for (int b = 0; b < R; ++b)
-                        sacc[b][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ka), qb[b][kk],
-                                                                            sacc[b][h], 0, 0, 0);
-                }
-            // ---- online softmax per column ------------------------------------------------------------
-            __builtin_amdgcn_s_setprio(0);
-            // the causal mask, only on the tiles that reach past some query of this wavefront (one
-            // uniform branch around all of it: most tiles lie wholly before every query)
-            if (base + 31 > min_pos) {
-#pragma unroll
-                for (int b = 0; b < R; ++b)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            sacc[b][h][i] = (base + 16 * h + 4 * i + quad <= pos[b]) ? sacc[b][h][i] : kNegInf;
+            for (int i = 0; i < 16; ++i) sc[i] = (base + 8 * (i >> 2) + (i & 3) <= my_pos) ? sc[i] : kNegInf;
+            if (unset) {
+                const float mx = column_max(sc);
+                if (neg_mc == kUnset && mx != kNegInf) neg_mc = -mx * a.scale_log2e;
+                unset = __builtin_amdgcn_ballot_w64(neg_mc == kUnset) != 0;
             }
-            bf16x8 pb[R];
-#pragma unroll
-            for (int b = 0; b < R; ++b) {
-                // Scores stay in the products' own units; the scale is folded into the exponent:
-                // t = (score - m) scale log2(e), weight = 2^t.  m[b] is a reference maximum that is
-                // allowed to lag behind the true running maximum by up to kLag in the exponent:
-                // weights then reach 2^kLag at most (exact in fp32 and in the bf16 operand alike), and
-                // the accumulators are rescaled only when some column's maximum has moved further than
-                // that -- rarely, after the first tiles.  m[b] is the same in the four lanes of a
-                // column, so each lane tests its own eight exponents and the maximum crosses lanes only
-                // on the rare tile that moves it.  While a column has seen no valid key (m = -inf; with
-                // the key range split it may never see one) its addend is kUnset: any finite score then
-                // gives a huge exponent and forces the first move, a masked one stays at -inf.
-                float t[8];
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        t[4 * h + i] = __builtin_fmaf(sacc[b][h][i], a.scale_log2e, neg_mc[b]);
-                const float tmax = fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])),
-                                         fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7])));
-                if (__builtin_amdgcn_ballot_w64(tmax > kLag) != 0) {
-                    float mx = fmaxf(fmaxf(fmaxf(sacc[b][0][0], sacc[b][0][1]), fmaxf(sacc[b][0][2], sacc[b][0][3])),
-                                     fmaxf(fmaxf(sacc[b][1][0], sacc[b][1][1]), fmaxf(sacc[b][1][2], sacc[b][1][3])));
-                    mx = column_max(mx);
-                    const float m_new = fmaxf(m[b], mx);
-                    if (m_new != kNegInf) {
-                        const float alpha = fast_exp2((m[b] - m_new) * a.scale_log2e);   // 0 on the first move
-                        l[b] *= alpha;
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) o[b][j] *= alpha;
-                        m[b] = m_new;
-                        neg_mc[b] = -m_new * a.scale_log2e;
-                    }
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            t[4 * h + i] = __builtin_fmaf(sacc[b][h][i], a.scale_log2e, neg_mc[b]);
-                }
-                float p[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) p[u] = fast_exp2(t[u]);
-                const kv_u32x4 pw = {pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
-                                     pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])};
-                // the denominator sums the same rounded weights
-#pragma unroll
-                for (int u = 0; u < 4; ++u) l[b] = add_pair(pw[u], l[b]);
-                pb[b] = as_bf16x8(pw);
-            }
-            // ---- O^T += V^T P^T --------------------------------------------------------------------------
-            __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                // elements [16 j + 4 (r % 4), + 4) of the row: piece 2 j + (r % 4) / 2 (swizzled), half r % 2
-                const char* const vt = sv + v_off[j & 3] + 128 * (j >> 2);
-                const bits16x4 lo = lds_read_transposed(vt);
-                const bits16x4 hi = lds_read_transposed(vt + 16 * 256);
-                const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-                for (int b = 0; b < R; ++b)
-                    o[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[b], o[b][j], 0, 0, 0);
-            }
-            __builtin_amdgcn_s_setprio(0);
         }
     };
-    for (int tile = t_begin; tile < n_tiles; tile += 2) {
-        stage_tile(s_k1, s_v1);
-        hop();
-        compute(0, tile);
+    // Scores stay in the products' own units; the scale is folded into the exponent: t = score scale log2(e) - r,
+    // weight = 2^t.  The reference r of a column may lag behind its running maximum by up to kLag: weights then
+    // reach 2^kLag at most (exact in fp32 and in the bf16 operand alike), and the accumulators are rescaled only when some
+    // column's maximum has moved further than that -- rarely, after the first tiles.  Both lanes of a column hold
+    // the same r, so each tests its own sixteen exponents and the maximum crosses lanes only on the rare tile that
+    // moves it.
+    auto move_reference = [&](float tmax) {
+        if (__builtin_amdgcn_ballot_w64(tmax > kLag) != 0) {
+            const float up = fmaxf(half_max(tmax), 0.f);
+            const float alpha = fast_exp2(-up);
+            l *= alpha;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] *= alpha;
+            neg_mc -= up;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) ex[i] -= up;
+        }
+    };
+    auto weight_operand = [&](int c) { return as_bf16x8(kv_u32x4{pw[4 * c], pw[4 * c + 1], pw[4 * c + 2], pw[4 * c + 3]}); };
+    auto weights = [&](int u) {   // two of the sixteen
+        const uint32_t w = pack_bf16x2(fast_exp2(ex[2 * u]), fast_exp2(ex[2 * u + 1]));
+        pw[u] = w;
+        l = add_pair(w, l);   // the denominator sums the same rounded weights
+    };
+    if (t_begin < my_tiles) {
+        sc = zero();
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(s_k0, kk), qb[kk], sc, 0, 0, 0);
+        mask(t_begin);
+        const float mx = column_max(sc);
+        neg_mc = mx == kNegInf ? kUnset : -mx * a.scale_log2e;
+        unset = __builtin_amdgcn_ballot_w64(mx == kNegInf) != 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) ex[i] = __builtin_fmaf(sc[i], a.scale_log2e, neg_mc);
+    }
+    __syncthreads();
+    // Tile t: its weights from the exponents beside the scores of tile t + 1, its output products beside the
+    // exponents of tile t + 1.  K of tile t + 2 and V of tile t + 1 land meanwhile.
+    auto stage_ahead = [&](int t, kv_u32x4* dk, kv_u32x4* dv) {
+        rows1 = rows2;
+        rows2 = next_rows();
+        if (t + 1 < n_tiles) stage_rows(rows1, v_lane, plane_bytes, dv);
+        if (t + 2 < n_tiles) stage_rows(rows2, k_lane, 0, dk);
+    };
+    auto step = [&](int t, kv_u32x4* k_now, kv_u32x4* k_next, kv_u32x4* v_now, kv_u32x4* v_next) {
+        stage_ahead(t, k_now, v_next);
+        // The order of the instructions is pinned: beside each product two exponentials with what follows from them, or
+        // three exponents of the next tile, and the read of the operand of the second product after it.
+        bf16x8 ka[8], va[8];
+#pragma unroll
+        for (int kk = 0; kk < kAhead; ++kk) ka[kk] = k_operand(k_next, kk);
+        __builtin_amdgcn_sched_barrier(0);
+        sc = zero();
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], qb[kk], sc, 0, 0, 0);
+            if (kk + kAhead < 8) ka[kk + kAhead] = k_operand(k_next, kk + kAhead);
+            else va[kk + kAhead - 8] = v_operand(v_now, kk + kAhead - 8);
+            weights(kk);
+            asm volatile("" : "+v"(pw[kk]), "+v"(l));   // (else moved to where they are used)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mask(t + 1);
+        const bf16x8 pb[2] = {weight_operand(0), weight_operand(1)};
+        float tmax = kNegInf;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            o[u & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[u], pb[u >> 2], o[u & 3], 0, 0, 0);
+            if (u + kAhead < 8) va[u + kAhead] = v_operand(v_now, u + kAhead);
+            // (the first two give the last score product time to finish)
+#pragma unroll
+            for (int i = u < 2 ? 16 : (8 * (u - 2) + 2) / 3; i < (8 * (u - 1) + 2) / 3; ++i) {
+                ex[i] = __builtin_fmaf(sc[i], a.scale_log2e, neg_mc);
+                tmax = fmaxf(tmax, ex[i]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        move_reference(tmax);
         staged();
-        stage_tile(s_k0, s_v0);
-        hop();
-        if (tile + 1 < n_tiles) compute(1, tile + 1);
+    };
+    int t = t_begin;
+    for (; t + 2 < my_tiles; t += 2) {
+        step(t, s_k0, s_k1, s_v0, s_v1);
+        step(t + 1, s_k1, s_k0, s_v1, s_v0);
+    }
+    const bool odd = t + 1 < my_tiles;
+    if (odd) {
+        step(t, s_k0, s_k1, s_v0, s_v1);
+        ++t;
+    }
+    if (t < my_tiles) {   // the wavefront's last tile
+        stage_ahead(t, odd ? s_k1 : s_k0, odd ? s_v0 : s_v1);
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) weights(kk);
+        const kv_u32x4* sv = odd ? s_v1 : s_v0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            o[u & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(sv, u), weight_operand(u >> 2), o[u & 3], 0, 0, 0);
+        staged();
+        ++t;
+    }
+    for (; t < n_tiles; ++t) {   // tiles that other wavefronts of the workgroup still have
+        const bool even = ((t - t_begin) & 1) == 0;
+        stage_ahead(t, even ? s_k0 : s_k1, even ? s_v1 : s_v0);
         staged();
     }
 
     // ---- normalise and store ------------------------------------------------------------------------
-#pragma unroll
-    for (int b = 0; b < R; ++b) {
-        const float lt = column_sum(l[b]);
-        const int64_t orow = row_of(b, false);
+    {
+        const float lt = half_sum(l);
+        const int64_t orow = row_of(false);
         if (CUT && orow >= 0 && pieces > 1) {
             const int64_t rec = (int64_t)record * v.n_q_local + orow / D;
-            float* dst = a.part_o + rec * D + 4 * quad;
+            float* dst = a.part_o + rec * D + 4 * half;
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(dst + 16 * jj) = o[b][jj];
-            if (quad == 0) {
-                a.part_ml[rec * 2 + 0] = m[b];
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    *reinterpret_cast<f32x4*>(dst + 32 * j + 8 * u) = f32x4{o[j][4 * u], o[j][4 * u + 1], o[j][4 * u + 2], o[j][4 * u + 3]};
+            if (half == 0) {
+                a.part_ml[rec * 2 + 0] = lt > 0.f ? -neg_mc / a.scale_log2e : kNegInf;   // (no valid key: left out)
                 a.part_ml[rec * 2 + 1] = lt;
             }
         } else if (orow >= 0) {
             const float inv = 1.0f / lt;
-            uint16_t* dst = a.out + orow + 4 * quad;
+            // the two lanes of a row exchange pieces so that each stores 16 bytes at a time
+            uint16_t* dst = a.out + orow + 8 * half;
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                uint2 pk;
-                pk.x = pack_bf16x2(o[b][jj][0] * inv, o[b][jj][1] * inv);
-                pk.y = pack_bf16x2(o[b][jj][2] * inv, o[b][jj][3] * inv);
-                *reinterpret_cast<uint2*>(dst + 16 * jj) = pk;
-            }
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int u = 0; u < 4; u += 2) {
+                    kv_u32x4 pk;
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const auto x = __builtin_amdgcn_permlane32_swap(
+                            pack_bf16x2(o[j][4 * u + 2 * w] * inv, o[j][4 * u + 2 * w + 1] * inv),
+                            pack_bf16x2(o[j][4 * u + 4 + 2 * w] * inv, o[j][4 * u + 5 + 2 * w] * inv), false, false);
+                        pk[w] = x[0];
+                        pk[2 + w] = x[1];
+                    }
+                    *reinterpret_cast<kv_u32x4*>(dst + 32 * j + 8 * u) = pk;
+                }
         }
     }
     }
@@ -855,7 +919,7 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(prefill_args a)
     *reinterpret_cast<uint2*>(a.out + ((int64_t)(tile.z + j) * a.v.n_q_local + h) * D + cg * 4) = pk;
 }
 
-constexpr int kRowBlocks = 2;  // 16-row blocks per wavefront (4 measured 2x slower: one wavefront per SIMD)
+constexpr int kTileRows = 32 * kThreads / 64;   // query rows per workgroup
 
 // Key ranges are cut (plan_pieces) only where the launch would otherwise leave compute units idle: few
 // sequences, few new tokens, long contexts.  The partial sums get room for so many pieces per query
@@ -866,7 +930,7 @@ int query_tile_tokens(const kv_view* view)
 {
     int shift = 0;
     while ((1 << shift) < view->group) ++shift;
-    return (64 * kRowBlocks) >> shift;
+    return kTileRows >> shift;
 }
 int prefill_pieces(int64_t wgs, int max_ctx_len, int least)
 {
@@ -966,7 +1030,6 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     while ((1ull << a.group_inverse_shift) < d) ++a.group_inverse_shift;
     a.group_inverse = (uint32_t)(((1ull << (31 + a.group_inverse_shift)) + d - 1) / d);
     hipStream_t st = (hipStream_t)hip_stream;
-    constexpr int R = kRowBlocks;
     a.most_records = 0;
     a.tiles = nullptr;
     a.part_o = nullptr;
@@ -993,7 +1056,7 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     }
     const int tokens_per_wg = query_tile_tokens(view);
     a.tile_shift = 0;
-    while ((1 << a.tile_shift) < tokens_per_wg) ++a.tile_shift;   // (64 R and the padded group are powers of two)
+    while ((1 << a.tile_shift) < tokens_per_wg) ++a.tile_shift;   // (the rows and the padded group are powers of two)
     a.batch = batch;
     const int64_t slots = room.slots;
     const int Hl = view->n_kv_local;
@@ -1023,10 +1086,10 @@ extern "C" int paged_prefill_attn(const void* q, void* out, const void* kv_pool,
     const dim3 grid((unsigned)n_wgs);
     int slot = kv_prof_begin(KV_PROF_PREFILL, st);
     if (cut) {
-        hipLaunchKernelGGL((prefill_kernel<R, true>), grid, dim3(kThreads), 0, st, a);
-        hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)slots, (unsigned)Hl, 64 * kRowBlocks / (kThreads / 32)), dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL((prefill_kernel<true>), grid, dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)slots, (unsigned)Hl, kTileRows / (kThreads / 32)), dim3(kThreads), 0, st, a);
     } else {
-        hipLaunchKernelGGL((prefill_kernel<R, false>), grid, dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL((prefill_kernel<false>), grid, dim3(kThreads), 0, st, a);
     }
     kv_prof_end(KV_PROF_PREFILL, slot, st);
     return kv_record_hip_error(hipGetLastError(), "paged_prefill_attn launch");
