@@ -413,10 +413,10 @@ __device__ __forceinline__ int piece_slot(const int2* s_slot, int slots, int idx
 // Products of 32 x 32 x 16 hide four vector instructions of 4 to 5 cycles, of the wavefront itself or of another; of
 // 16 x 16 x 32 they hide two at a cost (32 products and the softmax of a tile in one wavefront 703 cycles where the
 // products take 520; beside another wavefront's 32 x 32 x 16 products the softmax is free).  Long launches: the power
-// that the chip may draw.  The matrix pipe is busy 52 % of the cycles at 2.09 GHz with the tile by tile order
-// this replaces, and 61 % at 1.6 to 1.75 GHz with two of these wavefronts per SIMD; 16 x 16 x 32 products in the same order
-// 51 % at 2.09 GHz.  There the three orders are within 3 % of each other, and taking out the loads that stage K and V (in a
-// timing-only build) is worth 11 %, the exponentials 3 to 6 %.
+// that the chip may draw.  On 4 prompts of 8192 under a profiler the matrix pipe is busy 52 % of the cycles at 1.84 to 1.93 GHz
+// with the tile by tile order that this replaces, and 61 % at 1.59 to 1.72 GHz with two of these wavefronts per SIMD;
+// 16 x 16 x 32 products in the same order 51 % at 2.09 GHz.  All are within 4 % of each other in time, and taking out the
+// loads that stage K and V (in a timing-only build) is worth 10 to 11 %, the exponentials 3 to 6 %.
 // us per call, tile by tile -> now: 16 prompts of 128 to 4000 tokens, 32 query heads on 8, 748 -> 728; 6 of 500 to 3900
 // 286 -> 266; one of 1000 30.9 -> 23.3; 64 of 30 to 600 125 -> 118; 4 of 8192 1927 -> 1930; 512 on 4096 to 16384 in
 // four sequences, 4 heads, 203 -> 194.
