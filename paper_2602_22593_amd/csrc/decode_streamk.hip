@@ -39,6 +39,8 @@
 // transposed inside the lane with byte permutes.  Only the running maximum crosses lanes.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "decode_common.h"
 
 using namespace kvdec;
@@ -309,7 +311,7 @@ struct splitter {
 // of the tiles (2^TSHIFT tokens) into s_prefix, weighted positions into s_wpos, context lengths into
 // s_ctx, then the position of this wavefront's first tile (sp.x0 and the fields after it; sp.x1 is
 // left to range_end(), which the kernels call once their first loads are in flight).
-template <int TSHIFT>
+template <int TSHIFT, bool FUSED>
 __device__ __forceinline__ splitter split_prologue(const kv_streamk_args& a, int pairs, int32_t* s_prefix,
                                                    unsigned long long* s_wpos, int32_t* s_ctx, int32_t* s_wsum,
                                                    split_pos& sp)
@@ -365,7 +367,7 @@ __device__ __forceinline__ splitter split_prologue(const kv_streamk_args& a, int
 
     // Nobody else writes the output rows of a sequence without tokens: the workgroups share them
     // out (the merge kernel does it when there is one).
-    if (a.fused) {
+    if (FUSED) {
         const int words = a.v.n_q_local * (D / 2);
         for (int sq = blockIdx.x; sq < a.batch; sq += gridDim.x) {
             if (s_ctx[sq] != 0) continue;
@@ -671,6 +673,17 @@ struct group_pieces {
 };
 constexpr int kPieceFirst = 1, kPieceLast = 2;
 
+// What a workgroup keeps in LDS beside the cut: with one launch only the K tiles on their way.  The two ways of combining are
+// kernels of their own.  With both behind a flag of the arguments, either was slower, us per call: one launch, 31
+// sequences of 190 to 327 in two layouts under TP8 9.8 -> 10.2, 256 of 50 to 700, one KV head of two query heads, 17.1 ->
+// 17.9 (empty wavefronts that went through the loop, 34 KB of LDS more); two launches, 256 of 50 to 700, two
+// heads of one query head, 25.2 -> 26.4 (20 to 27 scalar registers spilled, none now); 73 shapes 1.8 % on average.
+struct key_stages {
+    kv_u32x4 rows[kSkWaves][16 * kRowUnits];
+};
+template <bool FUSED>
+using wave_store = std::conditional_t<FUSED, key_stages, group_pieces>;
+
 // Lane (r, quad), r < cols, holds o[j][i] = O[row r][32 quad + 8 i + j] of the piece; m and l are the row's maximum
 // and denominator (the same in the four lanes of a row).  The exclusive-or spreads the 16 rows over the banks.
 __device__ __forceinline__ void leave_piece(group_pieces& gp, int rec, int cols, int r, int quad, const f32x4 (&o)[8],
@@ -777,10 +790,10 @@ __device__ __forceinline__ void add_up_group(const kv_streamk_args& a, group_pie
     if (mask != 0) add_records(a, gp, mask, pair, flags, blockIdx.x);
 }
 
-template <bool MIXED>
+template <bool MIXED, bool FUSED>
 __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_streamk_args a)
 {
-    __shared__ group_pieces s_pieces;
+    __shared__ wave_store<FUSED> s_store;
     __shared__ int32_t s_prefix[kMaxBatch + 1];             // tiles of the sequences before s
     __shared__ int32_t s_ctx[kMaxBatch];
     __shared__ unsigned long long s_wpos[kMaxBatch + 1];    // weighted position of the first tile of s
@@ -790,13 +803,20 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
     const int wave = uniform(tid >> 6);
     const kv_view_dev& v = a.v;
     const int Hl = v.n_kv_local, G = a.group;
-    kv_u32x4* kstage = s_pieces.rows[2 * wave + 1];   // K tiles on their way, then the wavefront's last piece
-    if (lane < 2) s_pieces.note[2 * wave + lane] = int2{-1, 0};
+    // K tiles on their way (for a second launch, then the wavefront's last piece)
+    kv_u32x4* kstage = s_store.rows[FUSED ? wave : 2 * wave + 1];
+    if constexpr (!FUSED) {
+        if (lane < 2) s_store.note[2 * wave + lane] = int2{-1, 0};
+    }
 
     split_pos sp;
-    const splitter sx = split_prologue<5>(a, Hl, s_prefix, s_wpos, s_ctx, s_wsum, sp);
+    const splitter sx = split_prologue<5, FUSED>(a, Hl, s_prefix, s_wpos, s_ctx, s_wsum, sp);
     int x0 = sp.x0, s = sp.s, tiles_s = sp.tiles_s, hl = sp.pair, tile = sp.tile;
     const int w = sp.w;
+    if (FUSED && x0 >= sx.total) {   // the range starts where the batch ends: no tiles
+        empty_wavefront(a, s_prefix, Hl, x0, w, lane, kstage);
+        return;
+    }
     cut_pieces cp;
     cp.n = 0;
 
@@ -867,7 +887,7 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
     // out: that arithmetic then runs while the loads are under way.
     tile_regs ta, tb;
     bool primed = false;
-    if (x0 < sx.total) {   // (else the range starts where the batch ends: no tiles)
+    if (FUSED || x0 < sx.total) {   // (else the range starts where the batch ends: no tiles)
         open_pair();
         primed = tile < n_full;
         if (primed) {
@@ -876,9 +896,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
         }
     }
     const int x1 = sx.range_end(w);
+    if (FUSED && x0 >= x1) {
+        empty_wavefront(a, s_prefix, Hl, x1, w, lane, kstage);
+        return;
+    }
     const int x_start = x0;
 
-    while (x0 < x1) {
+    while (FUSED || x0 < x1) {
         const int seg_end = min(tiles_s, tile + (x1 - x0));
         const int full_end = min(seg_end, n_full);
 
@@ -928,13 +952,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
         const int64_t pair = (int64_t)s * Hl + hl;
         if (is_first && is_last) {
             store_final(a.out + ((int64_t)s * v.n_q_local + hl * G) * D, G, lc.r, lc.quad, st.o, st.l);
-            if (!a.fused && lane == 0)   // one piece: the merge kernel must find first == last here
+            if (!FUSED && lane == 0)   // one piece: the merge kernel must find first == last here
                 *reinterpret_cast<int2*>(a.pair_desc + pair * 2) = int2{(int)blockIdx.x, (int)blockIdx.x};
-        } else if (a.fused) {
+        } else if constexpr (FUSED) {
             store_partial(a, (int64_t)w + pair, G, lc.r, lc.quad, st.o, st.m, st.l, kstage, lane);
             note_piece(cp, s, hl, w, is_first, is_last);
         } else {
-            leave_piece(s_pieces, 2 * wave + (is_first ? 1 : 0), G, lc.r, lc.quad, st.o, st.m, st.l, (int)pair, is_first,
+            leave_piece(s_store, 2 * wave + (is_first ? 1 : 0), G, lc.r, lc.quad, st.o, st.m, st.l, (int)pair, is_first,
                         is_last, lane);
         }
 
@@ -951,9 +975,8 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_streamk_kernel(kv_stream
         }
         open_pair();
     }
-    if (!a.fused) add_up_group(a, s_pieces, s_prefix, x_start, x1 - x_start, wave, lane);
-    else if (x_start >= x1) empty_wavefront(a, s_prefix, Hl, x1, w, lane, kstage);
-    else settle_pieces(a, cp, lane, w, kstage);
+    if constexpr (FUSED) settle_pieces(a, cp, lane, w, kstage);
+    else add_up_group(a, s_store, s_prefix, x_start, x1 - x_start, wave, lane);
 }
 
 // ---- several adjacent KV heads per wavefront ----------------------------------------------------
@@ -1093,11 +1116,11 @@ __device__ __forceinline__ void compute_wide(const wide_tile& t, const bf16x8 (&
     }
 }
 
-template <int HPW, bool MIXED>
+template <int HPW, bool MIXED, bool FUSED>
 __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_args a)
 {
     constexpr int TG = 16 / HPW, TSHIFT = HPW == 4 ? 3 : 4, TILE = 1 << TSHIFT;
-    __shared__ group_pieces s_pieces;
+    __shared__ wave_store<FUSED> s_store;
     __shared__ int32_t s_prefix[kMaxBatch + 1];             // tiles of the sequences before s
     __shared__ int32_t s_ctx[kMaxBatch];
     __shared__ unsigned long long s_wpos[kMaxBatch + 1];    // weighted position of the first tile of s
@@ -1107,13 +1130,20 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
     const int wave = uniform(tid >> 6);
     const kv_view_dev& v = a.v;
     const int P = a.pairs, C = a.cols, G = a.group;
-    kv_u32x4* kstage = s_pieces.rows[2 * wave + 1];   // K tiles on their way, then the wavefront's last piece
-    if (lane < 2) s_pieces.note[2 * wave + lane] = int2{-1, 0};
+    // K tiles on their way (for a second launch, then the wavefront's last piece)
+    kv_u32x4* kstage = s_store.rows[FUSED ? wave : 2 * wave + 1];
+    if constexpr (!FUSED) {
+        if (lane < 2) s_store.note[2 * wave + lane] = int2{-1, 0};
+    }
 
     split_pos sp;
-    const splitter sx = split_prologue<TSHIFT>(a, P, s_prefix, s_wpos, s_ctx, s_wsum, sp);
+    const splitter sx = split_prologue<TSHIFT, FUSED>(a, P, s_prefix, s_wpos, s_ctx, s_wsum, sp);
     int x0 = sp.x0, s = sp.s, tiles_s = sp.tiles_s, hg = sp.pair, tile = sp.tile;
     const int w = sp.w;
+    if (FUSED && x0 >= sx.total) {   // the range starts where the batch ends: no tiles
+        empty_wavefront(a, s_prefix, P, x0, w, lane, kstage);
+        return;
+    }
     cut_pieces cp;
     cp.n = 0;
 
@@ -1194,15 +1224,19 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
     // out: that arithmetic then runs while the loads are under way.
     wide_tile ta, tb;
     bool primed = false;
-    if (x0 < sx.total) {   // (else the range starts where the batch ends: no tiles)
+    if (FUSED || x0 < sx.total) {   // (else the range starts where the batch ends: no tiles)
         open_pair();
         primed = tile < n_full;
         if (primed) load_wide<HPW>(ta, tile_base(tile), plane_bytes, wl, stride_bytes);
     }
     const int x1 = sx.range_end(w);
+    if (FUSED && x0 >= x1) {
+        empty_wavefront(a, s_prefix, P, x1, w, lane, kstage);
+        return;
+    }
     const int x_start = x0;
 
-    while (x0 < x1) {
+    while (FUSED || x0 < x1) {
         const int seg_end = min(tiles_s, tile + (x1 - x0));
         const int full_end = min(seg_end, n_full);
 
@@ -1235,13 +1269,13 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
         const int64_t pair = (int64_t)s * P + hg;
         if (is_first && is_last) {
             store_final(a.out + ((int64_t)s * v.n_q_local + hg * C) * D, C, wl.r, wl.quad, st.o, st.l);
-            if (!a.fused && lane == 0)   // one piece: the merge kernel must find first == last here
+            if (!FUSED && lane == 0)   // one piece: the merge kernel must find first == last here
                 *reinterpret_cast<int2*>(a.pair_desc + pair * 2) = int2{(int)blockIdx.x, (int)blockIdx.x};
-        } else if (a.fused) {
+        } else if constexpr (FUSED) {
             store_partial(a, (int64_t)w + pair, C, wl.r, wl.quad, st.o, m_col, st.l, kstage, lane);
             note_piece(cp, s, hg, w, is_first, is_last);
         } else {
-            leave_piece(s_pieces, 2 * wave + (is_first ? 1 : 0), C, wl.r, wl.quad, st.o, m_col, st.l, (int)pair, is_first,
+            leave_piece(s_store, 2 * wave + (is_first ? 1 : 0), C, wl.r, wl.quad, st.o, m_col, st.l, (int)pair, is_first,
                         is_last, lane);
         }
 
@@ -1258,9 +1292,8 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
         }
         open_pair();
     }
-    if (!a.fused) add_up_group(a, s_pieces, s_prefix, x_start, x1 - x_start, wave, lane);
-    else if (x_start >= x1) empty_wavefront(a, s_prefix, P, x1, w, lane, kstage);
-    else settle_pieces(a, cp, lane, w, kstage);
+    if constexpr (FUSED) settle_pieces(a, cp, lane, w, kstage);
+    else add_up_group(a, s_store, s_prefix, x_start, x1 - x_start, wave, lane);
 }
 
 // Merge the partials that the workgroups left of one (sequence, local query head), or write zeros for an empty
@@ -1501,7 +1534,7 @@ int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, h
     const int64_t mode = kv_option_merge_mode();
     const bool one_launch = !long_lists && (a.cols <= 4 ? (double)n_pairs * (double)bytes < 1.1e11
                                                         : a.cols <= 8 && n_pairs >= 256 && bytes < 150000000);
-    a.fused = (mode == 1 || (mode == 0 && one_launch)) && n_pairs <= KV_DECODE_SYNC_WORDS && a.n_waves < (1 << 16);
+    const bool fused = (mode == 1 || (mode == 0 && one_launch)) && n_pairs <= KV_DECODE_SYNC_WORDS && a.n_waves < (1 << 16);
     // Weights of the XCDs.  Workgroup L runs on XCD L mod 8 (read back from the hardware's XCC_ID by
     // kv_probe_read_placed), and the XCDs do not stream equally fast: with equal shares the
     // wavefronts of the odd-numbered ones end later on average (a plain read of equal contiguous
@@ -1529,19 +1562,21 @@ int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, h
         if (kv_prof_kernel_events(which, &e0, &e1)) hipExtLaunchKernelGGL(kernel, g, b, 0, st, e0, e1, 0, a);
         else hipLaunchKernelGGL(kernel, g, b, 0, st, a);
     };
-    if (hpw == 4) {
-        if (a.view_ids) launch(decode_wide_kernel<4, true>, grid, block, KV_PROF_DECODE_MAIN);
-        else launch(decode_wide_kernel<4, false>, grid, block, KV_PROF_DECODE_MAIN);
-    } else if (hpw == 2) {
-        if (a.view_ids) launch(decode_wide_kernel<2, true>, grid, block, KV_PROF_DECODE_MAIN);
-        else launch(decode_wide_kernel<2, false>, grid, block, KV_PROF_DECODE_MAIN);
-    } else if (a.view_ids) {
-        launch(decode_streamk_kernel<true>, grid, block, KV_PROF_DECODE_MAIN);
+    auto launch_main = [&](auto mixed, auto one) {
+        constexpr bool MIXED = mixed.value, FUSED = one.value;
+        if (hpw == 4) launch(decode_wide_kernel<4, MIXED, FUSED>, grid, block, KV_PROF_DECODE_MAIN);
+        else if (hpw == 2) launch(decode_wide_kernel<2, MIXED, FUSED>, grid, block, KV_PROF_DECODE_MAIN);
+        else launch(decode_streamk_kernel<MIXED, FUSED>, grid, block, KV_PROF_DECODE_MAIN);
+    };
+    if (a.view_ids) {
+        if (fused) launch_main(std::true_type(), std::true_type());
+        else launch_main(std::true_type(), std::false_type());
     } else {
-        launch(decode_streamk_kernel<false>, grid, block, KV_PROF_DECODE_MAIN);
+        if (fused) launch_main(std::false_type(), std::true_type());
+        else launch_main(std::false_type(), std::false_type());
     }
     int rc = kv_record_hip_error(hipGetLastError(), "paged_decode_attn launch");
-    if (rc || a.fused) return rc;
+    if (rc || fused) return rc;
     if (long_lists)
         launch(decode_streamk_merge_kernel<true>, dim3((unsigned)view->n_q_local, (unsigned)a.batch, (unsigned)kMergeSplit), dim3(256),
                KV_PROF_DECODE_MERGE);

@@ -130,7 +130,6 @@ struct kv_streamk_args {
     int32_t* pair_desc;   // [batch * pairs][2] numbers of the workgroups holding a pair's first and last piece
                           // (read by the merge kernel; unused when the main kernel combines the pieces)
     unsigned long long* pair_sync;  // [batch * pairs] arrival words of the pairs, zero between calls
-    int32_t fused;        // 1: the last piece of a pair to arrive combines them all (no merge kernel)
     const int32_t* view_ids;  // [batch] index into lay[] per sequence, or null: every sequence under v
     int32_t n_views;
     kv_layout_dev lay[KV_MAX_MIXED_VIEWS];

@@ -8,7 +8,7 @@ from oracle import LAYOUT_DP, LAYOUT_TP
 from paper_2602_22593_amd import binding as kv
 from paper_2602_22593_amd import workloads as wl
 
-from helpers import bf16_bits_to_f64, make_case
+from helpers import bf16_bits_to_f64, kernels_of, make_case, make_mixed_case
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -53,3 +53,33 @@ def test_pieces_of_a_workgroup(hq, hkv, triple, lens):
     err = np.abs(got - want)
     assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
     assert (got[ctx == 0] == 0).all()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("hq", [16, 32, 64])
+def test_each_way_of_combining_is_a_kernel_of_its_own(hq, mode):
+    """Sequences in two layouts (2, 4 or 8 rows a pair), fewer tiles than wavefronts: the kernel compiled for one launch
+    runs alone, the one compiled for two with the merge kernel, and both meet the oracle with the arrival words left zero."""
+    ctx = np.array([33, 0, 700, 1, 64] + [40 + 13 * i for i in range(30)], dtype=np.int32)
+    w = wl.Workload("both", 91 + hq // 8, hq, 8, 128, 16, len(ctx), "x", ())
+    triples = [(LAYOUT_TP, 4, 1), (LAYOUT_DP, 4, 1)]
+    c = make_mixed_case(w, triples, np.arange(len(ctx)) % 2, ctx)
+    views = [kv.kv_view_create(hq, 8, 128, 16, *t) for t in triples]
+    ws = torch.zeros(kv.paged_decode_attn_workspace_bytes(views[0], len(ctx), int(ctx.max())), dtype=torch.uint8, device=DEV)
+    dev = [torch.from_numpy(a.view(np.int16)).to(DEV) for a in (c.q, c.pool)] + [
+        torch.from_numpy(a).to(DEV) for a in (c.table, c.ctx, c.view_ids)]
+    kv.kv_set_option("merge_mode", mode)
+    kv.kv_set_option("heads_per_wave", 1)
+    try:
+        result = []
+        ran = kernels_of(lambda: result.append(kv.paged_decode_attn_mixed(*dev, views, int(ctx.max()), workspace=ws)))
+    finally:
+        kv.kv_set_option("merge_mode", 0)
+        kv.kv_set_option("heads_per_wave", 0)
+    assert ("decode_streamk_kernel<true, true>" in ran) == (mode == 1), ran
+    assert ("decode_streamk_kernel<true, false>" in ran and "decode_streamk_merge_kernel" in ran) == (mode == 2), ran
+    assert not bool(ws[:kv.KV_DECODE_SYNC_BYTES].any())
+    got = bf16_bits_to_f64(result[0].cpu().numpy().view(np.uint16))
+    err = np.abs(got - oracle.paged_decode_mixed(c.views, c.view_ids, c.q, c.pool, c.table, c.ctx))
+    assert np.isfinite(got).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
+    assert (got[c.ctx == 0] == 0).all()
