@@ -1522,13 +1522,19 @@ int kv_streamk_launch(kv_streamk_args a, const kv_view* view, void* workspace, h
     //   through pairs times MB = 110000;
     // - 5 to 8: two launches are faster (64 query heads under TP8, 256 of 1 to 16384: 72.6 against 70.9; 64 of 305 to 3050:
     //   19.5 against 18.7; TP4, 24 of 400 to 4000: 21.0 against 19.1; 8 heads, 64 of 550 to 1100: 45.0 against 42.9), but
-    //   for many short sequences (130 under TP4 of 375 to 750, 100 MB: 21.6 against 21.9).
+    //   for many short sequences (130 under TP4 of 375 to 750, 100 MB: 21.6 against 21.9), and with 8 rows, the form whose
+    //   rows are compiled for, also for fewer (batches in two layouts, which have no other kernel, 64 query heads: 160 pairs
+    //   of 50 to 250, 20 MB, 10.4 against 11.7; 120 of 20 to 130 8.1 against 9.0; 230 of 200 to 500, 59 MB, 15.6 against
+    //   15.9; but 80 of 50 to 250, 10 MB, 10.0 against 9.7; 100 of the same 10.1 against 10.1), or where most pairs are one
+    //   piece (60 of 20 to 60 tokens 7.8 against 8.5, of 50 to 250 9.9 against 9.6).  With 5 to 7 rows there never (7 rows,
+    //   100 pairs of 20 to 130 tokens 12.2 against 9.1).
     const int64_t n_pairs = (int64_t)a.batch * a.pairs;
     const int64_t bytes = (int64_t)a.batch * view->n_kv_local * a.max_ctx_len * (D * 4);
     const bool long_lists = n_pairs * kMergeLong <= a.n_waves / kSkWaves;
     const int64_t mode = kv_option_merge_mode();
+    const bool short_8 = a.cols == 8 && (n_pairs >= 110 ? bytes < 60000000 : a.max_ctx_len <= 96);
     const bool one_launch = !long_lists && (a.cols <= 4 ? (double)n_pairs * (double)bytes < 1.1e11
-                                                        : a.cols <= 8 && n_pairs >= 256 && bytes < 150000000);
+                                                        : short_8 || (a.cols <= 8 && n_pairs >= 256 && bytes < 150000000));
     const bool fused = (mode == 1 || (mode == 0 && one_launch)) && n_pairs <= KV_DECODE_SYNC_WORDS && a.n_waves < (1 << 16);
     // Weights of the XCDs.  Workgroup L runs on XCD L mod 8 (read back from the hardware's XCC_ID by
     // kv_probe_read_placed), and the XCDs do not stream equally fast: with equal shares the

@@ -83,3 +83,28 @@ def test_each_way_of_combining_is_a_kernel_of_its_own(hq, mode):
     err = np.abs(got - oracle.paged_decode_mixed(c.views, c.view_ids, c.q, c.pool, c.table, c.ctx))
     assert np.isfinite(got).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
     assert (got[c.ctx == 0] == 0).all()
+
+
+@pytest.mark.parametrize("hq,batch,lo,hi,one", [
+    (64, 40, 50, 250, True),     # 160 pairs of 8 rows, 20 MB
+    (64, 30, 400, 1100, False),  # 120, 68 MB
+    (64, 20, 20, 96, True),      # 80, three tiles at the most
+    (64, 20, 50, 250, False),
+    (64, 9, 20, 80, False),      # 36: a pair is cut over many wavefronts, however short
+    (56, 40, 50, 250, False),    # 7 rows
+    (32, 20, 50, 250, True),     # 4 rows
+])
+def test_batches_in_two_layouts_take_one_launch_or_two(hq, batch, lo, hi, one):
+    ctx = np.array([lo + (hi - lo) * i // (batch - 1) for i in range(batch)], dtype=np.int32)
+    w = wl.Workload("route", 99 + hq // 8, hq, 8, 128, 16, batch, "x", ())
+    triples = [(LAYOUT_TP, 2, 1), (LAYOUT_DP, 2, 1)]
+    c = make_mixed_case(w, triples, np.arange(batch) % 2, ctx)
+    views = [kv.kv_view_create(hq, 8, 128, 16, *t) for t in triples]
+    dev = [torch.from_numpy(a.view(np.int16)).to(DEV) for a in (c.q, c.pool)] + [
+        torch.from_numpy(a).to(DEV) for a in (c.table, c.ctx, c.view_ids)]
+    result = []
+    ran = kernels_of(lambda: result.append(kv.paged_decode_attn_mixed(*dev, views, hi)))
+    assert ("decode_streamk_kernel<true, true>" in ran) == one and ("decode_streamk_merge_kernel" in ran) != one, ran
+    got = bf16_bits_to_f64(result[0].cpu().numpy().view(np.uint16))
+    err = np.abs(got - oracle.paged_decode_mixed(c.views, c.view_ids, c.q, c.pool, c.table, c.ctx))
+    assert np.isfinite(got).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
