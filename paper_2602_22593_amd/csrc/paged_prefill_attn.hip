@@ -62,7 +62,7 @@ struct prefill_args {
     int32_t most_records;   // tokens that the partial arrays have room for
     int4* tiles;            // [slots] (first record, pieces, first token in q, tokens), for the merge kernel
     float* part_o;          // [record = a piece's token][n_q_local][128] un-normalised sums
-    float* part_ml;         // [record][n_q_local][2]  (reference maximum in score units, sum of weights)
+    float* part_ml;         // [record][n_q_local][2]  (reference maximum in exponent units, sum of weights)
 };
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -721,14 +721,15 @@ __global__ __launch_bounds__(kThreads, 3) void prefill_kernel(prefill_args a)
     // moves it.
     auto move_reference = [&](float tmax) {
         if (__builtin_amdgcn_ballot_w64(tmax > kLag) != 0) {
-            const float up = fmaxf(half_max(tmax), 0.f);
-            const float alpha = fast_exp2(-up);
+            // (from the scores again: exponents far above the old reference have lost the digits that the new one needs)
+            const float to = fminf(neg_mc, -column_max(sc) * a.scale_log2e);
+            const float alpha = fast_exp2(to - neg_mc);
             l *= alpha;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] *= alpha;
-            neg_mc -= up;
+            neg_mc = to;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) ex[i] -= up;
+            for (int i = 0; i < 16; ++i) ex[i] = __builtin_fmaf(sc[i], a.scale_log2e, neg_mc);
         }
     };
     auto weight_operand = [&](int c) { return as_bf16x8(kv_u32x4{pw[4 * c], pw[4 * c + 1], pw[4 * c + 2], pw[4 * c + 3]}); };
@@ -833,7 +834,7 @@ __global__ __launch_bounds__(kThreads, 3) void prefill_kernel(prefill_args a)
                 for (int u = 0; u < 4; ++u)
                     *reinterpret_cast<f32x4*>(dst + 32 * j + 8 * u) = f32x4{o[j][4 * u], o[j][4 * u + 1], o[j][4 * u + 2], o[j][4 * u + 3]};
             if (half == 0) {
-                a.part_ml[rec * 2 + 0] = lt > 0.f ? -neg_mc / a.scale_log2e : kNegInf;   // (no valid key: left out)
+                a.part_ml[rec * 2 + 0] = lt > 0.f ? -neg_mc : kNegInf;   // (no valid key: left out)
                 a.part_ml[rec * 2 + 1] = lt;
             }
         } else if (orow >= 0) {
@@ -860,7 +861,7 @@ __global__ __launch_bounds__(kThreads, 3) void prefill_kernel(prefill_args a)
     }
 }
 
-// out[row] = sum_z o_z 2^((m_z - M) c) / sum_z l_z 2^((m_z - M) c), M = max_z m_z, over the pieces z of
+// out[row] = sum_z o_z 2^(m_z - M) / sum_z l_z 2^(m_z - M), M = max_z m_z, over the pieces z of
 // the row's query tile; a piece that saw no valid key for the row has l = 0 and is skipped.  Block (x, y, z):
 // a sixteenth of the rows of slot x and KV head y; 32 lanes per row, 4 columns each.  Bound by the latency of its
 // loads: eight pieces are fetched at once, or two or four where a tile has no more, since what is fetched past the last
@@ -897,13 +898,13 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(prefill_args a)
                 mn = fmaxf(mn, ml[u].x);
             }
             if (mn == kNegInf) continue;
-            const float keep = fast_exp2((mm - mn) * a.scale_log2e);
+            const float keep = fast_exp2(mm - mn);
             lt *= keep;
             acc *= keep;
             mm = mn;
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                const float w = fast_exp2((ml[u].x - mn) * a.scale_log2e);
+                const float w = fast_exp2(ml[u].x - mn);
                 lt += ml[u].y * w;
                 acc += x[u] * w;
             }

@@ -67,3 +67,28 @@ def test_keys_that_score_minus_infinity_come_first(n_inf, n, q_len):
     want = torch.softmax(s.masked_fill(~seen[:, None], -math.inf), dim=-1) @ V.double()
     err = (out.cpu().double() - want).abs()
     assert torch.isfinite(out).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
+
+
+@pytest.mark.parametrize("n,q_len", [(700, 4), (6000, 16)])   # whole query tiles; key ranges cut into pieces
+def test_equal_scores_far_above_the_others_weigh_the_same(n, q_len):
+    """Two keys of a query score the same, 2^20 and more, after others have moved the reference maximum in steps that fp32
+    rounds.  With values 1 and -1 the output is 0, as both keys' exponents come from equal scores by the same operations,
+    whichever tile or piece they lie in; a reference moved by rounded differences ends elsewhere in every tile."""
+    K, V = torch.zeros(n, 128), torch.zeros(n, 128)
+    q = torch.zeros(q_len, 4, 128)
+    q[..., 0] = (1.0e6 * (1.0 + 0.017 * torch.arange(4 * q_len))).reshape(q_len, 4)
+    half = n // 2
+    for at, steps in ((0, (1.37, 4.13, 5.55, 7.61, 9.77)), (half, (0.93, 2.71, 5.57, 7.3, 8.9))):
+        for step, t in zip(steps, (40, 75, 110, 145, 180)):
+            K[at + t, 0] = step
+        K[at + 220, 0] = 11.3
+        V[at + 220] = 1.0 if at == 0 else -1.0
+    blocks = -(-n // 16)
+    pool = torch.zeros(blocks, 2, 16, 1, 128, dtype=torch.bfloat16)
+    for plane, x in enumerate((K, V)):
+        flat = torch.zeros(blocks * 16, 128, dtype=torch.bfloat16)
+        flat[:n] = x.to(torch.bfloat16)
+        pool[:, plane, :, 0] = flat.view(blocks, 16, 128)
+    out = run(q.to(torch.bfloat16).to(DEV), pool.to(DEV), np.arange(blocks, dtype=np.int32).reshape(1, blocks),
+              np.array([n], dtype=np.int32), np.array([0, q_len]), kv.kv_view_create(4, 1, 128, 16, LAYOUT_DP, 1, 0), q_len)
+    assert out.float().abs().max().item() <= 2.0 ** -20
