@@ -55,6 +55,55 @@ def test_pieces_of_a_workgroup(hq, hkv, triple, lens):
     assert (got[ctx == 0] == 0).all()
 
 
+# one long sequence among too few others, and among enough that the batch as a whole counts as one of short lists
+LISTS = {
+    "long": ([33, 40011, 700], "decode_streamk_merge_kernel<true>"),
+    "skewed": ([20011] + [17 + (53 * i) % 130 for i in range(47)], "decode_streamk_merge_kernel<false>"),
+}
+
+
+def visible_values(ctx, n_kv_heads):
+    """V rows that show in which 128th of its sequence a token lies: element e of a head's output is the weight of the tokens
+    of part e (times 1 + head / 8), so that a piece that is lost, or counted twice, changes elements by their own size."""
+    V = np.zeros((int(ctx.sum()), n_kv_heads, 128), dtype=np.float32)
+    at = 0
+    for n in ctx:
+        t = np.arange(n)
+        V[at + t, :, t * 128 // max(int(n), 1)] = 1.0 + np.arange(n_kv_heads) / 8.0
+        at += int(n)
+    return (V.view(np.uint32) >> 16).astype(np.uint16)   # (exact in bf16)
+
+
+@pytest.mark.parametrize("lists", list(LISTS))
+@pytest.mark.parametrize("hq,hkv,triple", [
+    (32, 8, (LAYOUT_DP, 1, 0)), (64, 8, (LAYOUT_TP, 2, 1)), (32, 8, (LAYOUT_TP, 4, 1)), (24, 8, (LAYOUT_TP, 8, 3)),
+    (16, 1, (LAYOUT_DP, 1, 0))])
+def test_every_piece_of_a_long_list_counts_once(hq, hkv, triple, lists):
+    """A pair of the long sequence is cut over 50 workgroups and more.  Per element: the weights are rounded to bf16, of
+    eight significant bits, by 2^-8 of each at the most, in the numerator and in the denominator, and the result once more:
+    3 x 2^-8 (the sums are in fp32), and 2^-6 is allowed.  Without one of 122 partials two elements of
+    a row of the long sequence are outside, without 40 keys one."""
+    lens, merge = LISTS[lists]
+    ctx = np.array(lens, dtype=np.int32)
+    w = wl.Workload("lists", 107 + hq // 8, hq, hkv, 128, 16, len(ctx), "x", ())
+    K, _ = wl.logical_kv(w, ctx)
+    c = make_case(w, triple, ctx, K=K, V=visible_values(ctx, hkv))
+    want = oracle.paged_decode(c.view, c.q, c.pool, c.table, c.ctx)
+    view = kv.kv_view_create(hq, hkv, 128, 16, *triple)
+    dev = [torch.from_numpy(a.view(np.int16)).to(DEV) for a in (c.q, c.pool)] + [
+        torch.from_numpy(a).to(DEV) for a in (c.table, c.ctx)]
+    kv.kv_set_option("merge_mode", 2)
+    try:
+        result = []
+        ran = kernels_of(lambda: result.append(kv.paged_decode_attn(*dev, view, int(ctx.max()))))
+    finally:
+        kv.kv_set_option("merge_mode", 0)
+    assert merge in ran, ran
+    got = bf16_bits_to_f64(result[0].cpu().numpy().view(np.uint16))
+    off = np.abs(got - want) > np.abs(want) * 2.0 ** -6 + 1e-12
+    assert not off.any(), (int(off.sum()), np.argwhere(off)[:4].tolist())
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("hq", [16, 32, 64])
 def test_each_way_of_combining_is_a_kernel_of_its_own(hq, mode):
