@@ -5,26 +5,26 @@
 //
 // The batch is flattened into tiles of 32 tokens of one (sequence, local KV head) pair, pairs
 // ordered (sequence, head) with the head fastest.  The T tiles are cut into W consecutive ranges,
-// one per launched wavefront (the grid is sized so that all W are resident at once), of nearly
-// equal length (a small, fixed correction per XCD, see split_prologue): every wavefront streams
-// about the same number of KV bytes whatever the mix of context lengths, and lives long enough
-// to amortise its start-up.  A wavefront's range may cover the end of one pair and the start of
-// the next; each (wavefront, pair) piece yields either the final output row (the piece is the
-// whole pair) or an un-normalised partial (m, l, acc[G][d]) in workspace slot w + pair_index,
-// which is unique and keeps the pieces of a pair in consecutive slots.
+// one per launched wavefront (one on each SIMD: with 290 to 330 registers no more are resident, so
+// where an option asks for more, the workgroups run in rounds), of nearly equal length (a small, fixed
+// correction per XCD, see split_prologue): every wavefront streams about the same number of KV bytes
+// whatever the mix of context lengths, and lives long enough to amortise its start-up.  A wavefront's
+// range may cover the end of one pair and the start of the next; each (wavefront, pair) piece yields
+// either the final output row (the piece is the whole pair) or an un-normalised partial (m, l,
+// acc[G][d]) in workspace slot w + pair_index, which is unique and keeps the pieces of a pair in
+// consecutive slots.
 //
 // Combining the pieces of a cut pair (m = max m_k, l = sum l_k 2^(m_k - m), acc likewise) happens
-// in one of two ways.  Normally inside this kernel, with no waiting anywhere: a wavefront writes
-// its partials with device-coherent stores, and at the end of its range, once those stores are
-// acknowledged, adds one 64-bit word to the pair's arrival word: 1 in the piece count, plus its
-// own number in a "first" field if it held the pair's first piece or in a "last" field if it held
-// the last.  The sum tells every arriver how many pieces there are and how many have arrived; the
-// one that completes the count reads all partials back (device-coherent loads), writes the output
-// rows and puts the word back to zero.  Batches in which a pair is cut over very many wavefronts
-// (few, very long sequences), and pairs of more than 8 rows, use a second launch instead,
-// decode_streamk_merge_kernel: the four wavefronts of a workgroup add their pieces up in LDS, the
-// workgroup leaves the sums in slot workgroup + pair_index, and the workgroups holding a pair's first and
-// last piece leave their numbers in the pair's descriptor.
+// in one of two ways, each a kernel of its own, by a rule on rows, pairs and bytes in kv_streamk_launch.
+// Inside this kernel (FUSED), with no waiting anywhere: a wavefront writes its partials with
+// device-coherent stores, and at the end of its range, once those stores are acknowledged, adds one
+// 64-bit word to the pair's arrival word: 1 in the piece count, plus its own number in a "first" field
+// if it held the pair's first piece or in a "last" field if it held the last.  The sum tells every
+// arriver how many pieces there are and how many have arrived; the one that completes the count reads
+// all partials back (device-coherent loads), writes the output rows and puts the word back to zero.
+// Or by a second launch, decode_streamk_merge_kernel: the four wavefronts of a workgroup add their
+// pieces up in LDS, the workgroup leaves the sums in slot workgroup + pair_index, and the workgroups
+// holding a pair's first and last piece leave their numbers in the pair's descriptor.
 //
 // Per tile, lane l = (r = l % 16, quad = l / 16).  Both products put the KV data in the MFMA
 // A operand (row index r) and the query group, padded to 16, in the B operand (column r = g):
@@ -660,10 +660,11 @@ __device__ __forceinline__ void empty_wavefront(const kv_streamk_args& a, const 
 // range starts inside in record 2 wave, that of the pair its range ends inside in record 2 wave + 1 (a range that
 // lies inside one pair leaves one, in the first), so that in the order of the records the pieces of a pair are
 // neighbours.  The workgroup adds them up and leaves two partials at most, a quarter of the pieces that the second
-// launch has to read (two sequences of 131072 tokens: 113 a pair and not 450; us per call 57.0 -> 53.8 with
-// both kernels, 64 sequences of 512 to 4096 with 16 rows a pair 109.6 -> 105.6).  Not where the pieces are combined inside the main kernel: there a
-// wavefront that is done sends its partial off while others still stream, and waiting for the workgroup
-// makes the chain from the last tile to the last row 1 us longer (256 sequences under TP8 29.4 -> 31.3).
+// launch has to read (two sequences of 131072 tokens: 113 a pair and not 450; us per call, together with the merge
+// kernels and the limit for several heads per wavefront that came with it, 57.0 -> 53.6, 64 sequences of 512 to 4096
+// with 16 rows a pair 109.4 -> 106.6).  Not where the pieces are combined inside the main kernel: there a wavefront that
+// is done sends its partial off while others still stream, and waiting for the workgroup makes the chain from the last
+// tile to the last row 1 us longer (256 sequences under TP8 29.4 -> 31.3).
 constexpr int kRowUnits = D / 4;   // 16-byte units of a row
 struct group_pieces {
     kv_u32x4 rows[2 * kSkWaves][16 * kRowUnits];   // row r of a record: unit p at r * 32 + (p ^ r)
@@ -1298,12 +1299,16 @@ __global__ __launch_bounds__(kSkThreads, 1) void decode_wide_kernel(kv_streamk_a
 //
 // Short lists (LONG false: the batch has enough pairs that few are cut over many workgroups): one wavefront a row,
 // lane e elements 2 e and 2 e + 1.  What bounds it is latency, so everything four partials hold for a row is requested
-// together (most lists are no longer), every lane works out the weights by itself, and no barrier is needed.  Against a workgroup a row (eight slices of the list, mostly empty, added through LDS), 256 sequences x 32
-// heads of 100 to 600 tokens: 72.3 -> 66.1 us per call.
+// together (most lists are no longer), every lane works out the weights by itself, and no barrier is needed.  Against a
+// workgroup a row (eight slices of the list, mostly empty, added through LDS), 256 sequences x 32 heads of 100 to 600 tokens:
+// 72.3 -> 66.1 us per call.  One long sequence among many short ones has a long list here too: 131072 tokens
+// among 31 of 1000, all 8 heads, about 100 partials a pair, 16 us of the call's 120 (23 with the workgroup a row; eight, 16
+// or 32 requested at a time take no less, and batches of short lists up to 4 % more).
 //
-// Long lists: kMergeSplit workgroups a row, each owning 128 / kMergeSplit columns as 8 column groups of 4 elements x 32
-// slices of the list.  In such a grid all but the first leave at once for a short list, which that one merges as
-// 32 column groups x 8 slices.
+// Long lists (the average pair is cut over kMergeLong workgroups and more): kMergeSplit workgroups a row, each owning 128 /
+// kMergeSplit columns as 8 column groups of 4 elements x 32 slices of the list.  In such a grid all but the first leave
+// at once for a short list, which that one merges as 32 column groups x 8 slices.  A slice's partials come one after the
+// other, see below.
 constexpr int kMergeSplit = 4;
 constexpr int kMergeLong = 6;  // partials from which a list counts as long
 
@@ -1384,7 +1389,8 @@ __global__ __launch_bounds__(256) void decode_streamk_merge_kernel(kv_streamk_ar
         float mr = kNegInf, ll = 0.f;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         constexpr int kBatch = 8;
-        // (eight requested at a time: one memory round trip per eight, not one each)
+        // (written for eight requests at a time, but as compiled each waits behind the branch that guards the use of the one
+        // before it, a memory round trip per partial: four for a list of 113)
         for (int w0 = w_first + slice; w0 <= w_last; w0 += kBatch * nsl) {
             float2 ml[kBatch];
             f32x4 part[kBatch];
@@ -1449,7 +1455,8 @@ static int wide_heads(const kv_view* view, int batch, int n_waves, int max_ctx_l
     //   260 MB: 32.2 against 31.5; 16 of 1000 to 2000, 130 MB: 26.9 against 25.2; at 340 MB 16 of 500 to 5200 35.3 against
     //   34.9, but 64 of 130 to 1300 42.2 against 42.7, 4 of 10000 to 20000 51.4 against 54.2; at 450 MB every one of nine
     //   shapes 2 to 6 % faster; G = 8, 64 of 500 to 1000, 8 heads, 260 MB: 41.5 against 42.5);
-    // - the same with 8 rows a pair (two-head rows): below 500 MB (64 of 2600 to 5200 under TP4, 340 MB: 48.1 against 47.1);
+    // - the same with 8 rows a pair (two-head rows): hardly a difference, the line lies at 400 MB (TP4, 50 to 256 sequences,
+    //   geometric means over twelve shapes each: at 300 MB 0.2 % slower, at 340 to 460 MB 0.1 to 0.4 % faster, at 560 MB 0.5 %);
     // - one or two: only where the pairs are few, whose lists of pieces then are long (G = 1, 4 heads: one sequence of
     //   60000, 123 MB, 40.3 against 32.4; with three short ones, 492 MB, 41.0 against 33.9; G = 2, 8 of 200 to 2000, 4
     //   heads, 134 MB: 15.1 against 12.0, but 8 of 8000 to 16000, 252 MB: 43.3 against 44.9).  With more pairs a
@@ -1490,7 +1497,7 @@ size_t kv_streamk_workspace_bytes(const kv_view* view, int batch, int n_waves)
         workspace_layout(view, batch, n_waves, hpw, acc, ml);
         if (acc + ml > need) need = acc + ml;
     }
-    // pair descriptors: two wavefront numbers per (sequence, pair)
+    // pair descriptors: two workgroup numbers per (sequence, pair)
     const size_t desc = ((size_t)batch * view->n_kv_local * 2 * 4 + 255) / 256 * 256;
     return KV_DECODE_SYNC_BYTES + need + desc;
 }

@@ -286,7 +286,9 @@ __global__ __launch_bounds__(256) void linear_tile_add_kernel(linear_args p, int
     f32x4 sum[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int z0 = 0; z0 < p.splits; z0 += 4) {   // four slices requested before any is added
+    // (written for four slices requested at a time, but as compiled each waits behind the branch that guards the use of the one
+    // before it; with selects in its place 3 % faster or 6 % slower from run to run, 300 rows of 6144 x 4096)
+    for (int z0 = 0; z0 < p.splits; z0 += 4) {
         f32x4 v[4][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)

@@ -696,8 +696,8 @@ int pick_kernel(const kv_view* view, int batch)
     return valu_ok ? 2 : 0;
 }
 
-// Wavefronts the even-split kernel launches: all resident at once, one per SIMD by default
-// (fewer, fatter streams measured faster than more, thinner ones).  The compute-unit count is that
+// Wavefronts the even-split kernel launches: one per SIMD by default, which is as many as its registers let be resident
+// (fewer, fatter streams measured faster than more, thinner ones; more than that run in rounds).  The compute-unit count is that
 // of the device current on the calling thread, asked once per device.
 int streamk_waves()
 {

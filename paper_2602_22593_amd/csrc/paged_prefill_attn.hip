@@ -417,9 +417,9 @@ __device__ __forceinline__ int piece_slot(const int2* s_slot, int slots, int idx
 // with the tile by tile order that this replaces, and 61 % at 1.59 to 1.72 GHz with two of these wavefronts per SIMD;
 // 16 x 16 x 32 products in the same order 51 % at 2.09 GHz.  All are within 4 % of each other in time, and taking out the
 // loads that stage K and V (in a timing-only build) is worth 10 to 11 %, the exponentials 3 to 6 %.
-// us per call, tile by tile -> now: 16 prompts of 128 to 4000 tokens, 32 query heads on 8, 748 -> 728; 6 of 500 to 3900
-// 286 -> 266; one of 1000 30.9 -> 23.3; 64 of 30 to 600 125 -> 118; 4 of 8192 1927 -> 1930; 512 on 4096 to 16384 in
-// four sequences, 4 heads, 203 -> 194.
+// us per call, tile by tile -> now: 16 prompts of 128 to 4000 tokens, 32 query heads on 8, 756 -> 727; 6 of 500 to 3900
+// 267 -> 258; one of 1000 29.4 -> 23.4; 64 of 30 to 600 136 -> 131; 4 of 8192 1920 -> 1924; 512 on 4096 to 16384 in
+// four sequences, 4 heads, 204 -> 196; 70 drawn shapes 9.8 % less.
 // Three workgroups per compute unit (32 KiB of LDS and at most 168 registers each; nothing is spilled in the loop): with two
 // of up to 190 registers launches of many tiles are slower (tp2 chunks above 221, 64 of 30 to 600 135).  Eight
 // wavefronts that share the staged tiles (half the loads) wait for each other: 16 prompts 810, 4 of 8192 1969.
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(kThreads, 3) void prefill_kernel(prefill_args a)
     }
     for (; item < item_end; item += item_step) {   // (the body is not indented for it)
     // what is derived from the lane number is worked out anew per item: kept across the loop it costs the
-    // registers that the inner loop needs (28 spilled instead of 18, 5 % slower)
+    // registers that the inner loop needs (12 spilled instead of 4, with the key range cut 15 instead of 9)
     int lane = lane0;
     asm volatile("" : "+v"(lane));
     const int col = lane & 31, half = lane >> 5;
